@@ -478,8 +478,8 @@ def measure_apps(steps: int):
         return bool((k[1:] >= k[:-1]).all().item())
 
     ms2 = timed(sort_once, max(2, steps // 2))
-    res["split_radix_sort"] = {"workload": "n=2^26 random 32-bit keys, 16 fused split passes on two bits each (flags from the keys, MFMA "
-                                           "scans, scatter: one kernel per pass), includes one 256 MiB copy per run",
+    res["split_radix_sort"] = {"workload": "n=2^26 random 32-bit keys, four passes on eight bits each (ranks, carry chain, scatter: one "
+                                           "kernel per pass), includes one 256 MiB copy per run",
                                "ms": ms2, "mkeys_per_s": m / (ms2 * 1e-3) / 1e6, "sorted": is_sorted()}
     try:
         tcuscan.set_sort_fusion(2)

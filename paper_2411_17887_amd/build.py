@@ -7,7 +7,7 @@ import sys
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-SOURCES = [os.path.join(HERE, "csrc", name) for name in ("tcuscan.hip", "levels.hip", "apps.hip", "stream.hip")]
+SOURCES = [os.path.join(HERE, "csrc", name) for name in ("tcuscan.hip", "levels.hip", "apps.hip", "sort.hip", "stream.hip")]
 LIB = os.path.join(HERE, "libtcuscan.so")
 OBJ_DIR = os.path.join(HERE, "_build")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

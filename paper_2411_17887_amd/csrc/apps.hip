@@ -11,6 +11,7 @@
 //                key i goes to  pos[i]            if f[i]      (zeros keep their order, in front)
 //                          to  Z + (i - pos[i])   otherwise   (ones keep their order, behind)
 //   radix sort : split(0), split(1), ..., split(bits-1)   -- least significant bit first, stable
+//                (by default with 256 buckets instead of two, eight bits at a time: sort.hip)
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -26,10 +27,8 @@ extern "C" tcuscan_status_t tcuscan_internal_split_pass(const void *d_keys, cons
                                                         int bit, const unsigned *d_zeros_total, void *d_ws, size_t ws_bytes,
                                                         tcuscan_stream_t stream);
 
-extern "C" tcuscan_status_t tcuscan_internal_digit_counts(const void *d_keys, size_t n, unsigned *d_counts64, tcuscan_stream_t stream);
-extern "C" tcuscan_status_t tcuscan_internal_split4_pass(const void *d_keys, const void *d_vals, void *d_keys_out, void *d_vals_out, size_t n,
-                                                         int bit, const unsigned *d_hist4, void *d_ws, size_t ws_bytes,
-                                                         tcuscan_stream_t stream);
+extern "C" tcuscan_status_t tcuscan_internal_digit_sort(void *d_keys, void *d_vals, size_t n, int bits, void *d_keys_tmp, void *d_vals_tmp,
+                                                        void *d_scratch, void *d_fault, tcuscan_stream_t stream);              // sort.hip
 
 namespace {
 
@@ -99,7 +98,7 @@ __global__ __launch_bounds__(kThreads) void copy_u32_kernel(const uint32_t *__re
 
 unsigned blocks_for(size_t items) { return (unsigned)((items + kThreads - 1) / kThreads); }
 
-// measurement / test knob, see tcuscan_set_sort_fusion: 1 fused passes on two bits, 2 fused passes on one bit, 0 three
+// measurement / test knob, see tcuscan_set_sort_fusion: 1 passes on eight bits, 2 fused passes on one bit, 0 three
 // kernels per bit.  One atomic word, read once at the top of a sort, so that a change made by another thread while a
 // sort is being enqueued cannot mix the forms (or their count tables) within that sort.
 std::atomic<int> g_sort_form{1};
@@ -147,28 +146,31 @@ tcuscan_status_t tcuscan_split_radix_sort_u32(void *d_keys, void *d_vals, size_t
     uint32_t *src_v = (uint32_t *)d_vals, *dst_v = (uint32_t *)d_vals_tmp;
     int8_t *flags = (int8_t *)d_flags;
     int32_t *pos = (int32_t *)d_positions;
-    // Fused passes (the default): the mask and the positions are never written; the split kernel builds the flags from
-    // the keys, scans them and scatters in one go -- two bits (four buckets) per pass, and one more pass on a single bit
-    // when `bits` is odd.  How many keys have which digit at each position does not change when the keys are permuted:
-    // it is counted once, up front, into the first 96 words of d_positions (64 digit counts, 32 zero-bit counts).  The
-    // unfused form below (mask kernel, tcuscan_exclusive, scatter kernel, one bit per pass) remains for n < 96 and as
-    // the plain statement of the reduction.
     const int form = g_sort_form.load(std::memory_order_relaxed);
-    const bool fused = n >= 96 && form != 0;
-    const int digit_bits = form == 2 ? 1 : 2;                                   // fused passes: bits per pass
+    // The default: passes on eight bits, or the whole sort in one workgroup (sort.hip); the first words of d_positions
+    // hold the digit counts and the carry chain's status words.  The chain of 16384 keys to a tile (8192 with payloads)
+    // that two-bit passes ran through the workspace is what callers have sized it for: a call that needs it is refused
+    // without it, although only its fault word is used.
+    if (form == 1) {
+        const size_t tile = d_vals && bits >= 2 ? 8192 : 16384;
+        const size_t need = n > tile ? 256 + 64 * ((n + tile - 1) / tile) : 0;
+        if (need && (!d_ws || ws_bytes < need || ((uintptr_t)d_ws % 8) != 0)) return TCUSCAN_ERR_WORKSPACE;
+        return tcuscan_internal_digit_sort(d_keys, d_vals, n, bits, d_keys_tmp, d_vals_tmp, d_positions, need ? d_ws : nullptr, stream);
+    }
+    // Form 2, one bit per pass: the mask and the positions are never written; the split kernel builds the flags from the
+    // keys, scans them and scatters in one go.  How many keys have a zero at each bit does not change when the keys are
+    // permuted: it is counted once, up front, into the first 32 words of d_positions.  The unfused form below (mask
+    // kernel, tcuscan_exclusive, scatter kernel) remains for n < 96 and as the plain statement of the reduction.
+    const bool fused = n >= 96 && form == 2;
     if (fused) {
-        unsigned *hist = (unsigned *)d_positions, *zeros = hist + 64;
-        tcuscan_status_t st = digit_bits == 2 ? tcuscan_internal_digit_counts(d_keys, n, hist, stream) : TCUSCAN_OK;
-        if (st == TCUSCAN_OK && (digit_bits != 2 || (bits & 1))) st = tcuscan_internal_bit_zero_counts(d_keys, n, zeros, stream);
+        unsigned *zeros = (unsigned *)d_positions;
+        tcuscan_status_t st = tcuscan_internal_bit_zero_counts(d_keys, n, zeros, stream);
         if (st != TCUSCAN_OK) return st;
-        for (int bit = 0; bit < bits;) {
-            const int step = digit_bits == 2 && bits - bit >= 2 ? 2 : 1;
-            st = step == 2 ? tcuscan_internal_split4_pass(src_k, src_v, dst_k, dst_v, n, bit, hist + 4 * (bit / 2), d_ws, ws_bytes, stream)
-                           : tcuscan_internal_split_pass(src_k, src_v, dst_k, dst_v, n, bit, zeros + bit, d_ws, ws_bytes, stream);
+        for (int bit = 0; bit < bits; ++bit) {
+            st = tcuscan_internal_split_pass(src_k, src_v, dst_k, dst_v, n, bit, zeros + bit, d_ws, ws_bytes, stream);
             if (st != TCUSCAN_OK) return st;
             uint32_t *t = src_k; src_k = dst_k; dst_k = t;
             t = src_v; src_v = dst_v; dst_v = t;
-            bit += step;
         }
     }
     for (int bit = 0; !fused && bit < bits; ++bit) {

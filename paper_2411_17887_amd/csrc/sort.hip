@@ -1,0 +1,537 @@
+// Split passes on digits of up to eight bits: Blelloch's reduction of radix sort to prefix sums with 256 buckets instead
+// of two.  A key goes to
+//     (keys of the whole array with a smaller digit) + (keys with the same digit in front of it)
+// and the second term is a prefix sum of "digit is d" flags taken at four levels, as everywhere in this library:
+//     row of 64 keys   lanes with the same digit in front of this one: eight ballots narrow the wavefront down to them
+//     wavefront        256 running counters in LDS, one row after the other
+//     workgroup        the counters of the wavefronts, added up digit by digit
+//     array            one status word per tile and digit, published and looked up as in the scan kernels' carry chain
+// A full sort is four passes of 8 bytes per key (16 with payloads) and one reading of the keys for the first term.
+//
+// Up to kBlockSortMax keys one workgroup does all passes in LDS: one launch, keys and payloads read and written once.
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "../../include/tcuscan.h"
+#include "wave_ops.h"
+
+// tcuscan.hip: clears `bytes` bytes on the stream; the process-wide chain policy and the look-back's poll limit
+extern "C" hipError_t tcuscan_internal_fill(void *d, size_t bytes, hipStream_t s);
+extern "C" void tcuscan_internal_chain_knobs(unsigned *ticket, unsigned *spin_limit);
+
+namespace {
+
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int kDigits = 256;
+constexpr int kMaxPasses = 4;
+
+struct Digit { int shift, width; };                        // digit = (key >> shift) & (2^width - 1), width 1 .. 8
+struct Passes { int count; Digit digit[kMaxPasses]; };
+
+__device__ __forceinline__ uint32_t digit_of(uint32_t key, Digit g) { return __builtin_amdgcn_ubfe(key, (uint32_t)g.shift, (uint32_t)g.width); }
+
+// What an LDS access of one lane wrote, other lanes of the wavefront see from here on.
+__device__ __forceinline__ void wavefront_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+constexpr unsigned kAndXnor = 0x90;        // truth table of a & ~(b ^ c)
+
+// rank[r]: keys of the wavefront with the same digit in front of key r of this lane (rows of 64 keys, lane order inside
+// a row); counters[d] (this wavefront's, zero before): its keys with digit d.
+template <int ITEMS>
+__device__ __forceinline__ void rank_rows(const uint32_t (&key)[ITEMS], Digit g, uint16_t *counters, uint32_t (&rank)[ITEMS])
+{
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+        const uint32_t d = digit_of(key[r], g);
+        // the lanes whose digit agrees with this lane's in every bit
+        uint32_t sign[8];
+        uint64_t ones[8];
+#pragma unroll
+        for (int b = 0; b < 8; ++b) {
+            sign[b] = (uint32_t)__builtin_amdgcn_sbfe((int)d, b, 1);                           // the bit in all 32 places
+            asm("" : "+v"(sign[b]));                       // (kept: else it is taken out of the digit once more for the compare)
+            ones[b] = __builtin_amdgcn_ballot_w64(sign[b] != 0u);
+        }
+        uint32_t lo = ~((uint32_t)ones[0] ^ sign[0]), hi = ~((uint32_t)(ones[0] >> 32) ^ sign[0]);
+#pragma unroll
+        for (int b = 1; b < 8; ++b) {
+            lo = __builtin_amdgcn_bitop3_b32(lo, (uint32_t)ones[b], sign[b], kAndXnor);
+            hi = __builtin_amdgcn_bitop3_b32(hi, (uint32_t)(ones[b] >> 32), sign[b], kAndXnor);
+        }
+        const uint32_t before = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
+        const uint32_t all = (uint32_t)(__builtin_popcount(lo) + __builtin_popcount(hi));
+        const uint32_t prev = counters[d];
+        wavefront_sync();                                  // (every lane has read before the first of its group writes)
+        if (before == 0u) counters[d] = (uint16_t)(prev + all);
+        wavefront_sync();
+        rank[r] = prev + before;
+    }
+}
+
+// The counters of W wavefronts -> byte offset of the first (wavefront, digit) place in the ordered tile; threads 0 ..
+// 255, one digit each, return the tile's keys with their digit (`count`) and the place of the first (`start`).  `early`
+// is called with the count as soon as it is known.
+template <int W, class Early>
+__device__ __forceinline__ void scan_counters(uint16_t (*counters)[kDigits], uint32_t *s_part, uint32_t &count, uint32_t &start, Early early)
+{
+    const int d = threadIdx.x, lane = d & 63, wave = d >> 6;
+    count = start = 0u;
+    uint32_t inc = 0u;
+    if (d < kDigits) {
+#pragma unroll
+        for (int w = 0; w < W; ++w) count += counters[w][d];
+        early(count);
+        inc = wave_inclusive_scan(count);
+        if (lane == 63) s_part[wave] = inc;
+    }
+    __syncthreads();
+    if (d < kDigits) {
+        start = inc - count;
+        for (int w = 0; w < wave; ++w) start += s_part[w];
+        uint32_t at = 4u * start;
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            const uint32_t c = counters[w][d];
+            counters[w][d] = (uint16_t)at;
+            at += 4u * c;
+        }
+    }
+    __syncthreads();
+}
+
+// Key r of this lane to its place in the ordered tile; at[r]: its rank, then the byte offset of the place.
+template <int ITEMS>
+__device__ __forceinline__ void put_in_order(const uint32_t (&key)[ITEMS], Digit g, const uint16_t *counters, uint32_t *order, uint32_t (&at)[ITEMS])
+{
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+        uint32_t k = key[r];
+        asm("" : "+v"(k));                                 // (the digit's address is not kept from the ranking on: 16 registers)
+        at[r] = 4u * at[r] + counters[digit_of(k, g)];
+        *(uint32_t *)((char *)order + at[r]) = k;
+    }
+}
+
+// ------------------------------------------------------------------------- digit histograms
+
+struct HistArgs {
+    const uint32_t *keys, *vals;
+    uint32_t *keys_copy, *vals_copy;      // null, or where the keys (and payloads) are copied for an odd number of passes
+    uint32_t *hist;                       // [pass][digit], zero before
+    uint32_t *status;                     // status words of all passes, zeroed here (16-byte aligned)
+    uint64_t n, status_quads;
+    Passes P;
+    bool stream;                          // as in PassArgs
+};
+
+// All passes' digit counts in one reading of the keys: the counts do not change when keys change places.  A digit has
+// 16 counters in LDS, chosen by lane: equal digits in a wavefront (the common case in the high bytes of small keys)
+// meet four at a time and not all 64, and random ones meet less often in a bank.  What bounds it is the four LDS
+// additions per key.  2^22 keys in all, payloads on top: 8 counters per digit and workgroups of 256 cost 13 us more, 32
+// counters (one workgroup per compute unit) 2 us more; 1024 workgroups instead of 512 add as much again in the final
+// additions to the same 1024 words.
+constexpr int kHistCopies = 16, kHistThreads = 1024, kHistGrid = 512;
+__global__ __launch_bounds__(kHistThreads) void digit_histograms_kernel(HistArgs H)
+{
+    __shared__ uint32_t s_hist[kMaxPasses * kDigits * kHistCopies];
+    for (int i = threadIdx.x; i < kMaxPasses * kDigits * kHistCopies; i += kHistThreads) s_hist[i] = 0u;
+    __syncthreads();
+    const uint64_t stride = (uint64_t)gridDim.x * kHistThreads, t0 = (uint64_t)blockIdx.x * kHistThreads + threadIdx.x;
+    const uint32_t copy = threadIdx.x & (kHistCopies - 1);
+    auto add = [&](uint32_t key) {
+#pragma unroll
+        for (int p = 0; p < kMaxPasses; ++p)
+            if (p < H.P.count) atomicAdd(&s_hist[((uint32_t)p * kDigits + digit_of(key, H.P.digit[p])) * kHistCopies + copy], 1u);
+    };
+    const uint64_t quads = H.n / 4;
+    const u32x4 *keys4 = (const u32x4 *)H.keys;
+    // the next four keys are on their way while four are counted
+    u32x4 next = {0u, 0u, 0u, 0u};
+    auto load = [&](uint64_t i) {
+        if (i < quads) next = H.stream ? __builtin_nontemporal_load(keys4 + i) : keys4[i];
+    };
+    load(t0);
+    for (uint64_t i = t0; i < quads; i += stride) {
+        const u32x4 k = next;
+        load(i + stride);
+        if (H.keys_copy) ((u32x4 *)H.keys_copy)[i] = k;
+        add(k[0]); add(k[1]); add(k[2]); add(k[3]);
+    }
+    if (t0 < (H.n & 3u)) {
+        const uint64_t i = 4 * quads + t0;
+        const uint32_t k = H.keys[i];
+        if (H.keys_copy) H.keys_copy[i] = k;
+        add(k);
+    }
+    if (H.vals_copy)
+        for (uint64_t i = t0; i < H.n; i += stride) H.vals_copy[i] = H.vals[i];
+    for (uint64_t i = t0; i < H.status_quads; i += stride) ((u32x4 *)H.status)[i] = u32x4{0u, 0u, 0u, 0u};
+    __syncthreads();
+    for (int i = threadIdx.x; i < H.P.count * kDigits; i += kHistThreads) {
+        uint32_t sum = 0u;
+#pragma unroll
+        for (int c = 0; c < kHistCopies; ++c) sum += s_hist[i * kHistCopies + c];
+        if (sum) atomicAdd(&H.hist[i], sum);
+    }
+}
+
+// ------------------------------------------------------------------------- one pass over the array
+
+// Status words, one per tile and digit: 2 state bits on top (0 = not published), the value below.  32-bit words hold
+// counts of up to 2^30 keys, 64-bit words all there are.
+constexpr uint32_t kCountOfTile = 1u, kCountUpToTile = 2u;
+template <class Word> struct StatusWord {
+    static constexpr int kStateAt = 8 * (int)sizeof(Word) - 2;
+    static __device__ __forceinline__ Word make(uint32_t state, uint32_t value) { return ((Word)state << kStateAt) | value; }
+    static __device__ __forceinline__ uint32_t state(Word w) { return (uint32_t)(w >> kStateAt); }
+    static __device__ __forceinline__ uint32_t value(Word w) { return (uint32_t)(w & (((Word)1 << kStateAt) - 1)); }
+};
+
+struct PassArgs {
+    const uint32_t *keys, *vals;
+    uint32_t *keys_out, *vals_out;
+    void *status;                         // this pass's status words (zero before)
+    const uint32_t *hist;                 // this pass's digit counts over the whole array
+    uint32_t *ticket;                     // null, or the counter the workgroups draw their tile from (zero before)
+    uint32_t *fault;                      // null (one tile), or the workspace's fault word
+    uint64_t n;
+    uint32_t spin_limit;
+    Digit digit;
+    bool stream;                          // the arrays do not fit the memory-side cache: keys are read around it
+};
+
+template <int ITEMS>
+__device__ __forceinline__ void load_rows(const uint32_t *src, uint32_t first, uint32_t valid, bool whole, bool stream, uint32_t fill, uint32_t (&x)[ITEMS])
+{
+    if (whole && stream) {                                 // straight-line loads
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) x[r] = __builtin_nontemporal_load(src + first + 64u * r);
+    } else if (whole) {
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) x[r] = src[first + 64u * r];
+    } else {
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) x[r] = first + 64u * r < valid ? src[first + 64u * r] : fill;
+    }
+}
+
+// Predecessors asked for at a time: 4.  Every word of a window is 1 KiB of traffic over the 256 digits, and words behind
+// the nearest prefix are asked for in vain (2^26 keys: 4 819, 2 831, 8 877, 16 1074 us per sort).
+constexpr int kWindow = 4;
+
+// The status words of digit `d` in tiles t, t - 1, ... (a tile before the first counts as "nothing up to here").  Offsets
+// are 32 bits: the words of 2^32 keys are less than 2^32 bytes.
+template <class Word>
+__device__ __forceinline__ void request_window(const Word *status, uint32_t d, int32_t t, Word (&w)[kWindow])
+{
+#pragma unroll
+    for (int u = 0; u < kWindow; ++u)
+        w[u] = t - u >= 0 ? __hip_atomic_load((const Word *)((const char *)status + ((uint32_t)(t - u) * kDigits + d) * (uint32_t)sizeof(Word)),
+                                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                          : StatusWord<Word>::make(kCountUpToTile, 0u);
+}
+
+// Keys with this thread's digit in front of the tile (those with smaller digits, anywhere, among them: tile 0 starts
+// from there).  `w` holds the window that was requested at tile t = tile - 1.
+template <class Word>
+__device__ __forceinline__ uint32_t digit_look_back(const Word *status, uint32_t d, int32_t t, Word (&w)[kWindow], const PassArgs &A)
+{
+    using S = StatusWord<Word>;
+    uint32_t sum = 0u, spins = 0u;
+    for (;;) {
+        bool found = false, waiting = false;
+#pragma unroll
+        for (int u = 0; u < kWindow; ++u) {
+            if (!found && !waiting) {
+                const uint32_t state = S::state(w[u]);
+                if (state == 0u) waiting = true;
+                else { sum += S::value(w[u]); --t; found = state == kCountUpToTile; }
+            }
+        }
+        if (found) return sum;
+        if (waiting) {
+            if (++spins > A.spin_limit) {                  // never in correct operation: give up instead of hanging
+                if (A.fault) __hip_atomic_store(A.fault, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                return sum;
+            }
+            __builtin_amdgcn_s_sleep(1);
+        }
+        request_window(status, d, t, w);
+    }
+}
+
+// What bounds a pass: writing 256 ranges of a tile each in pieces of 64 keys (2^26 keys: 150 us a pass; with the same
+// tiles written back in a row 111 us, and without the ranking on top 100 us, which is the device's copy rate; the
+// carry chain is 12 us of it).  The tile is therefore as large as two workgroups per compute unit allow: 16 wavefronts
+// of 16 rows, 73 KiB of LDS, and the register allocator is held to 64 registers so that all 32 wavefronts are resident
+// (at 101 registers one workgroup was, 215 us a pass); 8192 keys per tile: 18 us a pass more, 12288: 15 us more.
+template <int W, int ITEMS, bool VALS, class Word>
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(sizeof(Word) == 4 ? 8 : 4))) void digit_pass_kernel(PassArgs A)
+{
+    using S = StatusWord<Word>;
+    using Place = Word;                    // byte offsets in the destination: 32 bits hold those of 2^30 keys
+    constexpr int kThreads = 64 * W;
+    constexpr uint32_t kTile = kThreads * ITEMS;
+    static_assert(W >= 4 && kTile <= 16384u, "one thread per digit; byte offsets inside a tile are 16 bits");
+    __shared__ uint32_t s_order[kTile];
+    __shared__ uint16_t s_cnt[W][kDigits];
+    __shared__ Place s_dest[kDigits];
+    __shared__ uint32_t s_part[4], s_abort;
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (tid == 0) s_abort = 0u;
+    uint32_t tile = blockIdx.x;
+    if (A.ticket) {
+        if (tid == 0) s_part[0] = __hip_atomic_fetch_add(A.ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        tile = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_part[0]);
+        __syncthreads();
+    }
+    const uint64_t base = (uint64_t)tile * kTile;
+    const uint32_t valid = A.n - base < kTile ? (uint32_t)(A.n - base) : kTile;
+    const Digit g = A.digit;
+
+    // ---- the keys, in rows of 64 per wavefront; keys past the end have the highest digit and come last among its keys
+    const uint32_t first = (uint32_t)wave * 64u * ITEMS + (uint32_t)lane;
+    uint32_t key[ITEMS], at[ITEMS];
+    load_rows<ITEMS>(A.keys + base, first, valid, valid == kTile, A.stream, ~0u, key);
+    ((uint64_t *)s_cnt[wave])[lane] = 0u;
+    wavefront_sync();
+    rank_rows<ITEMS>(key, g, s_cnt[wave], at);
+    __syncthreads();
+
+    // ---- counters -> places; the chain sets out (thread d: digit d)
+    Word *column = (Word *)A.status + (tid & (kDigits - 1));
+    Word win[kWindow];
+    uint32_t count, start;
+    scan_counters<W>(s_cnt, s_part, count, start, [&](uint32_t c) {
+        if (tile != 0u) {
+            __hip_atomic_store(column + (size_t)tile * kDigits, S::make(kCountOfTile, c), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            request_window((const Word *)A.status, (uint32_t)tid, (int32_t)tile - 1, win);
+        }
+    });
+
+    // ---- meanwhile the tile is put in order
+    put_in_order<ITEMS>(key, g, s_cnt[wave], s_order, at);
+    uint32_t val[VALS ? ITEMS : 1];
+    if constexpr (VALS) {
+        load_rows<ITEMS>(A.vals + base, first, valid, valid == kTile, A.stream, 0u, val);
+    }
+
+    // ---- the chain arrives: where the tile's keys of each digit go
+    uint32_t before = 0u;                                  // keys in front of the tile's first with this thread's digit
+    if (tile == 0u) {                                      // (uniform over the workgroup)
+        uint32_t h = 0u, inc = 0u;
+        if (tid < kDigits) {
+            h = A.hist[tid];
+            inc = wave_inclusive_scan(h);
+            if (lane == 63) s_part[wave] = inc;
+        }
+        __syncthreads();
+        if (tid < kDigits) {
+            before = inc - h;
+            for (int w = 0; w < wave; ++w) before += s_part[w];
+        }
+    } else if (tid < kDigits) {
+        before = digit_look_back((const Word *)A.status, (uint32_t)tid, (int32_t)tile - 1, win, A);
+    }
+    if (tid < kDigits) {
+        __hip_atomic_store(column + (size_t)tile * kDigits, S::make(kCountUpToTile, before + count), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        s_dest[tid] = (Place)(before - start) * 4u;        // (modulo: the place inside the tile is added to it)
+        // a digit's range lies inside the array, unless a look-back gave up: then nothing of the tile is stored
+        const uint32_t n32 = (uint32_t)A.n;
+        if (before > n32 || (valid == kTile && count > n32 - before)) s_abort = 1u;
+    }
+    __syncthreads();
+    if (s_abort) return;
+
+    // ---- out: consecutive threads write consecutive places of a digit's range
+    Place dst[VALS ? ITEMS : 1];
+    char *kout = (char *)A.keys_out, *vout = (char *)A.vals_out;
+    if (valid == kTile) {
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) {
+            const uint32_t i = (uint32_t)tid + (uint32_t)r * kThreads, k = s_order[i];
+            const Place to = s_dest[digit_of(k, g)] + 4u * i;
+            *(uint32_t *)(kout + to) = k;
+            if constexpr (VALS) dst[r] = to;
+        }
+    } else {
+        for (int r = 0; r < ITEMS; ++r) {
+            const uint32_t i = (uint32_t)tid + (uint32_t)r * kThreads, k = s_order[i];
+            const Place to = s_dest[digit_of(k, g)] + 4u * i;
+            if (i < valid && to / 4u < A.n) *(uint32_t *)(kout + to) = k;
+            if constexpr (VALS) dst[r] = to;
+        }
+    }
+    if constexpr (VALS) {
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) *(uint32_t *)((char *)s_order + at[r]) = val[r];
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) {
+            const uint32_t i = (uint32_t)tid + (uint32_t)r * kThreads;
+            if (valid == kTile || (i < valid && dst[r] / 4u < A.n)) *(uint32_t *)(vout + dst[r]) = s_order[i];
+        }
+    }
+}
+
+// ------------------------------------------------------------------------- a whole sort in one workgroup
+
+template <int ITEMS, bool VALS>
+__global__ __launch_bounds__(1024) void block_sort_kernel(uint32_t *keys, uint32_t *vals, uint32_t n, Passes P)
+{
+    constexpr int W = 16, kThreads = 64 * W;
+    constexpr uint32_t kTile = kThreads * ITEMS;
+    __shared__ uint32_t s_order[kTile];
+    __shared__ uint16_t s_cnt[W][kDigits];
+    __shared__ uint32_t s_part[4];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t first = (uint32_t)wave * 64u * ITEMS + (uint32_t)lane;
+    uint32_t key[ITEMS], val[VALS ? ITEMS : 1], at[ITEMS];
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+        const uint32_t i = first + 64u * r;
+        key[r] = i < n ? keys[i] : ~0u;                    // past the end: last in every pass
+        if constexpr (VALS) val[r] = i < n ? vals[i] : 0u;
+    }
+    for (int p = 0; p < P.count; ++p) {
+        const Digit g = P.digit[p];
+        ((uint64_t *)s_cnt[wave])[lane] = 0u;
+        wavefront_sync();
+        rank_rows<ITEMS>(key, g, s_cnt[wave], at);
+        __syncthreads();
+        uint32_t count, start;
+        scan_counters<W>(s_cnt, s_part, count, start, [](uint32_t) {});
+        put_in_order<ITEMS>(key, g, s_cnt[wave], s_order, at);
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) key[r] = s_order[first + 64u * r];
+        if constexpr (VALS) {
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < ITEMS; ++r) *(uint32_t *)((char *)s_order + at[r]) = val[r];
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < ITEMS; ++r) val[r] = s_order[first + 64u * r];
+        }
+        // (the next pass's writes to s_order come after its barriers)
+    }
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+        const uint32_t i = first + 64u * r;
+        if (i < n) {
+            keys[i] = key[r];
+            if constexpr (VALS) vals[i] = val[r];
+        }
+    }
+}
+
+// ------------------------------------------------------------------------- host side
+
+constexpr size_t kBlockSortMax = 16384;
+
+hipError_t launch_block_sort(uint32_t *keys, uint32_t *vals, uint32_t n, const Passes &P, hipStream_t s)
+{
+    const void *fn;
+    if (n <= 1024)      fn = vals ? (const void *)block_sort_kernel<1, true> : (const void *)block_sort_kernel<1, false>;
+    else if (n <= 4096) fn = vals ? (const void *)block_sort_kernel<4, true> : (const void *)block_sort_kernel<4, false>;
+    else                fn = vals ? (const void *)block_sort_kernel<16, true> : (const void *)block_sort_kernel<16, false>;
+    Passes passes = P;
+    void *args[] = {&keys, &vals, &n, &passes};
+    return hipLaunchKernel(fn, dim3(1), dim3(1024), args, 0, s);
+}
+
+// Keys per lane of a pass.  Few keys: many small tiles, so that all compute units have one and each is done sooner;
+// many keys: long ranges to write and fewer status words (us per sort of random keys, 4 / 8 / 16 keys per lane:
+// 100,000 38 / 41 / 53; 400,000 50 / 50 / 60; 1,000,003 69 / 66 / 75; 2^22 150 / 116 / 117, with payloads 162 / 126 / 132;
+// 2^23 242 / 173 / 145; 2^26 1704 / 1104 / 776).
+constexpr int kPassWaves = 16;
+int pass_items(size_t n) { return n <= ((size_t)1 << 19) ? 4 : n < ((size_t)5 << 20) ? 8 : 16; }
+
+template <int ITEMS> const void *pass_kernel_of(bool vals)
+{
+    return vals ? (const void *)digit_pass_kernel<kPassWaves, ITEMS, true, uint32_t> : (const void *)digit_pass_kernel<kPassWaves, ITEMS, false, uint32_t>;
+}
+const void *pass_kernel(int items, bool vals, bool wide)
+{
+    if (wide) return vals ? (const void *)digit_pass_kernel<kPassWaves, 16, true, uint64_t> : (const void *)digit_pass_kernel<kPassWaves, 16, false, uint64_t>;
+    return items == 4 ? pass_kernel_of<4>(vals) : items == 8 ? pass_kernel_of<8>(vals) : pass_kernel_of<16>(vals);
+}
+
+}  // namespace
+
+// Used by tcuscan_split_radix_sort_u32 (apps.hip), which has checked the arguments.  d_scratch: n words (4-byte aligned);
+// d_fault: the workspace's fault word (null where the call needs no workspace).
+extern "C" __attribute__((visibility("hidden")))
+tcuscan_status_t tcuscan_internal_digit_sort(void *d_keys, void *d_vals, size_t n, int bits, void *d_keys_tmp, void *d_vals_tmp,
+                                             void *d_scratch, void *d_fault, tcuscan_stream_t stream)
+{
+    hipStream_t s = (hipStream_t)stream;
+    Passes P;
+    P.count = (bits + 7) / 8;
+    for (int p = 0, at = 0; p < kMaxPasses; ++p) {                       // as even as possible
+        const int width = p < P.count ? (bits - at + (P.count - p) - 1) / (P.count - p) : 1;
+        P.digit[p] = {at < 32 ? at : 0, width};
+        at += width;
+    }
+    if (n <= kBlockSortMax)
+        return launch_block_sort((uint32_t *)d_keys, (uint32_t *)d_vals, (uint32_t)n, P, s) == hipSuccess ? TCUSCAN_OK : TCUSCAN_ERR_HIP;
+
+    unsigned use_tickets, spin_limit;
+    tcuscan_internal_chain_knobs(&use_tickets, &spin_limit);
+    const bool wide = n >= ((size_t)1 << 30);
+    const int items = pass_items(n);
+    const size_t tile = (size_t)64 * kPassWaves * items, tiles = (n + tile - 1) / tile;
+    // Arrays that do not fit the memory-side cache (256 MiB) together are read around it, which leaves it to the pieces
+    // that are being written: 2^26 keys 815 -> 776 us, 2^25 407 -> 395, 2^24 with payloads 314 -> 296, 2^25 with payloads 691
+    // -> 595; below, what one pass wrote is what the next one finds there (2^24 keys: 224 against 229, 2^23 with payloads
+    // 169 against 175).
+    const bool around_cache = n * (d_vals ? 16 : 8) > ((size_t)192 << 20);
+    // scratch: digit counts of the passes, ticket counters, then status words from the next 16-byte boundary on
+    uint32_t *hist = (uint32_t *)d_scratch, *tickets = hist + kMaxPasses * kDigits;
+    uint32_t *status = (uint32_t *)(((uintptr_t)(tickets + kMaxPasses) + 15) & ~(uintptr_t)15);
+    const size_t pass_words = tiles * kDigits * (wide ? 2 : 1);
+    if (tcuscan_internal_fill(hist, 4 * (kMaxPasses * kDigits + kMaxPasses), s) != hipSuccess) return TCUSCAN_ERR_HIP;
+
+    uint32_t *src_k = (uint32_t *)d_keys, *dst_k = (uint32_t *)d_keys_tmp, *src_v = (uint32_t *)d_vals, *dst_v = (uint32_t *)d_vals_tmp;
+    const bool odd = P.count & 1;                                        // the first pass then starts from a copy, and the last ends at home
+    {
+        HistArgs H;
+        H.keys = src_k; H.vals = src_v;
+        H.keys_copy = odd ? dst_k : nullptr; H.vals_copy = odd && src_v ? dst_v : nullptr;
+        H.hist = hist; H.status = status; H.n = n; H.status_quads = pass_words * P.count / 4; H.P = P; H.stream = around_cache;
+        void *args[] = {&H};
+        const size_t want = (n / 4 + 2 * kHistThreads - 1) / (2 * kHistThreads);
+        const unsigned grid = (unsigned)(want < 1 ? 1 : want < kHistGrid ? want : kHistGrid);
+        if (hipLaunchKernel((const void *)digit_histograms_kernel, dim3(grid), dim3(kHistThreads), args, 0, s) != hipSuccess) return TCUSCAN_ERR_HIP;
+    }
+    if (odd) {
+        uint32_t *t = src_k; src_k = dst_k; dst_k = t;
+        t = src_v; src_v = dst_v; dst_v = t;
+    }
+    for (int p = 0; p < P.count; ++p) {
+        PassArgs A;
+        A.keys = src_k; A.vals = src_v; A.keys_out = dst_k; A.vals_out = dst_v;
+        A.status = status + pass_words * p; A.hist = hist + kDigits * p;
+        A.ticket = use_tickets ? tickets + p : nullptr;
+        A.fault = (uint32_t *)d_fault;
+        A.n = n; A.spin_limit = spin_limit; A.digit = P.digit[p]; A.stream = around_cache;
+        void *args[] = {&A};
+        if (hipLaunchKernel(pass_kernel(items, d_vals != nullptr, wide), dim3((unsigned)tiles), dim3(64 * kPassWaves), args, 0, s) != hipSuccess)
+            return TCUSCAN_ERR_HIP;
+        uint32_t *t = src_k; src_k = dst_k; dst_k = t;
+        t = src_v; src_v = dst_v; dst_v = t;
+    }
+    return TCUSCAN_OK;
+}

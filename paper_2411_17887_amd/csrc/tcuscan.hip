@@ -42,6 +42,7 @@
 
 #include "../../include/tcuscan.h"
 #include "chain_tags.h"
+#include "wave_ops.h"
 
 namespace {
 
@@ -95,54 +96,6 @@ struct TileDesc {
     uint32_t pad[2];
 };
 static_assert(sizeof(TileDesc) == 32, "descriptor size");
-
-// ---------------------------------------------------------------- small helpers
-
-template <class To, class From> __device__ __forceinline__ To bits(From v) { return __builtin_bit_cast(To, v); }
-
-template <int CTRL> __device__ __forceinline__ uint32_t dpp0(uint32_t v)
-{   // lanes whose DPP source does not exist receive 0
-    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, false);
-}
-constexpr int kRowShr = 0x110;   // DPP control: shift right by n lanes inside each row of 16
-
-__device__ __forceinline__ float    acc_add(float a, float b)       { return a + b; }
-__device__ __forceinline__ uint32_t acc_add(uint32_t a, uint32_t b) { return a + b; }
-__device__ __forceinline__ uint32_t acc_bits(float a)    { return bits<uint32_t>(a); }
-__device__ __forceinline__ uint32_t acc_bits(uint32_t a) { return a; }
-template <class A> __device__ __forceinline__ A acc_from_bits(uint32_t b);
-template <> __device__ __forceinline__ float    acc_from_bits<float>(uint32_t b)    { return bits<float>(b); }
-template <> __device__ __forceinline__ uint32_t acc_from_bits<uint32_t>(uint32_t b) { return b; }
-
-template <class A, int CTRL> __device__ __forceinline__ A dpp_shr(A v) { return acc_from_bits<A>(dpp0<CTRL>(acc_bits(v))); }
-
-// Sum over the 64 lanes, returned wave-uniform.  Row-local DPP shifts give every row's total in its
-// lane 15; row_bcast15 / row_bcast31 fold the four row totals into lane 63.
-constexpr int kRowBcast15 = 0x142, kRowBcast31 = 0x143;
-template <class A> __device__ __forceinline__ A wave_inclusive_scan(A v)
-{   // lane l receives v[0] + ... + v[l]
-    v = acc_add(v, dpp_shr<A, kRowShr + 1>(v));
-    v = acc_add(v, dpp_shr<A, kRowShr + 2>(v));
-    v = acc_add(v, dpp_shr<A, kRowShr + 4>(v));
-    v = acc_add(v, dpp_shr<A, kRowShr + 8>(v));
-    v = acc_add(v, acc_from_bits<A>((uint32_t)__builtin_amdgcn_update_dpp(0, (int)acc_bits(v), kRowBcast15, 0xa, 0xf, false)));
-    v = acc_add(v, acc_from_bits<A>((uint32_t)__builtin_amdgcn_update_dpp(0, (int)acc_bits(v), kRowBcast31, 0xc, 0xf, false)));
-    return v;
-}
-template <class A> __device__ __forceinline__ A wave_sum(A v)
-{
-    return acc_from_bits<A>((uint32_t)__builtin_amdgcn_readlane((int)acc_bits(wave_inclusive_scan(v)), 63));
-}
-constexpr int kWaveShr1 = 0x138;   // DPP control: shift right by one lane across the whole wavefront
-template <class A> __device__ __forceinline__ A wave_shift_up(A v)
-{   // lane l receives v[l - 1], lane 0 receives 0
-    return dpp_shr<A, kWaveShr1>(v);
-}
-
-template <class A> __device__ __forceinline__ A uniform_from_lane(A v, int lane)
-{   // wave-uniform copy of one lane's value
-    return acc_from_bits<A>((uint32_t)__builtin_amdgcn_readlane((int)acc_bits(v), lane));
-}
 
 // ------------------------------------------------------------------- dtype traits
 //
@@ -1208,306 +1161,6 @@ __global__ __launch_bounds__(64 * W) void split_kernel(Params P, SplitArgs S)
         load_run_words<NT>(lane, S.vals + base, rem, 0u, val);
         split_order<NT, kSlot, true>(lane, Aop, g, val, zeros_run, rem, s_pack[wave], lb, false);
         split_store<true>(lane, s_pack[wave], S.vals_out, zero_at, one_at, zeros_run, valid, n);
-    }
-}
-
-// ---- the split on two bits at once: four buckets per pass, half the passes
-//
-// The same reduction with a digit of two bits: keys go to four consecutive ranges by digit, old order kept inside
-// each.  Four flag vectors ("digit is d") would be four scans; they are one-hot, so two of them share a byte -- flag
-// of digit 0 (2) as 1, of digit 1 (3) as 64 -- and one product with the strict triangular blocks returns both counts
-// of earlier keys inside the granule (each below 16) in separate bit fields.  Granule totals come from the totals
-// operand the same way; from there on (16-lane scans, blocks, runs, workgroup) two counts travel in the halves of one
-// 32-bit word.  The carry chain has four values per tile: the four words share the tile's status slot, and the first
-// four wavefronts of a workgroup publish and look back for one digit each, at the same time.
-
-struct Split4Args {
-    const uint32_t *keys, *vals;       // vals may be null
-    uint32_t *keys_out, *vals_out;
-    const uint32_t *hist;              // number of keys with digit 0, 1, 2, 3 at this position (whole array)
-    int bit;                           // position of the digit's low bit
-};
-
-// 16 digit positions x 4 digits: counts[4 j + d] = keys whose bits 2j+1, 2j are d.  Digits 1, 2 and 3 are counted
-// (digit 0 is the rest): a key becomes three words with one bit per digit position ("the digit here is d", at the even
-// bits), and the bits of such words are added up in fields that widen as they fill: two keys' words in the 2-bit
-// fields they come in, the four keys of a load and up to three loads in 4-bit fields (even and odd positions in a
-// word each), 63 loads in byte-wide counters -- bits s, s + 8, s + 16, s + 24 in the four bytes of one word, for s = 0,
-// 2, 4, 6 -- which are emptied into 32-bit counters before a byte can overflow.  (With every key's words going
-// straight into the byte counters the kernel was bound by the vector unit: 46 instructions per key, 99 us for 2^26
-// keys.)
-__global__ __launch_bounds__(256) void digit_counts_kernel(const uint32_t *__restrict__ keys, size_t n, uint32_t *counts)
-{
-    __shared__ uint32_t s_cnt[64];
-    if (threadIdx.x < 64) s_cnt[threadIdx.x] = 0u;
-    __syncthreads();
-    uint32_t cnt[3][16];                                      // [digit - 1][position]
-#pragma unroll
-    for (int d = 0; d < 3; ++d)
-#pragma unroll
-        for (int j = 0; j < 16; ++j) cnt[d][j] = 0u;
-    // four keys per step (one 16-byte load per lane; the array is 16-byte aligned), the last n mod 4 keys by one thread
-    const size_t stride = (size_t)gridDim.x * blockDim.x, quads = n / 4;
-    const u32x4 *keys4 = (const u32x4 *)keys;
-    for (size_t i0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i0 < quads + 1; i0 += 63u * stride) {
-        uint32_t packed[3][4];                                // [digit - 1][s / 2]: byte b counts position s / 2 + 4 b
-#pragma unroll
-        for (int d = 0; d < 3; ++d)
-#pragma unroll
-            for (int k = 0; k < 4; ++k) packed[d][k] = 0u;
-        size_t i = i0;
-        for (int grp = 0; grp < 21 && i < quads + 1; ++grp) {                 // 21 x 3 loads of 4 keys: a byte counter stays below 256
-            uint32_t even[3] = {0u, 0u, 0u}, odd[3] = {0u, 0u, 0u};           // 4-bit fields: positions 0, 2, .. 14 / 1, 3, .. 15
-            u32x4 kqs[3];                                                     // 3 x 4 keys: a 4-bit field stays below 16; the loads side by side
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                const size_t ik = i + (size_t)k * stride;
-                kqs[k] = u32x4{0u, 0u, 0u, 0u};                               // (a key of 0 has digit 0 everywhere: counted by nobody)
-                if (ik < quads) kqs[k] = keys4[ik];
-                else if (ik == quads) { const uint32_t have = (uint32_t)(n - 4 * quads); for (uint32_t j = 0; j < have; ++j) kqs[k][j] = keys[4 * quads + j]; }
-            }
-            i += 3 * stride;
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                const u32x4 kq = kqs[k];
-                uint32_t is[4][3];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const uint32_t lo = kq[j] & 0x55555555u, hi = (kq[j] >> 1) & 0x55555555u;
-                    is[j][0] = lo & ~hi; is[j][1] = hi & ~lo; is[j][2] = lo & hi;
-                }
-#pragma unroll
-                for (int d = 0; d < 3; ++d) {
-                    const uint32_t a = is[0][d] + is[1][d], b = is[2][d] + is[3][d];      // 2-bit fields, at most 2 each
-                    even[d] += (a & 0x33333333u) + (b & 0x33333333u);
-                    odd[d] += ((a >> 2) & 0x33333333u) + ((b >> 2) & 0x33333333u);
-                }
-            }
-#pragma unroll
-            for (int d = 0; d < 3; ++d) {
-                packed[d][0] += even[d] & 0x0F0F0F0Fu;
-                packed[d][2] += (even[d] >> 4) & 0x0F0F0F0Fu;
-                packed[d][1] += odd[d] & 0x0F0F0F0Fu;
-                packed[d][3] += (odd[d] >> 4) & 0x0F0F0F0Fu;
-            }
-        }
-#pragma unroll
-        for (int d = 0; d < 3; ++d)
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-#pragma unroll
-                for (int b = 0; b < 4; ++b) cnt[d][q + 4 * b] += (packed[d][q] >> (8 * b)) & 0xFFu;
-    }
-#pragma unroll
-    for (int d = 0; d < 3; ++d)
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const uint32_t w = wave_sum(cnt[d][j]);
-            if ((threadIdx.x & 63) == 0 && w) atomicAdd(&s_cnt[4 * j + d + 1], w);
-        }
-    __syncthreads();
-    if (threadIdx.x < 64 && (threadIdx.x & 3) && s_cnt[threadIdx.x]) atomicAdd(&counts[threadIdx.x], s_cnt[threadIdx.x]);
-}
-
-// counts[4 j] = n - counts[4 j + 1] - counts[4 j + 2] - counts[4 j + 3]
-__global__ void digit_zero_counts_kernel(uint32_t *counts, size_t n)
-{
-    const int j = threadIdx.x;
-    if (j < 16) counts[4 * j] = (uint32_t)n - counts[4 * j + 1] - counts[4 * j + 2] - counts[4 * j + 3];
-}
-
-// The words x of one wavefront's run put in order in the wavefront's slot: digit 0's first, then digit 1's, 2's, 3's,
-// each in the old order (cnt[d] of them).  Nothing here depends on where the ranges go in the destination, so this
-// runs while the tile's predecessors are still publishing: if `polling`, the chain is polled once per result block.
-// `slots` is the workgroup's array of slots and slot0 this wavefront's first word in it: positions are kept as word
-// offsets into the array, two to a register (16-bit halves), so that picking the one for a key's digit is one byte
-// permute.  Words past the end of a ragged run go to the slot's spare last word.
-template <int NT, uint32_t SLOT, class Chain>
-__device__ __forceinline__ void split4_order(int lane, const typename Tr<TCUSCAN_I8_I32>::AConst &Aex, const u32x4 (&gA)[NT],
-                                             const u32x4 (&gB)[NT], const u32x4 (&key)[NT][4], int bit, const u32x4 (&x)[NT][4],
-                                             const uint32_t (&cnt)[4], uint32_t rem, uint32_t *slots, uint32_t slot0, Chain &chain, bool polling)
-{
-    using T = Tr<TCUSCAN_I8_I32>;
-    const bool ragged = rem < NT * 1024u;
-    uint32_t runA = slot0 | ((slot0 + cnt[0]) << 16);                 // where the next key of digit 0 / 1 goes (two halves)
-    uint32_t runB = (slot0 + cnt[0] + cnt[1]) | ((slot0 + cnt[0] + cnt[1] + cnt[2]) << 16);      // ... of digit 2 / 3
-    const uint32_t in_blk = 16u * (lane & 15) + 4u * (lane >> 4);
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        const u32x4 ttA = bits<u32x4>(T::totals(Aex, gA[t])), ttB = bits<u32x4>(T::totals(Aex, gB[t]));
-#pragma unroll
-        for (int p = 0; p < T::kBlocks; ++p) {
-            const i32x4 z = {0, 0, 0, 0};                            // same-digit keys before this one in its granule:
-            const i32x4 dA = __builtin_amdgcn_mfma_i32_16x16x64_i8(Aex.a[p], bits<i32x4>(gA[t]), z, 0, 0, 0);   // result block p
-            const i32x4 dB = __builtin_amdgcn_mfma_i32_16x16x64_i8(Aex.a[p], bits<i32x4>(gB[t]), z, 0, 0, 0);
-            const uint32_t pairA = (ttA[p] & 63u) | ((ttA[p] >> 6) << 16), pairB = (ttB[p] & 63u) | ((ttB[p] >> 6) << 16);
-            const uint32_t exA = row_exclusive_scan(pairA), exB = row_exclusive_scan(pairB);
-            const uint32_t blkA = uniform_from_lane(exA + pairA, 15), blkB = uniform_from_lane(exB + pairB, 15);
-            const uint32_t baseA = runA + exA, baseB = runB + exB;
-            const uint32_t idx0 = (uint32_t)t * 1024u + 256u * p + in_blk;
-            uint32_t at[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const uint32_t d = (key[t][p][r] >> bit) & 3u;
-                // half d of {baseB : baseA}: bytes 2 d and 2 d + 1 of the pair, zeros above
-                const uint32_t bs = __builtin_amdgcn_perm(baseB, baseA, 0x0c0c0100u + 0x0202u * d);
-                // the four 6-bit counts of the two products side by side, field d of them
-                const uint32_t ranks = (uint32_t)dA[r] | ((uint32_t)dB[r] << 12);
-                at[r] = bs + ((ranks >> (6u * d)) & 63u);
-            }
-            if (ragged) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    if (idx0 + r >= rem) at[r] = slot0 + SLOT - 1u;
-            }
-#pragma unroll
-            for (int r = 0; r < 4; ++r) slots[at[r]] = x[t][p][r];
-            runA += blkA; runB += blkB;
-            if (polling) chain.poll();
-        }
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// The four ordered ranges of the slot to the destination: digit d's from dst[at0[d]] on.
-__device__ __forceinline__ void split4_store(int lane, const uint32_t *slot, uint32_t *dst, const uint64_t (&at0)[4], const uint32_t (&cnt)[4],
-                                             uint64_t n)
-{
-    uint32_t q = 0u;
-#pragma unroll
-    for (int d = 0; d < 4; ++d) {
-        const uint64_t room = at0[d] < n ? n - at0[d] : 0u;
-        split_store_range(lane, slot, q, cnt[d], dst + at0[d], (uint32_t)(room < 0x40000000ull ? room : 0x40000000ull));
-        q += cnt[d];
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-template <int NT, int W, bool VALS>
-__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(VALS ? 1 : 4))) void split4_kernel(Params P, Split4Args S)
-{
-    constexpr int DT = TCUSCAN_I8_I32;
-    using T = Tr<DT>;
-    static_assert(T::kBlocks == 4 && W >= 4, "four result blocks of 256 per MFMA tile; one wavefront per digit for the carry chain");
-    constexpr uint32_t kEPW = NT * Geo<DT>::kTileElems;
-    constexpr uint32_t kSlot = kEPW + 16u;                      // the run in order, and a spare last word
-    static_assert(W * kSlot < 65536u, "positions in the workgroup's slots travel in 16-bit halves");
-    __shared__ uint32_t s_cnt[W][2];
-    __shared__ uint32_t s_prefix[4];
-    __shared__ __attribute__((aligned(16))) uint32_t s_pack[W][kSlot];
-
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const uint32_t tile = take_tile(P, &s_prefix[0]), tag = P.tag;
-    const uint64_t n = P.cols;
-    const uint64_t base = ((uint64_t)tile * W + wave) * kEPW;                       // first key of this wavefront's run
-    const uint32_t rem = base < n ? (n - base < 0x40000000ull ? (uint32_t)(n - base) : 0x40000000u) : 0u;
-    const int bit = S.bit;
-    const uint32_t in_blk = 16u * (lane & 15) + 4u * (lane >> 4);
-    const bool ragged = rem < kEPW;
-
-    // ---- the keys; their digit flags as bytes for the two products; this lane's keys per digit
-    u32x4 key[NT][4], gA[NT], gB[NT];
-    __builtin_amdgcn_s_setprio(3);                  // loads first, as in scan_kernel
-    load_run_words<NT>(lane, S.keys + base, rem, ~0u, key);
-    __builtin_amdgcn_s_setprio(0);
-    uint32_t sumA = 0u, sumB = 0u;
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        uint32_t wA[4], wB[4];
-#pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            // the four digits in the four bytes of one word, then all four flag bytes at once: 1 or 64 by the digit's
-            // low bit, to stream B where its high bit is set and to stream A where it is not
-            uint32_t dig = 0u;
-            for (int i = 0; i < 4; ++i) dig |= ((key[t][p][i] >> bit) & 3u) << (8 * i);
-            uint32_t one = 0x01010101u + 63u * (dig & 0x01010101u);
-            if (ragged) {
-                const uint32_t idx0 = (uint32_t)t * 1024u + 256u * p + in_blk;            // keys past the end: no flag
-                const uint32_t have = idx0 >= rem ? 0u : (rem - idx0 >= 4u ? 4u : rem - idx0);
-                one &= have == 4u ? ~0u : ((1u << (8u * have)) - 1u);
-            }
-            const uint32_t high = ((dig >> 1) & 0x01010101u) * 255u;
-            wB[p] = one & high;
-            wA[p] = one ^ wB[p];
-            sumA = __builtin_amdgcn_udot4(wA[p], 0x01010101u, sumA, false);    // bytes added up: digit 0 (2) counts 1, digit 1 (3) counts 64
-            sumB = __builtin_amdgcn_udot4(wB[p], 0x01010101u, sumB, false);
-        }
-        gA[t] = rows_transpose(wA);
-        gB[t] = rows_transpose(wB);
-    }
-    static_assert(NT * 16 < 64, "a lane's keys per digit stay below 64: the two counts of a byte sum do not mix");
-    const uint32_t c01 = (sumA & 63u) | ((sumA >> 6) << 16), c23 = (sumB & 63u) | ((sumB >> 6) << 16);
-    const uint32_t run01 = wave_sum(c01), run23 = wave_sum(c23);                    // at most 2048 per half
-    if (lane == 0) { s_cnt[wave][0] = run01; s_cnt[wave][1] = run23; }
-    __syncthreads();
-    uint32_t off01 = 0u, off23 = 0u, wg01 = 0u, wg23 = 0u;
-#pragma unroll
-    for (int w = 0; w < W; ++w) {
-        const uint32_t v01 = s_cnt[w][0], v23 = s_cnt[w][1];
-        if (w < wave) { off01 += v01; off23 += v23; }
-        wg01 += v01; wg23 += v23;
-    }
-
-    // ---- the carry chain sets out: wavefront d < 4 publishes the tile's count of digit d in its word of the tile's
-    // status slot and asks for the words of the tiles before
-    const bool chained = P.num_tiles > 1 && wave < 4;
-    uint64_t *row_status = (uint64_t *)(P.ws + 1) + (wave & 3);
-    const uint32_t mine = ((wave & 2 ? wg23 : wg01) >> (16 * (wave & 1))) & 0xFFFFu;
-    LookBackPoll<uint32_t> lb;
-    lb.done = true;
-    if (chained) {
-        if (lane == 0)
-            __hip_atomic_store(row_status + (size_t)tile * kStatusStride, status_word(tag, tile == 0 ? kStatePrefix : kStateAggregate, mine),
-                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        lb.start(row_status, (int)tile, tag);
-    }
-
-    // ---- meanwhile the run is put in order in the slot
-    uint32_t cnt[4];
-#pragma unroll
-    for (int d = 0; d < 4; ++d)
-        cnt[d] = (uint32_t)__builtin_amdgcn_readfirstlane((int)(((d & 2 ? run23 : run01) >> (16 * (d & 1))) & 0xFFFFu));
-    const typename T::AConst Aex = T::make(lane, true, false);
-    split4_order<NT, kSlot>(lane, Aex, gA, gB, key, bit, key, cnt, rem, &s_pack[0][0], (uint32_t)wave * kSlot, lb, chained);
-
-    // ---- the chain arrives
-    uint32_t prefix[4] = {0u, 0u, 0u, 0u};
-    if (P.num_tiles > 1) {
-        if (wave < 4) {
-            const uint32_t pre = lb.finish(P.ws, P.spin_limit);
-            if (lane == 0) {
-                if (tile != 0)
-                    __hip_atomic_store(row_status + (size_t)tile * kStatusStride, status_word(tag, kStatePrefix, pre + mine),
-                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                s_prefix[wave] = pre;
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int d = 0; d < 4; ++d) prefix[d] = s_prefix[d];
-    }
-
-    // ---- where this run's keys of each digit go: behind the smaller digits of the whole array, the same digit of the
-    // tiles before, of the wavefronts before
-    uint64_t at0[4];
-    uint64_t bucket = 0u;
-#pragma unroll
-    for (int d = 0; d < 4; ++d) {
-        const uint32_t off = ((d & 2 ? off23 : off01) >> (16 * (d & 1))) & 0xFFFFu;
-        at0[d] = bucket + prefix[d] + off;
-        bucket += S.hist[d];
-    }
-    split4_store(lane, s_pack[wave], S.keys_out, at0, cnt, n);
-    if constexpr (VALS) {
-        u32x4 val[NT][4];
-        load_run_words<NT>(lane, S.vals + base, rem, 0u, val);
-        split4_order<NT, kSlot>(lane, Aex, gA, gB, key, bit, val, cnt, rem, &s_pack[0][0], (uint32_t)wave * kSlot, lb, false);
-        split4_store(lane, s_pack[wave], S.vals_out, at0, cnt, n);
     }
 }
 
@@ -2773,41 +2426,14 @@ tcuscan_status_t tcuscan_internal_split_pass(const void *d_keys, const void *d_v
     return hipLaunchKernel(fn, dim3(P.num_tiles), dim3(64 * W), args, 0, s) == hipSuccess ? TCUSCAN_OK : TCUSCAN_ERR_HIP;
 }
 
+// Used by the sort (sort.hip): clearing, and the process-wide settings of the carry chain.
 extern "C" __attribute__((visibility("hidden")))
-tcuscan_status_t tcuscan_internal_digit_counts(const void *d_keys, size_t n, unsigned *d_counts64, tcuscan_stream_t stream)
-{
-    hipStream_t s = (hipStream_t)stream;
-    if (launch_fill(d_counts64, 64 * sizeof(unsigned), s) != hipSuccess) return TCUSCAN_ERR_HIP;
-    const uint32_t *k = (const uint32_t *)d_keys; uint32_t *c = d_counts64;
-    void *args[] = {&k, &n, &c};
-    // 512 workgroups: every workgroup ends with 48 atomic adds on the same 48 counters, and with 2048 of them those were
-    // a third of the run time (2^26 keys: 84 us against 70)
-    const unsigned grid = (unsigned)((n + 255) / 256 < 512 ? (n + 255) / 256 : 512);
-    if (hipLaunchKernel((const void *)digit_counts_kernel, dim3(grid), dim3(256), args, 0, s) != hipSuccess) return TCUSCAN_ERR_HIP;
-    void *args2[] = {&c, &n};
-    return hipLaunchKernel((const void *)digit_zero_counts_kernel, dim3(1), dim3(64), args2, 0, s) == hipSuccess ? TCUSCAN_OK : TCUSCAN_ERR_HIP;
-}
-
+hipError_t tcuscan_internal_fill(void *d, size_t bytes, hipStream_t s) { return launch_fill(d, bytes, s); }
 extern "C" __attribute__((visibility("hidden")))
-tcuscan_status_t tcuscan_internal_split4_pass(const void *d_keys, const void *d_vals, void *d_keys_out, void *d_vals_out, size_t n, int bit,
-                                              const unsigned *d_hist4, void *d_ws, size_t ws_bytes, tcuscan_stream_t stream)
+void tcuscan_internal_chain_knobs(unsigned *ticket, unsigned *spin_limit)
 {
-    // Keys alone: 8 wavefronts per workgroup, and the register allocator is held to 128 registers so that two workgroups
-    // (64.5 KiB of LDS each) share a compute unit (a dozen spilled registers; without the limit one workgroup: 208 us
-    // per pass of 2^26 keys against 177).  With payloads, which cost 32 registers more, 4 wavefronts per workgroup.
-    constexpr int NT = kFlagNT;
-    const int W = d_vals ? 4 : kFlagW;
-    hipStream_t s = (hipStream_t)stream;
-    Params P;
-    const tcuscan_status_t st = flag_kernel_params(P, n, (size_t)NT * W * 1024, d_ws, ws_bytes, s);
-    if (st != TCUSCAN_OK) return st;
-    Split4Args S;
-    S.keys = (const uint32_t *)d_keys; S.vals = (const uint32_t *)d_vals;
-    S.keys_out = (uint32_t *)d_keys_out; S.vals_out = (uint32_t *)d_vals_out;
-    S.hist = d_hist4; S.bit = bit;
-    void *args[] = {&P, &S};
-    const void *fn = d_vals ? (const void *)split4_kernel<NT, 4, true> : (const void *)split4_kernel<NT, kFlagW, false>;
-    return hipLaunchKernel(fn, dim3(P.num_tiles), dim3(64 * W), args, 0, s) == hipSuccess ? TCUSCAN_OK : TCUSCAN_ERR_HIP;
+    *ticket = g_chain_policy.load(std::memory_order_relaxed) == 1 ? 1u : 0u;
+    *spin_limit = g_spin_limit.load(std::memory_order_relaxed);
 }
 
 // Used by tcuscan_compact_u32 (apps.hip) when the caller does not ask for the positions: one pass over the mask

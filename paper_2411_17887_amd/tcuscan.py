@@ -234,14 +234,14 @@ def set_segmented_form(flat: bool) -> None:
 
 
 def set_sort_fusion(form: int) -> None:
-    """1: fused split passes on two bits (default); 2: fused passes on one bit; 0: mask kernel + scan + scatter kernel."""
+    """1: passes on eight bits (default); 2: fused passes on one bit; 0: mask kernel + scan + scatter kernel."""
     rc = load().tcuscan_set_sort_fusion(int(form))
     if rc != OK:
         raise TcuscanError(rc, "tcuscan_set_sort_fusion")
 
 
 def split_radix_sort_u32(keys, keys_tmp, flags, positions, vals=None, vals_tmp=None, bits: int = 32, ws=None, stream=None) -> None:
-    """Stable LSD radix sort of 32-bit keys (and optional payloads) by `bits` split passes, one mask scan each."""
+    """Stable LSD radix sort of 32-bit keys (and optional payloads) by its low `bits` bits, eight (one: set_sort_fusion) per pass."""
     rc = load().tcuscan_split_radix_sort_u32(_ptr(keys), _ptr(vals), keys.numel(), int(bits), _ptr(keys_tmp), _ptr(vals_tmp),
                                              _ptr(flags), _ptr(positions), *_ws_args(ws), _stream(stream))
     if rc != OK:
