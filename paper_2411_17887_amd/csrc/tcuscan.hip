@@ -82,6 +82,7 @@ struct Params {
     uint32_t    spin_limit;  // look-back polls per status word before the wait gives up and raises the fault word
     uint32_t    mute_tile;   // test hook: the tile with this index does not publish its status word (kNoTile: none)
     uint32_t    reverse;     // non-zero: suffix sums (every row is scanned from its end)
+    uint32_t    line = 0;    // non-zero: rows are tiled from the 128-byte line of the output they start in (see row_lead)
     WsHeader   *ws;          // null when tiles_per_row == 1
     // segmented scans only: what every tile has to know about its row (built by seg_desc_kernel)
     const struct TileDesc *tile_desc;
@@ -703,10 +704,26 @@ __device__ __forceinline__ Run make_run(const Params &P, uint64_t row, uint64_t 
 // (fewer than one granule) are read as zero and never written -- BatchMatMul's zero-pad, at the front -- and every
 // full granule behind them takes the 128-bit path.  With both base pointers 16-byte aligned the outputs line up too:
 // lead = off mod (elements per granule), and (off - lead) outputs are a whole number of 16-byte groups.
+//
+// `line`: from the 128-byte line of the OUTPUT the row starts in, fewer than 32 elements in front of it, so that store
+// instructions write whole lines (the memory pays for a partial line with a read: 2-D arrays whose rows start at
+// 16-byte boundaries inside lines ran 8 .. 17 % slower than the same amount of work in whole lines).  The host asks for it
+// 4095 x 65537 bf16 from the end 283 -> 265 us, 4096 x 32769 i32 195 -> 172, 300 x 1,000,004 f32 418 -> 394, 127,000 x 2101 f32
+// 395 -> 367 (with the short-row kernel's tile counts and order of rows).  The host asks for it
+// when the input is 16-byte aligned wherever the output is line aligned (line_compatible); a row whose line starts
+// before the arrays is tiled from the 16-byte boundary like any other.
+__host__ __device__ __forceinline__ uint32_t row_lead(uintptr_t in_addr, uintptr_t out_addr, uint32_t esz, long long off, bool line)
+{
+    if (line) {
+        const uint32_t l = (uint32_t)((out_addr + 4u * (uint64_t)off) & 127u) / 4u;
+        if (off >= (long long)l) return l;
+    }
+    return (uint32_t)((in_addr + (uint64_t)off * esz) & 15u) / esz;
+}
 template <int DT>
 __device__ __forceinline__ uint32_t seg_lead(const Params &P, long long off)
 {
-    return (uint32_t)((((uintptr_t)P.in + (uint64_t)off * Tr<DT>::kEsz) & 15) / Tr<DT>::kEsz);
+    return row_lead((uintptr_t)P.in, (uintptr_t)P.out, Tr<DT>::kEsz, off, P.line != 0u);
 }
 template <int DT>
 __device__ __forceinline__ Run make_seg_run(const Params &P, long long off, uint64_t len, uint32_t lead, uint64_t base)
@@ -1739,7 +1756,17 @@ __global__ __launch_bounds__(kThreads) void scan_rows_kernel(Params P)
     using A = typename T::acc;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const uint64_t row = (uint64_t)blockIdx.x * kWaves + wave;
+    // Workgroups are handed out to the eight dies in turn, and each die has an L2 of its own: neighbouring rows that share
+    // a line should meet in one.  64 consecutive workgroups' rows go to one die (262,144 x 1001 f32 391 -> 370 us, 131,072 x
+    // 2047 bf16 289 -> 278); a call of a few thousand rows is over before it matters.
+    uint32_t block = blockIdx.x;
+    if constexpr (LEAD && NT > 1) {
+        constexpr uint32_t kDies = 8u, kRun = 64u;
+        const uint32_t in = block % (kDies * kRun), group = block - in;
+        const uint64_t blocks = (P.rows + kWaves - 1) / kWaves;        // (the grid; asking for gridDim is a load more: 0.4 us)
+        if (blocks >= 4096u && group + kDies * kRun <= blocks) block = group + (in % kDies) * kRun + in / kDies;
+    }
+    const uint64_t row = (uint64_t)block * kWaves + wave;
     if (row >= P.rows) return;
     u32x4 g[NT];
     const typename T::AConst Aop = T::make(lane, EXCL, REV);
@@ -1782,8 +1809,8 @@ __global__ __launch_bounds__(kThreads) void scan_rows_kernel(Params P)
 // caller's arrays.  Entry `rows` is zero: the exclusive scan of this array then ends with the total number of tiles.
 // Tiles of row r (a row is tiled from the 16-byte boundary at or below its first element); offsets that leave the
 // arrays or run backwards get no tiles and raise fault word 2.
-__device__ __forceinline__ int32_t seg_row_tiles(const long long *offsets, size_t r, size_t total, uintptr_t in_addr, uint32_t esz,
-                                                 uint32_t tile, WsHeader *ws)
+__device__ __forceinline__ int32_t seg_row_tiles(const long long *offsets, size_t r, size_t total, uintptr_t in_addr, uintptr_t out_addr,
+                                                 uint32_t esz, uint32_t line, uint32_t tile, WsHeader *ws)
 {
     const long long off = offsets[r], end = offsets[r + 1];
     if (off < 0 || end < off || (unsigned long long)end > total) {
@@ -1791,7 +1818,7 @@ __device__ __forceinline__ int32_t seg_row_tiles(const long long *offsets, size_
         return 0;
     }
     if (end == off) return 0;
-    const uint64_t lead = ((in_addr + (uint64_t)off * esz) & 15) / esz;
+    const uint64_t lead = row_lead(in_addr, out_addr, esz, off, line != 0u);
     return (int32_t)((lead + (uint64_t)(end - off) + tile - 1) / tile);
 }
 
@@ -1813,12 +1840,12 @@ __device__ __forceinline__ TileDesc seg_tile_desc(const uint32_t *tile_start, co
     return d;
 }
 
-__global__ void seg_tiles_kernel(const long long *offsets, size_t rows, size_t total, uintptr_t in_addr, uint32_t esz,
-                                 uint32_t tile, int32_t *counts, WsHeader *ws)
+__global__ void seg_tiles_kernel(const long long *offsets, size_t rows, size_t total, uintptr_t in_addr, uintptr_t out_addr, uint32_t esz,
+                                 uint32_t line, uint32_t tile, int32_t *counts, WsHeader *ws)
 {
     const size_t r = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (r > rows) return;
-    counts[r] = r < rows ? seg_row_tiles(offsets, r, total, in_addr, esz, tile, ws) : 0;
+    counts[r] = r < rows ? seg_row_tiles(offsets, r, total, in_addr, out_addr, esz, line, tile, ws) : 0;
 }
 __global__ void seg_desc_kernel(const uint32_t *tile_start, const long long *offsets, size_t rows, TileDesc *desc, uint32_t max_tiles)
 {
@@ -1832,8 +1859,8 @@ __global__ void seg_desc_kernel(const uint32_t *tile_start, const long long *off
 // workgroup works out the first tile of every row by itself -- kSegPrepRows / 1024 rows per thread, one scan over the
 // workgroup in LDS -- and then writes the descriptors and clears the status slots of its own 1024 tiles.
 constexpr size_t kSegPrepRows = 4096;                  // rows + 1 entries must fit: calls with fewer rows than this
-__global__ __launch_bounds__(1024) void seg_prepare_kernel(const long long *offsets, size_t rows, size_t total, uintptr_t in_addr, uint32_t esz,
-                                                           uint32_t tile, TileDesc *desc, uint32_t max_tiles, WsHeader *ws)
+__global__ __launch_bounds__(1024) void seg_prepare_kernel(const long long *offsets, size_t rows, size_t total, uintptr_t in_addr,
+                                                           uintptr_t out_addr, uint32_t esz, uint32_t line, uint32_t tile, TileDesc *desc, uint32_t max_tiles, WsHeader *ws)
 {
     constexpr int kPer = (int)(kSegPrepRows / 1024);
     __shared__ uint32_t s_start[kSegPrepRows + 1];
@@ -1843,7 +1870,7 @@ __global__ __launch_bounds__(1024) void seg_prepare_kernel(const long long *offs
 #pragma unroll
     for (int j = 0; j < kPer; ++j) {
         const size_t r = (size_t)kPer * threadIdx.x + j;
-        c[j] = r < rows ? (uint32_t)seg_row_tiles(offsets, r, total, in_addr, esz, tile, ws) : 0u;
+        c[j] = r < rows ? (uint32_t)seg_row_tiles(offsets, r, total, in_addr, out_addr, esz, line, tile, ws) : 0u;
         mine += c[j];
     }
     const uint32_t incl = wave_inclusive_scan(mine);
@@ -1992,21 +2019,42 @@ template <int DT, int NT, int W> const void *scan_kernel_for(bool excl, bool rev
     return excl ? (const void *)scan_kernel<DT, NT, true, false, W> : (const void *)scan_kernel<DT, NT, false, false, W>;
 }
 
-template <int DT, int NT> hipError_t launch_rows_nt(Params P, bool excl, bool lead, hipStream_t s)
+template <int DT, int NT> hipError_t launch_rows_lead(Params P, bool excl, hipStream_t s)
 {
     void *args[] = {&P};
-    const void *fn = lead ? rows_kernel_for<DT, NT, true>(excl, P.reverse != 0) : rows_kernel_for<DT, NT, false>(excl, P.reverse != 0);
+    return hipLaunchKernel(rows_kernel_for<DT, NT, true>(excl, P.reverse != 0), dim3((unsigned)((P.rows + kWaves - 1) / kWaves)), dim3(kThreads), args, 0, s);
+}
+template <int DT, int NT> hipError_t launch_rows_nt(Params P, bool excl, bool lead, hipStream_t s)
+{
+    if (lead) return launch_rows_lead<DT, NT>(P, excl, s);
+    void *args[] = {&P};
+    const void *fn = rows_kernel_for<DT, NT, false>(excl, P.reverse != 0);
     return hipLaunchKernel(fn, dim3((unsigned)((P.rows + kWaves - 1) / kWaves)), dim3(kThreads), args, 0, s);
 }
 
 template <int DT> hipError_t launch_rows(Params P, bool excl, hipStream_t s)
 {
-    // rows that start at 16-byte boundaries take the plain form; the others are tiled from the boundary below their
-    // start, which can cost one more MFMA tile
-    const bool lead = ((uintptr_t)P.in & 15) != 0 || (P.cols * Tr<DT>::kEsz) % 16 != 0;
-    const size_t tiles = (P.cols + (lead ? Tr<DT>::kG - 1 : 0) + Geo<DT>::kTileElems - 1) / Geo<DT>::kTileElems;
+    // Rows that start at 16-byte boundaries take the plain form; the others are tiled from the boundary below their
+    // start, which can cost one more MFMA tile.  Rows that start inside a line of the output are tiled from the line
+    // when that costs no tile on top (500,000 x 501 i32, 2 tiles: 351 us, 382 with three) and they are longer than a
+    // tile (2,000,000 x 101 f32: 634 against 700).  The tiles of these forms are counted out -- a masked tile is not free --
+    // and not rounded up to 1, 2, 4, 8 or 12 (160,000 x 1501 bf16 275 -> 261).
+    constexpr size_t kTile = Geo<DT>::kTileElems;
+    const bool off_granule = ((uintptr_t)P.in & 15) != 0 || (P.cols * Tr<DT>::kEsz) % 16 != 0;
+    const size_t tiles = (P.cols + (off_granule ? Tr<DT>::kG - 1 : 0) + kTile - 1) / kTile;
+    if (tiles == 1 || (P.cols + 31 + kTile - 1) / kTile > tiles) P.line = 0u;
+    const bool lead = P.line || off_granule;
     if (tiles <= 1) return launch_rows_nt<DT, 1>(P, excl, lead, s);
     if (tiles <= 2) return launch_rows_nt<DT, 2>(P, excl, lead, s);
+    if (lead && tiles == 3) return launch_rows_lead<DT, 3>(P, excl, s);
+    if constexpr (Tr<DT>::kEsz > 1)
+        if (lead && tiles == 5) return launch_rows_lead<DT, 5>(P, excl, s);
+    if constexpr (Tr<DT>::kEsz == 4) {
+        if (lead && tiles == 6) return launch_rows_lead<DT, 6>(P, excl, s);
+        if (lead && tiles == 7) return launch_rows_lead<DT, 7>(P, excl, s);
+        if (lead && tiles == 9) return launch_rows_lead<DT, 9>(P, excl, s);
+        if (lead && tiles == 10) return launch_rows_lead<DT, 10>(P, excl, s);
+    }
     if (tiles <= 4) return launch_rows_nt<DT, 4>(P, excl, lead, s);
     if (tiles <= 8) return launch_rows_nt<DT, 8>(P, excl, lead, s);
     return launch_rows_nt<DT, 12>(P, excl, lead, s);
@@ -2087,8 +2135,18 @@ struct Plan {
     int path;            // TCUSCAN_PATH_*
     int seg_cls;         // tiles from the boundary below: which tile (kSegSmall / kSegLarge)
     size_t tpr, need;    // ... tiles per row (the row and the elements in front of it) and workspace bytes they take
+    bool line;           // ... from the 128-byte line of the output (row_lead)
 };
 Plan plan_for(uintptr_t in_addr, size_t rows, size_t cols, int dt, bool ws_usable, size_t ws_bytes);     // below, with the segmented launches
+void plan_lines(Plan &plan, size_t rows, size_t cols, int dt, bool ws_usable, size_t ws_bytes);
+// Outputs (words) from which rows are tiled from lines of the output: 32 MiB, what the dies' L2s hold together.  Below,
+// parts of a line are put together there anyway, and the call is as long as its launch (5000 x 701 bf16: 7.1 us, 7.5 from
+// lines).
+constexpr size_t kLinesFrom = (size_t)8 << 20;
+// Some row of the output starts or ends inside a 128-byte line.
+bool rows_cross_lines(uintptr_t out_addr, size_t rows, size_t cols) { return (out_addr & 127) != 0 || (rows > 1 && (cols * 4) % 128 != 0); }
+// Wherever the output is line aligned, the input is 16-byte aligned.
+bool line_compatible(uintptr_t in_addr, uintptr_t out_addr, size_t esz) { return ((in_addr + ((0 - out_addr) & 127) / 4 * esz) & 15) == 0; }
 tcuscan_status_t run_unaligned_rows(const void *d_in, void *d_out, size_t rows, size_t cols, int dt, int exclusive, int reverse, void *d_ws,
                                     const Plan &plan, bool clear_first, hipStream_t s);
 
@@ -2110,9 +2168,12 @@ tcuscan_status_t run(const void *d_in, void *d_out, size_t rows, size_t cols, in
     if (need && (!ws_usable || ws_bytes < need)) return TCUSCAN_ERR_WORKSPACE;
 
     hipStream_t s = (hipStream_t)stream;
-    const Plan plan = plan_for((uintptr_t)d_in, rows, cols, dt, ws_usable, ws_bytes);
-    // long rows that do not start at 16-byte boundaries: tiled from the boundary below, like segmented rows
-    if (plan.path == TCUSCAN_PATH_TILES_FROM_BOUNDARY)
+    Plan plan = plan_for((uintptr_t)d_in, rows, cols, dt, ws_usable, ws_bytes);
+    const bool line = rows * cols >= kLinesFrom && rows_cross_lines((uintptr_t)d_out, rows, cols) && line_compatible((uintptr_t)d_in, (uintptr_t)d_out, in_size(dt));
+    if (line) plan_lines(plan, rows, cols, dt, ws_usable, ws_bytes);
+    // long rows that do not start at 16-byte boundaries, or inside a line of the output: tiled from the boundary below,
+    // like segmented rows
+    if (plan.path == TCUSCAN_PATH_TILES_FROM_BOUNDARY || plan.line)
         return run_unaligned_rows(d_in, d_out, rows, cols, dt, exclusive, reverse, d_ws, plan, clear_first, s);
     const int size = choose_tile(dt, rows, cols);
     const size_t tile = tile_elems(dt, size);
@@ -2122,6 +2183,7 @@ tcuscan_status_t run(const void *d_in, void *d_out, size_t rows, size_t cols, in
     P.tiles_per_row = (uint32_t)tpr; P.num_tiles = (uint32_t)(rows * tpr);
     P.ws = need ? (WsHeader *)d_ws : nullptr;
     P.reverse = reverse ? 1u : 0u;
+    P.line = line ? 1u : 0u;                                             // (only rows of one wavefront each look at it)
     P.tile_desc = nullptr;
     // Every call gets a fresh tag, so status words of earlier calls are stale by construction.
     const tcuscan_status_t bst = begin_chain(P, P.ws && tpr > 1 ? d_ws : nullptr, rows * tpr, clear_first, s);
@@ -2254,6 +2316,15 @@ tcuscan_status_t run_segmented_flat(const void *d_in, void *d_out, const long lo
     return hipLaunchKernel(fn, dim3(P.num_tiles), dim3(64 * kFlatW), args, 0, s) == hipSuccess ? TCUSCAN_OK : TCUSCAN_ERR_HIP;
 }
 
+// The tile for such rows.  8- and 16-bit inputs: small or large as the plain tiles' rule has it (us, small / large: 500 x
+// 400,001 bf16 239 / 220, i8 229 / 182; 4 x 600,001 bf16 8.0 / 16.7, i8 7.5 / 14.9), with the large one in place of the huge.
+// 32-bit: large from 2^19 on (500 x 400,001 f32 348 / 340, but 17 x 323,410 i32 10.1 / 11.1).
+int unaligned_tile(int dt, size_t rows, size_t cols)
+{
+    if (in_size(dt) == 4) return cols < ((size_t)1 << 19) ? kSegSmall : kSegLarge;
+    return choose_tile(dt, rows, cols) == kTileSmall ? kSegSmall : kSegLarge;
+}
+
 // Equal rows of a batched call that do not start at 16-byte boundaries (odd row length, unaligned array) and are too
 // long for one wavefront each: the segmented kernel without descriptors (it derives the row from the tile index), so
 // that every full granule takes the 128-bit path (element by element such rows run at 22 .. 40 % of peak instead of
@@ -2262,12 +2333,12 @@ tcuscan_status_t run_segmented_flat(const void *d_in, void *d_out, const long lo
 // other tile size is tried, and failing that the call is left to the element-wise path.
 Plan plan_for(uintptr_t in_addr, size_t rows, size_t cols, int dt, bool ws_usable, size_t ws_bytes)
 {
-    Plan plan = {TCUSCAN_PATH_TILES, kSegSmall, 0, 0};
+    Plan plan = {TCUSCAN_PATH_TILES, kSegSmall, 0, 0, false};
     const size_t row_max = in_size(dt) == 4 ? kShortRowMax32 : in_size(dt) == 1 ? kShortRowMax8 : kShortRowMax;
     if (rows >= kShortRowMinRows && cols <= row_max) { plan.path = TCUSCAN_PATH_ROWS; return plan; }
     if ((in_addr & 15) == 0 && (rows <= 1 || (cols * in_size(dt)) % 16 == 0)) return plan;       // every row starts at a 16-byte boundary
     // the tile the row-length rule picks, or the other one if the workspace only has the status words for that
-    int cls = cols < ((size_t)1 << 19) ? kSegSmall : kSegLarge;
+    int cls = unaligned_tile(dt, rows, cols);
     for (int attempt = 0; attempt < 2; ++attempt, cls = cls == kSegSmall ? kSegLarge : kSegSmall) {
         const size_t tile = seg_tile_elems(dt, cls), granule = 16 / in_size(dt);
         const size_t tpr = (cols + granule - 1 + tile - 1) / tile;
@@ -2281,6 +2352,18 @@ Plan plan_for(uintptr_t in_addr, size_t rows, size_t cols, int dt, bool ws_usabl
     return plan;
 }
 
+// Rows of the tile paths that start inside lines of the output are tiled from the line where the workspace has the status
+// words for it; a plan that has none stays as it is.
+void plan_lines(Plan &plan, size_t rows, size_t cols, int dt, bool ws_usable, size_t ws_bytes)
+{
+    if (plan.path != TCUSCAN_PATH_TILES && plan.path != TCUSCAN_PATH_TILES_FROM_BOUNDARY) return;
+    const int cls = plan.path == TCUSCAN_PATH_TILES_FROM_BOUNDARY ? plan.seg_cls : unaligned_tile(dt, rows, cols);
+    const size_t tile = seg_tile_elems(dt, cls), tpr = (cols + 31 + tile - 1) / tile;
+    const size_t need = tpr > 1 ? sizeof(WsHeader) + 8 * kStatusStride * rows * tpr : 0;
+    if (rows * tpr > 0x7FFFFFFFull || rows > 0x7FFFFFFFull || (need && (!ws_usable || ws_bytes < need))) return;
+    plan.seg_cls = cls; plan.tpr = tpr; plan.need = need; plan.line = true;
+}
+
 tcuscan_status_t run_unaligned_rows(const void *d_in, void *d_out, size_t rows, size_t cols, int dt, int exclusive, int reverse, void *d_ws,
                                     const Plan &plan, bool clear_first, hipStream_t s)
 {
@@ -2291,6 +2374,7 @@ tcuscan_status_t run_unaligned_rows(const void *d_in, void *d_out, size_t rows, 
     P.tiles_per_row = (uint32_t)tpr; P.num_tiles = (uint32_t)(rows * tpr);
     P.ws = need ? (WsHeader *)d_ws : nullptr;
     P.reverse = reverse ? 1u : 0u;
+    P.line = plan.line ? 1u : 0u;
     P.tile_desc = nullptr;
     const tcuscan_status_t bst = begin_chain(P, need ? d_ws : nullptr, rows * tpr, clear_first, s);
     if (bst != TCUSCAN_OK) return bst;
@@ -2328,17 +2412,18 @@ tcuscan_status_t run_segmented(const void *d_in, void *d_out, const long long *d
     uint32_t *starts = (uint32_t *)((char *)d_ws + L.starts_off);
     TileDesc *desc = (TileDesc *)((char *)d_ws + L.rowmap_off);
     const bool few_rows = rows < kSegPrepRows;
+    uint32_t line = total >= kLinesFrom && line_compatible((uintptr_t)d_in, (uintptr_t)d_out, in_size(dt)) ? 1u : 0u;
     if (few_rows) {   // steps 1 - 3 and the clearing of the status words in one launch
-        const long long *off = d_offsets; size_t r = rows, t = total; uintptr_t in_addr = (uintptr_t)d_in;
+        const long long *off = d_offsets; size_t r = rows, t = total; uintptr_t in_addr = (uintptr_t)d_in, out_addr = (uintptr_t)d_out;
         uint32_t esz = (uint32_t)in_size(dt), tl = (uint32_t)tile, mt = (uint32_t)L.max_tiles; WsHeader *h = (WsHeader *)d_ws;
-        void *args[] = {&off, &r, &t, &in_addr, &esz, &tl, &desc, &mt, &h};
+        void *args[] = {&off, &r, &t, &in_addr, &out_addr, &esz, &line, &tl, &desc, &mt, &h};
         if (hipLaunchKernel((const void *)seg_prepare_kernel, dim3((unsigned)((L.max_tiles + 1023) / 1024)), dim3(1024), args, 0, s) != hipSuccess)
             return TCUSCAN_ERR_HIP;
     } else {
         {   // step 1: tiles per row
-            const long long *off = d_offsets; size_t r = rows, t = total; uintptr_t in_addr = (uintptr_t)d_in;
+            const long long *off = d_offsets; size_t r = rows, t = total; uintptr_t in_addr = (uintptr_t)d_in, out_addr = (uintptr_t)d_out;
             uint32_t esz = (uint32_t)in_size(dt), tl = (uint32_t)tile; WsHeader *h = (WsHeader *)d_ws;
-            void *args[] = {&off, &r, &t, &in_addr, &esz, &tl, &counts, &h};
+            void *args[] = {&off, &r, &t, &in_addr, &out_addr, &esz, &line, &tl, &counts, &h};
             if (hipLaunchKernel((const void *)seg_tiles_kernel, dim3((unsigned)((rows + 1 + 255) / 256)), dim3(256), args, 0, s) != hipSuccess)
                 return TCUSCAN_ERR_HIP;
         }
@@ -2360,6 +2445,7 @@ tcuscan_status_t run_segmented(const void *d_in, void *d_out, const long long *d
     P.tiles_per_row = 0; P.num_tiles = (uint32_t)L.max_tiles;
     P.ws = (WsHeader *)d_ws;
     P.reverse = reverse ? 1u : 0u;
+    P.line = line;
     P.tile_desc = desc;
     const tcuscan_status_t bst = begin_chain(P, d_ws, L.max_tiles, true, s, nullptr, 0, few_rows);
     if (bst != TCUSCAN_OK) return bst;

@@ -1,0 +1,41 @@
+"""Rows whose outputs start inside 128-byte lines: tiled from the line below (or from the 16-byte boundary of the input)."""
+import pytest
+
+from paper_2411_17887_amd import tcuscan
+
+pytestmark = pytest.mark.gpu
+
+KINDS = ["i32", "f16", "i8", "f32", "bf16"]
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("flags", [0, 3])
+def test_rows_that_start_inside_output_lines(kind, flags):
+    """Rows tiled from the 128-byte line of the output: row lengths on either side of a line, of a tile and of the tile
+    counts the short-row kernel is built for; arrays whose input and output fit no common line; an output that starts
+    inside a line.  Exact integers, floats with small integer values (exact in every order)."""
+    import torch
+    tile = {"i8": 1024, "f16": 512, "bf16": 512}.get(kind, 256)
+    lengths = [tile - 1, tile + 1, 2 * tile - 33, 2 * tile - 31, 2 * tile + 1, 3 * tile - 5, 5 * tile // 2 + 1, 8192 - 31, 8192 - 1, 8192 + 33, 40000 + 1]
+    lengths += [k * tile - 16 for k in range(3, 12) if k * tile - 16 <= 2816]
+    for cols in lengths + [20 * tile + 7]:
+        rows = (8 << 20) // cols + 3                       # the form is taken from 2^23 outputs on
+        n = rows * cols
+        for shift_in, shift_out in ((0, 0), (0, 4), (16 // {"i8": 1, "f16": 2, "bf16": 2}.get(kind, 4), 8), (1, 1), (0, 1)):
+            g = torch.Generator(device="cuda")
+            g.manual_seed(cols + shift_in)
+            x = torch.randint(-3, 4, (n + shift_in,), generator=g, device="cuda").to(
+                {"i32": torch.int32, "i8": torch.int8, "f16": torch.float16, "bf16": torch.bfloat16, "f32": torch.float32}[kind])[shift_in:]
+            buf = torch.full((n + shift_out + 40,), -99, dtype=torch.int32 if kind in ("i32", "i8") else torch.float32, device="cuda")
+            out = buf[shift_out:shift_out + n]
+            ws = tcuscan.new_workspace(rows, cols, kind)
+            tcuscan.scan(x, out, rows, cols, kind, flags=flags, ws=ws)
+            ref = x.view(rows, cols).to(torch.int64)
+            if flags & tcuscan.REVERSE:
+                ref = ref.flip(1)
+            ref = torch.cumsum(ref, 1) - (ref if flags & tcuscan.EXCLUSIVE else 0)
+            if flags & tcuscan.REVERSE:
+                ref = ref.flip(1)
+            assert bool((out.view(rows, cols).to(torch.int64) == ref).all()), (kind, rows, cols, shift_in, shift_out)
+            assert bool((buf[:shift_out] == -99).all()) and bool((buf[shift_out + n:] == -99).all())
+            assert ws is None or tcuscan.workspace_fault(ws) == 0
