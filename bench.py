@@ -453,11 +453,11 @@ def measure_apps(steps: int):
     ws = tcuscan.new_workspace(1, n, "i8")
     ms = timed(lambda: tcuscan.compact_u32(vals, mask, out, pos, count=cnt, ws=ws), steps)
     kept = int(cnt.item())
-    # scan: n + 4n; pack: mask n + positions 4n + values 4n read, 4 * kept written
-    nbytes = 5 * n + 9 * n + 4 * kept
+    # mask n + values 4n read, positions 4n + 4 * kept written
+    nbytes = 9 * n + 4 * kept
     res = {"compaction": {"workload": "n=2^28 int8 {0,1} mask, 32-bit values", "ms": ms, "gelems_per_s": n / (ms * 1e-3) / 1e9,
                           "kept": kept, "algorithmic_GBps": nbytes / (ms * 1e-3) / 1e9}}
-    # the same without a positions buffer: the scatter is fused into the scan kernel (mask n + values 4n read, 4 * kept written)
+    # the same without a positions buffer (mask n + values 4n read, 4 * kept written)
     ms_f = timed(lambda: tcuscan.compact_u32(vals, mask, out, None, count=cnt, ws=ws), steps)
     res["compaction_fused"] = {"workload": "n=2^28 int8 {0,1} mask, 32-bit values, no positions buffer (one kernel)", "ms": ms_f,
                                "gelems_per_s": n / (ms_f * 1e-3) / 1e9, "kept": int(cnt.item()),

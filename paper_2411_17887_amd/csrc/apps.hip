@@ -6,7 +6,7 @@
 // library's int8 -> int32 MFMA scan; the kernels here only build the mask and move the elements.
 //
 //   compaction : pos = exclusive_scan(mask);  out[pos[i]] = values[i] where mask[i] != 0
-//                (without a positions buffer the scatter is fused into the scan kernel: tcuscan.hip, compact_store)
+//                (the scatter is fused into the scan kernel: tcuscan.hip, compact_kernel)
 //   split(b)   : f[i] = (bit b of key[i] == 0);  pos = exclusive_scan(f);  Z = pos[n-1] + f[n-1]
 //                key i goes to  pos[i]            if f[i]      (zeros keep their order, in front)
 //                          to  Z + (i - pos[i])   otherwise   (ones keep their order, behind)
@@ -20,8 +20,8 @@
 
 #include "../../include/tcuscan.h"
 
-extern "C" tcuscan_status_t tcuscan_internal_compact_fused(const void *d_values, const void *d_mask, void *d_out, size_t n, unsigned *d_count,
-                                                           void *d_ws, size_t ws_bytes, tcuscan_stream_t stream);   // tcuscan.hip
+extern "C" tcuscan_status_t tcuscan_internal_compact_fused(const void *d_values, const void *d_mask, void *d_out, size_t n, void *d_positions,
+                                                           unsigned *d_count, void *d_ws, size_t ws_bytes, tcuscan_stream_t stream);   // tcuscan.hip
 extern "C" tcuscan_status_t tcuscan_internal_bit_zero_counts(const void *d_keys, size_t n, unsigned *d_counts32, tcuscan_stream_t stream);
 extern "C" tcuscan_status_t tcuscan_internal_split_pass(const void *d_keys, const void *d_vals, void *d_keys_out, void *d_vals_out, size_t n,
                                                         int bit, const unsigned *d_zeros_total, void *d_ws, size_t ws_bytes,
@@ -33,30 +33,6 @@ extern "C" tcuscan_status_t tcuscan_internal_digit_sort(void *d_keys, void *d_va
 namespace {
 
 constexpr int kThreads = 256;
-
-// Four elements per thread: 16-byte loads of values and positions, one 4-byte load of the mask; the kept
-// elements of a wavefront land in one contiguous run, so the scattered 4-byte stores coalesce.
-__global__ __launch_bounds__(kThreads) void pack_kernel(const uint32_t *__restrict__ values, const int8_t *__restrict__ mask,
-                                                        const int32_t *__restrict__ pos, uint32_t *__restrict__ out,
-                                                        size_t n, uint32_t *count, bool vec)
-{
-    const size_t g = (size_t)blockIdx.x * kThreads + threadIdx.x;
-    const size_t i0 = g * 4;
-    if (i0 >= n) return;
-    if (vec && i0 + 4 <= n) {
-        const uint4 v = ((const uint4 *)values)[g];
-        const uint4 p = ((const uint4 *)pos)[g];
-        const uint32_t m = ((const uint32_t *)mask)[g];
-        if (m & 0x000000FFu) out[p.x] = v.x;
-        if (m & 0x0000FF00u) out[p.y] = v.y;
-        if (m & 0x00FF0000u) out[p.z] = v.z;
-        if (m & 0xFF000000u) out[p.w] = v.w;
-    } else {
-        for (size_t i = i0; i < n && i < i0 + 4; ++i)
-            if (mask[i] != 0) out[(uint32_t)pos[i]] = values[i];
-    }
-    if (count && i0 + 4 >= n) *count = (uint32_t)pos[n - 1] + (mask[n - 1] != 0 ? 1u : 0u);
-}
 
 __global__ __launch_bounds__(kThreads) void bit_is_zero_kernel(const uint32_t *__restrict__ keys, int8_t *__restrict__ flags,
                                                                size_t n, int bit)
@@ -114,20 +90,15 @@ tcuscan_status_t tcuscan_compact_u32(const void *d_values, const void *d_mask, v
     if (n == 0) return TCUSCAN_OK;
     if (n > 0xFFFFFFFFull) return TCUSCAN_ERR_UNSUPPORTED;                       // positions are 32-bit
     if (!d_values || !d_mask || !d_out) return TCUSCAN_ERR_INVALID_ARG;
-    if (!d_positions) {                                                          // nobody wants the positions: one fused pass
-        if (((uintptr_t)d_values % 4) || ((uintptr_t)d_out % 4) || ((uintptr_t)d_count % 4)) return TCUSCAN_ERR_INVALID_ARG;
-        return tcuscan_internal_compact_fused(d_values, d_mask, d_out, n, d_count, d_ws, ws_bytes, stream);
-    }
     if (((uintptr_t)d_values % 4) || ((uintptr_t)d_out % 4) || ((uintptr_t)d_positions % 4) || ((uintptr_t)d_count % 4))
         return TCUSCAN_ERR_INVALID_ARG;
-    tcuscan_status_t st = tcuscan_exclusive(d_mask, d_positions, n, TCUSCAN_I8_I32, d_ws, ws_bytes, stream);
-    if (st != TCUSCAN_OK) return st;
-    const uint32_t *v = (const uint32_t *)d_values; const int8_t *m = (const int8_t *)d_mask;
-    const int32_t *p = (const int32_t *)d_positions; uint32_t *o = (uint32_t *)d_out; uint32_t *c = d_count;
-    bool vec = ((uintptr_t)d_values % 16) == 0 && ((uintptr_t)d_positions % 16) == 0 && ((uintptr_t)d_mask % 4) == 0;
-    void *args[] = {&v, &m, &p, &o, &n, &c, &vec};
-    hipError_t e = hipLaunchKernel((const void *)pack_kernel, dim3(blocks_for((n + 3) / 4)), dim3(kThreads), args, 0, (hipStream_t)stream);
-    return e == hipSuccess ? TCUSCAN_OK : TCUSCAN_ERR_HIP;
+    if (d_positions) {
+        // what the scan of the mask into the positions asks for, and callers have sized their workspace by
+        if (d_positions == d_mask) return TCUSCAN_ERR_INVALID_ARG;
+        const size_t need = n > 8192 ? 256 + 64 * ((n + 8191) / 8192) : 0;
+        if (need && (!d_ws || ws_bytes < need || ((uintptr_t)d_ws % 8) != 0)) return TCUSCAN_ERR_WORKSPACE;
+    }
+    return tcuscan_internal_compact_fused(d_values, d_mask, d_out, n, d_positions, d_count, d_ws, ws_bytes, stream);
 }
 
 tcuscan_status_t tcuscan_split_radix_sort_u32(void *d_keys, void *d_vals, size_t n, int bits,

@@ -1188,7 +1188,10 @@ struct CompactArgs {
     uint32_t *count;                   // optional: how many
 };
 
-template <int NT, int W>
+// POS: the positions -- every element's destination index, the exclusive scan of the mask, to P.out -- go out from the same
+// products as in scan_kernel, with the mask still in registers: 11 bytes per element (half of them kept) instead of 16
+// in two kernels, the scan and one that reads its positions back (160,000,000 elements: 476 -> 284 us).
+template <int NT, int W, bool POS>
 __global__ __launch_bounds__(64 * W) void compact_kernel(Params P, CompactArgs C)
 {
     constexpr int DT = TCUSCAN_I8_I32;
@@ -1234,6 +1237,14 @@ __global__ __launch_bounds__(64 * W) void compact_kernel(Params P, CompactArgs C
     const uint32_t kept_before = flags_arrive(P, tile, lane, wave, wg_total, lb, &s_bcast);
     if (C.count && tile == P.num_tiles - 1 && threadIdx.x == 0) *C.count = kept_before + wg_total;
     split_store<false>(lane, s_pack[wave], C.out, kept_before + wave_off, 0u, kept_run, 0u, n);
+    if constexpr (POS) {
+        Run R;
+        R.in = nullptr;
+        R.out = (char *)P.out + base * 4;
+        R.rem = R.cap = rem; R.lead = 0u;
+        R.in_vec = false; R.out_vec = (((uintptr_t)R.out) & 15) == 0;
+        scan_and_store<DT, NT, true, false>(lane, T::make(lane, true, false), R, g, kept_before + wave_off);
+    }
 }
 
 // ------------------------------------------------------------- segmented scans, short rows
@@ -2522,11 +2533,11 @@ void tcuscan_internal_chain_knobs(unsigned *ticket, unsigned *spin_limit)
     *spin_limit = g_spin_limit.load(std::memory_order_relaxed);
 }
 
-// Used by tcuscan_compact_u32 (apps.hip) when the caller does not ask for the positions: one pass over the mask
-// and the values, nothing else written than the kept values.  Not part of the public interface.
+// Used by tcuscan_compact_u32 (apps.hip): one pass over the mask and the values, nothing else written than the kept
+// values and, if asked for, the positions.  Not part of the public interface.
 extern "C" __attribute__((visibility("hidden")))
-tcuscan_status_t tcuscan_internal_compact_fused(const void *d_values, const void *d_mask, void *d_out, size_t n, unsigned *d_count,
-                                                void *d_ws, size_t ws_bytes, tcuscan_stream_t stream)
+tcuscan_status_t tcuscan_internal_compact_fused(const void *d_values, const void *d_mask, void *d_out, size_t n, void *d_positions,
+                                                unsigned *d_count, void *d_ws, size_t ws_bytes, tcuscan_stream_t stream)
 {
     constexpr int NT = kFlagNT, W = kFlagW;
     hipStream_t s = (hipStream_t)stream;
@@ -2535,8 +2546,10 @@ tcuscan_status_t tcuscan_internal_compact_fused(const void *d_values, const void
     if (st != TCUSCAN_OK) return st;
     CompactArgs C;
     C.mask = (const uint8_t *)d_mask; C.values = (const uint32_t *)d_values; C.out = (uint32_t *)d_out; C.count = d_count;
+    P.out = d_positions;
     void *args[] = {&P, &C};
-    return hipLaunchKernel((const void *)compact_kernel<NT, W>, dim3(P.num_tiles), dim3(64 * W), args, 0, s) == hipSuccess ? TCUSCAN_OK : TCUSCAN_ERR_HIP;
+    const void *fn = d_positions ? (const void *)compact_kernel<NT, W, true> : (const void *)compact_kernel<NT, W, false>;
+    return hipLaunchKernel(fn, dim3(P.num_tiles), dim3(64 * W), args, 0, s) == hipSuccess ? TCUSCAN_OK : TCUSCAN_ERR_HIP;
 }
 
 // ---- the entry point that allocates nothing: its carry-chain workspace is a fixed device array of the library
