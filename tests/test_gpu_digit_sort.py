@@ -31,9 +31,9 @@ def check(k, pairs, bits):
     assert gv is None or np.array_equal(gv, order.astype(np.int32))
 
 
-# one workgroup: 1024, 4096, 16384 keys; tiles of 4096 up to 2^19 keys, of 8192 below 5 * 2^20, of 16384 from there
+# one workgroup: 1024, 2048, 4096, 8192, 12288, 16384 keys; tiles of 4096 up to 2^19 keys, of 8192 below 5 * 2^20, of 16384 from there
 @pytest.mark.parametrize("pairs", [False, True], ids=["keys", "pairs"])
-@pytest.mark.parametrize("n", [2, 63, 64, 65, 1023, 1024, 1025, 4095, 4096, 4097, 8192, 8193, 16383, 16384, 16385, 5 * 4096, 5 * 4096 + 1,
+@pytest.mark.parametrize("n", [2, 63, 64, 65, 1023, 1024, 1025, 2048, 2049, 4095, 4096, 4097, 8192, 8193, 12288, 12289, 16383, 16384, 16385, 5 * 4096, 5 * 4096 + 1,
                                (1 << 19) - 1, 1 << 19, (1 << 19) + 1, 70 * 8192 - 1, (5 << 20) - 1, 5 << 20, 321 * 16384 + 1])
 def test_sizes_around_tiles_and_shapes(n, pairs):
     check(inputs.int32_full(n, 3 * n + 1).view(np.uint32), pairs, 32)
