@@ -2368,6 +2368,10 @@ Plan plan_for(uintptr_t in_addr, size_t rows, size_t cols, int dt, bool ws_usabl
 void plan_lines(Plan &plan, size_t rows, size_t cols, int dt, bool ws_usable, size_t ws_bytes)
 {
     if (plan.path != TCUSCAN_PATH_TILES && plan.path != TCUSCAN_PATH_TILES_FROM_BOUNDARY) return;
+    // Plain tiles stay ahead for one row (100,000,000 f32 140 us, 155 from the line; 2^24 bf16 22.5, 23.3) and for rows long
+    // enough to live off the huge 32-bit tile, which this path does not have (16 x 16,000,004 f32 343, 361; 100 x 1,000,004 146,
+    // 141 from the line).
+    if (plan.path == TCUSCAN_PATH_TILES && (rows == 1 || (cols > ((size_t)1 << 20) && choose_tile(dt, rows, cols) == kTileHuge))) return;
     const int cls = plan.path == TCUSCAN_PATH_TILES_FROM_BOUNDARY ? plan.seg_cls : unaligned_tile(dt, rows, cols);
     const size_t tile = seg_tile_elems(dt, cls), tpr = (cols + 31 + tile - 1) / tile;
     const size_t need = tpr > 1 ? sizeof(WsHeader) + 8 * kStatusStride * rows * tpr : 0;
