@@ -14,6 +14,7 @@
 #include <stdint.h>
 
 #include "../../include/tcuscan.h"
+#include "digit_places.h"
 #include "wave_ops.h"
 
 // tcuscan.hip: clears `bytes` bytes on the stream; the process-wide chain policy and the look-back's poll limit
@@ -345,10 +346,10 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(sizeof(W
     }
     if (tid < kDigits) {
         __hip_atomic_store(column + (size_t)tile * kDigits, S::make(kCountUpToTile, before + count), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        s_dest[tid] = (Place)(before - start) * 4u;        // (modulo: the place inside the tile is added to it)
-        // a digit's range lies inside the array, unless a look-back gave up: then nothing of the tile is stored
-        const uint32_t n32 = (uint32_t)A.n;
-        if (before > n32 || (valid == kTile && count > n32 - before)) s_abort = 1u;
+        s_dest[tid] = digit_base<Place>(before, start);
+        // A digit's range lies inside the array unless a look-back gave up, here or earlier: a tile with one that does not
+        // is not stored.  (The counts of the last tile include its keys past the end; its stores are bounded one by one.)
+        if (!digit_range_fits(before, valid == kTile ? count : 0u, (uint32_t)A.n)) s_abort = 1u;
     }
     __syncthreads();
     if (s_abort) return;
@@ -360,14 +361,14 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(sizeof(W
 #pragma unroll
         for (int r = 0; r < ITEMS; ++r) {
             const uint32_t i = (uint32_t)tid + (uint32_t)r * kThreads, k = s_order[i];
-            const Place to = s_dest[digit_of(k, g)] + 4u * i;
+            const Place to = digit_place(s_dest[digit_of(k, g)], i);
             *(uint32_t *)(kout + to) = k;
             if constexpr (VALS) dst[r] = to;
         }
     } else {
         for (int r = 0; r < ITEMS; ++r) {
             const uint32_t i = (uint32_t)tid + (uint32_t)r * kThreads, k = s_order[i];
-            const Place to = s_dest[digit_of(k, g)] + 4u * i;
+            const Place to = digit_place(s_dest[digit_of(k, g)], i);
             if (i < valid && to / 4u < A.n) *(uint32_t *)(kout + to) = k;
             if constexpr (VALS) dst[r] = to;
         }

@@ -1,0 +1,11 @@
+// C entry points around paper_2411_17887_amd/csrc/digit_places.h for tests/test_digit_places_cpu.py, which compiles this
+// file with g++.
+#include "../paper_2411_17887_amd/csrc/digit_places.h"
+
+extern "C" {
+
+unsigned long long shim_place32(unsigned before, unsigned start, unsigned i) { return digit_place(digit_base<uint32_t>(before, start), i); }
+unsigned long long shim_place64(unsigned before, unsigned start, unsigned i) { return digit_place(digit_base<uint64_t>(before, start), i); }
+int shim_range_fits(unsigned before, unsigned count, unsigned n) { return digit_range_fits(before, count, n) ? 1 : 0; }
+
+}

@@ -1,0 +1,42 @@
+"""Destinations of a sort pass on digits (paper_2411_17887_amd/csrc/digit_places.h), compiled for the CPU.
+
+What has to hold for both widths of a place: whatever number of keys a look-back returned as lying in front of a tile's
+digit -- also one that is smaller than the digit's place inside the tile, which a wait that gave up can return -- every
+range the guard lets through is stored to bytes 4 * before .. 4 * (before + count) - 1 and nowhere else."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+TILE = 16384
+
+
+@pytest.fixture(scope="module")
+def shim(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("digit_places") / "libshim.so")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-fPIC", "-shared", "-Wall", "-Wextra", "-Werror", "-o", so,
+                    os.path.join(HERE, "digit_places_shim.cpp")], check=True)
+    L = ctypes.CDLL(so)
+    for f in (L.shim_place32, L.shim_place64, L.shim_range_fits):
+        f.argtypes = [ctypes.c_uint] * 3
+    L.shim_place32.restype = L.shim_place64.restype = ctypes.c_ulonglong
+    return L
+
+
+@pytest.mark.parametrize("width,n", [(32, 16385), (32, (1 << 30) - 1), (64, 1 << 30), (64, (1 << 30) + 12345), (64, (1 << 32) - 1)])
+def test_every_range_the_guard_lets_through_goes_to_its_own_bytes(shim, width, n):
+    place = shim.shim_place32 if width == 32 else shim.shim_place64
+    stored = 0
+    for start in (0, 1, 5000, TILE - 1):
+        for count in {c for c in (0, 1, 1000, TILE - start) if start + c <= TILE}:
+            for before in {b for b in (0, 1, start - 1, start, start + 1, n - count - 1, n - count, n - count + 1, n, n + 1, 0xFFFFFFFF)
+                           if 0 <= b <= 0xFFFFFFFF}:
+                fits = before + count <= n
+                assert bool(shim.shim_range_fits(before, count, n)) == fits
+                if fits and count:
+                    for i in (start, start + count // 2, start + count - 1):
+                        assert place(before, start, i) == 4 * (before + i - start) <= 4 * (n - 1), (before, start, i)
+                        stored += 1
+    assert stored > 30

@@ -102,3 +102,30 @@ def test_more_than_2_to_30_keys():
     assert bool((u[1:] >= u[:-1]).all())
     del u
     assert (int(d_k.to(torch.int64).sum().item()), int((d_k.to(torch.int64) ** 2 % 1000003).sum().item())) == sums
+
+
+@pytest.mark.parametrize("tickets", [0, 1])
+def test_payloads_from_2_to_30_keys_on(tickets):
+    """The 64-bit form with payloads: every payload is the index of its key, so keys and payloads together say that the
+    sort is a permutation, in order and stable."""
+    import torch
+    n = (1 << 30) + 12345
+    g = torch.Generator(device="cuda")
+    g.manual_seed(7 + tickets)
+    k = torch.randint(-(1 << 31), 1 << 31, (n,), generator=g, device="cuda", dtype=torch.int64).to(torch.int32)
+    d_k, d_v = k.clone(), torch.arange(n, dtype=torch.int32, device="cuda")
+    d_f, d_p = torch.empty(n, dtype=torch.int8, device="cuda"), torch.empty(n, dtype=torch.int32, device="cuda")
+    ws = tcuscan.new_workspace(1, n, "i8")
+    tcuscan.set_chain_policy(tickets)
+    try:
+        tcuscan.split_radix_sort_u32(d_k, torch.empty_like(d_k), d_f, d_p, vals=d_v, vals_tmp=torch.empty_like(d_v), bits=32, ws=ws)
+        torch.cuda.synchronize()
+    finally:
+        tcuscan.set_chain_policy(0)
+    assert tcuscan.workspace_fault(ws) == 0
+    del d_f, d_p, ws
+    both = ((d_k.to(torch.int64) & 0xFFFFFFFF) << 31) | d_v.to(torch.int64)      # 63 bits: by key, then by index
+    assert bool((both[1:] > both[:-1]).all())                                    # so all payloads differ
+    del both
+    assert int(d_v.min().item()) == 0 and int(d_v.max().item()) == n - 1
+    assert bool((k[d_v.to(torch.int64)] == d_k).all())
