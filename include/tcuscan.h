@@ -260,9 +260,10 @@ tcuscan_status_t tcuscan_measure_stream(const void *d_in, void *d_out, size_t ou
  *                                tags (tcuscan_test_tag_period() of them bring the same tag round again).
  *   tcuscan_test_chain_fault     spin_limit: polls of one status word before a carry-chain wait gives up and raises
  *                                fault word 1 (0: back to the default, 2^24); mute_tile: the workgroup tile with this
- *                                index does not publish its status word (negative: none; plain scans only).  With a
- *                                muted tile and a small limit every later tile of the row gives up, all kernels end
- *                                normally, the results are wrong and the fault word says so.
+ *                                index does not publish its status word (negative: none; plain scans and the sort's
+ *                                passes on eight bits only).  With a muted tile and a small limit every later tile of
+ *                                the row (of a sort's pass) gives up, all kernels end normally, the results are wrong
+ *                                and the fault word says so.
  */
 tcuscan_status_t tcuscan_test_advance_calls(unsigned long long calls);
 unsigned long long tcuscan_test_tag_period(void);

@@ -17,11 +17,14 @@
 #define DIGIT_PLACES_FN inline
 #endif
 
-// Place: uint32_t below 2^30 keys, uint64_t from there.
-template <class Place> DIGIT_PLACES_FN Place digit_base(uint32_t before, uint32_t start) { return ((Place)before - (Place)start) * 4u; }
+// Place: uint32_t below 2^30 - 1 keys, uint64_t from there.
+template <class Place> DIGIT_PLACES_FN Place digit_base(Place before, uint32_t start) { return (before - (Place)start) * 4u; }
 template <class Place> DIGIT_PLACES_FN Place digit_place(Place base, uint32_t i) { return base + 4u * i; }
 
 // The digit's range [before, before + count) lies inside an array of n keys, whatever the look-back returned.
-DIGIT_PLACES_FN bool digit_range_fits(uint32_t before, uint32_t count, uint32_t n) { return before <= n && count <= n - before; }
+template <class Place> DIGIT_PLACES_FN bool digit_range_fits(Place before, uint32_t count, uint32_t n)
+{
+    return before <= n && count <= n - (uint32_t)before;
+}
 
 #endif

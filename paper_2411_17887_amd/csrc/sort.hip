@@ -17,9 +17,10 @@
 #include "digit_places.h"
 #include "wave_ops.h"
 
-// tcuscan.hip: clears `bytes` bytes on the stream; the process-wide chain policy and the look-back's poll limit
+// tcuscan.hip: clears `bytes` bytes on the stream; the process-wide chain policy, the look-back's poll limit and the tile
+// that a test keeps silent
 extern "C" hipError_t tcuscan_internal_fill(void *d, size_t bytes, hipStream_t s);
-extern "C" void tcuscan_internal_chain_knobs(unsigned *ticket, unsigned *spin_limit);
+extern "C" void tcuscan_internal_chain_knobs(unsigned *ticket, unsigned *spin_limit, unsigned *mute_tile);
 
 namespace {
 
@@ -185,14 +186,17 @@ __global__ __launch_bounds__(kHistThreads) void digit_histograms_kernel(HistArgs
 
 // ------------------------------------------------------------------------- one pass over the array
 
-// Status words, one per tile and digit: 2 state bits on top (0 = not published), the value below.  32-bit words hold
-// counts of up to 2^30 keys, 64-bit words all there are.
+// Status words, one per tile and digit: 2 state bits on top (0 = not published), the value below.  The largest value is no
+// count: a tile that could not learn what lies in front of it publishes it, and every sum it goes into is one that lies
+// in front of nothing (digit_range_fits; a state of its own, looked at word by word, cost 26 us of a sort of 2^26 keys and 7 of
+// one of 2^22 pairs).  32-bit words hold the counts of fewer than 2^30 - 1 keys, 64-bit words all there are.
 constexpr uint32_t kCountOfTile = 1u, kCountUpToTile = 2u;
 template <class Word> struct StatusWord {
     static constexpr int kStateAt = 8 * (int)sizeof(Word) - 2;
-    static __device__ __forceinline__ Word make(uint32_t state, uint32_t value) { return ((Word)state << kStateAt) | value; }
+    static constexpr Word kUnknown = ((Word)1 << kStateAt) - 1;
+    static __device__ __forceinline__ Word make(uint32_t state, Word value) { return ((Word)state << kStateAt) | (value < kUnknown ? value : kUnknown); }
     static __device__ __forceinline__ uint32_t state(Word w) { return (uint32_t)(w >> kStateAt); }
-    static __device__ __forceinline__ uint32_t value(Word w) { return (uint32_t)(w & (((Word)1 << kStateAt) - 1)); }
+    static __device__ __forceinline__ Word value(Word w) { return w & kUnknown; }
 };
 
 struct PassArgs {
@@ -204,6 +208,7 @@ struct PassArgs {
     uint32_t *fault;                      // null (one tile), or the workspace's fault word
     uint64_t n;
     uint32_t spin_limit;
+    uint32_t mute_tile;                   // test hook: the tile with this index publishes nothing
     Digit digit;
     bool stream;                          // the arrays do not fit the memory-side cache: keys are read around it
 };
@@ -240,12 +245,14 @@ __device__ __forceinline__ void request_window(const Word *status, uint32_t d, i
 }
 
 // Keys with this thread's digit in front of the tile (those with smaller digits, anywhere, among them: tile 0 starts
-// from there).  `w` holds the window that was requested at tile t = tile - 1.
+// from there); kUnknown or more if this wait or one it depends on gave up.  `w` holds the window that was requested at tile
+// t = tile - 1.
 template <class Word>
-__device__ __forceinline__ uint32_t digit_look_back(const Word *status, uint32_t d, int32_t t, Word (&w)[kWindow], const PassArgs &A)
+__device__ __forceinline__ Word digit_look_back(const Word *status, uint32_t d, int32_t t, Word (&w)[kWindow], const PassArgs &A)
 {
     using S = StatusWord<Word>;
-    uint32_t sum = 0u, spins = 0u;
+    Word sum = 0u;
+    uint32_t spins = 0u;
     for (;;) {
         bool found = false, waiting = false;
 #pragma unroll
@@ -260,7 +267,7 @@ __device__ __forceinline__ uint32_t digit_look_back(const Word *status, uint32_t
         if (waiting) {
             if (++spins > A.spin_limit) {                  // never in correct operation: give up instead of hanging
                 if (A.fault) __hip_atomic_store(A.fault, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                return sum;
+                return S::kUnknown;
             }
             __builtin_amdgcn_s_sleep(1);
         }
@@ -311,11 +318,12 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(sizeof(W
 
     // ---- counters -> places; the chain sets out (thread d: digit d)
     Word *column = (Word *)A.status + (tid & (kDigits - 1));
+    const bool speaks = tile != A.mute_tile;
     Word win[kWindow];
     uint32_t count, start;
     scan_counters<W>(s_cnt, s_part, count, start, [&](uint32_t c) {
         if (tile != 0u) {
-            __hip_atomic_store(column + (size_t)tile * kDigits, S::make(kCountOfTile, c), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (speaks) __hip_atomic_store(column + (size_t)tile * kDigits, S::make(kCountOfTile, c), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             request_window((const Word *)A.status, (uint32_t)tid, (int32_t)tile - 1, win);
         }
     });
@@ -328,7 +336,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(sizeof(W
     }
 
     // ---- the chain arrives: where the tile's keys of each digit go
-    uint32_t before = 0u;                                  // keys in front of the tile's first with this thread's digit
+    Word before = 0u;                                      // keys in front of the tile's first with this thread's digit
     if (tile == 0u) {                                      // (uniform over the workgroup)
         uint32_t h = 0u, inc = 0u;
         if (tid < kDigits) {
@@ -345,11 +353,12 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(sizeof(W
         before = digit_look_back((const Word *)A.status, (uint32_t)tid, (int32_t)tile - 1, win, A);
     }
     if (tid < kDigits) {
-        __hip_atomic_store(column + (size_t)tile * kDigits, S::make(kCountUpToTile, before + count), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (speaks) __hip_atomic_store(column + (size_t)tile * kDigits, S::make(kCountUpToTile, before + count), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         s_dest[tid] = digit_base<Place>(before, start);
-        // A digit's range lies inside the array unless a look-back gave up, here or earlier: a tile with one that does not
-        // is not stored.  (The counts of the last tile include its keys past the end; its stores are bounded one by one.)
-        if (!digit_range_fits(before, valid == kTile ? count : 0u, (uint32_t)A.n)) s_abort = 1u;
+        // Nothing is stored of a tile that does not know its places, nor, in the passes after one that left tiles out, of a
+        // tile whose places the counts over the array do not hold.  (The counts of the last tile include its keys past the
+        // end; its stores are bounded one by one.)
+        if (!digit_range_fits<Place>(before, valid == kTile ? count : 0u, (uint32_t)A.n)) s_abort = 1u;
     }
     __syncthreads();
     if (s_abort) return;
@@ -493,9 +502,9 @@ tcuscan_status_t tcuscan_internal_digit_sort(void *d_keys, void *d_vals, size_t 
     if (n <= kBlockSortMax)
         return launch_block_sort((uint32_t *)d_keys, (uint32_t *)d_vals, (uint32_t)n, P, s) == hipSuccess ? TCUSCAN_OK : TCUSCAN_ERR_HIP;
 
-    unsigned use_tickets, spin_limit;
-    tcuscan_internal_chain_knobs(&use_tickets, &spin_limit);
-    const bool wide = n >= ((size_t)1 << 30);
+    unsigned use_tickets, spin_limit, mute_tile;
+    tcuscan_internal_chain_knobs(&use_tickets, &spin_limit, &mute_tile);
+    const bool wide = n >= StatusWord<uint32_t>::kUnknown;
     const int items = pass_items(n);
     const size_t tile = (size_t)64 * kPassWaves * items, tiles = (n + tile - 1) / tile;
     // Arrays that do not fit the memory-side cache (256 MiB) together are read around it, which leaves it to the pieces
@@ -531,7 +540,7 @@ tcuscan_status_t tcuscan_internal_digit_sort(void *d_keys, void *d_vals, size_t 
         A.status = status + pass_words * p; A.hist = hist + kDigits * p;
         A.ticket = use_tickets ? tickets + p : nullptr;
         A.fault = (uint32_t *)d_fault;
-        A.n = n; A.spin_limit = spin_limit; A.digit = P.digit[p]; A.stream = around_cache;
+        A.n = n; A.spin_limit = spin_limit; A.mute_tile = mute_tile; A.digit = P.digit[p]; A.stream = around_cache;
         void *args[] = {&A};
         if (hipLaunchKernel(pass_kernel(items, d_vals != nullptr, wide), dim3((unsigned)tiles), dim3(64 * kPassWaves), args, 0, s) != hipSuccess)
             return TCUSCAN_ERR_HIP;

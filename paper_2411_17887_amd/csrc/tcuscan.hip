@@ -2531,10 +2531,11 @@ tcuscan_status_t tcuscan_internal_split_pass(const void *d_keys, const void *d_v
 extern "C" __attribute__((visibility("hidden")))
 hipError_t tcuscan_internal_fill(void *d, size_t bytes, hipStream_t s) { return launch_fill(d, bytes, s); }
 extern "C" __attribute__((visibility("hidden")))
-void tcuscan_internal_chain_knobs(unsigned *ticket, unsigned *spin_limit)
+void tcuscan_internal_chain_knobs(unsigned *ticket, unsigned *spin_limit, unsigned *mute_tile)
 {
     *ticket = g_chain_policy.load(std::memory_order_relaxed) == 1 ? 1u : 0u;
     *spin_limit = g_spin_limit.load(std::memory_order_relaxed);
+    *mute_tile = g_mute_tile.load(std::memory_order_relaxed);
 }
 
 // Used by tcuscan_compact_u32 (apps.hip): one pass over the mask and the values, nothing else written than the kept

@@ -4,8 +4,9 @@
 
 extern "C" {
 
-unsigned long long shim_place32(unsigned before, unsigned start, unsigned i) { return digit_place(digit_base<uint32_t>(before, start), i); }
-unsigned long long shim_place64(unsigned before, unsigned start, unsigned i) { return digit_place(digit_base<uint64_t>(before, start), i); }
-int shim_range_fits(unsigned before, unsigned count, unsigned n) { return digit_range_fits(before, count, n) ? 1 : 0; }
+unsigned long long shim_place32(unsigned long long before, unsigned start, unsigned i) { return digit_place(digit_base<uint32_t>((uint32_t)before, start), i); }
+unsigned long long shim_place64(unsigned long long before, unsigned start, unsigned i) { return digit_place(digit_base<uint64_t>(before, start), i); }
+int shim_fits32(unsigned long long before, unsigned count, unsigned n) { return digit_range_fits<uint32_t>((uint32_t)before, count, n) ? 1 : 0; }
+int shim_fits64(unsigned long long before, unsigned count, unsigned n) { return digit_range_fits<uint64_t>(before, count, n) ? 1 : 0; }
 
 }

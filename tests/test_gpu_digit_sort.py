@@ -129,3 +129,48 @@ def test_payloads_from_2_to_30_keys_on(tickets):
     del both
     assert int(d_v.min().item()) == 0 and int(d_v.max().item()) == n - 1
     assert bool((k[d_v.to(torch.int64)] == d_k).all())
+
+
+@pytest.mark.parametrize("pairs", [False, True], ids=["keys", "pairs"])
+def test_a_tile_that_does_not_know_its_places_is_not_stored(pairs):
+    """Tile 3 keeps silent, so the wait of tile 4 gives up, and every later tile does.  One pass: keys of tiles 0 .. 3 are
+    where they belong, no other place of the array is touched.  Four passes: all kernels end and nothing is written outside
+    the arrays.  The fault word reads 1 either way, and once it is cleared the same call sorts again."""
+    import torch
+    tile = 4096
+    n = 40 * tile + 11
+    k = inputs.int32_full(n, 21).view(np.uint32)
+    room = (n + 3) // 4 * 4 + 128                                                # rows start at 16-byte boundaries
+    for bits in (8, 32):
+        buf = torch.full((4, room), -7, dtype=torch.int32, device="cuda")
+        d_k, d_kt, d_v, d_vt = (buf[i, 64:64 + n] for i in range(4))
+        d_f, d_p = torch.empty(n, dtype=torch.int8, device="cuda"), torch.empty(n, dtype=torch.int32, device="cuda")
+        ws = tcuscan.new_workspace(1, n, "i8")
+
+        def sort():
+            d_k.copy_(torch.from_numpy(k.view(np.int32)))
+            d_v.copy_(torch.arange(n, dtype=torch.int32))
+            tcuscan.split_radix_sort_u32(d_k, d_kt, d_f, d_p, vals=d_v if pairs else None, vals_tmp=d_vt if pairs else None, bits=bits, ws=ws)
+            torch.cuda.synchronize()
+
+        tcuscan.test_chain_fault(4096, 3)
+        try:
+            sort()
+        finally:
+            tcuscan.test_chain_fault(0, -1)
+        assert tcuscan.workspace_fault(ws) == 1
+        for b in buf:
+            assert bool((b[:64] == -7).all()) and bool((b[64 + n:] == -7).all())
+        order = np.argsort(k & np.uint32((1 << bits) - 1), kind="stable")
+        if bits == 8:
+            at = np.empty(n, np.int64)
+            at[order] = np.arange(n)
+            want_k, want_v = k.copy(), np.arange(n, dtype=np.int32)
+            want_k[at[:4 * tile]], want_v[at[:4 * tile]] = k[:4 * tile], np.arange(4 * tile)
+            assert np.array_equal(d_k.cpu().numpy().view(np.uint32), want_k)
+            assert not pairs or np.array_equal(d_v.cpu().numpy(), want_v)
+        tcuscan.workspace_init(ws)
+        sort()
+        assert tcuscan.workspace_fault(ws) == 0
+        assert np.array_equal(d_k.cpu().numpy().view(np.uint32), k[order])
+        assert not pairs or np.array_equal(d_v.cpu().numpy(), order.astype(np.int32))
