@@ -25,6 +25,7 @@ extern "C" void tcuscan_internal_chain_knobs(unsigned *ticket, unsigned *spin_li
 namespace {
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef uint64_t CounterQuad __attribute__((may_alias));   // four 16-bit counters in LDS
 
 constexpr int kDigits = 256;
 constexpr int kMaxPasses = 4;
@@ -289,7 +290,8 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(sizeof(W
     constexpr uint32_t kTile = kThreads * ITEMS;
     static_assert(W >= 4 && kTile <= 16384u, "one thread per digit; byte offsets inside a tile are 16 bits");
     __shared__ uint32_t s_order[kTile];
-    __shared__ uint16_t s_cnt[W][kDigits];
+    __shared__ __attribute__((aligned(16))) uint16_t s_cnt[W][kDigits];
+    static_assert(__alignof__(s_cnt) >= alignof(CounterQuad), "cleared four counters at a time");
     __shared__ Place s_dest[kDigits];
     __shared__ uint32_t s_part[4], s_abort;
 
@@ -311,7 +313,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(sizeof(W
     const uint32_t first = (uint32_t)wave * 64u * ITEMS + (uint32_t)lane;
     uint32_t key[ITEMS], at[ITEMS];
     load_rows<ITEMS>(A.keys + base, first, valid, valid == kTile, A.stream, ~0u, key);
-    ((uint64_t *)s_cnt[wave])[lane] = 0u;
+    ((CounterQuad *)s_cnt[wave])[lane] = 0u;
     wavefront_sync();
     rank_rows<ITEMS>(key, g, s_cnt[wave], at);
     __syncthreads();
@@ -403,7 +405,8 @@ __global__ __launch_bounds__(1024) void block_sort_kernel(uint32_t *keys, uint32
     constexpr int W = 16, kThreads = 64 * W;
     constexpr uint32_t kTile = kThreads * ITEMS;
     __shared__ uint32_t s_order[kTile];
-    __shared__ uint16_t s_cnt[W][kDigits];
+    __shared__ __attribute__((aligned(16))) uint16_t s_cnt[W][kDigits];
+    static_assert(__alignof__(s_cnt) >= alignof(CounterQuad), "cleared four counters at a time");
     __shared__ uint32_t s_part[4];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -417,7 +420,7 @@ __global__ __launch_bounds__(1024) void block_sort_kernel(uint32_t *keys, uint32
     }
     for (int p = 0; p < P.count; ++p) {
         const Digit g = P.digit[p];
-        ((uint64_t *)s_cnt[wave])[lane] = 0u;
+        ((CounterQuad *)s_cnt[wave])[lane] = 0u;
         wavefront_sync();
         rank_rows<ITEMS>(key, g, s_cnt[wave], at);
         __syncthreads();
