@@ -2329,10 +2329,10 @@ tcuscan_status_t run_segmented_flat(const void *d_in, void *d_out, const long lo
 
 // The tile for such rows.  8- and 16-bit inputs: small or large as the plain tiles' rule has it (us, small / large: 500 x
 // 400,001 bf16 239 / 220, i8 229 / 182; 4 x 600,001 bf16 8.0 / 16.7, i8 7.5 / 14.9), with the large one in place of the huge.
-// 32-bit: large from 2^19 on (500 x 400,001 f32 348 / 340, but 17 x 323,410 i32 10.1 / 11.1).
+// 32-bit: large from 2^19 on (500 x 400,001 f32 348 / 340, but 17 x 323,410 i32 10.1 / 11.1).  A tile policy is obeyed.
 int unaligned_tile(int dt, size_t rows, size_t cols)
 {
-    if (in_size(dt) == 4) return cols < ((size_t)1 << 19) ? kSegSmall : kSegLarge;
+    if (in_size(dt) == 4 && g_tile_policy.load(std::memory_order_relaxed) == 0) return cols < ((size_t)1 << 19) ? kSegSmall : kSegLarge;
     return choose_tile(dt, rows, cols) == kTileSmall ? kSegSmall : kSegLarge;
 }
 
@@ -2368,6 +2368,8 @@ Plan plan_for(uintptr_t in_addr, size_t rows, size_t cols, int dt, bool ws_usabl
 void plan_lines(Plan &plan, size_t rows, size_t cols, int dt, bool ws_usable, size_t ws_bytes)
 {
     if (plan.path != TCUSCAN_PATH_TILES && plan.path != TCUSCAN_PATH_TILES_FROM_BOUNDARY) return;
+    // A tile policy asks for plain tiles of one size.
+    if (plan.path == TCUSCAN_PATH_TILES && g_tile_policy.load(std::memory_order_relaxed) != 0) return;
     // Plain tiles stay ahead for one row (100,000,000 f32 140 us, 155 from the line; 2^24 bf16 22.5, 23.3) and for rows long
     // enough to live off the huge 32-bit tile, which this path does not have (16 x 16,000,004 f32 343, 361; 100 x 1,000,004 146,
     // 141 from the line).

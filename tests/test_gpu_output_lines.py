@@ -39,3 +39,28 @@ def test_rows_that_start_inside_output_lines(kind, flags):
             assert bool((out.view(rows, cols).to(torch.int64) == ref).all()), (kind, rows, cols, shift_in, shift_out)
             assert bool((buf[:shift_out] == -99).all()) and bool((buf[shift_out + n:] == -99).all())
             assert ws is None or tcuscan.workspace_fault(ws) == 0
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("policy", [tcuscan.TILE_SMALL, tcuscan.TILE_LARGE, tcuscan.TILE_HUGE], ids=["small", "large", "huge"])
+def test_tile_policy_is_obeyed_by_rows_that_cross_lines(kind, policy):
+    """The status words that a call leaves in a fresh workspace say how many tiles it ran: rows at 16-byte boundaries on the
+    tile asked for, odd rows on it too, with the large one in place of the huge (their path has none)."""
+    import torch
+    rows = 9                                                                     # 9 x 1,000,001 > 2^23 outputs
+    for cols in (1_000_016, 1_000_001):
+        sizes = [tcuscan.tile_elems(kind), tcuscan.large_tile_elems(kind), tcuscan.huge_tile_elems(kind)]
+        tile = sizes[policy - 1] if cols % 16 == 0 else sizes[min(policy, 2) - 1]
+        x = torch.randint(-2, 3, (rows, cols), device="cuda").to(
+            {"i32": torch.int32, "i8": torch.int8, "f16": torch.float16, "bf16": torch.bfloat16, "f32": torch.float32}[kind])
+        out = torch.empty(rows, cols, dtype=torch.int32 if kind in ("i32", "i8") else torch.float32, device="cuda")
+        ws = tcuscan.new_workspace(rows, cols, kind)
+        tcuscan.set_tile_policy(policy)
+        try:
+            tcuscan.scan(x, out, rows, cols, kind, flags=0, ws=ws)
+            torch.cuda.synchronize()
+        finally:
+            tcuscan.set_tile_policy(tcuscan.TILE_AUTO)
+        assert -(-cols // tile) == -(-(cols + 31) // tile)                       # the elements in front cost no tile here
+        assert int((ws.view(torch.int64)[32::8] != 0).sum().item()) == rows * -(-cols // tile), (cols, tile)
+        assert bool((out.to(torch.int64) == torch.cumsum(x.to(torch.int64), 1)).all())
