@@ -72,6 +72,8 @@ constexpr uint32_t kStatePrefix    = 2u;   // value = total of this tile and all
 constexpr uint32_t kDefaultSpinLimit = 1u << 24;   // look-back polls before giving up (seconds of waiting)
 constexpr uint32_t kNoTile           = 0xFFFFFFFFu;
 
+constexpr uint32_t kFromLine = 1u, kByDie = 2u;     // Params::line; kByDie: see scan_rows_kernel
+
 struct Params {
     const void *in;
     void       *out;
@@ -82,7 +84,7 @@ struct Params {
     uint32_t    spin_limit;  // look-back polls per status word before the wait gives up and raises the fault word
     uint32_t    mute_tile;   // test hook: the tile with this index does not publish its status word (kNoTile: none)
     uint32_t    reverse;     // non-zero: suffix sums (every row is scanned from its end)
-    uint32_t    line = 0;    // non-zero: rows are tiled from the 128-byte line of the output they start in (see row_lead)
+    uint32_t    line = 0;    // kFromLine: rows are tiled from the 128-byte line of the output they start in (see row_lead); kByDie
     WsHeader   *ws;          // null when tiles_per_row == 1
     // segmented scans only: what every tile has to know about its row (built by seg_desc_kernel)
     const struct TileDesc *tile_desc;
@@ -725,7 +727,7 @@ __host__ __device__ __forceinline__ uint32_t row_lead(uintptr_t in_addr, uintptr
 template <int DT, bool LINES = true>
 __device__ __forceinline__ uint32_t seg_lead(const Params &P, long long off)
 {
-    return row_lead((uintptr_t)P.in, (uintptr_t)P.out, Tr<DT>::kEsz, off, LINES && P.line != 0u);
+    return row_lead((uintptr_t)P.in, (uintptr_t)P.out, Tr<DT>::kEsz, off, LINES && (P.line & kFromLine) != 0u);
 }
 template <int DT>
 __device__ __forceinline__ Run make_seg_run(const Params &P, long long off, uint64_t len, uint32_t lead, uint64_t base)
@@ -1770,14 +1772,14 @@ __global__ __launch_bounds__(kThreads) void scan_rows_kernel(Params P)
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     // Workgroups are handed out to the eight dies in turn, and each die has an L2 of its own: neighbouring rows that share
-    // a line should meet in one.  64 consecutive workgroups' rows go to one die (262,144 x 1001 f32 391 -> 370 us, 131,072 x
-    // 2047 bf16 289 -> 278); a call of a few thousand rows is over before it matters.
+    // a line should meet in one.  64 consecutive workgroups' rows go to one die (kByDie; 262,144 x 1001 f32 391 -> 370 us,
+    // 131,072 x 2047 bf16 289 -> 278; launch_rows says which rows).
     uint32_t block = blockIdx.x;
     if constexpr (LEAD && NT > 1) {
         constexpr uint32_t kDies = 8u, kRun = 64u;
         const uint32_t in = block % (kDies * kRun), group = block - in;
         const uint64_t blocks = (P.rows + kWaves - 1) / kWaves;        // (the grid; asking for gridDim is a load more: 0.4 us)
-        if (blocks >= 4096u && group + kDies * kRun <= blocks) block = group + (in % kDies) * kRun + in / kDies;
+        if ((P.line & kByDie) && group + kDies * kRun <= blocks) block = group + (in % kDies) * kRun + in / kDies;
     }
     const uint64_t row = (uint64_t)block * kWaves + wave;
     if (row >= P.rows) return;
@@ -2048,15 +2050,29 @@ template <int DT, int NT> hipError_t launch_rows_nt(Params P, bool excl, bool le
 template <int DT> hipError_t launch_rows(Params P, bool excl, hipStream_t s)
 {
     // Rows that start at 16-byte boundaries take the plain form; the others are tiled from the boundary below their
-    // start, which can cost one more MFMA tile.  Rows that start inside a line of the output are tiled from the line
-    // when that costs no tile on top (500,000 x 501 i32, 2 tiles: 351 us, 382 with three) and they are longer than a
-    // tile (2,000,000 x 101 f32: 634 against 700).  The tiles of these forms are counted out -- a masked tile is not free --
-    // and not rounded up to 1, 2, 4, 8 or 12 (160,000 x 1501 bf16 275 -> 261).
+    // start, which can cost one more MFMA tile.  The tiles of odd rows are counted out -- a masked tile is not free -- and not
+    // rounded up to 1, 2, 4, 8 or 12 (160,000 x 1501 bf16 275 -> 261).
     constexpr size_t kTile = Geo<DT>::kTileElems;
-    const bool off_granule = ((uintptr_t)P.in & 15) != 0 || (P.cols * Tr<DT>::kEsz) % 16 != 0;
+    constexpr int kEsz = Tr<DT>::kEsz;
+    const bool off_granule = ((uintptr_t)P.in & 15) != 0 || (P.cols * kEsz) % 16 != 0;
     const size_t tiles = (P.cols + (off_granule ? Tr<DT>::kG - 1 : 0) + kTile - 1) / kTile;
-    if (tiles == 1 || (P.cols + 31 + kTile - 1) / kTile > tiles) P.line = 0u;
-    const bool lead = P.line || off_granule;
+    // Rows that start inside a line of the output are tiled from the line when that costs no tile on top (500,000 x 501 i32, 2
+    // tiles: 351 us, 382 with three) and they are longer than a tile (2,000,000 x 101 f32: 634 against 700); neighbouring rows
+    // then go to one die, from a few thousand workgroups on.  That gains 2 .. 18 % from the third tile on, with 8-bit rows
+    // from the second.  The other rows of two tiles, relative speed of the form over 12, 50 and 150 million outputs:
+    //   16-bit, 1.02 .. 1.35 tiles   0.89 .. 1.00, odd rows 0.95 .. 1.01; from 1.5 tiles on 1.01 .. 1.09
+    //   32-bit, 1.02 tiles           0.95 .. 1.00, 1.09 tiles 0.99 .. 1.02, from 1.2 on 1.01 .. 1.16; odd rows below 1.5 tiles
+    //                                0.95 .. 0.99, above 0.99 .. 1.03, and the order by dies costs these 1 %
+    // 32-bit rows of three and four tiles at 16-byte boundaries, which the plain form rounds up to four: 0.94 .. 1.02 over 12,
+    // 0.96 .. 1.07 over 50, 0.99 .. 1.12 over 150 million outputs.
+    bool line = P.line != 0u && tiles > 1 && (P.cols + 31 + kTile - 1) / kTile <= tiles;
+    bool by_die = tiles > 1 && (P.rows + kWaves - 1) / kWaves >= 4096;
+    if (kEsz == 2 && tiles == 2 && 2 * P.cols < 3 * kTile) line = by_die = false;
+    if (kEsz == 4 && tiles == 2 && (off_granule ? 2 * P.cols < 3 * kTile : 16 * P.cols < 17 * kTile)) line = false;
+    if (kEsz == 4 && tiles == 2 && off_granule) by_die = false;
+    if (kEsz == 4 && (tiles == 3 || tiles == 4) && !off_granule && P.rows * P.cols < ((uint64_t)1 << 25)) line = false;
+    P.line = (line ? kFromLine : 0u) | (by_die ? kByDie : 0u);
+    const bool lead = line || off_granule;
     if (tiles <= 1) return launch_rows_nt<DT, 1>(P, excl, lead, s);
     if (tiles <= 2) return launch_rows_nt<DT, 2>(P, excl, lead, s);
     if (lead && tiles == 3) return launch_rows_lead<DT, 3>(P, excl, s);
@@ -2196,7 +2212,7 @@ tcuscan_status_t run(const void *d_in, void *d_out, size_t rows, size_t cols, in
     P.tiles_per_row = (uint32_t)tpr; P.num_tiles = (uint32_t)(rows * tpr);
     P.ws = need ? (WsHeader *)d_ws : nullptr;
     P.reverse = reverse ? 1u : 0u;
-    P.line = line ? 1u : 0u;                                             // (only rows of one wavefront each look at it)
+    P.line = line ? kFromLine : 0u;                                      // (only rows of one wavefront each look at it)
     P.tile_desc = nullptr;
     // Every call gets a fresh tag, so status words of earlier calls are stale by construction.
     const tcuscan_status_t bst = begin_chain(P, P.ws && tpr > 1 ? d_ws : nullptr, rows * tpr, clear_first, s);
@@ -2393,7 +2409,7 @@ tcuscan_status_t run_unaligned_rows(const void *d_in, void *d_out, size_t rows, 
     P.tiles_per_row = (uint32_t)tpr; P.num_tiles = (uint32_t)(rows * tpr);
     P.ws = need ? (WsHeader *)d_ws : nullptr;
     P.reverse = reverse ? 1u : 0u;
-    P.line = plan.line ? 1u : 0u;
+    P.line = plan.line ? kFromLine : 0u;
     P.tile_desc = nullptr;
     const tcuscan_status_t bst = begin_chain(P, need ? d_ws : nullptr, rows * tpr, clear_first, s);
     if (bst != TCUSCAN_OK) return bst;
@@ -2431,7 +2447,7 @@ tcuscan_status_t run_segmented(const void *d_in, void *d_out, const long long *d
     uint32_t *starts = (uint32_t *)((char *)d_ws + L.starts_off);
     TileDesc *desc = (TileDesc *)((char *)d_ws + L.rowmap_off);
     const bool few_rows = rows < kSegPrepRows;
-    uint32_t line = total >= kLinesFrom && line_compatible((uintptr_t)d_in, (uintptr_t)d_out, in_size(dt)) ? 1u : 0u;
+    uint32_t line = total >= kLinesFrom && line_compatible((uintptr_t)d_in, (uintptr_t)d_out, in_size(dt)) ? kFromLine : 0u;
     if (few_rows) {   // steps 1 - 3 and the clearing of the status words in one launch
         const long long *off = d_offsets; size_t r = rows, t = total; uintptr_t in_addr = (uintptr_t)d_in, out_addr = (uintptr_t)d_out;
         uint32_t esz = (uint32_t)in_size(dt), tl = (uint32_t)tile, mt = (uint32_t)L.max_tiles; WsHeader *h = (WsHeader *)d_ws;

@@ -64,3 +64,35 @@ def test_tile_policy_is_obeyed_by_rows_that_cross_lines(kind, policy):
         assert -(-cols // tile) == -(-(cols + 31) // tile)                       # the elements in front cost no tile here
         assert int((ws.view(torch.int64)[32::8] != 0).sum().item()) == rows * -(-cols // tile), (cols, tile)
         assert bool((out.to(torch.int64) == torch.cumsum(x.to(torch.int64), 1)).all())
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("flags", [0, 1, 2, 3])
+def test_short_rows_on_either_side_of_the_form_rules(kind, flags):
+    """Rows of one wavefront each whose form changes with their length, at 16-byte boundaries and odd, on both sides of each
+    switch: 17/16 and 3/2 of two tiles, two to five tiles; in calls with and without the order by dies (16384 rows), and for
+    three tiles with and without lines (2^25 outputs).  Exact."""
+    import torch
+    esz = {"i8": 1, "f16": 2, "bf16": 2}.get(kind, 4)
+    tile = 1024 // esz
+    lengths = [17 * tile // 16, 3 * tile // 2, 2 * tile - 32, 2 * tile + 16] + ([3 * tile - 48, 4 * tile + 16] if esz > 1 else [5 * tile // 2])
+    for base in lengths:
+        for cols in (base - 16, base, base + 1):
+            for rows in {16384 - 64, 16384 + 64} | ({(1 << 25) // cols + 5} if esz == 4 and 2 * tile < cols <= 4 * tile else set()):
+                if rows * cols < 1 << 23:
+                    rows = (1 << 23) // cols + 1
+                g = torch.Generator(device="cuda")
+                g.manual_seed(cols)
+                x = torch.randint(-3, 4, (rows, cols), generator=g, device="cuda").to(
+                    {"i32": torch.int32, "i8": torch.int8, "f16": torch.float16, "bf16": torch.bfloat16, "f32": torch.float32}[kind])
+                buf = torch.full((rows * cols + 40,), -99, dtype=torch.int32 if kind in ("i32", "i8") else torch.float32, device="cuda")
+                out = buf[:rows * cols].view(rows, cols)
+                tcuscan.scan(x, out, rows, cols, kind, flags=flags, ws=tcuscan.new_workspace(rows, cols, kind))
+                ref = x.to(torch.int32)
+                if flags & tcuscan.REVERSE:
+                    ref = ref.flip(1)
+                ref = torch.cumsum(ref, 1, dtype=torch.int32) - (ref if flags & tcuscan.EXCLUSIVE else 0)
+                if flags & tcuscan.REVERSE:
+                    ref = ref.flip(1)
+                assert bool((out.to(torch.int32) == ref).all()), (rows, cols)
+                assert bool((buf[rows * cols:] == -99).all())
