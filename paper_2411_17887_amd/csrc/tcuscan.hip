@@ -2345,12 +2345,18 @@ tcuscan_status_t run_segmented_flat(const void *d_in, void *d_out, const long lo
     return hipLaunchKernel(fn, dim3(P.num_tiles), dim3(64 * kFlatW), args, 0, s) == hipSuccess ? TCUSCAN_OK : TCUSCAN_ERR_HIP;
 }
 
-// The tile for such rows.  8- and 16-bit inputs: small or large as the plain tiles' rule has it (us, small / large: 500 x
-// 400,001 bf16 239 / 220, i8 229 / 182; 4 x 600,001 bf16 8.0 / 16.7, i8 7.5 / 14.9), with the large one in place of the huge.
-// 32-bit: large from 2^19 on (500 x 400,001 f32 348 / 340, but 17 x 323,410 i32 10.1 / 11.1).  A tile policy is obeyed.
+// The tile for such rows.  8- and 16-bit inputs: small or large as the plain tiles' rule has it (4 x 600,001 us, small /
+// large: bf16 8.0 / 16.7, i8 7.5 / 14.9), with the large one in place of the huge, but below 2^19 elements the large one only
+// in big calls (rows tiled from lines, us, small / large: i8 60 million elements in rows of 200,001 46 / 53, of 400,001 52 / 55,
+// 135 million in rows of 210,001 117 / 109; bf16 9 million in rows of 300,001 13 / 16, 30 million in rows of 400,001 33 / 35,
+// 60 million in rows of 520,001 71 / 67, 150 million 183 / 163).  32-bit: large from 2^19 on (60 million f32 in rows of 700,001
+// 93 / 86, but 17 x 323,410 i32 10.1 / 11.1).  A tile policy is obeyed.
 int unaligned_tile(int dt, size_t rows, size_t cols)
 {
-    if (in_size(dt) == 4 && g_tile_policy.load(std::memory_order_relaxed) == 0) return cols < ((size_t)1 << 19) ? kSegSmall : kSegLarge;
+    const bool by_shape = g_tile_policy.load(std::memory_order_relaxed) == 0;
+    const size_t esz = in_size(dt), to_large = esz == 1 ? (size_t)5 << 24 : (size_t)1 << 25;
+    if (by_shape && cols < ((size_t)1 << 19) && (esz == 4 || rows * cols < to_large)) return kSegSmall;
+    if (by_shape && esz == 4) return kSegLarge;
     return choose_tile(dt, rows, cols) == kTileSmall ? kSegSmall : kSegLarge;
 }
 

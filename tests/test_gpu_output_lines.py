@@ -96,3 +96,21 @@ def test_short_rows_on_either_side_of_the_form_rules(kind, flags):
                     ref = ref.flip(1)
                 assert bool((out.to(torch.int32) == ref).all()), (rows, cols)
                 assert bool((buf[rows * cols:] == -99).all())
+
+
+@pytest.mark.parametrize("kind,cols,total,tile", [
+    ("i8", 200_001, 1 << 24, "small"), ("i8", 400_001, 60_000_000, "small"), ("i8", 400_001, 100_000_000, "large"), ("i8", 600_001, 60_000_000, "large"),
+    ("bf16", 400_001, 1 << 24, "small"), ("f16", 500_001, 1 << 24, "small"), ("bf16", 400_001, 1 << 26, "large"), ("f16", 600_001, 1 << 25, "large"),
+    ("f32", 400_001, 1 << 26, "small"), ("i32", 600_001, 1 << 26, "large")])
+def test_tile_of_odd_rows(kind, cols, total, tile):
+    """Which tile odd rows take, told by the status words that a call leaves in a fresh workspace, and the sums."""
+    import torch
+    rows = total // cols + 1
+    elems = tcuscan.tile_elems(kind) if tile == "small" else tcuscan.large_tile_elems(kind)
+    x = torch.randint(-2, 3, (rows, cols), device="cuda").to(
+        {"i32": torch.int32, "i8": torch.int8, "f16": torch.float16, "bf16": torch.bfloat16, "f32": torch.float32}[kind])
+    out = torch.empty(rows, cols, dtype=torch.int32 if kind in ("i32", "i8") else torch.float32, device="cuda")
+    ws = tcuscan.new_workspace(rows, cols, kind)
+    tcuscan.scan(x, out, rows, cols, kind, flags=0, ws=ws)
+    assert int((ws.view(torch.int64)[32::8] != 0).sum().item()) == rows * -(-(cols + 31) // elems)
+    assert bool((out.to(torch.int32) == torch.cumsum(x.to(torch.int32), 1, dtype=torch.int32)).all())
