@@ -2387,19 +2387,38 @@ Plan plan_for(uintptr_t in_addr, size_t rows, size_t cols, int dt, bool ws_usabl
     return plan;
 }
 
-// Rows of the tile paths that start inside lines of the output are tiled from the line where the workspace has the status
-// words for it; a plan that has none stays as it is.
+// Rows of the tile paths that start inside lines of the output are tiled from the line where that gains; a plan for which it
+// does not stays as it is.  Figures: speed of the form relative to the plan without it, over rows of 2816 elements on.
 void plan_lines(Plan &plan, size_t rows, size_t cols, int dt, bool ws_usable, size_t ws_bytes)
 {
-    if (plan.path != TCUSCAN_PATH_TILES && plan.path != TCUSCAN_PATH_TILES_FROM_BOUNDARY) return;
+    const bool aligned = plan.path == TCUSCAN_PATH_TILES;                      // rows that start at 16-byte boundaries
+    if (!aligned && plan.path != TCUSCAN_PATH_TILES_FROM_BOUNDARY) return;
     // A tile policy asks for plain tiles of one size.
-    if (plan.path == TCUSCAN_PATH_TILES && g_tile_policy.load(std::memory_order_relaxed) != 0) return;
+    if (aligned && g_tile_policy.load(std::memory_order_relaxed) != 0) return;
     // Plain tiles stay ahead for one row (100,000,000 f32 140 us, 155 from the line; 2^24 bf16 22.5, 23.3) and for rows long
     // enough to live off the huge 32-bit tile, which this path does not have (16 x 16,000,004 f32 343, 361; 100 x 1,000,004 146,
     // 141 from the line).
-    if (plan.path == TCUSCAN_PATH_TILES && (rows == 1 || (cols > ((size_t)1 << 20) && choose_tile(dt, rows, cols) == kTileHuge))) return;
-    const int cls = plan.path == TCUSCAN_PATH_TILES_FROM_BOUNDARY ? plan.seg_cls : unaligned_tile(dt, rows, cols);
+    if (aligned && (rows == 1 || (cols > ((size_t)1 << 20) && choose_tile(dt, rows, cols) == kTileHuge))) return;
+    const size_t esz = in_size(dt), total = rows * cols;
+    // Rows that leave half of their one tile empty do not gain (aligned 0.80 .. 0.97, odd 0.96 .. 1.02; 22,025 x 3184 f32 96 us,
+    // 109 from the line), fuller ones do (1.03 .. 1.17): 16-bit ones of 3500 in big calls (1.02 .. 1.09, 3000 0.85 .. 0.94), in small
+    // aligned calls a little later (4192 elements 0.95 .. 0.98, 5000 1.00 .. 1.08; 16-bit at 9 million outputs 0.91 .. 1.01).
+    if (cols < (esz == 2 && total >= ((size_t)1 << 25) ? 13 * kSmallTile / 32 : kSmallTile / 2)) return;
+    if (aligned && esz == 2 && total < (size_t)3 << 22 && cols < kSmallTile) return;
+    if (aligned && esz != 2 && total < ((size_t)1 << 24) && cols < 9 * kSmallTile / 16) return;
+    int cls = aligned ? unaligned_tile(dt, rows, cols) : plan.seg_cls;
+    if (aligned) {
+        // On the large tile: 8-bit 0.83 .. 1.07 at 16 million outputs and 0.96 .. 1.01 at 30 million, 1.00 .. 1.05 from there; 16-bit
+        // 0.83 .. 1.08 at 9 million, 0.97 .. 1.12 from 16 million on.
+        if (cls == kSegLarge && esz < 4 && total < (esz == 1 ? (size_t)1 << 25 : (size_t)3 << 22)) return;
+        // 32-bit rows that the plain rule has on the large tile are to stay there in big calls (60 and 150 million outputs in
+        // rows of 230,000 .. 520,000: small 0.93 .. 1.00, large 0.99 .. 1.06).
+        if (esz == 4 && cols > ((size_t)1 << 17) && total >= (size_t)3 << 24) cls = kSegLarge;
+    }
+    // A tile more for the elements in front is more than the lines bring: rows of 24,560 in four small tiles 0.80 .. 1.00, of
+    // 65,520 in nine 0.92 .. 1.07.  (The status words are then those that the plan has, or a plain call needs, without it.)
     const size_t tile = seg_tile_elems(dt, cls), tpr = (cols + 31 + tile - 1) / tile;
+    if (tpr > (cols + (aligned ? 0 : 16 / esz - 1) + tile - 1) / tile) return;
     const size_t need = tpr > 1 ? sizeof(WsHeader) + 8 * kStatusStride * rows * tpr : 0;
     if (rows * tpr > 0x7FFFFFFFull || rows > 0x7FFFFFFFull || (need && (!ws_usable || ws_bytes < need))) return;
     plan.seg_cls = cls; plan.tpr = tpr; plan.need = need; plan.line = true;

@@ -114,3 +114,31 @@ def test_tile_of_odd_rows(kind, cols, total, tile):
     tcuscan.scan(x, out, rows, cols, kind, flags=0, ws=ws)
     assert int((ws.view(torch.int64)[32::8] != 0).sum().item()) == rows * -(-(cols + 31) // elems)
     assert bool((out.to(torch.int32) == torch.cumsum(x.to(torch.int32), 1, dtype=torch.int32)).all())
+
+
+@pytest.mark.parametrize("kind", KINDS)
+def test_long_rows_on_either_side_of_the_form_rules(kind):
+    """Rows of workgroup tiles whose form changes with their length, at 16-byte boundaries and odd: rows that leave their one
+    tile half empty, lengths at which the elements in front would cost a tile, in a small and a big call.  A workspace larger
+    than advised changes nothing: the status words left behind are those of the tiles of the rows themselves."""
+    import torch
+    esz = {"i8": 1, "f16": 2, "bf16": 2}.get(kind, 4)
+    tile = tcuscan.tile_elems(kind)
+    lengths = [13 * tile // 32, tile // 2, 9 * tile // 16, tile - 16, tile - 32, 2 * tile - 16, 2 * tile - 32, 3 * tile - 16, 8 * tile - 16]
+    for base in lengths:
+        for cols in (base, base - 15, base + 1):
+            for total in (1 << 23, (1 << 25) + 1):
+                rows = total // cols + 1
+                x = torch.randint(-3, 4, (rows, cols), device="cuda").to(
+                    {"i32": torch.int32, "i8": torch.int8, "f16": torch.float16, "bf16": torch.bfloat16, "f32": torch.float32}[kind])
+                buf = torch.full((rows * cols + 40,), -99, dtype=torch.int32 if kind in ("i32", "i8") else torch.float32, device="cuda")
+                out = buf[:rows * cols].view(rows, cols)
+                ref = torch.cumsum(x.to(torch.int32), 1, dtype=torch.int32)
+                advised = tcuscan.workspace_bytes(rows, cols, kind)
+                for extra in (0, 64 * rows):
+                    ws = torch.zeros((advised + extra + 7) // 8 + 1, dtype=torch.int64, device="cuda")
+                    buf.fill_(-99)
+                    tcuscan.scan(x, out, rows, cols, kind, flags=0, ws=ws)
+                    assert bool((out.to(torch.int32) == ref).all()) and bool((buf[rows * cols:] == -99).all()), (rows, cols)
+                    tpr = -(-(cols + (16 // esz - 1 if cols * esz % 16 else 0)) // tile)      # all on the small tile here
+                    assert int((ws[32::8] != 0).sum().item()) == (rows * tpr if tpr > 1 else 0), (rows, cols, extra)
