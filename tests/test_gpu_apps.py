@@ -92,8 +92,8 @@ def gpu_sort(k, vals=None, bits=32):
 
 @pytest.fixture(params=[1, 2, 0], ids=["fused_two_bits", "fused_one_bit", "three_kernels"])
 def sort_form(request):
-    """The forms of a split pass: the fused kernels (two bits per pass, the default; one bit per pass) and mask kernel +
-    scan + scatter kernel."""
+    """The forms of the sort: passes on eight bits or one workgroup (the default; the id is older), fused passes on one bit, and
+    mask kernel + scan + scatter kernel."""
     tcuscan.set_sort_fusion(request.param)
     yield request.param
     tcuscan.set_sort_fusion(1)

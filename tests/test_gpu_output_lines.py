@@ -142,3 +142,98 @@ def test_long_rows_on_either_side_of_the_form_rules(kind):
                     assert bool((out.to(torch.int32) == ref).all()) and bool((buf[rows * cols:] == -99).all()), (rows, cols)
                     tpr = -(-(cols + (16 // esz - 1 if cols * esz % 16 else 0)) // tile)      # all on the small tile here
                     assert int((ws[32::8] != 0).sum().item()) == (rows * tpr if tpr > 1 else 0), (rows, cols, extra)
+
+
+DTYPES = {"i32": "int32", "i8": "int8", "f16": "float16", "bf16": "bfloat16", "f32": "float32"}
+
+
+def values_with_loud_neighbours(kind, row_of, n, seed):
+    """Integers over their whole range; floats of -3 .. 3, with every third row infinite, NaN or the largest finite value: an
+    element of a neighbouring row that is not masked shows in the sums of a quiet row.  -> values, "this element is quiet"."""
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    dtype = getattr(torch, DTYPES[kind])
+    if kind == "i8":
+        return torch.randint(-128, 128, (n,), generator=g, device="cuda").to(dtype), torch.ones(n, dtype=torch.bool, device="cuda")
+    if kind == "i32":
+        return torch.randint(-(1 << 31), 1 << 31, (n,), generator=g, device="cuda").to(dtype), torch.ones(n, dtype=torch.bool, device="cuda")
+    x = torch.randint(-3, 4, (n,), generator=g, device="cuda").to(dtype)
+    loud = torch.tensor([float("inf"), float("nan"), -float("inf"), torch.finfo(dtype).max], device="cuda").to(dtype)
+    quiet = row_of % 3 != 1
+    return torch.where(quiet, x, loud[row_of // 3 % 4]), quiet
+
+
+def row_sums(x, quiet, starts, row_of, flags):
+    """Sums of the rows that begin at `starts`, in 64 bits; loud rows count as zero."""
+    import torch
+    v = torch.where(quiet, x, torch.zeros_like(x)).to(torch.int64)
+    inc = torch.cumsum(v, 0)
+    before = torch.cat([inc.new_zeros(1), inc])
+    ends = torch.cat([starts[1:], starts.new_tensor([v.numel()])])
+    if flags & tcuscan.REVERSE:
+        return before[ends][row_of] - (inc if flags & tcuscan.EXCLUSIVE else inc - v)
+    return inc - before[starts][row_of] - (v if flags & tcuscan.EXCLUSIVE else 0)
+
+
+def agree(got, ref, quiet):
+    import torch
+    if got.dtype == torch.int32:
+        return bool((got == ref.to(torch.int32)).all())                          # modulo 2^32
+    return bool((got[quiet].to(torch.int64) == ref[quiet]).all())
+
+
+@pytest.mark.parametrize("how,kind", [(how, kind) for how in ("workspace", "tickets", "static") for kind in KINDS]
+                         + [("in place", "i32"), ("in place", "f32")])
+def test_rows_from_lines_are_masked_and_chained(kind, how):
+    """All four kinds of scan, rows of one wavefront and of workgroup tiles, odd and at 16-byte boundaries, with loud
+    neighbours; through a workspace, with tickets, through the fixed scratch, in place (32-bit)."""
+    import torch
+    for rows, cols in ((6000, 1501), (8300, 2024), (260, 33001), (130, 65552), (1000, 9001)):
+        n = rows * cols
+        row_of = torch.arange(n, device="cuda") // cols
+        x, quiet = values_with_loud_neighbours(kind, row_of, n, cols)
+        starts = torch.arange(rows, device="cuda") * cols
+        ws = tcuscan.new_workspace(rows, cols, kind)
+        for flags in (0, 1, 2, 3):
+            src = x.clone()
+            out = src if how == "in place" else torch.full((n,), -99, dtype=torch.int32 if kind in ("i32", "i8") else torch.float32, device="cuda")
+            tcuscan.set_chain_policy(1 if how == "tickets" else 0)
+            try:
+                if how == "static":
+                    tcuscan.scan_static(src, out, rows, cols, kind, flags=flags)
+                else:
+                    tcuscan.scan(src, out, rows, cols, kind, flags=flags, ws=ws)
+            finally:
+                tcuscan.set_chain_policy(0)
+            assert agree(out, row_sums(x, quiet, starts, row_of, flags), quiet), (rows, cols, flags)
+        assert ws is None or tcuscan.workspace_fault(ws) == 0
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("rows", [300, 5000])
+def test_segmented_rows_from_lines(kind, rows):
+    """Long rows of different lengths, prepared in one launch (few rows) and in three, outputs that start inside a line,
+    inputs that fit them and one that does not, elements in front of the first row and behind the last, loud neighbours."""
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(rows)
+    lengths = torch.randint(0, 2 * (45_000_000 // rows), (rows,), generator=g, device="cuda")
+    lengths[::17] = 0
+    off = torch.cat([lengths.new_tensor([37]), 37 + torch.cumsum(lengths, 0)])
+    n, total = int(lengths.sum().item()), int(off[-1].item()) + 91
+    assert n > 1 << 23
+    row_of = torch.repeat_interleave(torch.arange(rows, device="cuda"), lengths)
+    x, quiet = values_with_loud_neighbours(kind, row_of, n, 7)
+    starts = off[:-1] - 37
+    for shift_in, shift_out in ((0, 0), (1, 1), (16, 16), (0, 4), (0, 1)):
+        src = torch.full((total + shift_in,), 99, device="cuda").to(x.dtype)[shift_in:]
+        src[37:37 + n] = x
+        for flags in (0, 1, 2, 3) if shift_out == 4 else (shift_out & 3,):
+            buf = torch.full((total + shift_out + 40,), -99, dtype=torch.int32 if kind in ("i32", "i8") else torch.float32, device="cuda")
+            out = buf[shift_out:shift_out + total]
+            ws = tcuscan.new_segmented_workspace(rows, total, kind)
+            tcuscan.segmented(src, out, off, rows, total, kind, flags=flags, ws=ws)
+            assert tcuscan.workspace_fault(ws) == 0
+            assert agree(out[37:37 + n], row_sums(x, quiet, starts, row_of, flags), quiet), (shift_in, shift_out, flags)
+            assert bool((buf[:shift_out + 37] == -99).all()) and bool((buf[shift_out + 37 + n:] == -99).all())
