@@ -67,7 +67,8 @@ typedef void *tcuscan_stream_t; /* a hipStream_t; NULL is the default stream */
  * to a 16-byte boundary, which is how rows that do not start at such a boundary are
  * tiled; for row lengths within 16 bytes of a multiple of the tile this is one word per
  * row more than the rows alone would need.  (Workspaces sized without that word are
- * still accepted; such rows then take the other tile size, a few per cent slower.)
+ * still accepted; such rows then take the other tile size, a few per cent slower.)  Rows
+ * tiled from lines of the output (tcuscan_path_for) never need more words than that.
  *
  * The caller zero-fills it ONCE after allocation (hipMemset, or tcuscan_workspace_init)
  * and may then reuse it for any number of calls whose requirement is not larger: every
@@ -96,8 +97,9 @@ tcuscan_status_t tcuscan_workspace_init(void *d_ws, size_t ws_bytes, tcuscan_str
  *          when that is 0.
  * 16-byte aligned d_in and d_out take the 128-bit load/store path.  Other alignments are
  * accepted: an input that does not start at a 16-byte boundary (and, in the row-wise calls,
- * rows whose length in bytes is not a multiple of 16) is tiled from the boundary below, the
- * elements in front read as zero and never written; an output whose alignment differs from
+ * rows whose length in bytes is not a multiple of 16) is tiled from the boundary below, in
+ * large calls from the 128-byte line of the output where that is faster, the elements in
+ * front masked out and never written; an output whose alignment differs from
  * the input's is written element by element.
  * Floating-point results are any valid fp32 summation order (MFMA accumulation order
  * and the carry chain's grouping are not fixed), so they may differ in the last bits
@@ -150,8 +152,8 @@ tcuscan_status_t tcuscan_scan(const void *d_in, void *d_out, size_t rows, size_t
  * launch.  The tile size follows the average row length total / rows.  Short rows (average below 2048 / 4096 / 8192 elements for 32- / 16- / 8-bit inputs) take another
  * form, three launches: the row starts become one bit per element, and the range the rows cover is scanned like one
  * row whose sums restart at every set bit (tcuscan_set_segmented_form(0) switches that form off).
- * Rows may start at any element: a row is tiled from the 16-byte boundary at or below its start, the few elements in
- * front of it are read as zero and not written.  Offsets that decrease or leave [0, total] are not followed: the
+ * Rows may start at any element: a row is tiled from the 16-byte boundary at or below its start (from 2^23 elements on,
+ * from the 128-byte line of the output it starts in), the elements in front of it are masked out and not written.  Offsets that decrease or leave [0, total] are not followed: the
  * workspace's fault word is set to 2 (see tcuscan_workspace_fault) and the results of the call are unspecified (such
  * rows are skipped or clipped, rows may overlap); no access outside the n = total elements is made.
  * A segmented call keeps row maps in its workspace besides status words, at places that depend on its shape, so it
@@ -228,8 +230,10 @@ tcuscan_status_t tcuscan_scan_static(const void *d_in, void *d_out, size_t rows,
  * enqueued; d_in is only looked at for its alignment).  Rows that start at 16-byte boundaries take ROWS or TILES; other
  * rows are tiled from the boundary below (Section 2.2's segments, with BatchMatMul's zero-pad in front), unless the
  * workspace has status words for neither tile size that takes -- then ELEMENTWISE, the plain tiles read element by
- * element, several times slower.  A workspace of tcuscan_workspace_bytes() never gets ELEMENTWISE.  Returns -1 for an
- * unknown dtype or an empty shape.
+ * element, several times slower.  A workspace of tcuscan_workspace_bytes() never gets ELEMENTWISE.  The query does not see
+ * the output: from 2^23 outputs on, rows of the three other paths whose outputs start inside 128-byte lines are tiled
+ * from the line where that is faster (TILES then in the manner of TILES_FROM_BOUNDARY), and the path reported is the one
+ * they would take otherwise.  Returns -1 for an unknown dtype or an empty shape.
  */
 #define TCUSCAN_PATH_ROWS                0 /* one row per wavefront, no carry chain */
 #define TCUSCAN_PATH_TILES               1 /* workgroup tiles and the carry chain */
@@ -299,8 +303,8 @@ tcuscan_status_t tcuscan_matmulscan_levels_radix(const void *d_in, void *d_out, 
 
 /*
  * Applications the paper's introduction gives as its motivation, built on the exclusive scan of a 0/1
- * int8 mask (the I8_I32 MFMA path).  The caller provides every scratch buffer; workspace as for
- * tcuscan_exclusive(.., n, TCUSCAN_I8_I32, ..).  n < 2^32.  Asynchronous on `stream`.
+ * int8 mask (the I8_I32 MFMA path; the default sort ranks its keys without it).  The caller provides every scratch
+ * buffer; workspace as for tcuscan_exclusive(.., n, TCUSCAN_I8_I32, ..).  n < 2^32.  Asynchronous on `stream`.
  *
  * Stream compaction: d_out receives, in order, the 32-bit d_values[i] whose d_mask[i] (int8) is non-zero
  * (mask entries must be 0 or 1).
@@ -313,8 +317,8 @@ tcuscan_status_t tcuscan_compact_u32(const void *d_values, const void *d_mask, v
                                      void *d_ws, size_t ws_bytes, tcuscan_stream_t stream);
 
 /*
- * Radix sort by Blelloch's reduction to prefix sums: `bits` stable split passes, least significant bit
- * first; pass b scans the mask "bit b is 0" and sends the zeros to the front and the ones behind them,
+ * Radix sort by Blelloch's reduction to prefix sums.  As the paper poses it: `bits` stable split passes, least significant
+ * bit first; pass b scans the mask "bit b is 0" and sends the zeros to the front and the ones behind them,
  * both in their old order.  Sorts the n unsigned 32-bit d_keys in place by their low `bits` bits (32 for a
  * full sort); d_vals, if not NULL, are n 32-bit payloads permuted along with the keys (so the sort is
  * observably stable).

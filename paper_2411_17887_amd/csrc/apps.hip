@@ -2,8 +2,10 @@
 // putting prefix sums on the matrix unit: stream compaction (the "split" / "pack" primitive) and, through
 // Blelloch's reduction of radix sort to prefix sums, sorting ("can TCU sort?").
 //
-// Both are thin: the only non-trivial step is the exclusive scan of a 0/1 byte mask, which is the
-// library's int8 -> int32 MFMA scan; the kernels here only build the mask and move the elements.
+// This file checks the arguments and picks the form.  Compaction and the fused one-bit split are kernels around the
+// int8 -> int32 MFMA scan of a 0/1 byte mask (tcuscan.hip); the default sort is neither (sort.hip: ranks from ballots, no
+// matrix products); the three-kernel split is the reduction spelled out, with kernels here that build the mask and move
+// the elements.
 //
 //   compaction : pos = exclusive_scan(mask);  out[pos[i]] = values[i] where mask[i] != 0
 //                (the scatter is fused into the scan kernel: tcuscan.hip, compact_kernel)
@@ -19,6 +21,7 @@
 #include <atomic>
 
 #include "../../include/tcuscan.h"
+#include "chain_layout.h"
 
 extern "C" tcuscan_status_t tcuscan_internal_compact_fused(const void *d_values, const void *d_mask, void *d_out, size_t n, void *d_positions,
                                                            unsigned *d_count, void *d_ws, size_t ws_bytes, tcuscan_stream_t stream);   // tcuscan.hip
@@ -95,7 +98,7 @@ tcuscan_status_t tcuscan_compact_u32(const void *d_values, const void *d_mask, v
     if (d_positions) {
         // what the scan of the mask into the positions asks for, and callers have sized their workspace by
         if (d_positions == d_mask) return TCUSCAN_ERR_INVALID_ARG;
-        const size_t need = n > 8192 ? 256 + 64 * ((n + 8191) / 8192) : 0;
+        const size_t need = chain_layout::bytes_for(n, chain_layout::kSmallTile);
         if (need && (!d_ws || ws_bytes < need || ((uintptr_t)d_ws % 8) != 0)) return TCUSCAN_ERR_WORKSPACE;
     }
     return tcuscan_internal_compact_fused(d_values, d_mask, d_out, n, d_positions, d_count, d_ws, ws_bytes, stream);
@@ -123,8 +126,7 @@ tcuscan_status_t tcuscan_split_radix_sort_u32(void *d_keys, void *d_vals, size_t
     // that two-bit passes ran through the workspace is what callers have sized it for: a call that needs it is refused
     // without it, although only its fault word is used.
     if (form == 1) {
-        const size_t tile = d_vals && bits >= 2 ? 8192 : 16384;
-        const size_t need = n > tile ? 256 + 64 * ((n + tile - 1) / tile) : 0;
+        const size_t need = chain_layout::bytes_for(n, d_vals && bits >= 2 ? chain_layout::kFlagTile / 2 : chain_layout::kFlagTile);
         if (need && (!d_ws || ws_bytes < need || ((uintptr_t)d_ws % 8) != 0)) return TCUSCAN_ERR_WORKSPACE;
         return tcuscan_internal_digit_sort(d_keys, d_vals, n, bits, d_keys_tmp, d_vals_tmp, d_positions, need ? d_ws : nullptr, stream);
     }

@@ -6,7 +6,8 @@
 //     wavefront        256 running counters in LDS, one row after the other
 //     workgroup        the counters of the wavefronts, added up digit by digit
 //     array            one status word per tile and digit, published and looked up as in the scan kernels' carry chain
-// A full sort is four passes of 8 bytes per key (16 with payloads) and one reading of the keys for the first term.
+// (the published scheme of least-significant-digit passes with a decoupled look-back per digit: Merrill and Garland 2016,
+// Adinets and Merrill, "Onesweep", 2022).  A full sort is four passes of 8 bytes per key (16 with payloads) and one reading of the keys for the first term.
 //
 // Up to kBlockSortMax keys one workgroup does all passes in LDS: one launch, keys and payloads read and written once.
 
@@ -206,7 +207,7 @@ struct PassArgs {
     void *status;                         // this pass's status words (zero before)
     const uint32_t *hist;                 // this pass's digit counts over the whole array
     uint32_t *ticket;                     // null, or the counter the workgroups draw their tile from (zero before)
-    uint32_t *fault;                      // null (one tile), or the workspace's fault word
+    uint32_t *fault;                      // the workspace's fault word
     uint64_t n;
     uint32_t spin_limit;
     uint32_t mute_tile;                   // test hook: the tile with this index publishes nothing
@@ -267,7 +268,7 @@ __device__ __forceinline__ Word digit_look_back(const Word *status, uint32_t d, 
         if (found) return sum;
         if (waiting) {
             if (++spins > A.spin_limit) {                  // never in correct operation: give up instead of hanging
-                if (A.fault) __hip_atomic_store(A.fault, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(A.fault, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 return S::kUnknown;
             }
             __builtin_amdgcn_s_sleep(1);
@@ -280,7 +281,9 @@ __device__ __forceinline__ Word digit_look_back(const Word *status, uint32_t d, 
 // tiles written back in a row 111 us, and without the ranking on top 100 us, which is the device's copy rate; the
 // carry chain is 12 us of it).  The tile is therefore as large as two workgroups per compute unit allow: 16 wavefronts
 // of 16 rows, 73 KiB of LDS, and the register allocator is held to 64 registers so that all 32 wavefronts are resident
-// (at 101 registers one workgroup was, 215 us a pass); 8192 keys per tile: 18 us a pass more, 12288: 15 us more.
+// (at 101 registers one workgroup was, 215 us a pass); 8192 keys per tile: 18 us a pass more, 12288: 15 us more.  The form for
+// 2^30 keys and more keeps 64-bit words and places and takes 80 to 82 registers, which is one workgroup: 2^30 + 12345 keys
+// 16.4 ms per sort, with payloads 25.1 (two-bit passes took 37.6 and 80.1), where 16 sorts of 2^26 keys take 12.2.
 template <int W, int ITEMS, bool VALS, class Word>
 __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(sizeof(Word) == 4 ? 8 : 4))) void digit_pass_kernel(PassArgs A)
 {
@@ -489,7 +492,7 @@ const void *pass_kernel(int items, bool vals, bool wide)
 }  // namespace
 
 // Used by tcuscan_split_radix_sort_u32 (apps.hip), which has checked the arguments.  d_scratch: n words (4-byte aligned);
-// d_fault: the workspace's fault word (null where the call needs no workspace).
+// d_fault: the workspace's fault word (null where the call needs no workspace, which one workgroup then sorts).
 extern "C" __attribute__((visibility("hidden")))
 tcuscan_status_t tcuscan_internal_digit_sort(void *d_keys, void *d_vals, size_t n, int bits, void *d_keys_tmp, void *d_vals_tmp,
                                              void *d_scratch, void *d_fault, tcuscan_stream_t stream)

@@ -41,6 +41,7 @@
 #include <mutex>
 
 #include "../../include/tcuscan.h"
+#include "chain_layout.h"
 #include "chain_tags.h"
 #include "wave_ops.h"
 
@@ -65,7 +66,7 @@ struct WsHeader {
     uint32_t ticket;   // ticket policy only: the next tile index to hand out (cleared in front of every such call)
     uint32_t pad[62];
 };
-static_assert(sizeof(WsHeader) == 256, "header size");
+static_assert(sizeof(WsHeader) == chain_layout::kHeaderBytes && 8 * kStatusStride == chain_layout::kSlotBytes, "header and slot size");
 
 constexpr uint32_t kStateAggregate = 1u;   // value = total of this tile only
 constexpr uint32_t kStatePrefix    = 2u;   // value = total of this tile and all before it in the row
@@ -708,12 +709,11 @@ __device__ __forceinline__ Run make_run(const Params &P, uint64_t row, uint64_t 
 // lead = off mod (elements per granule), and (off - lead) outputs are a whole number of 16-byte groups.
 //
 // `line`: from the 128-byte line of the OUTPUT the row starts in, fewer than 32 elements in front of it, so that store
-// instructions write whole lines (the memory pays for a partial line with a read: 2-D arrays whose rows start at
-// 16-byte boundaries inside lines ran 8 .. 17 % slower than the same amount of work in whole lines).  The host asks for it
-// 4095 x 65537 bf16 from the end 283 -> 265 us, 4096 x 32769 i32 195 -> 172, 300 x 1,000,004 f32 418 -> 394, 127,000 x 2101 f32
-// 395 -> 367 (with the short-row kernel's tile counts and order of rows).  The host asks for it
-// when the input is 16-byte aligned wherever the output is line aligned (line_compatible); a row whose line starts
-// before the arrays is tiled from the 16-byte boundary like any other.
+// instructions write whole lines (the memory pays for a partial line with a read).  The host asks for it when the input is
+// 16-byte aligned wherever the output is line aligned (line_compatible) and where it gains (plan_lines, launch_rows): 4095 x
+// 65537 bf16 from the end 283 -> 264 us, 4096 x 32769 i32 195 -> 172, 300 x 1,000,004 f32 418 -> 394, 127,000 x 2101 f32 393 -> 362
+// (with the short-row kernel's tile counts and order of rows).  A row whose line starts before the arrays is tiled from
+// the 16-byte boundary like any other.
 __host__ __device__ __forceinline__ uint32_t row_lead(uintptr_t in_addr, uintptr_t out_addr, uint32_t esz, long long off, bool line)
 {
     if (line) {
@@ -1819,10 +1819,10 @@ __global__ __launch_bounds__(kThreads) void scan_rows_kernel(Params P)
 }
 
 // Segmented scans, step 1: tiles per row.  A row [off, off + len) is tiled from the 16-byte boundary at or below its
-// start, so it needs ceil((lead + len) / tile) tiles (none when it is empty).  Offsets that decrease or leave
+// start, or from the line of the output it starts in (row_lead), so it needs ceil((lead + len) / tile) tiles (none when it is empty).  Offsets that decrease or leave
 // [0, total] give the row no tiles and raise the fault word instead of letting the scan touch memory outside the
 // caller's arrays.  Entry `rows` is zero: the exclusive scan of this array then ends with the total number of tiles.
-// Tiles of row r (a row is tiled from the 16-byte boundary at or below its first element); offsets that leave the
+// Tiles of row r, with the elements in front of it; offsets that leave the
 // arrays or run backwards get no tiles and raise fault word 2.
 __device__ __forceinline__ int32_t seg_row_tiles(const long long *offsets, size_t r, size_t total, uintptr_t in_addr, uintptr_t out_addr,
                                                  uint32_t esz, uint32_t line, uint32_t tile, WsHeader *ws)
@@ -1931,7 +1931,7 @@ __global__ void fill_zero_kernel(uint32_t *p, size_t words, uint32_t *p2, size_t
 
 // ------------------------------------------------------------------------ host side
 
-constexpr size_t kSmallTile = 8192;                      // elements per workgroup tile, small variant (all dtypes)
+constexpr size_t kSmallTile = chain_layout::kSmallTile;  // elements per workgroup tile, small variant (all dtypes)
 constexpr size_t kShortRowMax = 2048;                    // rows up to this length can be scanned one per wavefront
 constexpr size_t kShortRowMax32 = 2816;                  // ... 32-bit inputs: up to 11 of their 256-element MFMA tiles
 constexpr size_t kShortRowMax8 = 2560;                   // ... 8-bit inputs: two and a half of their 1024-element MFMA tiles
@@ -2159,10 +2159,11 @@ tcuscan_status_t begin_chain(Params &P, void *d_ws, size_t tiles, bool clear_fir
     return TCUSCAN_OK;
 }
 
-// Which way a row-wise call takes (tcuscan_path_for reports it; run() follows it).
+// Which way a row-wise call takes.  tcuscan_path_for reports `path`, which depends on the input; run() follows it, except
+// that plan_lines, which looks at the output too, has rows of both tile paths tiled from lines of the output (`line`).
 struct Plan {
     int path;            // TCUSCAN_PATH_*
-    int seg_cls;         // tiles from the boundary below: which tile (kSegSmall / kSegLarge)
+    int seg_cls;         // tiles from the boundary below or from lines: which tile (kSegSmall / kSegLarge)
     size_t tpr, need;    // ... tiles per row (the row and the elements in front of it) and workspace bytes they take
     bool line;           // ... from the 128-byte line of the output (row_lead)
 };
@@ -2539,6 +2540,7 @@ tcuscan_status_t flag_kernel_params(Params &P, size_t n, size_t tile, void *d_ws
 // workgroup, 64.5 KiB of LDS, two workgroups per compute unit.  (1024 per wavefront, four workgroups and twice the
 // wavefronts per compute unit: compaction 407 us against 367, sort 3.76 ms against 3.11 -- more tiles, no better overlap.)
 constexpr int kFlagNT = 2, kFlagW = 8;
+static_assert((size_t)kFlagNT * kFlagW * 1024 == chain_layout::kFlagTile, "tile of the fused split and compaction kernels");
 
 }  // namespace
 

@@ -155,8 +155,8 @@ def test_process_wide_knobs():
 
 
 def test_path_query_and_workspace_promise():
-    """tcuscan_path_for is the host-side decision run() itself follows.  With a workspace of tcuscan_workspace_bytes()
-    no shape is left to the element-wise path."""
+    """tcuscan_path_for is the part of run()'s host-side decision that depends on the input (lines of the output come on
+    top).  With a workspace of tcuscan_workspace_bytes() no shape is left to the element-wise path."""
     A, U = 0x10000, 0x10004            # a 16-byte aligned address and one that is not
     for kind, esz in (("i8", 1), ("f16", 2), ("bf16", 2), ("f32", 4), ("i32", 4)):
         tile, large = tcuscan.tile_elems(kind), tcuscan.large_tile_elems(kind)
