@@ -147,18 +147,20 @@ tcuscan_status_t tcuscan_scan(const void *d_in, void *d_out, size_t rows, size_t
  *   d_offsets  rows + 1 signed 64-bit element offsets on the DEVICE, non-decreasing, within [0, total]; 8-byte aligned
  *   total      number of elements d_in and d_out hold (an upper bound for d_offsets[rows]); sizes the launch
  *   d_ws       tcuscan_segmented_workspace_bytes(rows, total, dt) bytes, zero-filled once like every workspace here
- * Four steps are enqueued: tiles per row, their exclusive scan (this library's int32 scan), one descriptor per
- * tile (its row's extent and its place in the row), the scan itself; with fewer than 4096 rows the first three are one
- * launch.  The tile size follows the average row length total / rows.  Short rows (average below 2048 / 4096 / 8192 elements for 32- / 16- / 8-bit inputs) take another
- * form, three launches: the row starts become one bit per element, and the range the rows cover is scanned like one
- * row whose sums restart at every set bit (tcuscan_set_segmented_form(0) switches that form off).
- * Rows may start at any element: a row is tiled from the 16-byte boundary at or below its start (from 2^23 elements on,
- * from the 128-byte line of the output it starts in), the elements in front of it are masked out and not written.  Offsets that decrease or leave [0, total] are not followed: the
+ * By default the range that the rows cover is scanned like one row whose sums restart at every row start, which every tile
+ * looks up in the offsets: one launch, two in calls of 12,582,912 elements and more with short rows (average below 2048 / 4096
+ * elements for 32-bit / narrower inputs).  32-bit rows of 16,384 elements and more, from 50,331,648 elements in all and 256 rows
+ * on, do better with tiles of their own, as do all rows after tcuscan_set_segmented_form(0): tiles per row, their exclusive scan
+ * (this library's int32 scan), one descriptor per tile (its row's extent and its place in the row), the scan itself; with fewer
+ * than 4096 rows the first three are one launch.  The tile size follows the average row length total / rows.
+ * Rows may start at any element: the range, or a row with tiles of its own, is tiled from the 16-byte boundary at or below its
+ * start (such a row from 2^23 elements on from the 128-byte line of the output it starts in), the elements in front are masked
+ * out and not written.  Offsets that decrease or leave [0, total] are not followed: the
  * workspace's fault word is set to 2 (see tcuscan_workspace_fault) and the results of the call are unspecified (such
  * rows are skipped or clipped, rows may overlap); no access outside the n = total elements is made.
- * A segmented call keeps row maps in its workspace besides status words, at places that depend on its shape, so it
- * clears its status words in front of every run, and the library clears them again before another kind of call uses the
- * same workspace.  It cannot see a segmented call being REPLAYED from a graph: give such a graph a workspace that no
+ * A segmented call of more than one launch keeps row maps in its workspace besides status words, at places that depend on
+ * its shape, so it clears its status words in front of every run, and the library clears them again before another kind of call
+ * uses the same workspace.  It cannot see a segmented call being REPLAYED from a graph: give such a graph a workspace that no
  * call outside the graph uses.
  */
 size_t tcuscan_segmented_workspace_bytes(size_t rows, size_t total, tcuscan_dtype_t dt);
@@ -195,9 +197,9 @@ tcuscan_status_t tcuscan_set_tile_policy(int policy);
  */
 tcuscan_status_t tcuscan_set_chain_policy(int policy);
 
-/* 1 (default): short rows of a segmented scan are scanned as one range with row-start bits; 0: every
- * row gets tiles of its own, as for all other segmented calls.  Process-wide; a measurement and test knob, results do
- * not depend on it beyond floating-point summation order. */
+/* 1 (default): a segmented scan goes over the range of the rows as a whole where that is faster; 0: every row gets tiles
+ * of its own.  Process-wide; a measurement and test knob, results do not depend on it beyond floating-point summation
+ * order. */
 tcuscan_status_t tcuscan_set_segmented_form(int flat);
 
 /*

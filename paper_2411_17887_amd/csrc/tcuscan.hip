@@ -623,9 +623,10 @@ template <class A> __device__ __forceinline__ A row_exclusive_scan(A v)
 // a2 + a3 + a5 + a6 for the run, tile by tile with a running carry (`carry` = everything before the run).
 // Nothing passes through LDS: lane l feeds the MFMA with the granule it loaded, and results are stored
 // straight from the MFMA's result registers, 1 KiB of consecutive outputs per store instruction.
-template <int DT, int NT, bool EXCL, bool REV, bool SEG = false>
-__device__ __forceinline__ void scan_and_store(int lane, const typename Tr<DT>::AConst &Aop, const Run &R,
-                                               const u32x4 (&g)[NT], typename Tr<DT>::acc carry)
+// COUNT tiles of the run from tile t0 on; returns the carry behind them.
+template <int DT, int NT, bool EXCL, bool REV, bool SEG = false, int COUNT = NT>
+__device__ __forceinline__ typename Tr<DT>::acc scan_and_store(int lane, const typename Tr<DT>::AConst &Aop, const Run &R,
+                                                               const u32x4 (&g)[NT], typename Tr<DT>::acc carry, const int t0 = 0)
 {
     using T = Tr<DT>;
     using A = typename T::acc;
@@ -633,7 +634,7 @@ __device__ __forceinline__ void scan_and_store(int lane, const typename Tr<DT>::
     constexpr int kBlocks = T::kBlocks;
     const int c = lane & 15, q = lane >> 4;         // result layout: column, row group
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
+    for (int t = t0; t < t0 + COUNT; ++t) {
         // a2: level 0, the local scans of the 64 granules on the MFMA unit
         A4 d[kBlocks];
         T::mma(Aop, g[t], lane, EXCL, REV, d);
@@ -682,6 +683,7 @@ __device__ __forceinline__ void scan_and_store(int lane, const typename Tr<DT>::
             }
         }
     }
+    return carry;
 }
 
 template <int DT>
@@ -1333,41 +1335,250 @@ __global__ __launch_bounds__(64 * kSegPack) void seg_short_kernel(Params P)
     }
 }
 
-// ------------------------------------------------------------- segmented scans, short rows of 32-bit elements
+// ------------------------------------------------------------- segmented scans as one range
 //
-// Rows of a few hundred 32-bit elements do not get tiles of their own: the rows lie back to back, so the whole range
-// [offsets[0], offsets[rows]) is tiled like one long row -- every load and store instruction full, no descriptor per
-// tile -- and the row starts come in as one bit per element (set by seg_heads_kernel from the offsets).  The scan is
-// then the segmented one, sums restart at every set bit:
-//   level 0   a lane's granule (4 elements): the MFMA product with the triangular blocks as everywhere else; a granule
-//             with a row start at its element 1, 2 or 3 is redone by the lane in three dependent adds (the operand is
-//             the same for the 16 granules of a product, so it cannot know where one of them is cut -- and subtracting
-//             the part before the cut would not be exact in floating point);
+// The rows lie back to back, so the whole range [offsets[0], offsets[rows]) is tiled like one long row -- every load and
+// store instruction full, nothing but the range's ends to be known in front of a tile's loads -- and the scan is the segmented
+// one, sums restart at every row start.  A tile finds the row starts that fall into it in the offsets while its data are on
+// their way and marks them as bits in LDS, one per element (RowMarks, RunMarks).
+//   level 0   in the lane: its granule's elements by dependent adds that drop what came before a row start (subtracting it
+//             afterwards would not be exact in floating point; in these kernels three adds are also faster than the f32
+//             product: 2^26 f32 in rows of mean length 200 106 -> 102 us);
 //   levels 1, 2   (sum since the last row start, "a row starts here") pairs scanned over the 64 lanes with DPP shifts:
 //             a pair that has a start keeps its sum, the others add the incoming one;
 //   beyond    the pair of the wavefront's run, of the workgroup, of the tile.  A tile that contains a row start knows
 //             what its successors need without asking anybody -- it publishes its pair as a finished prefix at once --
 //             so with short rows the carry chain is one hop long, and with long rows it is the usual one.
-// The results stay in the registers that held the inputs (one granule in, one granule out) while the tile waits for
-// what comes before it; that sum is then added to the elements that no row start precedes within the tile.
 // A reverse scan is the same in mirrored order, restarting at row ends.
+//
+// Two kernels.  Calls below kSegStreamFrom elements are as long as their launches (with the bits set in memory by kernels of
+// their own they took three: 13.5 us for 10^5 elements, 7.3 now), and their tiles are small; the results stay in the
+// registers that held the inputs while the tile waits for what comes before it (seg_flat_kernel, seg_flat_narrow_kernel).
+// In large calls what counts is bytes in flight (seg_stream_kernel).
 
-__global__ void seg_heads_kernel(const long long *offsets, size_t rows, size_t total, uint32_t shift, uint32_t *heads, WsHeader *ws)
+// What an LDS access of one lane wrote, other lanes of the wavefront see from here on.
+__device__ __forceinline__ void wavefront_sync()
 {
-    const size_t r = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= rows) return;
-    const long long off = offsets[r], end = offsets[r + 1];
-    const bool bad = off < 0 || end < off || (unsigned long long)end > total;
-    if (bad) __hip_atomic_store(&ws->fault, 2u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if ((end > off || bad) && off >= 0 && (unsigned long long)off < total) {   // (a bad row still ends the row before it)
-        const uint64_t b = (uint64_t)off + shift;                      // bit of element i: i + shift (granules start at multiples of 4)
-        atomicOr(&heads[b >> 5], 1u << (b & 31));
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// The row starts of a tile -- elements first .. first + ELEMS of the arrays, the last one only for a reverse scan, in which it ends
+// the row before -- as bits in LDS.  All threads of the workgroup call.  The entries that matter are a stretch of the sorted
+// offsets: a search that asks for one offset per thread at a time finds about where it begins (one dependent load up to
+// 2^19 rows, the same offsets for every workgroup, which the L2 has; two beyond; none up to kWindow offsets, which are read
+// as a whole), then a window of the offsets is read and what falls into the tile is marked.  begin() puts the first loads
+// in flight ahead of the tile's data, which do not depend on them.  Whatever the offsets hold, reads stay inside their
+// array and every round of mark() moves on by a window.
+template <int W, uint32_t ELEMS> struct RowMarks {
+    static constexpr uint32_t kT = 64u * W, kPer = 4u, kWindow = kPer * kT;
+    static constexpr long long kNone = 0x7FFFFFFFFFFFFFFFll;
+    struct Lds {
+        uint32_t bits[ELEMS / 32u + 2u * W];          // RunMarks: two words more per wavefront
+        uint32_t in_front[2][W];
+        long long edge[2][2];              // first and last offset of the window
+    };
+    const long long *offsets;
+    uint32_t n, lo, len;                   // number of offsets; the first one that is not in front of the key is entry lo .. lo + len
+    uint32_t round, size;                  // size: entries in the window
+    typedef long long Offsets __attribute__((ext_vector_type(4)));
+    Offsets v;                             // (a vector: an array member is put into LDS by the compiler)
+    static_assert(kPer == 4u, "offsets per thread");
+
+    __device__ __forceinline__ uint32_t step() const { return (len + kT - 1u) / kT; }
+    __device__ __forceinline__ void probe()
+    {
+        const uint32_t at = lo + (threadIdx.x + 1u) * step() - 1u;
+        v[0] = at < lo + len ? offsets[at] : kNone;
     }
-    if (r == rows - 1 && !bad) {                                       // behind the last row: its last element ends a row (reverse scans)
-        const uint64_t b = (uint64_t)end + shift;
-        atomicOr(&heads[b >> 5], 1u << (b & 31));
+    __device__ __forceinline__ uint32_t sized(uint32_t rows) const { return rows < kWindow ? (rows + kT) / kT * kT : kWindow; }
+    __device__ __forceinline__ void window()
+    {
+#pragma unroll
+        for (uint32_t u = 0; u < kPer; ++u) {
+            const uint32_t at = lo + u * kT + threadIdx.x;
+            v[u] = u * kT < size && at < n ? offsets[at] : kNone;
+        }
+    }
+    __device__ __forceinline__ void begin(const long long *off, uint32_t entries, Lds &s)
+    {
+        offsets = off; n = entries; lo = 0u; len = entries; round = 0u; size = kWindow;
+        if (n <= kWindow) window(); else probe();
+        for (uint32_t i = threadIdx.x; i < ELEMS / 32u + 1u; i += kT) s.bits[i] = 0u;
+    }
+    // With a probe in flight: on to a stretch of at most half a window.
+    __device__ __forceinline__ void search(long long key, Lds &s)
+    {
+        for (;;) {
+            const uint64_t b = __ballot(v[0] < key);
+            uint32_t *in_front = s.in_front[round++ & 1u];             // (read by all before anybody is two barriers on)
+            if ((threadIdx.x & 63u) == 0u) in_front[threadIdx.x >> 6] = (uint32_t)__builtin_popcountll(b);
+            __syncthreads();
+            uint32_t c = 0u;
+#pragma unroll
+            for (int w = 0; w < W; ++w) c += in_front[w];
+            const uint32_t past = (uint32_t)__builtin_amdgcn_readfirstlane((int)c) * step(), st = step();
+            lo += past;
+            len = len - past < st ? len - past : st;
+            if (len <= kWindow / 2u) return;
+            probe();
+        }
+    }
+    // `expect`: about how many rows start in a tile.
+    __device__ __forceinline__ void mark(long long first, uint32_t expect, Lds &s)
+    {
+        if (len <= kWindow) {                                          // the window is in flight
+            __syncthreads();                                           // (the bits are clear)
+        } else {
+            search(first, s);
+            size = sized(len + expect);
+            window();
+        }
+        for (;;) {
+            long long *edge = s.edge[round++ & 1u];
+#pragma unroll
+            for (uint32_t u = 0; u < kPer; ++u) {
+                const uint64_t j = (uint64_t)v[u] - (uint64_t)first;
+                if (j <= ELEMS) atomicOr(&s.bits[(uint32_t)j >> 5], 1u << ((uint32_t)j & 31u));
+                if (u == 0u && threadIdx.x == 0u) edge[0] = v[u];
+                if (u * kT + threadIdx.x == size - 1u) edge[1] = v[u];
+            }
+            __syncthreads();
+            if (n - lo <= size) return;                                // (lo < n: the window began with an entry)
+            const long long last = edge[1];
+            if (last > first + (long long)ELEMS) return;
+            const uint64_t distinct = (uint64_t)last - (uint64_t)edge[0];
+            lo += size;
+            if (distinct < size / 16u) {                               // nearly all rows empty: on to the next offset that differs
+                len = n - lo;
+                probe();
+                search(last < kNone ? last + 1 : last, s);
+                if (lo >= n) return;
+            }
+            size = kWindow;
+            window();
+        }
+    }
+};
+
+// The same for one wavefront's run, whose first row is known (seg_first_rows_kernel), by the wavefront alone: no search and no
+// barrier.
+template <uint32_t ELEMS> struct RunMarks {
+    static constexpr uint32_t kPer = 4u, kWindow = 64u * kPer;
+    static constexpr long long kNone = 0x7FFFFFFFFFFFFFFFll;
+    const long long *offsets;
+    uint32_t n, lo, size;
+    typedef long long Offsets __attribute__((ext_vector_type(4)));
+    Offsets v;
+
+    __device__ __forceinline__ void window(uint32_t lane)
+    {
+#pragma unroll
+        for (uint32_t u = 0; u < kPer; ++u) {
+            const uint32_t at = lo + 64u * u + lane;
+            v[u] = 64u * u < size && at < n ? offsets[at] : kNone;
+        }
+    }
+    __device__ __forceinline__ void begin(const long long *off, uint32_t entries, uint32_t at, uint32_t expect, uint32_t lane, uint32_t *run_bits)
+    {
+        offsets = off; n = entries; lo = at < n ? at : n - 1u;
+        size = expect < kWindow ? (expect + 64u) / 64u * 64u : kWindow;
+        window(lane);
+        for (uint32_t i = lane; i < ELEMS / 32u + 1u; i += 64u) run_bits[i] = 0u;
+    }
+    static __device__ __forceinline__ long long from_lane(long long x, int l)
+    {
+        return (long long)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)((uint64_t)x >> 32), l) << 32) |
+                           (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(uint64_t)x, l));
+    }
+    __device__ __forceinline__ void mark(long long first, uint32_t lane, uint32_t *run_bits)
+    {
+        wavefront_sync();                                              // the bits are clear
+        for (;;) {
+            long long last = kNone;
+#pragma unroll
+            for (uint32_t u = 0; u < kPer; ++u) {
+                const uint64_t j = (uint64_t)v[u] - (uint64_t)first;
+                if (j <= ELEMS) atomicOr(&run_bits[(uint32_t)j >> 5], 1u << ((uint32_t)j & 31u));
+                if (64u * (u + 1u) == size) last = from_lane(v[u], 63);
+            }
+            if (n - lo <= size || last > first + (long long)ELEMS) break;
+            const uint64_t distinct = (uint64_t)last - (uint64_t)from_lane(v[0], 0);
+            lo += size;
+            if (distinct < size / 16u) {                               // nearly all rows empty: on to about the next offset that differs
+                for (uint32_t len = n - lo; len > 64u;) {
+                    const uint32_t step = (len + 63u) / 64u, at = lo + (lane + 1u) * step - 1u;
+                    const uint32_t past = (uint32_t)__builtin_popcountll(__ballot(at < lo + len && offsets[at] <= last)) * step;
+                    lo += past;
+                    len = len - past < step ? len - past : step;
+                }
+                if (lo >= n) break;
+            }
+            size = kWindow;
+            window(lane);
+        }
+        wavefront_sync();
+    }
+};
+
+// Offsets that decrease or leave [0, total] raise fault word 2: workgroup `tile` looks at `per` rows.
+__device__ __forceinline__ void seg_check_offsets(const long long *offsets, const Params &P, uint32_t tile, uint32_t per, uint32_t thread, uint32_t threads)
+{
+    const uint64_t from = (uint64_t)tile * per, to = from + per < P.rows ? from + per : P.rows;
+    bool bad = false;
+    for (uint64_t r = from + thread; r < to; r += threads) {
+        const long long off = offsets[r], end = offsets[r + 1];
+        bad = bad || off < 0 || end < off || (unsigned long long)end > P.cols;
+    }
+    if (bad) __hip_atomic_store(&P.ws->fault, 2u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// In front of large calls of short rows: every run's first row -- the first offset at or behind the run's start; the offsets are
+// checked and the status words cleared on the way.  The launch costs 5 us, and up to 10 in calls that come from HBM; with a
+// search in the scan instead, two dependent loads in front of every tile: 2^26 f32 in rows of mean length 16 / 200 112 / 101 ->
+// 126 / 112 us, but of 20,000 106 -> 104 (i8: 59 -> 55), hence the search where the average row is long.
+template <int TILE, int W>
+__global__ __launch_bounds__(256) void seg_first_rows_kernel(Params P, const long long *offsets, uint32_t esz, uint32_t *first_rows)
+{
+    const uint64_t r = (uint64_t)blockIdx.x * 256u + threadIdx.x;
+    const long long total = (long long)P.cols;
+    long long begin = offsets[0], end = offsets[P.rows];       // as the scan kernel takes them
+    begin = begin < 0 ? 0 : (begin > total ? total : begin);
+    end = end < begin ? begin : (end > total ? total : end);
+    begin -= (long long)row_lead((uintptr_t)P.in, (uintptr_t)P.out, esz, begin, false);
+    // runs, rounded up to whole tiles: a reverse scan counts tiles, and the runs of a tile, from the end
+    const uint32_t tiles = (uint32_t)((uint64_t)(end - begin + TILE * W - 1) / (TILE * W)) * W;
+    if (r < P.num_tiles) *((uint64_t *)(P.ws + 1) + r * kStatusStride) = 0ull;
+    long long from = 0, to = -1;                               // the tiles that begin behind the offset before and not behind this one
+    if (r <= P.rows) {
+        const long long off = offsets[r];
+        if (r != 0) {
+            const long long prev = offsets[r - 1];
+            if (prev < 0 || off < prev || off > total) __hip_atomic_store(&P.ws->fault, 2u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            from = prev < begin ? 0 : prev > total ? (long long)tiles : (prev - begin) / TILE + 1;
+        }
+        to = off < begin ? -1 : off > total ? (long long)tiles - 1 : (off - begin) / TILE;
+        to = r < P.rows && to < (long long)tiles ? to : (long long)tiles - 1;         // (the last offset: of all runs behind it too)
+    }
+    // (in processing order: a reverse scan's first tile is the last)
+    if (from == to) first_rows[P.reverse ? tiles - 1u - (uint32_t)from : (uint32_t)from] = (uint32_t)r;
+    // a row of several tiles: all lanes write
+    for (uint64_t more = __ballot(from < to); more != 0ull; more &= more - 1ull) {
+        const int l = __builtin_ctzll(more);
+        const uint32_t a = (uint32_t)__builtin_amdgcn_readlane((int)from, l), b = (uint32_t)__builtin_amdgcn_readlane((int)to, l);
+        const uint32_t row = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)r, l);
+        for (uint32_t t = a + (threadIdx.x & 63u); t <= b; t += 64u) first_rows[P.reverse ? tiles - 1u - t : t] = row;
     }
 }
+
+struct FlatArgs {
+    const long long *offsets;
+    const uint32_t *first_rows;            // seg_stream_kernel: every run's first row
+    uint32_t expect;                       // about how many rows start in a tile
+    uint32_t check_rows;                   // rows whose offsets a workgroup checks 
+    uint32_t stream;                       // input and output do not fit the memory-side cache: the input is read around it (32-bit)
+};
 
 // (sum since the last row start, a row starts at or before here) of lanes 0 .. l, in lane l
 template <class A> __device__ __forceinline__ void seg_wave_inclusive(A &v, uint32_t &h)
@@ -1424,7 +1635,10 @@ __device__ __forceinline__ A seg_open_sum_before_run(const Params &P, uint32_t t
     A prefix = acc_from_bits<A>(0u);
     if (P.num_tiles > 1) {
         uint64_t *row_status = (uint64_t *)(P.ws + 1);
-        if (wave == 0) {
+        // The wavefront that comes first looks back; if a row starts in its run, no other needs what it finds.
+        constexpr int kFirst = REV ? W - 1 : 0;
+        const bool for_all = s_head[kFirst] == 0u;
+        if (wave == kFirst) {
             if (tile == 0 || wg_head) {
                 if (lane == 0)
                     __hip_atomic_store(row_status + (size_t)tile * kStatusStride, status_word(tag, kStatePrefix, acc_bits(wg_sum)),
@@ -1439,16 +1653,18 @@ __device__ __forceinline__ A seg_open_sum_before_run(const Params &P, uint32_t t
                     __hip_atomic_store(row_status + (size_t)tile * kStatusStride, status_word(tag, kStatePrefix, acc_bits(acc_add(prefix, wg_sum))),
                                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
-            if (lane == 0) *s_bcast = acc_bits(prefix);
+            if (for_all && lane == 0) *s_bcast = acc_bits(prefix);
         }
-        __syncthreads();
-        prefix = acc_from_bits<A>(*s_bcast);
+        if (for_all) {
+            __syncthreads();
+            prefix = acc_from_bits<A>(*s_bcast);
+        }
     }
     return before_head ? before : acc_add(prefix, before);
 }
 
 template <int DT, int NT, bool EXCL, bool REV, int W>
-__global__ __launch_bounds__(64 * W) void seg_flat_kernel(Params P, const long long *offsets, const uint32_t *heads, uint32_t shift)
+__global__ __launch_bounds__(64 * W) void seg_flat_kernel(Params P, FlatArgs F)
 {
     using T = Tr<DT>;
     using A = typename T::acc;
@@ -1457,111 +1673,112 @@ __global__ __launch_bounds__(64 * W) void seg_flat_kernel(Params P, const long l
     constexpr uint32_t kWgElems = kEPW * W;
     __shared__ uint32_t s_sum[W], s_head[W];
     __shared__ uint32_t s_bcast;
+    using Marks = RowMarks<W, kWgElems>;
+    __shared__ typename Marks::Lds s_marks;
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const uint32_t tile = take_tile(P, &s_bcast);
+    if (tile >= P.num_tiles) {                                 // beyond the largest number of tiles: here for the offsets only
+        seg_check_offsets(F.offsets, P, tile, F.check_rows, threadIdx.x, 64 * W);
+        return;
+    }
+    Marks marks;
+    __builtin_amdgcn_s_setprio(3);                  // loads first, as in scan_kernel
+    marks.begin(F.offsets, (uint32_t)P.rows + 1u, s_marks);
 
-    // the range the rows cover, clamped to the arrays (offsets that leave them have raised the fault word already)
-    long long lo = offsets[0], hi = offsets[P.rows];
+    // the range the rows cover, clamped to the arrays
+    long long lo = F.offsets[0], hi = F.offsets[P.rows];
     const long long total = (long long)P.cols;
     lo = lo < 0 ? 0 : (lo > total ? total : lo);
     hi = hi < lo ? lo : (hi > total ? total : hi);
     const uint32_t lead = seg_lead<DT, false>(P, lo);
     const uint64_t vlen = (uint64_t)(hi - lo) + lead;
     const uint64_t tiles = (vlen + kWgElems - 1) / kWgElems;
-    if (tile >= tiles) return;                                 // the grid is an upper bound
+    if (tile >= tiles) {                                       // the grid is an upper bound
+        seg_check_offsets(F.offsets, P, tile, F.check_rows, threadIdx.x, 64 * W);
+        return;
+    }
     const uint64_t pos = REV ? tiles - 1 - tile : tile;        // a reverse scan starts at the end of the range
     const uint64_t base = pos * kWgElems + (uint64_t)wave * kEPW;
     const Run R = make_seg_run<DT>(P, lo, (uint64_t)(hi - lo), lead, base);
     // Everything below works in processing order: element i of a granule is its memory element mem(i); a reverse scan
     // mirrors the granules of the run (slot_offset), the elements inside a granule, the wavefronts and the tiles, and
-    // restarts at row ENDS -- element j ends a row when a row starts at j + 1 (the kernel that sets the bits also sets
-    // the one behind the last row).
+    // restarts at row ENDS -- element j ends a row when a row starts at j + 1 (the offset behind the last row is
+    // marked too).
     auto mem = [](int i) { return REV ? 3 - i : i; };
 
     // a run that lies inside the range as a whole (all but the first and the last few) takes straight-line loads and stores
     const bool whole_in = !REV && __builtin_amdgcn_readfirstlane((int)(R.in_vec && R.lead == 0u && R.rem >= kEPW)) != 0;
     const bool whole_out = __builtin_amdgcn_readfirstlane((int)(R.out_vec && R.lead == 0u && R.rem >= kEPW)) != 0;   // (either direction)
-    __builtin_amdgcn_s_setprio(3);                  // loads first, as in scan_kernel
     u32x4 g[NT];
-    // row starts among this lane's elements: 4 bits per granule, granule t in bits 4t .. 4t + 3
-    const uint64_t bit0 = (uint64_t)(lo - (long long)lead) + base + shift;     // bit of the run's first slot (a multiple of 4)
-    uint32_t starts = 0u;
     if (whole_in) {
 #pragma unroll
         for (int t = 0; t < NT; ++t) g[t] = *(const u32x4 *)(R.in + ((uint32_t)t * 256u + 4u * lane) * 4u);
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            const uint64_t b = bit0 + (uint32_t)t * 256u + 4u * lane;
-            starts |= ((heads[b >> 5] >> (b & 31)) & 0xFu) << (4 * t);
-        }
     } else {
         load_run<DT, NT, REV, true>(R, lane, g);
+    }
+    marks.mark(lo - (long long)lead + (long long)(pos * kWgElems), F.expect, s_marks);
+    const uint32_t *run_bits = s_marks.bits + kEPW / 32u * wave;
+    // row starts among this lane's elements: 4 bits per granule, granule t in bits 4t .. 4t + 3
+    uint32_t starts = 0u;
 #pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            const uint32_t e0 = slot_offset<DT, NT, REV>(t, lane);
-            if (e0 < R.rem) {
-                const uint64_t b = bit0 + e0;
-                if constexpr (REV) {
-                    const uint64_t w = (uint64_t)heads[b >> 5] | ((uint64_t)heads[(b >> 5) + 1] << 32);
-                    const uint32_t ends = (uint32_t)(w >> ((b & 31) + 1)) & 0xFu;                     // memory order
-                    starts |= (((ends & 1u) << 3) | ((ends & 2u) << 1) | ((ends & 4u) >> 1) | ((ends & 8u) >> 3)) << (4 * t);
-                } else {
-                    starts |= ((heads[b >> 5] >> (b & 31)) & 0xFu) << (4 * t);
-                }
-            }
+    for (int t = 0; t < NT; ++t) {
+        const uint32_t j = slot_offset<DT, NT, REV>(t, lane);        // (a multiple of 4)
+        if (!whole_in && j >= R.rem) continue;
+        const uint32_t w = run_bits[j >> 5];
+        if constexpr (REV) {
+            const uint32_t ends = (uint32_t)((((uint64_t)run_bits[(j >> 5) + 1u] << 32) | w) >> ((j & 31u) + 1u)) & 0xFu;       // memory order
+            starts |= (((ends & 1u) << 3) | ((ends & 2u) << 1) | ((ends & 4u) >> 1) | ((ends & 8u) >> 3)) << (4 * t);
+        } else {
+            starts |= ((w >> (j & 31u)) & 0xFu) << (4 * t);
         }
     }
 
     __builtin_amdgcn_s_setprio(0);
     // ---- the run by itself: segmented scan in place, (sum since the last row start, any row start) of the run
-    const typename T::AConst Aop = T::make(lane, false, REV);
     A carry = acc_from_bits<A>(0u);                            // sum since the last row start, up to the end of the tile before
     bool run_open = true;                                      // no row start in the run so far
     uint32_t open = 0u;                                        // bit t: no row start in the run before this lane's granule of tile t
-    A in[NT];                                                  // what the open row brings into that granule from inside the run
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
         const uint32_t fb = (starts >> (4 * t)) & 0xFu;
-        A y[4];
-        if (__ballot((fb & 0xEu) != 0u) == 0ull) {             // no granule of this tile is cut: the product is the scan
-            typename T::acc4 d[1];
-            T::mma(Aop, g[t], lane, false, REV, d);
-            for (int i = 0; i < 4; ++i) y[i] = acc_from_bits<A>(bits<u32x4>(d[0])[mem(i)]);
-        } else {                                               // three dependent adds; a row start drops what came before
-            y[0] = acc_from_bits<A>(g[t][mem(0)]);
-            for (int i = 1; i < 4; ++i) {
-                const uint32_t keep = (uint32_t)(((int32_t)(~fb << (31 - i))) >> 31);       // all ones unless a row starts at i
-                y[i] = acc_add(acc_from_bits<A>(acc_bits(y[i - 1]) & keep), acc_from_bits<A>(g[t][mem(i)]));
-            }
+        A y[4];                                                // three dependent adds; a row start drops what came before
+        y[0] = acc_from_bits<A>(g[t][mem(0)]);
+        for (int i = 1; i < 4; ++i) {
+            const uint32_t keep = (uint32_t)(((int32_t)(~fb << (31 - i))) >> 31);           // all ones unless a row starts at i
+            y[i] = acc_add(acc_from_bits<A>(acc_bits(y[i - 1]) & keep), acc_from_bits<A>(g[t][mem(i)]));
         }
-        for (int i = 0; i < 4; ++i) g[t][mem(i)] = acc_bits(y[i]);
         A v = y[3];
         uint32_t h = fb ? 1u : 0u;
         seg_wave_inclusive(v, h);
         const A vex = wave_shift_up(v);
         const uint32_t hex = dpp0<kWaveShr1>(h);
-        in[t] = hex ? vex : acc_add(carry, vex);
+        const A in = hex ? vex : acc_add(carry, vex);         // what the open row brings into the granule from inside the run
+        const uint32_t first = fb ? (uint32_t)__builtin_ctz(fb) : 4u;     // elements before the granule's first row start
+        for (int i = 0; i < 4; ++i) g[t][mem(i)] = acc_bits((uint32_t)i < first ? acc_add(in, y[i]) : y[i]);
         if (run_open && !hex) open |= 1u << t;
-        carry = uniform_from_lane(fb ? y[3] : acc_add(in[t], y[3]), 63);
+        carry = uniform_from_lane(acc_from_bits<A>(g[t][mem(3)]), 63);
         run_open = run_open && __ballot(fb != 0u) == 0ull;
     }
 
     // ---- the wavefronts of the workgroup, then the tiles before this one: the open row's sum at the start of this run
+    // (the wavefronts that do not look back check offsets meanwhile)
+    if (wave != (REV ? W - 1 : 0))
+        seg_check_offsets(F.offsets, P, tile, F.check_rows, threadIdx.x - (REV ? 0u : 64u), 64u * (W - 1));
     const A wave_in = seg_open_sum_before_run<A, W, REV>(P, tile, lane, wave, carry, run_open, s_sum, s_head, &s_bcast);
 
-    // ---- what the open row brings, to the elements that no row start of their granule precedes; store
+    // ---- what the open row brings, to the elements that no row start of the run precedes; store
+    asm("" : "+v"(starts));                                    // (taken apart once more: kept from above, the parts cost 16 registers)
     A last = wave_in;                                          // the inclusive result of the element before the granule (exclusive scans)
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
         const uint32_t fb = (starts >> (4 * t)) & 0xFu;
-        const A add = ((open >> t) & 1u) ? acc_add(wave_in, in[t]) : in[t];
-        const uint32_t first = fb ? (uint32_t)__builtin_ctz(fb) : 4u;     // elements before the granule's first row start
+        const uint32_t first = !((open >> t) & 1u) ? 0u : fb ? (uint32_t)__builtin_ctz(fb) : 4u;
         A y[4];
         for (int i = 0; i < 4; ++i) {
             y[i] = acc_from_bits<A>(g[t][mem(i)]);
-            if ((uint32_t)i < first) y[i] = acc_add(add, y[i]);
+            if ((uint32_t)i < first) y[i] = acc_add(wave_in, y[i]);
         }
         u32x4 v;
         if constexpr (EXCL) {
@@ -1585,7 +1802,7 @@ __global__ __launch_bounds__(64 * W) void seg_flat_kernel(Params P, const long l
     }
 }
 
-// ---- the same for 8- and 16-bit inputs
+// ---- the small kernel for 8- and 16-bit inputs
 //
 // A lane's granule is 16 or 8 elements, and the matrix unit would hand its results to four or two other lanes (the
 // result layout that makes the plain scan's stores contiguous).  Here level 0 stays in the lane: the granule is
@@ -1609,7 +1826,7 @@ template <> __device__ __forceinline__ float narrow_elem<TCUSCAN_F16_F32>(const 
 }
 
 template <int DT, bool EXCL, bool REV, int W>
-__global__ __launch_bounds__(64 * W) void seg_flat_narrow_kernel(Params P, const long long *offsets, const uint32_t *heads, uint32_t shift)
+__global__ __launch_bounds__(64 * W) void seg_flat_narrow_kernel(Params P, FlatArgs F)
 {
     using T = Tr<DT>;
     using A = typename T::acc;
@@ -1621,19 +1838,31 @@ __global__ __launch_bounds__(64 * W) void seg_flat_narrow_kernel(Params P, const
     constexpr uint32_t kMask = (1u << G) - 1u;
     __shared__ uint32_t s_sum[W], s_head[W];
     __shared__ uint32_t s_bcast;
+    using Marks = RowMarks<W, kWgElems>;
+    __shared__ typename Marks::Lds s_marks;
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const uint32_t tile = take_tile(P, &s_bcast);
+    if (tile >= P.num_tiles) {                                 // beyond the largest number of tiles: here for the offsets only
+        seg_check_offsets(F.offsets, P, tile, F.check_rows, threadIdx.x, 64 * W);
+        return;
+    }
+    Marks marks;
+    __builtin_amdgcn_s_setprio(3);                  // loads first, as in scan_kernel
+    marks.begin(F.offsets, (uint32_t)P.rows + 1u, s_marks);
 
-    long long lo = offsets[0], hi = offsets[P.rows];
+    long long lo = F.offsets[0], hi = F.offsets[P.rows];
     const long long total = (long long)P.cols;
     lo = lo < 0 ? 0 : (lo > total ? total : lo);
     hi = hi < lo ? lo : (hi > total ? total : hi);
     const uint32_t lead = seg_lead<DT, false>(P, lo);
     const uint64_t vlen = (uint64_t)(hi - lo) + lead;
     const uint64_t tiles = (vlen + kWgElems - 1) / kWgElems;
-    if (tile >= tiles) return;                                 // the grid is an upper bound
+    if (tile >= tiles) {                                       // the grid is an upper bound
+        seg_check_offsets(F.offsets, P, tile, F.check_rows, threadIdx.x, 64 * W);
+        return;
+    }
     const uint64_t pos = REV ? tiles - 1 - tile : tile;        // a reverse scan starts at the end of the range
     const uint64_t base = pos * kWgElems + (uint64_t)wave * kEPW;
     const Run R = make_seg_run<DT>(P, lo, (uint64_t)(hi - lo), lead, base);
@@ -1641,33 +1870,26 @@ __global__ __launch_bounds__(64 * W) void seg_flat_narrow_kernel(Params P, const
     const bool whole_in = !REV && __builtin_amdgcn_readfirstlane((int)(R.in_vec && R.lead == 0u && R.rem >= kEPW)) != 0;
     const bool whole_out = __builtin_amdgcn_readfirstlane((int)(R.out_vec && R.lead == 0u && R.rem >= kEPW)) != 0;
 
-    __builtin_amdgcn_s_setprio(3);                  // loads first, as in scan_kernel
     u32x4 g[NT];
-    const uint64_t bit0 = (uint64_t)(lo - (long long)lead) + base + shift;     // bit of the run's first slot (a multiple of G)
-    uint32_t starts = 0u;                                      // G bits per granule, granule t in bits G t ..
     if (whole_in) {
 #pragma unroll
         for (int t = 0; t < NT; ++t) g[t] = *(const u32x4 *)(R.in + ((uint32_t)t * kTile + (uint32_t)G * lane) * T::kEsz);
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            const uint64_t b = bit0 + (uint32_t)t * kTile + (uint32_t)G * lane;
-            starts |= ((heads[b >> 5] >> (b & 31)) & kMask) << (G * t);
-        }
     } else {
         load_run<DT, NT, REV, true>(R, lane, g);
+    }
+    marks.mark(lo - (long long)lead + (long long)(pos * kWgElems), F.expect, s_marks);
+    const uint32_t *run_bits = s_marks.bits + kEPW / 32u * wave;
+    uint32_t starts = 0u;                                      // G bits per granule, granule t in bits G t ..
 #pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            const uint32_t e0 = slot_offset<DT, NT, REV>(t, lane);
-            if (e0 < R.rem) {
-                const uint64_t b = bit0 + e0;
-                if constexpr (REV) {                           // row ends: a row starts one element further on; mirrored
-                    const uint64_t w = (uint64_t)heads[b >> 5] | ((uint64_t)heads[(b >> 5) + 1] << 32);
-                    const uint32_t ends = (uint32_t)(w >> ((b & 31) + 1)) & kMask;
-                    starts |= (__builtin_bitreverse32(ends) >> (32 - G)) << (G * t);
-                } else {
-                    starts |= ((heads[b >> 5] >> (b & 31)) & kMask) << (G * t);
-                }
-            }
+    for (int t = 0; t < NT; ++t) {
+        const uint32_t j = slot_offset<DT, NT, REV>(t, lane);        // (a multiple of G)
+        if (!whole_in && j >= R.rem) continue;
+        const uint32_t w = run_bits[j >> 5];
+        if constexpr (REV) {                                   // row ends: a row starts one element further on; mirrored
+            const uint32_t ends = (uint32_t)((((uint64_t)run_bits[(j >> 5) + 1u] << 32) | w) >> ((j & 31u) + 1u)) & kMask;
+            starts |= (__builtin_bitreverse32(ends) >> (32 - G)) << (G * t);
+        } else {
+            starts |= ((w >> (j & 31u)) & kMask) << (G * t);
         }
     }
 
@@ -1699,6 +1921,9 @@ __global__ __launch_bounds__(64 * W) void seg_flat_narrow_kernel(Params P, const
     }
 
     // ---- the wavefronts of the workgroup, then the tiles before this one: the open row's sum at the start of this run
+    // (the wavefronts that do not look back check offsets meanwhile)
+    if (wave != (REV ? W - 1 : 0))
+        seg_check_offsets(F.offsets, P, tile, F.check_rows, threadIdx.x - (REV ? 0u : 64u), 64u * (W - 1));
     const A wave_in = seg_open_sum_before_run<A, W, REV>(P, tile, lane, wave, carry, run_open, s_sum, s_head, &s_bcast);
 
     // ---- the open row's sum to the elements that no row start of their granule precedes; results change lanes; store
@@ -1750,6 +1975,206 @@ __global__ __launch_bounds__(64 * W) void seg_flat_narrow_kernel(Params P, const
                     if (e[k] + i < R.rem && e[k] + i >= R.lead) ((uint32_t *)R.out)[e[k] + i] = v[k][i];
             }
         }
+    }
+}
+
+// ---- large calls, all input types
+//
+// The flat kernels hold their results while they wait for what comes before the run, four bytes an element, and read the
+// offsets by a search; where a call is long enough that its first rows are found beforehand (seg_first_rows_kernel), this one
+// does as scan_kernel does: reduce, publish, wait with the narrow inputs in registers, then scan -- twice the additions, and
+// twice or more as many bytes in flight.  What the open row of a run adds up to begins behind the last row start of the run:
+// everything in front is masked out of the sum.  An MFMA tile that no row starts in takes scan_kernel's way (products with
+// the triangular blocks), one that is cut keeps level 0 in the lane, as in the flat kernels.
+
+// A tile of the run in which rows start: fb has this lane's, in processing order.  carry: the open row's sum in front of the tile,
+// and behind it.
+template <int DT, int NT, bool EXCL, bool REV>
+__device__ __forceinline__ void seg_scan_and_store_cut_tile(int lane, const Run &R, bool whole, int t, const u32x4 &gt, uint32_t fb,
+                                                            typename Tr<DT>::acc &carry)
+{
+    using A = typename Tr<DT>::acc;
+    constexpr int G = Tr<DT>::kG, Q = G / 4;
+    auto mem = [](int i) { return REV ? G - 1 - i : i; };      // processing order -> element of the granule
+    A y[G];
+#pragma unroll
+    for (int i = 0; i < G; ++i) {
+        A x;
+        if constexpr (G == 4) x = acc_from_bits<A>(gt[mem(i)]);
+        else x = narrow_elem<DT>(gt, mem(i));
+        const uint32_t keep = (uint32_t)(((int32_t)(~fb << (31 - i))) >> 31);               // all ones unless a row starts at i
+        y[i] = i == 0 ? x : acc_add(acc_from_bits<A>(acc_bits(y[i == 0 ? 0 : i - 1]) & keep), x);
+    }
+    A v = y[G - 1];
+    uint32_t h = fb ? 1u : 0u;
+    seg_wave_inclusive(v, h);
+    const A vex = wave_shift_up(v);
+    const A in = dpp0<kWaveShr1>(h) ? vex : acc_add(carry, vex);
+    const uint32_t first = fb ? (uint32_t)__builtin_ctz(fb) : (uint32_t)G;
+#pragma unroll
+    for (int i = 0; i < G; ++i)
+        if ((uint32_t)i < first) y[i] = acc_add(in, y[i]);
+    u32x4 out[Q];
+    if constexpr (EXCL) {
+        A prev = wave_shift_up(y[G - 1]);
+        if (lane == 0) prev = carry;
+        out[mem(0) >> 2][mem(0) & 3] = (fb & 1u) ? 0u : acc_bits(prev);
+#pragma unroll
+        for (int i = 1; i < G; ++i) out[mem(i) >> 2][mem(i) & 3] = ((fb >> i) & 1u) ? 0u : acc_bits(y[i - 1]);
+    } else {
+#pragma unroll
+        for (int i = 0; i < G; ++i) out[mem(i) >> 2][mem(i) & 3] = acc_bits(y[i]);
+    }
+    carry = uniform_from_lane(y[G - 1], 63);
+    // results change lanes, as in seg_flat_narrow_kernel
+    uint32_t e[Q];
+    if constexpr (Q == 4) {
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const uint32_t col[4] = {out[0][w], out[1][w], out[2][w], out[3][w]};
+            const u32x4 tr = rows_transpose(col);
+            for (int k = 0; k < 4; ++k) out[k][w] = tr[k];
+        }
+        for (int k = 0; k < 4; ++k) e[k] = slot_offset<DT, NT, REV>(t, 16 * k + (lane & 15)) + 4u * (lane >> 4);
+    } else if constexpr (Q == 2) {
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const auto sw = __builtin_amdgcn_permlane32_swap(out[0][w], out[1][w], false, false);
+            out[0][w] = sw[0]; out[1][w] = sw[1];
+        }
+        for (int k = 0; k < 2; ++k) e[k] = slot_offset<DT, NT, REV>(t, 32 * k + (lane & 31)) + 4u * (lane >> 5);
+    } else {
+        e[0] = slot_offset<DT, NT, REV>(t, lane);
+    }
+#pragma unroll
+    for (int k = 0; k < Q; ++k) {
+        if (whole || (R.out_vec && e[k] + 4 <= R.rem && e[k] >= R.lead)) {
+            __builtin_nontemporal_store(out[k], (u32x4 *)(R.out + e[k] * 4));
+        } else {
+            for (int i = 0; i < 4; ++i)
+                if (e[k] + i < R.rem && e[k] + i >= R.lead) ((uint32_t *)R.out)[e[k] + i] = out[k][i];
+        }
+    }
+}
+
+template <int DT, int NT, bool EXCL, bool REV, int W, bool SEARCH>
+__global__ __launch_bounds__(64 * W) void seg_stream_kernel(Params P, FlatArgs F)
+{
+    using T = Tr<DT>;
+    using A = typename T::acc;
+    constexpr int G = T::kG;
+    constexpr uint32_t kTile = 64u * G, kEPW = NT * kTile, kWgElems = kEPW * W, kWords = kEPW / 32u;
+    constexpr uint32_t kMask = (1u << G) - 1u;
+    __shared__ uint32_t s_sum[W], s_head[W];
+    __shared__ uint32_t s_bcast;
+    using Marks = RowMarks<W, kWgElems>;
+    __shared__ typename Marks::Lds s_marks;
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const uint32_t tile = take_tile(P, &s_bcast);
+    if (tile >= P.num_tiles) return;
+    // SEARCH: long rows, whose first ones are searched for here unless one window holds all offsets; else they have been found
+    // beforehand, or one window holds all.
+    const uint32_t entries = (uint32_t)P.rows + 1u;
+    const bool search = SEARCH && entries > RunMarks<kEPW>::kWindow;
+    uint32_t *run_bits = s_marks.bits + (kWords + (search ? 0u : 2u)) * wave;
+    Marks marks;
+    RunMarks<kEPW> run_marks;
+    __builtin_amdgcn_s_setprio(3);                  // loads first, as in scan_kernel
+    if (search) marks.begin(F.offsets, entries, s_marks);
+    else run_marks.begin(F.offsets, entries, !SEARCH && F.first_rows ? F.first_rows[tile * W + (REV ? W - 1 - wave : wave)] : 0u,
+                         !SEARCH && F.first_rows ? F.expect : entries, lane, run_bits);
+    long long lo = F.offsets[0], hi = F.offsets[P.rows];       // (clamped: seg_first_rows_kernel has raised the fault word)
+    const long long total = (long long)P.cols;
+    lo = lo < 0 ? 0 : (lo > total ? total : lo);
+    hi = hi < lo ? lo : (hi > total ? total : hi);
+    const uint32_t lead = seg_lead<DT, false>(P, lo);
+    const uint64_t vlen = (uint64_t)(hi - lo) + lead;
+    const uint64_t tiles = (vlen + kWgElems - 1) / kWgElems;
+    if (tile >= tiles) {                                       // the grid is an upper bound
+        seg_check_offsets(F.offsets, P, tile, F.check_rows, threadIdx.x, 64 * W);
+        return;
+    }
+    const uint64_t pos = REV ? tiles - 1 - tile : tile;
+    const uint64_t base = pos * kWgElems + (uint64_t)wave * kEPW;
+    const Run R = make_seg_run<DT>(P, lo, (uint64_t)(hi - lo), lead, base);
+    const bool inside = R.lead == 0u && R.rem >= kEPW;
+    const bool whole_in = __builtin_amdgcn_readfirstlane((int)(R.in_vec && inside)) != 0;
+    const bool whole_out = __builtin_amdgcn_readfirstlane((int)(R.out_vec && inside)) != 0;
+    u32x4 g[NT];
+    if (whole_in && T::kEsz == 4 && F.stream) {
+#pragma unroll
+        for (int t = 0; t < NT; ++t) g[t] = __builtin_nontemporal_load((const u32x4 *)(R.in + slot_offset<DT, NT, REV>(t, lane) * T::kEsz));
+    } else if (whole_in) {
+#pragma unroll
+        for (int t = 0; t < NT; ++t) g[t] = *(const u32x4 *)(R.in + slot_offset<DT, NT, REV>(t, lane) * T::kEsz);
+    } else {
+        load_run<DT, NT, REV, true>(R, lane, g);
+    }
+    __builtin_amdgcn_s_setprio(0);
+    if (search) marks.mark(lo - (long long)lead + (long long)(pos * kWgElems), F.expect, s_marks);
+    else run_marks.mark(lo - (long long)lead + (long long)base, lane, run_bits);
+
+    // ---- where the open row of the run begins: element `from` (forward) or, from the end, the element in front of `from`
+    constexpr uint32_t kPerLane = (kWords + 63u) / 64u;
+    uint32_t from = REV ? kEPW : 0u;
+    bool run_open = true;
+    {
+        uint32_t mine = REV ? ~0u : 0u;                        // this lane's last start in processing order, and whether it has one
+        bool any = false;
+#pragma unroll
+        for (uint32_t k = 0; k < kPerLane; ++k) {
+            const uint32_t i = (uint32_t)lane * kPerLane + k;
+            uint32_t w = i < kWords ? run_bits[i] : 0u;
+            if (REV) {                                         // bits 1 .. kEPW: shifted down by one
+                if (i < kWords) w = (w >> 1) | (run_bits[i + 1u] << 31);
+                if (w != 0u && !any) mine = 32u * i + (uint32_t)__builtin_ctz(w) + 1u;
+            } else if (w != 0u) {
+                mine = 32u * i + 31u - (uint32_t)__builtin_clz(w);
+            }
+            any = any || w != 0u;
+        }
+        const uint64_t have = __ballot(any);
+        if (have != 0ull) {
+            run_open = false;
+            from = (uint32_t)__builtin_amdgcn_readlane((int)mine, REV ? __builtin_ctzll(have) : 63 - __builtin_clzll(have));
+        }
+    }
+    // ---- what it adds up to
+    const typename T::AConst Aop = T::make(lane, EXCL, REV);
+    typename T::red rsum = T::red_init();
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        const uint32_t t0 = REV ? (uint32_t)(NT - 1 - t) * kTile : (uint32_t)t * kTile;     // the tile's first element
+        if (REV ? t0 >= from : t0 + kTile <= from) continue;
+        u32x4 x = g[t];
+        if (REV ? t0 + kTile > from : t0 < from) {
+            const uint32_t e0 = slot_offset<DT, NT, REV>(t, lane);
+            const int cut = (int)from - (int)e0, c = cut < 0 ? 0 : (cut > G ? G : cut);     // elements of the granule in front of `from`
+            x = REV ? keep_bytes(x, 0, c * T::kEsz) : keep_bytes(x, c * T::kEsz, 16);
+        }
+        rsum = T::red_add(Aop, rsum, x);
+    }
+    const A open_sum = wave_sum(T::red_lane(rsum, lane));
+
+    if (F.check_rows != 0u && wave != (REV ? W - 1 : 0)) seg_check_offsets(F.offsets, P, tile, F.check_rows, threadIdx.x - (REV ? 0u : 64u), 64u * (W - 1));
+    A carry = seg_open_sum_before_run<A, W, REV>(P, tile, lane, wave, open_sum, run_open, s_sum, s_head, &s_bcast);
+
+    // ---- tile by tile
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        const uint32_t j = slot_offset<DT, NT, REV>(t, lane);  // (a multiple of G)
+        const uint32_t w = run_bits[j >> 5];
+        uint32_t fb;
+        if constexpr (REV) {                                   // row ends: a row starts one element further on; mirrored
+            const uint32_t ends = (uint32_t)((((uint64_t)run_bits[(j >> 5) + 1u] << 32) | w) >> ((j & 31u) + 1u)) & kMask;
+            fb = __builtin_bitreverse32(ends) >> (32 - G);
+        } else {
+            fb = (w >> (j & 31u)) & kMask;
+        }
+        if (__ballot(fb != 0u) == 0ull) carry = scan_and_store<DT, NT, EXCL, REV, true, 1>(lane, Aop, R, g, carry, t);
+        else seg_scan_and_store_cut_tile<DT, NT, EXCL, REV>(lane, R, whole_out, t, g[t], fb, carry);
     }
 }
 
@@ -1910,13 +2335,9 @@ __global__ __launch_bounds__(1024) void seg_prepare_kernel(const long long *offs
 
 // One 16-byte store per thread where the address allows it (p is 4-byte aligned; the words in front of the first
 // 16-byte boundary and behind the last go one by one).
-// A second range (p2, words2) is cleared by the blocks behind the first range's `blocks1` blocks: two regions of a
-// workspace in one launch.
-__global__ void fill_zero_kernel(uint32_t *p, size_t words, uint32_t *p2, size_t words2, unsigned blocks1)
+__global__ void fill_zero_kernel(uint32_t *p, size_t words)
 {
-    unsigned block = blockIdx.x;
-    if (block >= blocks1) { p = p2; words = words2; block -= blocks1; }
-    const size_t i = (size_t)block * blockDim.x + threadIdx.x;           // group of four words, counted from the boundary
+    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;        // group of four words, counted from the boundary
     const size_t head = ((16u - ((uintptr_t)p & 15u)) & 15u) / 4u;         // words before the first boundary
     const size_t h = head < words ? head : words;
     const size_t first = h + 4 * i;
@@ -2111,14 +2532,12 @@ template <int DT> hipError_t launch_dt(Params P, bool excl, int size, hipStream_
     return hipLaunchKernel(fn, dim3(P.num_tiles), dim3(64 * waves), args, 0, s);
 }
 
-hipError_t launch_fill(void *d, size_t bytes, hipStream_t s, void *d2 = nullptr, size_t bytes2 = 0)
+hipError_t launch_fill(void *d, size_t bytes, hipStream_t s)
 {
-    size_t words = bytes / 4, words2 = d2 ? bytes2 / 4 : 0;
-    uint32_t *p = (uint32_t *)d, *p2 = (uint32_t *)d2;
-    unsigned blocks1 = (unsigned)((words / 4 + 1 + 255) / 256);
-    const unsigned blocks2 = words2 ? (unsigned)((words2 / 4 + 1 + 255) / 256) : 0u;
-    void *args[] = {&p, &words, &p2, &words2, &blocks1};
-    return hipLaunchKernel((const void *)fill_zero_kernel, dim3(blocks1 + blocks2), dim3(256), args, 0, s);
+    size_t words = bytes / 4;
+    uint32_t *p = (uint32_t *)d;
+    void *args[] = {&p, &words};
+    return hipLaunchKernel((const void *)fill_zero_kernel, dim3((unsigned)((words / 4 + 1 + 255) / 256)), dim3(256), args, 0, s);
 }
 
 // What a launch has to know about the carry chain, and whatever has to run in front of it on the stream.  `tiles`
@@ -2129,9 +2548,8 @@ hipError_t launch_fill(void *d, size_t bytes, hipStream_t s, void *d2 = nullptr,
 //     workspace region whose contents the library cannot vouch for: both get the reserved tag and a fill kernel in
 //     front of every run (a kernel, not a memset node).
 //   * Ticket policy: the header's ticket counter is cleared.
-// `also` / `also_bytes`: another region of the workspace that a clear-first call wants zeroed (same launch).
-tcuscan_status_t begin_chain(Params &P, void *d_ws, size_t tiles, bool clear_first, hipStream_t s, void *also = nullptr,
-                             size_t also_bytes = 0, bool cleared_by_caller = false)
+// `cleared_by_caller`: a kernel of a clear-first call does the clearing.
+tcuscan_status_t begin_chain(Params &P, void *d_ws, size_t tiles, bool clear_first, hipStream_t s, bool cleared_by_caller = false)
 {
     P.ticket = 0u;
     P.spin_limit = g_spin_limit.load(std::memory_order_relaxed);
@@ -2144,9 +2562,8 @@ tcuscan_status_t begin_chain(Params &P, void *d_ws, size_t tiles, bool clear_fir
     if (hipStreamIsCapturing(s, &cs) != hipSuccess) { (void)hipGetLastError(); cs = hipStreamCaptureStatusNone; }
     if (clear_first || cs == hipStreamCaptureStatusActive) {
         P.tag = chain_tags::kClearFirstTag;
-        if (!cleared_by_caller && launch_fill(status, status_bytes, s, also, also_bytes) != hipSuccess) return TCUSCAN_ERR_HIP;
+        if (!cleared_by_caller && launch_fill(status, status_bytes, s) != hipSuccess) return TCUSCAN_ERR_HIP;
     } else {
-        if (also && launch_fill(also, also_bytes, s) != hipSuccess) return TCUSCAN_ERR_HIP;
         const chain_tags::CallId id = chain_tags::call_id(g_calls.fetch_add(1u, std::memory_order_relaxed));
         P.tag = id.tag;
         if (g_clean.needs_clear((uintptr_t)d_ws, sizeof(WsHeader) + status_bytes, id.generation) &&
@@ -2251,7 +2668,8 @@ size_t seg_tile_elems(int dt, int cls)
 struct SegLayout {
     size_t max_tiles;        // upper bound on the number of tiles = grid size
     size_t counts_off, starts_off, rowmap_off, inner_off, inner_bytes, total_bytes;
-    size_t heads_off, heads_words;   // row-start bits (short 32-bit rows only, else 0 words): never where status words may lie
+    bool short_rows;         // scanned as one range with row starts (run_segmented_range) unless that form is switched off
+    size_t first_rows_off, first_rows_bytes;   // every run's first row (run_segmented_range), in rows' place where that form has no use for them
 };
 
 bool seg_layout(int dt, size_t rows, size_t total, SegLayout &L)
@@ -2265,9 +2683,12 @@ bool seg_layout(int dt, size_t rows, size_t total, SegLayout &L)
     L.rowmap_off = up(L.starts_off + 4 * (rows + 1));
     L.inner_off = up(L.rowmap_off + sizeof(TileDesc) * L.max_tiles);
     L.inner_bytes = tcuscan_workspace_bytes(1, rows + 1, TCUSCAN_I32_I32);
-    L.heads_off = up(L.inner_off + L.inner_bytes);
-    L.heads_words = seg_tile_class(dt, rows, total) == kSegShort ? (total + 32) / 32 + 2 : 0;
-    L.total_bytes = L.heads_off + 4 * L.heads_words;
+    L.short_rows = seg_tile_class(dt, rows, total) == kSegShort;
+    // (for short rows a word per tile of kFlatTile elements lies there; callers have sized their workspaces by a bit per element)
+    const size_t end = up(L.inner_off + L.inner_bytes);
+    L.first_rows_off = L.short_rows ? end : L.rowmap_off;
+    L.first_rows_bytes = L.short_rows ? 4 * ((total + 32) / 32 + 2) : sizeof(TileDesc) * L.max_tiles;
+    L.total_bytes = end + (L.short_rows ? L.first_rows_bytes : 0);
     return true;
 }
 
@@ -2293,57 +2714,111 @@ template <int DT> hipError_t launch_seg(Params P, bool excl, int cls, hipStream_
     return hipLaunchKernel(seg_short_kernel_for<DT>(excl, rev), dim3((P.num_tiles + per_wg - 1) / per_wg), dim3(64 * kSegPack), args, 0, s);
 }
 
-// Short rows of 32-bit elements: the covered range as one row with row-start bits (seg_flat_kernel).  Three
-// launches: clear the bits, set them from the offsets, scan.  Measured on 2^26 fp32 elements cut at random into rows of
-// mean length 20 / 200 / 1500 / 5000 / 20000: 172 / 107 / 108 / 110 / 114 us against 1436 / 213 / 137 / 102 / 97 us with
-// tiles of their own for every row -- hence for the short class only (average below 2048 elements).  The status words are the first ones of the general
-// layout; the bits have a region of their own behind everything else (a word of bits where another call expects a
-// status word could pass for one).
-constexpr int kFlatNT = 8, kFlatW = 8;
+// The range form (us, before: row-start bits set in memory by two launches / rows with tiles of their own).  The small kernels'
+// workgroup is 4 wavefronts of 2048 elements (2^22 f32 of mean length 200 11.3, with 8 wavefronts 12.0); 10^5 elements 13.5 -> 7.3,
+// 2^22 bf16 in 209 rows 13.0 -> 8.0.
+constexpr int kFlatNT = 8, kFlatW = 4;
+constexpr size_t kFlatTile = (size_t)2048 * kFlatW;
+constexpr size_t kFlatCheckRows = 4096;      // offsets a workgroup checks at most (rows far shorter than a tile of them)
+// From here on the large kernel (3 x 2^22 f32 of mean length 16 / 200 / 1500: 28.6 / 23.3 / 23.2 -> 22.9 / 20.7 / 21.9).
+constexpr size_t kSegStreamFrom = (size_t)3 << 22;
+// From 200 MB of input and output on, 32-bit inputs are read around the memory-side cache (2^26 f32 of mean length 16 115 -> 111,
+// 2^24 the other way round: 30 -> 35).
+constexpr size_t kSegAroundCacheFrom = (size_t)25 << 20;
+// From here on 32-bit rows of 2^14 elements and more keep tiles of their own unless one window holds the offsets: a chain
+// over the whole range is longer than theirs and loses more than the launch in front costs (2^26 f32 in 3355 rows 108 / 100,
+// 2^27 in 2684 200 / 188; but 2^25 in 1677 53 / 57, and 2^26 in 223, without a search, 97 .. 104 / 108).
+constexpr size_t kOwnTilesFrom = (size_t)3 << 24;
 template <int DT> const void *seg_flat_kernel_for(bool excl, bool rev)
 {
-    if (rev) return excl ? (const void *)seg_flat_kernel<DT, kFlatNT, true, true, kFlatW> : (const void *)seg_flat_kernel<DT, kFlatNT, false, true, kFlatW>;
-    return excl ? (const void *)seg_flat_kernel<DT, kFlatNT, true, false, kFlatW> : (const void *)seg_flat_kernel<DT, kFlatNT, false, false, kFlatW>;
+    if constexpr (Tr<DT>::kEsz == 4) {
+        if (rev) return excl ? (const void *)seg_flat_kernel<DT, kFlatNT, true, true, kFlatW> : (const void *)seg_flat_kernel<DT, kFlatNT, false, true, kFlatW>;
+        return excl ? (const void *)seg_flat_kernel<DT, kFlatNT, true, false, kFlatW> : (const void *)seg_flat_kernel<DT, kFlatNT, false, false, kFlatW>;
+    } else {
+        if (rev) return excl ? (const void *)seg_flat_narrow_kernel<DT, true, true, kFlatW> : (const void *)seg_flat_narrow_kernel<DT, false, true, kFlatW>;
+        return excl ? (const void *)seg_flat_narrow_kernel<DT, true, false, kFlatW> : (const void *)seg_flat_narrow_kernel<DT, false, false, kFlatW>;
+    }
 }
-template <int DT> const void *seg_flat_narrow_kernel_for(bool excl, bool rev)
+// MFMA tiles per wavefront and wavefronts per workgroup of the large calls: for short rows 4096 elements of 8- and 16-bit inputs
+// and 2048 of 32-bit ones per wavefront, for long rows, whose chain is what they wait for, twice that and 8 wavefronts (2^27 bf16
+// of mean length 200 145 / 155 us, of 20,000 147 / 143; 2^26 f32 of 200 101 / 106, of 300,000 114 / 106).
+template <int DT, bool LONG> struct SegStream {
+    static constexpr int kNT = (Tr<DT>::kEsz == 1 ? 4 : 8) * (LONG ? 2 : 1);
+    static constexpr int kW = LONG || Tr<DT>::kEsz == 1 ? 8 : 4;
+    static constexpr size_t kRun = (size_t)kNT * Geo<DT>::kTileElems, kTile = kRun * kW;
+};
+template <int DT, bool LONG> hipError_t launch_seg_stream(Params P, FlatArgs F, bool excl, uint32_t *first_rows, hipStream_t s)
 {
-    if (rev) return excl ? (const void *)seg_flat_narrow_kernel<DT, true, true, kFlatW> : (const void *)seg_flat_narrow_kernel<DT, false, true, kFlatW>;
-    return excl ? (const void *)seg_flat_narrow_kernel<DT, true, false, kFlatW> : (const void *)seg_flat_narrow_kernel<DT, false, false, kFlatW>;
+    using C = SegStream<DT, LONG>;
+    constexpr int NT = C::kNT, W = C::kW, kRun = (int)C::kRun;
+    if (first_rows) {
+        const long long *off = F.offsets; uint32_t esz = Tr<DT>::kEsz, *first = first_rows;
+        void *args[] = {&P, &off, &esz, &first};
+        const size_t threads = P.rows + 1 > P.num_tiles ? P.rows + 1 : P.num_tiles;
+        const hipError_t e = hipLaunchKernel((const void *)seg_first_rows_kernel<kRun, W>, dim3((unsigned)((threads + 255) / 256)), dim3(256), args, 0, s);
+        if (e != hipSuccess) return e;
+    }
+    F.first_rows = first_rows;
+    void *args[] = {&P, &F};
+    const void *fn;
+    if (P.reverse) fn = excl ? (const void *)seg_stream_kernel<DT, NT, true, true, W, LONG> : (const void *)seg_stream_kernel<DT, NT, false, true, W, LONG>;
+    else           fn = excl ? (const void *)seg_stream_kernel<DT, NT, true, false, W, LONG> : (const void *)seg_stream_kernel<DT, NT, false, false, W, LONG>;
+    return hipLaunchKernel(fn, dim3(P.num_tiles), dim3(64 * W), args, 0, s);
 }
-tcuscan_status_t run_segmented_flat(const void *d_in, void *d_out, const long long *d_offsets, size_t rows, size_t total, int dt,
-                                    int exclusive, int reverse, void *d_ws, const SegLayout &L, hipStream_t s)
+// TCUSCAN_ERR_UNSUPPORTED: not in this form (rows in tiles of their own do better, or the workspace's layout has no room).
+template <int DT> tcuscan_status_t run_segmented_range_dt(Params P, const long long *d_offsets, size_t rows, size_t total, bool excl, void *d_ws,
+                                                          const SegLayout &L, hipStream_t s)
 {
-    const size_t tile = (size_t)kFlatNT * kFlatW * 256;
+    using Short = SegStream<DT, false>;
+    using Long = SegStream<DT, true>;
+    const bool flat = total < kSegStreamFrom && total / kFlatTile + 2 <= L.max_tiles;
+    const bool long_rows = total / rows >= (Tr<DT>::kEsz == 4 ? 2048 : 4096);
+    const bool few_rows = rows < RunMarks<Short::kRun>::kWindow, first = !flat && !long_rows && !few_rows;     // (are first rows found beforehand?)
+    if (Tr<DT>::kEsz == 4 && total >= kOwnTilesFrom && !few_rows && total / rows >= ((size_t)1 << 14)) return TCUSCAN_ERR_UNSUPPORTED;
+    const size_t run = flat ? 2048 : long_rows ? Long::kRun : Short::kRun;
+    const size_t tile = flat ? kFlatTile : long_rows ? Long::kTile : Short::kTile;
     const size_t tiles = total / tile + 2;                       // the range is at most `total` long and starts less than a granule late
-    if (tiles > L.max_tiles) return TCUSCAN_ERR_UNSUPPORTED;     // (never: the general layout counts smaller tiles)
-    uint32_t *heads = (uint32_t *)((char *)d_ws + L.heads_off);
-    const uint32_t shift = (uint32_t)(((uintptr_t)d_in / in_size(dt)) & (16 / in_size(dt) - 1));    // granules start at bit multiples of their length
+    if (tiles > L.max_tiles || (first && 4 * tiles * (tile / run) > L.first_rows_bytes)) return TCUSCAN_ERR_UNSUPPORTED;
+    P.num_tiles = (uint32_t)tiles;
+    FlatArgs F;
+    F.offsets = d_offsets; F.first_rows = nullptr;
+    F.stream = total >= kSegAroundCacheFrom ? 1u : 0u;
+    const size_t per_run = rows / (total / run + 1);             // rows that start in a run (a quarter more: few need a second window)
+    F.expect = (uint32_t)(per_run < run ? per_run + per_run / 4 + 16 : run);
+    if (!first) F.expect *= (uint32_t)(tile / run);
+    const size_t checks = first ? 0 : (rows + kFlatCheckRows - 1) / kFlatCheckRows, grid = tiles > checks ? tiles : checks;
+    F.check_rows = first ? 0u : (uint32_t)((rows + grid - 1) / grid);
+    uint32_t *first_rows = first ? (uint32_t *)((char *)d_ws + L.first_rows_off) : nullptr;
+    // The first rows lie where a later call of another shape may expect status words: the workspace is then no longer known to be
+    // clean.  (The kernel that finds them clears this call's status words.)
+    if (first) g_clean.mark_dirty((uintptr_t)d_ws, chain_tags::call_id(g_calls.load(std::memory_order_relaxed)).generation);
+    const tcuscan_status_t bst = begin_chain(P, d_ws, tiles, first, s, first);
+    if (bst != TCUSCAN_OK) return bst;
+    hipError_t e;
+    if (flat) {
+        void *args[] = {&P, &F};
+        e = hipLaunchKernel(seg_flat_kernel_for<DT>(excl, P.reverse != 0), dim3((unsigned)grid), dim3(64 * kFlatW), args, 0, s);
+    } else {
+        e = long_rows ? launch_seg_stream<DT, true>(P, F, excl, first_rows, s) : launch_seg_stream<DT, false>(P, F, excl, first_rows, s);
+    }
+    return e == hipSuccess ? TCUSCAN_OK : TCUSCAN_ERR_HIP;
+}
+tcuscan_status_t run_segmented_range(const void *d_in, void *d_out, const long long *d_offsets, size_t rows, size_t total, int dt,
+                                     int exclusive, int reverse, void *d_ws, const SegLayout &L, hipStream_t s)
+{
     Params P;
     P.in = d_in; P.out = d_out; P.rows = rows; P.cols = total;
-    P.tiles_per_row = 0; P.num_tiles = (uint32_t)tiles;
+    P.tiles_per_row = 0; P.num_tiles = 0;
     P.ws = (WsHeader *)d_ws;
     P.reverse = reverse ? 1u : 0u; P.tile_desc = nullptr;
-    // one fill launch clears the status words and the row-start bits
-    const tcuscan_status_t bst = begin_chain(P, d_ws, tiles, true, s, heads, 4 * L.heads_words);
-    if (bst != TCUSCAN_OK) return bst;
-    {
-        const long long *off = d_offsets; size_t r = rows, t = total; uint32_t sh = shift; WsHeader *h = (WsHeader *)d_ws;
-        void *args[] = {&off, &r, &t, &sh, &heads, &h};
-        if (hipLaunchKernel((const void *)seg_heads_kernel, dim3((unsigned)((rows + 255) / 256)), dim3(256), args, 0, s) != hipSuccess)
-            return TCUSCAN_ERR_HIP;
-    }
-    const long long *off = d_offsets; const uint32_t *hd = heads; uint32_t sh = shift;
-    void *args[] = {&P, &off, &hd, &sh};
     const bool ex = exclusive != 0;
-    const void *fn;
     switch (dt) {
-    case TCUSCAN_F32_F32:  fn = seg_flat_kernel_for<TCUSCAN_F32_F32>(ex, reverse != 0); break;
-    case TCUSCAN_I32_I32:  fn = seg_flat_kernel_for<TCUSCAN_I32_I32>(ex, reverse != 0); break;
-    case TCUSCAN_I8_I32:   fn = seg_flat_narrow_kernel_for<TCUSCAN_I8_I32>(ex, reverse != 0); break;
-    case TCUSCAN_F16_F32:  fn = seg_flat_narrow_kernel_for<TCUSCAN_F16_F32>(ex, reverse != 0); break;
-    default:               fn = seg_flat_narrow_kernel_for<TCUSCAN_BF16_F32>(ex, reverse != 0); break;
+    case TCUSCAN_I32_I32:  return run_segmented_range_dt<TCUSCAN_I32_I32>(P, d_offsets, rows, total, ex, d_ws, L, s);
+    case TCUSCAN_F16_F32:  return run_segmented_range_dt<TCUSCAN_F16_F32>(P, d_offsets, rows, total, ex, d_ws, L, s);
+    case TCUSCAN_I8_I32:   return run_segmented_range_dt<TCUSCAN_I8_I32>(P, d_offsets, rows, total, ex, d_ws, L, s);
+    case TCUSCAN_F32_F32:  return run_segmented_range_dt<TCUSCAN_F32_F32>(P, d_offsets, rows, total, ex, d_ws, L, s);
+    default:               return run_segmented_range_dt<TCUSCAN_BF16_F32>(P, d_offsets, rows, total, ex, d_ws, L, s);
     }
-    return hipLaunchKernel(fn, dim3(P.num_tiles), dim3(64 * kFlatW), args, 0, s) == hipSuccess ? TCUSCAN_OK : TCUSCAN_ERR_HIP;
 }
 
 // The tile for such rows.  8- and 16-bit inputs: small or large as the plain tiles' rule has it (4 x 600,001 us, small /
@@ -2463,11 +2938,13 @@ tcuscan_status_t run_segmented(const void *d_in, void *d_out, const long long *d
     if (!d_ws || ws_bytes < L.total_bytes || ((uintptr_t)d_ws % 8) != 0) return TCUSCAN_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
     const int cls = seg_tile_class(dt, rows, total);
+    if (g_seg_flat.load(std::memory_order_relaxed)) {
+        const tcuscan_status_t st = run_segmented_range(d_in, d_out, d_offsets, rows, total, dt, exclusive, reverse, d_ws, L, s);
+        if (st != TCUSCAN_ERR_UNSUPPORTED) return st;
+    }
     // This call puts row maps where a later call of another shape may expect status words: the workspace is no
-    // longer known to be clean (segmented calls themselves clear their status words in front of every run).
+    // longer known to be clean (the call itself clears its status words in front of every run).
     g_clean.mark_dirty((uintptr_t)d_ws, chain_tags::call_id(g_calls.load(std::memory_order_relaxed)).generation);
-    if (L.heads_words && g_seg_flat.load(std::memory_order_relaxed))
-        return run_segmented_flat(d_in, d_out, d_offsets, rows, total, dt, exclusive, reverse, d_ws, L, s);
     const size_t tile = seg_tile_elems(dt, cls);
     int32_t *counts = (int32_t *)((char *)d_ws + L.counts_off);
     uint32_t *starts = (uint32_t *)((char *)d_ws + L.starts_off);
@@ -2508,7 +2985,7 @@ tcuscan_status_t run_segmented(const void *d_in, void *d_out, const long long *d
     P.reverse = reverse ? 1u : 0u;
     P.line = line;
     P.tile_desc = desc;
-    const tcuscan_status_t bst = begin_chain(P, d_ws, L.max_tiles, true, s, nullptr, 0, few_rows);
+    const tcuscan_status_t bst = begin_chain(P, d_ws, L.max_tiles, true, s, few_rows);
     if (bst != TCUSCAN_OK) return bst;
     hipError_t e;
     switch (dt) {

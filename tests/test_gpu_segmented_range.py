@@ -1,0 +1,107 @@
+"""GPU parity of segmented scans that go over the rows' range as a whole, where the search for a tile's row starts can go
+wrong: numbers of rows at the edges of its windows and rounds, stretches of empty rows longer than a window, calls at the edge
+between the small and the large kernel, tiles with more rows than expected; bad offsets in every kernel."""
+import numpy as np
+import pytest
+
+from paper_2411_17887_amd import inputs, tcuscan
+from test_gpu_segmented import INT_GEN, RND_GEN, check, offsets_from, run_segmented
+
+pytestmark = pytest.mark.gpu
+
+LARGE = 3 << 22                     # elements from which on the large kernel runs
+
+
+def spread(rng, rows, total):
+    """`rows` lengths, exponentially distributed, that fill `total` elements."""
+    ends = np.cumsum(rng.exponential(size=rows))
+    off = np.floor(ends / ends[-1] * total).astype(np.int64)
+    off[-1] = total
+    return np.diff(np.concatenate([[0], off]))
+
+
+def with_empty(lens, at, count):
+    return np.concatenate([lens[:at], np.zeros(count, np.int64), lens[at:]])
+
+
+def layout(name, rng):
+    """Row lengths.  Windows hold 1024 offsets (small kernel), 256 (a run of the large one) and 2048 (its tiles of long rows)."""
+    kind, _, arg = name.partition(":")
+    n = int(arg) if arg else 0
+    if kind == "small":             # n rows in a call of one launch
+        return spread(rng, n, 300_000 + n)
+    if kind == "long":              # n long rows in a large call
+        return spread(rng, n, LARGE + 12345)
+    if kind == "short":             # n elements per row on average in a large call
+        return spread(rng, LARGE // n, LARGE + 77)
+    if kind == "empty_small":       # n empty rows in the middle, and at the end
+        return with_empty(with_empty(spread(rng, 5000, 200_003), 2500, n), 5000 + n, n)
+    if kind == "empty_short":
+        return with_empty(with_empty(spread(rng, 100_000, LARGE + 9), 40_000, n), 100_000 + n, n)
+    if kind == "empty_long":
+        return with_empty(spread(rng, 900, 2 * LARGE + 5), 450, n)
+    if kind == "dense":             # rows of one element for a stretch, one row for the rest: many more rows in a tile than expected
+        return np.concatenate([np.ones(40_000, np.int64), [n - 40_000]])
+    raise AssertionError(name)
+
+
+@pytest.mark.parametrize("flags", [0, 3])
+@pytest.mark.parametrize("name,kinds", [
+    ("small:1022", "i32 bf16"), ("small:1023", "i8 i32"), ("small:1024", "i32 f16"), ("small:3000", "i8"), ("small:1100000", "i32 i8"),
+    ("long:254", "i8 f32"), ("long:255", "i32 bf16"), ("long:256", "i8 i32"), ("long:2046", "i8"), ("long:2047", "bf16 i8"), ("long:2500", "i8"),
+    ("short:16", "i32 i8"), ("short:200", "i8 f32"), ("short:1900", "i32 f16"), ("short:4200", "i8"),
+    ("empty_small:5000", "i32 i8"), ("empty_small:1100000", "i8"), ("empty_short:300000", "i32 i8"), ("empty_long:5000", "i8 bf16"),
+    ("dense:300000", "i32 i8"), ("dense:13000000", "i8 i32"),
+])
+def test_row_starts_are_found(name, kinds, flags):
+    rng = np.random.default_rng(len(name) + flags)
+    lens = layout(name, rng)
+    off = offsets_from(lens, start=flags)                        # (also a range that does not start at a boundary)
+    for kind in kinds.split():
+        x = (INT_GEN if kind in INT_GEN else RND_GEN)[kind](int(off[-1]) + 5, 77)
+        got, fault = run_segmented(x, kind, off, flags=flags)
+        assert fault == 0
+        check(x, kind, off, got, bool(flags & 1), bool(flags & 2))
+
+
+@pytest.mark.parametrize("total", [LARGE - 1, LARGE, LARGE + 8191, 4 * LARGE - 3, 4 * LARGE])
+@pytest.mark.parametrize("rows", [3, 700, 3000])
+def test_edges_of_the_rules_and_one_workspace(total, rows):
+    """One workspace through both forms and a plain scan in between: status words, first rows and row maps do not get mixed up."""
+    rng = np.random.default_rng(total + rows)
+    off = offsets_from(spread(rng, rows, total))
+    x = inputs.int32_full(total, 5)
+    ws = tcuscan.new_segmented_workspace(rows, total, "i32")
+    want = None
+    for flat in (True, False, True):
+        tcuscan.set_segmented_form(flat)
+        try:
+            got, fault = run_segmented(x, "i32", off, ws=ws)
+        finally:
+            tcuscan.set_segmented_form(True)
+        assert fault == 0
+        if want is None:
+            check(x, "i32", off, got, False, False)
+            want = got
+        assert np.array_equal(got, want)
+        got, fault = run_segmented(x[:50_000], "i32", np.array([0, 50_000], np.int64), ws=ws)
+        assert fault == 0 and np.array_equal(got, np.cumsum(x[:50_000], dtype=np.int64).astype(np.int32))
+
+
+@pytest.mark.parametrize("name", ["small:3000", "small:60000", "long:250", "long:2500", "short:200"])
+@pytest.mark.parametrize("break_at", ["swap", "beyond", "negative"])
+def test_bad_offsets_raise_the_fault_word_in_every_kernel(name, break_at):
+    import torch
+    lens = layout(name, np.random.default_rng(3))
+    off = offsets_from(lens)
+    total, k = int(off[-1]), lens.size * 2 // 3
+    if break_at == "swap":
+        off[k] = off[k + 2] + 1 if off[k + 2] < total else off[k - 2] - 1
+    else:
+        off[k] = total + 1000 if break_at == "beyond" else -1000
+    d_in = torch.ones(total + 4096, dtype=torch.int32, device="cuda")
+    d_out = torch.full((total + 8192,), -77, dtype=torch.int32, device="cuda")
+    ws = tcuscan.new_segmented_workspace(lens.size, total, "i32")
+    tcuscan.segmented(d_in, d_out[4096:], torch.from_numpy(off).cuda(), lens.size, total, "i32", ws=ws)
+    assert tcuscan.workspace_fault(ws) == 2
+    assert bool((d_out[:4096] == -77).all()) and bool((d_out[4096 + total:] == -77).all())          # nothing outside the arrays is written
