@@ -9,7 +9,12 @@
 // (the published scheme of least-significant-digit passes with a decoupled look-back per digit: Merrill and Garland 2016,
 // Adinets and Merrill, "Onesweep", 2022).  A full sort is four passes of 8 bytes per key (16 with payloads) and one reading of the keys for the first term.
 //
-// Up to kBlockSortMax keys one workgroup does all passes in LDS: one launch, keys and payloads read and written once.
+// Sorts of up to 6.2 million keys on more than 16 bits do with one pass on the top eight bits if the 256 buckets then fit a
+// workgroup each, which sorts its bucket by the other bits in LDS: whether they do is seen on the device, and where they do not,
+// that first pass is the least significant one and the others follow (random keys, us before / now: 100,000 36.6 / 26, 10^6
+// 62.2 / 40, with payloads 76.4 / 49, 2^22 104 / 70, with payloads 125 / 90; keys that do not split, 10^6 equal ones 56 / 59, normally
+// distributed floats 62 / 64, 2^22 104 / 99).  Up to kBlockSortFew keys one workgroup does everything: one launch, keys and payloads
+// read and written once.
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -46,43 +51,75 @@ __device__ __forceinline__ void wavefront_sync()
 
 constexpr unsigned kAndXnor = 0x90;        // truth table of a & ~(b ^ c)
 
+// The lanes whose digit agrees with this lane's in every bit, from eight ballots: 36 vector instructions.
+__device__ __forceinline__ void same_digit_by_ballots(uint32_t d, uint32_t &lo, uint32_t &hi)
+{
+    uint32_t sign[8];
+    uint64_t ones[8];
+#pragma unroll
+    for (int b = 0; b < 8; ++b) {
+        sign[b] = (uint32_t)__builtin_amdgcn_sbfe((int)d, b, 1);                           // the bit in all 32 places
+        asm("" : "+v"(sign[b]));                           // (kept: else it is taken out of the digit once more for the compare)
+        ones[b] = __builtin_amdgcn_ballot_w64(sign[b] != 0u);
+    }
+    lo = ~((uint32_t)ones[0] ^ sign[0]);
+    hi = ~((uint32_t)(ones[0] >> 32) ^ sign[0]);
+#pragma unroll
+    for (int b = 1; b < 8; ++b) {
+        lo = __builtin_amdgcn_bitop3_b32(lo, (uint32_t)ones[b], sign[b], kAndXnor);
+        hi = __builtin_amdgcn_bitop3_b32(hi, (uint32_t)(ones[b] >> 32), sign[b], kAndXnor);
+    }
+}
+
 // rank[r]: keys of the wavefront with the same digit in front of key r of this lane (rows of 64 keys, lane order inside
 // a row); counters[d] (this wavefront's, zero before): its keys with digit d.
-template <int ITEMS>
-__device__ __forceinline__ void rank_rows(const uint32_t (&key)[ITEMS], Digit g, uint16_t *counters, uint32_t (&rank)[ITEMS])
+// MASKS: every other row learns its lanes of equal digits from LDS instead, a mask of 64 bits per digit (`masks`, zero before and
+// after) that the lanes set their bits in: LDS and vector unit take turns at being busy.  A workgroup alone on its compute
+// unit, which waits for nothing but its instructions, gains (16,000 keys 32.4 -> 29.1 us; all rows by masks 34.7, two of three
+// 30.7); the passes over an array, which wait for their stores, do not.
+// `valid`: the lane's keys from row ceil(valid / 64) on are past the end -- with the highest digit, behind everything -- and set
+// no bits: lanes that add to one mask go one after the other (16,000 equal keys: 30 us by ballots, 45 with masks, 30 with the lanes
+// of the first one's digit left out).
+template <int ITEMS, bool MASKS = false>
+__device__ __forceinline__ void rank_rows(const uint32_t (&key)[ITEMS], Digit g, uint16_t *counters, uint32_t (&rank)[ITEMS], uint64_t *masks = nullptr, int valid = 64 * ITEMS)
 {
 #pragma unroll
     for (int r = 0; r < ITEMS; ++r) {
         const uint32_t d = digit_of(key[r], g);
-        // the lanes whose digit agrees with this lane's in every bit
-        uint32_t sign[8];
-        uint64_t ones[8];
-#pragma unroll
-        for (int b = 0; b < 8; ++b) {
-            sign[b] = (uint32_t)__builtin_amdgcn_sbfe((int)d, b, 1);                           // the bit in all 32 places
-            asm("" : "+v"(sign[b]));                       // (kept: else it is taken out of the digit once more for the compare)
-            ones[b] = __builtin_amdgcn_ballot_w64(sign[b] != 0u);
-        }
-        uint32_t lo = ~((uint32_t)ones[0] ^ sign[0]), hi = ~((uint32_t)(ones[0] >> 32) ^ sign[0]);
-#pragma unroll
-        for (int b = 1; b < 8; ++b) {
-            lo = __builtin_amdgcn_bitop3_b32(lo, (uint32_t)ones[b], sign[b], kAndXnor);
-            hi = __builtin_amdgcn_bitop3_b32(hi, (uint32_t)(ones[b] >> 32), sign[b], kAndXnor);
+        const bool by_mask = MASKS && r % 2 == 0;
+        uint32_t lo, hi;
+        if (by_mask) {
+            // (the lanes that agree with the first one need no bits: equal keys)
+            const uint32_t d0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)d);
+            const uint64_t as_first = __ballot(d == d0);
+            if (d != d0 && 64 * r < valid) atomicOr((unsigned long long *)&masks[d], 1ull << (threadIdx.x & 63u));
+            wavefront_sync();
+            const uint64_t m = d == d0 ? as_first : masks[d];
+            lo = (uint32_t)m;
+            hi = (uint32_t)(m >> 32);
+        } else {
+            same_digit_by_ballots(d, lo, hi);
         }
         const uint32_t before = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
         const uint32_t all = (uint32_t)(__builtin_popcount(lo) + __builtin_popcount(hi));
         const uint32_t prev = counters[d];
         wavefront_sync();                                  // (every lane has read before the first of its group writes)
-        if (before == 0u) counters[d] = (uint16_t)(prev + all);
+        if (before == 0u) {
+            counters[d] = (uint16_t)(prev + all);
+            if (by_mask) masks[d] = 0ull;
+        }
         wavefront_sync();
         rank[r] = prev + before;
     }
 }
 
-// The counters of W wavefronts -> byte offset of the first (wavefront, digit) place in the ordered tile; threads 0 ..
+// Offsets in the ordered tile are 16 bits: of bytes up to 16384 keys, of words beyond.
+template <int ITEMS, int W> constexpr uint32_t kUnit = ITEMS * 64 * W <= 16384 ? 4u : 1u;
+
+// The counters of W wavefronts -> offset (in kUnit) of the first (wavefront, digit) place in the ordered tile; threads 0 ..
 // 255, one digit each, return the tile's keys with their digit (`count`) and the place of the first (`start`).  `early`
 // is called with the count as soon as it is known.
-template <int W, class Early>
+template <int W, uint32_t UNIT, class Early>
 __device__ __forceinline__ void scan_counters(uint16_t (*counters)[kDigits], uint32_t *s_part, uint32_t &count, uint32_t &start, Early early)
 {
     const int d = threadIdx.x, lane = d & 63, wave = d >> 6;
@@ -99,26 +136,26 @@ __device__ __forceinline__ void scan_counters(uint16_t (*counters)[kDigits], uin
     if (d < kDigits) {
         start = inc - count;
         for (int w = 0; w < wave; ++w) start += s_part[w];
-        uint32_t at = 4u * start;
+        uint32_t at = UNIT * start;
 #pragma unroll
         for (int w = 0; w < W; ++w) {
             const uint32_t c = counters[w][d];
             counters[w][d] = (uint16_t)at;
-            at += 4u * c;
+            at += UNIT * c;
         }
     }
     __syncthreads();
 }
 
 // Key r of this lane to its place in the ordered tile; at[r]: its rank, then the byte offset of the place.
-template <int ITEMS>
+template <int ITEMS, uint32_t UNIT>
 __device__ __forceinline__ void put_in_order(const uint32_t (&key)[ITEMS], Digit g, const uint16_t *counters, uint32_t *order, uint32_t (&at)[ITEMS])
 {
 #pragma unroll
     for (int r = 0; r < ITEMS; ++r) {
         uint32_t k = key[r];
         asm("" : "+v"(k));                                 // (the digit's address is not kept from the ranking on: 16 registers)
-        at[r] = 4u * at[r] + counters[digit_of(k, g)];
+        at[r] = UNIT == 4u ? 4u * at[r] + counters[digit_of(k, g)] : 4u * (at[r] + counters[digit_of(k, g)]);
         *(uint32_t *)((char *)order + at[r]) = k;
     }
 }
@@ -128,11 +165,12 @@ __device__ __forceinline__ void put_in_order(const uint32_t (&key)[ITEMS], Digit
 struct HistArgs {
     const uint32_t *keys, *vals;
     uint32_t *keys_copy, *vals_copy;      // null, or where the keys (and payloads) are copied for an odd number of passes
-    uint32_t *hist;                       // [pass][digit], zero before
+    uint32_t *hist;                       // [table][pass][digit], zero before unless `own`
     uint32_t *status;                     // status words of all passes, zeroed here (16-byte aligned)
     uint64_t n, status_quads;
     Passes P;
     bool stream;                          // as in PassArgs
+    bool own;                             // no more workgroups than tables
 };
 
 // All passes' digit counts in one reading of the keys: the counts do not change when keys change places.  A digit has
@@ -142,6 +180,18 @@ struct HistArgs {
 // counters (one workgroup per compute unit) 2 us more; 1024 workgroups instead of 512 add as much again in the final
 // additions to the same 1024 words.
 constexpr int kHistCopies = 16, kHistThreads = 1024, kHistGrid = 512;
+// The workgroups add up in one of eight tables -- additions to one word from all dies go one after the other, 27 ns each: 2^22
+// keys 14.5 -> 7 us -- and up to eight workgroups have one each, which then needs no clearing in front (HistArgs::own).
+constexpr uint32_t kTables = 8, kTableWords = kMaxPasses * kDigits;
+template <class T> __device__ __forceinline__ T sum_of_tables(const T *hist, uint32_t tables)
+{
+    T x[kTables], sum = T{};
+#pragma unroll
+    for (uint32_t t = 0; t < kTables; ++t) x[t] = t < tables ? hist[t * (kTableWords * sizeof(uint32_t) / sizeof(T))] : T{};     // all in flight together
+#pragma unroll
+    for (uint32_t t = 0; t < kTables; ++t) sum += x[t];
+    return sum;
+}
 __global__ __launch_bounds__(kHistThreads) void digit_histograms_kernel(HistArgs H)
 {
     __shared__ uint32_t s_hist[kMaxPasses * kDigits * kHistCopies];
@@ -182,7 +232,9 @@ __global__ __launch_bounds__(kHistThreads) void digit_histograms_kernel(HistArgs
         uint32_t sum = 0u;
 #pragma unroll
         for (int c = 0; c < kHistCopies; ++c) sum += s_hist[i * kHistCopies + c];
-        if (sum) atomicAdd(&H.hist[i], sum);
+        uint32_t *at = &H.hist[(blockIdx.x % kTables) * kTableWords + i];
+        if (H.own) *at = sum;
+        else if (sum) atomicAdd(at, sum);
     }
 }
 
@@ -201,11 +253,20 @@ template <class Word> struct StatusWord {
     static __device__ __forceinline__ Word value(Word w) { return w & kUnknown; }
 };
 
+constexpr int kBlockWaves = 16, kBlockItems = 24;
+constexpr size_t kBlockCapacity = (size_t)64 * kBlockWaves * kBlockItems;      // keys of a bucket that one workgroup sorts
+constexpr size_t kBlockSortMax = 16384;                                         // keys of a sort that one workgroup does, if it must
+
+// What the first pass finds out: have the keys gone into buckets by their top digit, and where does each begin.
+enum : uint32_t { kNotSplit = 0u, kSplit = 1u, kAllInOne = 2u };       // kAllInOne: nothing done, the first workgroup sorts all keys
+struct Buckets { uint32_t split; uint32_t start[kDigits]; };
+
 struct PassArgs {
     const uint32_t *keys, *vals;
     uint32_t *keys_out, *vals_out;
     void *status;                         // this pass's status words (zero before)
-    const uint32_t *hist;                 // this pass's digit counts over the whole array
+    const uint32_t *hist;                 // this pass's digit counts over the whole array, to be summed over the tables
+    uint32_t tables;
     uint32_t *ticket;                     // null, or the counter the workgroups draw their tile from (zero before)
     uint32_t *fault;                      // the workspace's fault word
     uint64_t n;
@@ -213,7 +274,14 @@ struct PassArgs {
     uint32_t mute_tile;                   // test hook: the tile with this index publishes nothing
     Digit digit;
     bool stream;                          // the arrays do not fit the memory-side cache: keys are read around it
+    // Sorts that may take one pass and buckets (null otherwise).  First pass: the counts of the top digit, which is taken if no
+    // bucket has more than kBlockCapacity keys; later passes have nothing to do then.
+    const uint32_t *top_hist;
+    Buckets *buckets;
+    Digit top;
 };
+
+enum PassRole { kPlainPass, kChoosingPass, kLaterPass };
 
 template <int ITEMS>
 __device__ __forceinline__ void load_rows(const uint32_t *src, uint32_t first, uint32_t valid, bool whole, bool stream, uint32_t fill, uint32_t (&x)[ITEMS])
@@ -284,7 +352,7 @@ __device__ __forceinline__ Word digit_look_back(const Word *status, uint32_t d, 
 // (at 101 registers one workgroup was, 215 us a pass); 8192 keys per tile: 18 us a pass more, 12288: 15 us more.  The form for
 // 2^30 keys and more keeps 64-bit words and places and takes 80 to 82 registers, which is one workgroup: 2^30 + 12345 keys
 // 16.4 ms per sort, with payloads 25.1 (two-bit passes took 37.6 and 80.1), where 16 sorts of 2^26 keys take 12.2.
-template <int W, int ITEMS, bool VALS, class Word>
+template <int W, int ITEMS, bool VALS, class Word, PassRole ROLE = kPlainPass>
 __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(sizeof(Word) == 4 ? 8 : 4))) void digit_pass_kernel(PassArgs A)
 {
     using S = StatusWord<Word>;
@@ -300,6 +368,9 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(sizeof(W
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if constexpr (ROLE == kLaterPass) {
+        if (A.buckets->split != kNotSplit) return;
+    }
     if (tid == 0) s_abort = 0u;
     uint32_t tile = blockIdx.x;
     if (A.ticket) {
@@ -310,13 +381,26 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(sizeof(W
     }
     const uint64_t base = (uint64_t)tile * kTile;
     const uint32_t valid = A.n - base < kTile ? (uint32_t)(A.n - base) : kTile;
-    const Digit g = A.digit;
+    Digit g = A.digit;
 
     // ---- the keys, in rows of 64 per wavefront; keys past the end have the highest digit and come last among its keys
     const uint32_t first = (uint32_t)wave * 64u * ITEMS + (uint32_t)lane;
     uint32_t key[ITEMS], at[ITEMS];
     load_rows<ITEMS>(A.keys + base, first, valid, valid == kTile, A.stream, ~0u, key);
     ((CounterQuad *)s_cnt[wave])[lane] = 0u;
+    const uint32_t *hist = A.hist;
+    if constexpr (ROLE == kChoosingPass) {
+        // every wavefront looks at the counts: does the largest bucket fit a workgroup?
+        const u32x4 c = sum_of_tables((const u32x4 *)A.top_hist + lane, A.tables);
+        const bool fits = c[0] <= (uint32_t)kBlockCapacity && c[1] <= (uint32_t)kBlockCapacity && c[2] <= (uint32_t)kBlockCapacity && c[3] <= (uint32_t)kBlockCapacity;
+        const bool split = __ballot(!fits) == 0ull;
+        // keys that one workgroup can sort, most of them in one bucket: without the detour
+        const uint32_t half = (uint32_t)A.n / 2u;
+        const bool one = A.n <= kBlockSortMax && __ballot(c[0] > half || c[1] > half || c[2] > half || c[3] > half) != 0ull;
+        if (tile == 0u && tid == 0) A.buckets->split = one ? kAllInOne : split ? kSplit : kNotSplit;
+        if (one) return;
+        if (split) { g = A.top; hist = A.top_hist; }
+    }
     wavefront_sync();
     rank_rows<ITEMS>(key, g, s_cnt[wave], at);
     __syncthreads();
@@ -326,7 +410,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(sizeof(W
     const bool speaks = tile != A.mute_tile;
     Word win[kWindow];
     uint32_t count, start;
-    scan_counters<W>(s_cnt, s_part, count, start, [&](uint32_t c) {
+    scan_counters<W, kUnit<ITEMS, W>>(s_cnt, s_part, count, start, [&](uint32_t c) {
         if (tile != 0u) {
             if (speaks) __hip_atomic_store(column + (size_t)tile * kDigits, S::make(kCountOfTile, c), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             request_window((const Word *)A.status, (uint32_t)tid, (int32_t)tile - 1, win);
@@ -334,7 +418,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(sizeof(W
     });
 
     // ---- meanwhile the tile is put in order
-    put_in_order<ITEMS>(key, g, s_cnt[wave], s_order, at);
+    put_in_order<ITEMS, kUnit<ITEMS, W>>(key, g, s_cnt[wave], s_order, at);
     uint32_t val[VALS ? ITEMS : 1];
     if constexpr (VALS) {
         load_rows<ITEMS>(A.vals + base, first, valid, valid == kTile, A.stream, 0u, val);
@@ -345,7 +429,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(sizeof(W
     if (tile == 0u) {                                      // (uniform over the workgroup)
         uint32_t h = 0u, inc = 0u;
         if (tid < kDigits) {
-            h = A.hist[tid];
+            h = sum_of_tables(hist + tid, A.tables);
             inc = wave_inclusive_scan(h);
             if (lane == 63) s_part[wave] = inc;
         }
@@ -353,6 +437,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(sizeof(W
         if (tid < kDigits) {
             before = inc - h;
             for (int w = 0; w < wave; ++w) before += s_part[w];
+            if constexpr (ROLE == kChoosingPass) A.buckets->start[tid] = (uint32_t)before;
         }
     } else if (tid < kDigits) {
         before = digit_look_back((const Word *)A.status, (uint32_t)tid, (int32_t)tile - 1, win, A);
@@ -400,20 +485,36 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(sizeof(W
     }
 }
 
-// ------------------------------------------------------------------------- a whole sort in one workgroup
+// ------------------------------------------------------------------------- a sort in one workgroup
+//
+// A whole sort of few keys, or a bucket of the keys that a first pass on the top digit has split.  What bounds it is the ranking's
+// instructions, so the rows per lane are counted out (kLaneCounts) -- each with code of its own: counted out by a loop, the
+// instructions of neighbouring rows lose their place between each other (12,000 keys 26 -> 30 us).
+
+struct BlockArgs {
+    const uint32_t *keys, *vals;
+    uint32_t *keys_out, *vals_out;        // (may be where the keys come from: a workgroup reads all of its own first)
+    const Buckets *buckets;               // null: one workgroup sorts all keys; else workgroup b those of bucket b, if there are buckets
+    uint32_t n;                           // keys in all
+    Passes P[2];                          // a bucket's digits, all digits
+};
+struct BlockLds {
+    uint32_t order[kBlockCapacity];
+    alignas(16) uint16_t cnt[kBlockWaves][kDigits];
+    uint64_t masks[kBlockWaves][kDigits];
+    uint32_t part[4];
+};
+static_assert(sizeof(BlockLds) <= 160 * 1024, "LDS of a compute unit");
 
 template <int ITEMS, bool VALS>
-__global__ __launch_bounds__(1024) void block_sort_kernel(uint32_t *keys, uint32_t *vals, uint32_t n, Passes P)
+__device__ __forceinline__ void sort_in_block(const BlockArgs &B, bool all, uint32_t begin, uint32_t n, BlockLds &s)
 {
-    constexpr int W = 16, kThreads = 64 * W;
-    constexpr uint32_t kTile = kThreads * ITEMS;
-    __shared__ uint32_t s_order[kTile];
-    __shared__ __attribute__((aligned(16))) uint16_t s_cnt[W][kDigits];
-    static_assert(__alignof__(s_cnt) >= alignof(CounterQuad), "cleared four counters at a time");
-    __shared__ uint32_t s_part[4];
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    constexpr int W = kBlockWaves;
+    constexpr uint32_t kU = kUnit<ITEMS, W>;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const uint32_t first = (uint32_t)wave * 64u * ITEMS + (uint32_t)lane;
+    const uint32_t *keys = (all ? B.keys_out : B.keys) + begin, *vals = VALS ? (all ? B.vals_out : B.vals) + begin : nullptr;
     uint32_t key[ITEMS], val[VALS ? ITEMS : 1], at[ITEMS];
 #pragma unroll
     for (int r = 0; r < ITEMS; ++r) {
@@ -421,55 +522,96 @@ __global__ __launch_bounds__(1024) void block_sort_kernel(uint32_t *keys, uint32
         key[r] = i < n ? keys[i] : ~0u;                    // past the end: last in every pass
         if constexpr (VALS) val[r] = i < n ? vals[i] : 0u;
     }
-    for (int p = 0; p < P.count; ++p) {
-        const Digit g = P.digit[p];
-        ((CounterQuad *)s_cnt[wave])[lane] = 0u;
+    for (int i = lane; i < kDigits; i += 64) s.masks[wave][i] = 0ull;
+    for (int p = 0; p < B.P[all].count; ++p) {
+        const Digit g = B.P[all].digit[p];
+        ((CounterQuad *)s.cnt[wave])[lane] = 0u;
         wavefront_sync();
-        rank_rows<ITEMS>(key, g, s_cnt[wave], at);
+        rank_rows<ITEMS, (ITEMS <= 20)>(key, g, s.cnt[wave], at, s.masks[wave], (int)n - (int)first);       // (24 rows with payloads: registers)
         __syncthreads();
         uint32_t count, start;
-        scan_counters<W>(s_cnt, s_part, count, start, [](uint32_t) {});
-        put_in_order<ITEMS>(key, g, s_cnt[wave], s_order, at);
+        scan_counters<W, kU>(s.cnt, s.part, count, start, [](uint32_t) {});
+        put_in_order<ITEMS, kU>(key, g, s.cnt[wave], s.order, at);
         __syncthreads();
 #pragma unroll
-        for (int r = 0; r < ITEMS; ++r) key[r] = s_order[first + 64u * r];
+        for (int r = 0; r < ITEMS; ++r) {
+            const uint32_t k = s.order[first + 64u * r];
+            key[r] = first + 64u * r < n ? k : ~0u;
+        }
         if constexpr (VALS) {
             __syncthreads();
 #pragma unroll
-            for (int r = 0; r < ITEMS; ++r) *(uint32_t *)((char *)s_order + at[r]) = val[r];
+            for (int r = 0; r < ITEMS; ++r) *(uint32_t *)((char *)s.order + at[r]) = val[r];
             __syncthreads();
 #pragma unroll
-            for (int r = 0; r < ITEMS; ++r) val[r] = s_order[first + 64u * r];
+            for (int r = 0; r < ITEMS; ++r) val[r] = s.order[first + 64u * r];
         }
-        // (the next pass's writes to s_order come after its barriers)
+        // (the next pass's writes to s.order come after its barriers)
     }
+    uint32_t *keys_out = B.keys_out + begin, *vals_out = VALS ? B.vals_out + begin : nullptr;
 #pragma unroll
     for (int r = 0; r < ITEMS; ++r) {
         const uint32_t i = first + 64u * r;
         if (i < n) {
-            keys[i] = key[r];
-            if constexpr (VALS) vals[i] = val[r];
+            keys_out[i] = key[r];
+            if constexpr (VALS) vals_out[i] = val[r];
         }
     }
+}
+// 1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 16, 18, 20 or 24 rows per lane.
+template <bool VALS, int ITEMS = 1>
+__device__ __forceinline__ void sort_in_block_of(const BlockArgs &B, bool all, uint32_t begin, uint32_t n, BlockLds &s)
+{
+    if constexpr (ITEMS >= kBlockItems) {
+        sort_in_block<kBlockItems, VALS>(B, all, begin, n, s);
+    } else {
+        if (n <= 64u * kBlockWaves * ITEMS) sort_in_block<ITEMS, VALS>(B, all, begin, n, s);
+        else sort_in_block_of<VALS, ITEMS < 8 ? ITEMS + 1 : ITEMS < 20 ? ITEMS + 2 : ITEMS + 4>(B, all, begin, n, s);
+    }
+}
+
+template <bool VALS>
+__global__ __launch_bounds__(64 * kBlockWaves) void block_sort_kernel(BlockArgs B)
+{
+    __shared__ BlockLds s;
+    static_assert(alignof(BlockLds) >= alignof(CounterQuad), "counters cleared four at a time");
+    uint32_t begin = 0u, n = B.n;
+    bool all = true;                                       // all keys, which are where the sorted ones go
+    if (B.buckets) {
+        const uint32_t split = B.buckets->split;
+        if (split == kNotSplit || (split == kAllInOne && blockIdx.x != 0u)) return;
+        all = split == kAllInOne;
+        if (!all) {
+            begin = B.buckets->start[blockIdx.x];
+            const uint32_t end = blockIdx.x + 1u < kDigits ? B.buckets->start[blockIdx.x + 1u] : B.n;
+            n = end > begin && end <= B.n ? end - begin : 0u;
+        }
+        n = n < (uint32_t)kBlockCapacity ? n : (uint32_t)kBlockCapacity;
+    }
+    n = (uint32_t)__builtin_amdgcn_readfirstlane((int)n);
+    if (n != 0u) sort_in_block_of<VALS>(B, all, begin, n, s);
 }
 
 // ------------------------------------------------------------------------- host side
 
-// Keys per lane: 1, 2, 4, 8, 12 or 16, whichever holds them (us per sort, with 1, 4 and 16 only: 5000 keys 29.8, with 8 18.7;
-// 10,000 keys 31.0, with 12 25.6).  Above 16384 keys the passes are as fast (17,000 keys 31 us).
-constexpr size_t kBlockSortMax = 16384;
-
-template <int ITEMS> const void *block_kernel_of(const uint32_t *vals)
+// us per sort of random keys, one workgroup / a pass and buckets (three launches): 7000 keys 16.6 / 17, 9000 22 / 17.4, 16,000 29 /
+// 17.4, 16,000 pairs 36 / 18.7.  Below kBlockSortMax every bucket fits, and most keys in one bucket (kAllInOne) cost the two launches
+// in front: 16,000 equal keys 30 -> 32.
+constexpr size_t kBlockSortFew = 7168;
+// Up to here the counting kernel has eight workgroups and no launch that clears tables in front (a quarter where it also copies).
+constexpr size_t kOwnTables = (size_t)1 << 17;
+hipError_t launch_block_sort(const BlockArgs &args_in, unsigned grid, hipStream_t s)
 {
-    return vals ? (const void *)block_sort_kernel<ITEMS, true> : (const void *)block_sort_kernel<ITEMS, false>;
+    BlockArgs B = args_in;
+    void *args[] = {&B};
+    const void *fn = B.vals ? (const void *)block_sort_kernel<true> : (const void *)block_sort_kernel<false>;
+    return hipLaunchKernel(fn, dim3(grid), dim3(64 * kBlockWaves), args, 0, s);
 }
-hipError_t launch_block_sort(uint32_t *keys, uint32_t *vals, uint32_t n, const Passes &P, hipStream_t s)
+// May random keys be expected to have buckets (of 256) that fit a workgroup each: mean and six standard deviations?
+bool buckets_fit(size_t n)
 {
-    const void *fn = n <= 1024 ? block_kernel_of<1>(vals) : n <= 2048 ? block_kernel_of<2>(vals) : n <= 4096 ? block_kernel_of<4>(vals)
-                   : n <= 8192 ? block_kernel_of<8>(vals) : n <= 12288 ? block_kernel_of<12>(vals) : block_kernel_of<16>(vals);
-    Passes passes = P;
-    void *args[] = {&keys, &vals, &n, &passes};
-    return hipLaunchKernel(fn, dim3(1), dim3(1024), args, 0, s);
+    const double mean = (double)n / kDigits;
+    return mean + 6.0 * __builtin_sqrt(mean) <= (double)kBlockCapacity;
 }
 
 // Keys per lane of a pass.  Few keys: many small tiles, so that all compute units have one and each is done sooner;
@@ -479,14 +621,28 @@ hipError_t launch_block_sort(uint32_t *keys, uint32_t *vals, uint32_t n, const P
 constexpr int kPassWaves = 16;
 int pass_items(size_t n) { return n <= ((size_t)1 << 19) ? 4 : n < ((size_t)5 << 20) ? 8 : 16; }
 
-template <int ITEMS> const void *pass_kernel_of(bool vals)
+template <int ITEMS, PassRole ROLE> const void *pass_kernel_of(bool vals)
 {
-    return vals ? (const void *)digit_pass_kernel<kPassWaves, ITEMS, true, uint32_t> : (const void *)digit_pass_kernel<kPassWaves, ITEMS, false, uint32_t>;
+    return vals ? (const void *)digit_pass_kernel<kPassWaves, ITEMS, true, uint32_t, ROLE> : (const void *)digit_pass_kernel<kPassWaves, ITEMS, false, uint32_t, ROLE>;
 }
-const void *pass_kernel(int items, bool vals, bool wide)
+template <PassRole ROLE> const void *pass_kernel(int items, bool vals)
 {
-    if (wide) return vals ? (const void *)digit_pass_kernel<kPassWaves, 16, true, uint64_t> : (const void *)digit_pass_kernel<kPassWaves, 16, false, uint64_t>;
-    return items == 4 ? pass_kernel_of<4>(vals) : items == 8 ? pass_kernel_of<8>(vals) : pass_kernel_of<16>(vals);
+    return items == 4 ? pass_kernel_of<4, ROLE>(vals) : items == 8 ? pass_kernel_of<8, ROLE>(vals) : pass_kernel_of<16, ROLE>(vals);
+}
+const void *wide_pass_kernel(bool vals)
+{
+    return vals ? (const void *)digit_pass_kernel<kPassWaves, 16, true, uint64_t> : (const void *)digit_pass_kernel<kPassWaves, 16, false, uint64_t>;
+}
+
+// `bits` low bits in digits as even as possible.
+void split_digits(int bits, Passes &P)
+{
+    P.count = (bits + 7) / 8;
+    for (int p = 0, at = 0; p < kMaxPasses; ++p) {
+        const int width = p < P.count ? (bits - at + (P.count - p) - 1) / (P.count - p) : 1;
+        P.digit[p] = {at < 32 ? at : 0, width};
+        at += width;
+    }
 }
 
 }  // namespace
@@ -499,57 +655,77 @@ tcuscan_status_t tcuscan_internal_digit_sort(void *d_keys, void *d_vals, size_t 
 {
     hipStream_t s = (hipStream_t)stream;
     Passes P;
-    P.count = (bits + 7) / 8;
-    for (int p = 0, at = 0; p < kMaxPasses; ++p) {                       // as even as possible
-        const int width = p < P.count ? (bits - at + (P.count - p) - 1) / (P.count - p) : 1;
-        P.digit[p] = {at < 32 ? at : 0, width};
-        at += width;
-    }
-    if (n <= kBlockSortMax)
-        return launch_block_sort((uint32_t *)d_keys, (uint32_t *)d_vals, (uint32_t)n, P, s) == hipSuccess ? TCUSCAN_OK : TCUSCAN_ERR_HIP;
-
+    split_digits(bits, P);
     unsigned use_tickets, spin_limit, mute_tile;
     tcuscan_internal_chain_knobs(&use_tickets, &spin_limit, &mute_tile);
-    const bool wide = n >= StatusWord<uint32_t>::kUnknown;
+    const bool wide = n >= StatusWord<uint32_t>::kUnknown, surely = n <= kBlockSortMax;
+    // One pass on the top eight bits, if the buckets then fit a workgroup each, which sorts them by the other bits.
+    const bool buckets_wanted = !wide && d_fault && P.count >= (surely ? 2 : 3) && buckets_fit(n);
+    if (n <= kBlockSortMax && (n <= kBlockSortFew || !buckets_wanted || use_tickets)) {      // (tickets: more scratch than there is)
+        const BlockArgs B = {(const uint32_t *)d_keys, (const uint32_t *)d_vals, (uint32_t *)d_keys, (uint32_t *)d_vals, nullptr, (uint32_t)n, {P, P}};
+        return launch_block_sort(B, 1, s) == hipSuccess ? TCUSCAN_OK : TCUSCAN_ERR_HIP;
+    }
+    Passes rest = P;
+    if (buckets_wanted) {
+        split_digits(bits - 8, rest);                                    // (also for the passes that run where the buckets do not fit)
+        P = rest;
+        P.digit[P.count++] = {bits - 8, 8};
+    }
+    const int passes = buckets_wanted && surely ? 1 : P.count;           // passes over the array that are launched
     const int items = pass_items(n);
-    const size_t tile = (size_t)64 * kPassWaves * items, tiles = (n + tile - 1) / tile;
+    auto tiles_of = [n](int per_lane) { const size_t tile = (size_t)64 * kPassWaves * per_lane; return (n + tile - 1) / tile; };
+    const size_t tiles = tiles_of(items);
     // Arrays that do not fit the memory-side cache (256 MiB) together are read around it, which leaves it to the pieces
     // that are being written: 2^26 keys 815 -> 776 us, 2^25 407 -> 395, 2^24 with payloads 314 -> 296, 2^25 with payloads 691
     // -> 595; below, what one pass wrote is what the next one finds there (2^24 keys: 224 against 229, 2^23 with payloads
     // 169 against 175).
     const bool around_cache = n * (d_vals ? 16 : 8) > ((size_t)192 << 20);
-    // scratch: digit counts of the passes, ticket counters, then status words from the next 16-byte boundary on
-    uint32_t *hist = (uint32_t *)d_scratch, *tickets = hist + kMaxPasses * kDigits;
-    uint32_t *status = (uint32_t *)(((uintptr_t)(tickets + kMaxPasses) + 15) & ~(uintptr_t)15);
+    const size_t want = (n / 4 + 2 * kHistThreads - 1) / (2 * kHistThreads);
+    const bool odd = (P.count & 1) && !(buckets_wanted && surely);       // the first pass then starts from a copy, and the last ends at home
+    const bool own = n <= (odd ? kOwnTables / 4 : kOwnTables) && !use_tickets;       // (few workgroups are slow copiers)
+    const unsigned hist_grid = (unsigned)(want < 1 ? 1 : own && want > kTables ? kTables : want < kHistGrid ? want : kHistGrid);
+    const uint32_t tables = own ? hist_grid : kTables;
+    // scratch: digit counts of the passes from the next 16-byte boundary on, ticket counters, what the first pass finds out, status words
+    uint32_t *hist = (uint32_t *)(((uintptr_t)d_scratch + 15) & ~(uintptr_t)15), *tickets = hist + tables * kTableWords;
+    Buckets *buckets = (Buckets *)(tickets + kMaxPasses);
+    uint32_t *status = (uint32_t *)(((uintptr_t)(buckets + 1) + 15) & ~(uintptr_t)15);
     const size_t pass_words = tiles * kDigits * (wide ? 2 : 1);
-    if (tcuscan_internal_fill(hist, 4 * (kMaxPasses * kDigits + kMaxPasses), s) != hipSuccess) return TCUSCAN_ERR_HIP;
+    if (!own && tcuscan_internal_fill(hist, 4 * (kTables * kTableWords + kMaxPasses), s) != hipSuccess) return TCUSCAN_ERR_HIP;
 
     uint32_t *src_k = (uint32_t *)d_keys, *dst_k = (uint32_t *)d_keys_tmp, *src_v = (uint32_t *)d_vals, *dst_v = (uint32_t *)d_vals_tmp;
-    const bool odd = P.count & 1;                                        // the first pass then starts from a copy, and the last ends at home
     {
         HistArgs H;
         H.keys = src_k; H.vals = src_v;
         H.keys_copy = odd ? dst_k : nullptr; H.vals_copy = odd && src_v ? dst_v : nullptr;
-        H.hist = hist; H.status = status; H.n = n; H.status_quads = pass_words * P.count / 4; H.P = P; H.stream = around_cache;
+        H.hist = hist; H.status = status; H.n = n; H.status_quads = pass_words * passes / 4; H.P = P; H.stream = around_cache; H.own = own;
+        if (buckets_wanted && surely) H.P = {1, {P.digit[P.count - 1]}};
         void *args[] = {&H};
-        const size_t want = (n / 4 + 2 * kHistThreads - 1) / (2 * kHistThreads);
-        const unsigned grid = (unsigned)(want < 1 ? 1 : want < kHistGrid ? want : kHistGrid);
-        if (hipLaunchKernel((const void *)digit_histograms_kernel, dim3(grid), dim3(kHistThreads), args, 0, s) != hipSuccess) return TCUSCAN_ERR_HIP;
+        if (hipLaunchKernel((const void *)digit_histograms_kernel, dim3(hist_grid), dim3(kHistThreads), args, 0, s) != hipSuccess) return TCUSCAN_ERR_HIP;
     }
     if (odd) {
         uint32_t *t = src_k; src_k = dst_k; dst_k = t;
         t = src_v; src_v = dst_v; dst_v = t;
     }
-    for (int p = 0; p < P.count; ++p) {
+    for (int p = 0; p < passes; ++p) {
         PassArgs A;
         A.keys = src_k; A.vals = src_v; A.keys_out = dst_k; A.vals_out = dst_v;
-        A.status = status + pass_words * p; A.hist = hist + kDigits * p;
+        A.status = status + pass_words * p; A.hist = hist + kDigits * p; A.tables = tables;
         A.ticket = use_tickets ? tickets + p : nullptr;
         A.fault = (uint32_t *)d_fault;
         A.n = n; A.spin_limit = spin_limit; A.mute_tile = mute_tile; A.digit = P.digit[p]; A.stream = around_cache;
+        A.top_hist = hist + (surely ? 0 : kDigits * (P.count - 1)); A.buckets = buckets; A.top = P.digit[P.count - 1];
         void *args[] = {&A};
-        if (hipLaunchKernel(pass_kernel(items, d_vals != nullptr, wide), dim3((unsigned)tiles), dim3(64 * kPassWaves), args, 0, s) != hipSuccess)
+        const bool v = d_vals != nullptr;
+        // (passes that seldom have anything to do are cheaper with fewer, larger tiles)
+        const int later_items = n >= ((size_t)3 << 20) ? 16 : items;
+        const void *fn = wide ? wide_pass_kernel(v) : !buckets_wanted ? pass_kernel<kPlainPass>(items, v)
+                       : p == 0 ? pass_kernel<kChoosingPass>(items, v) : pass_kernel<kLaterPass>(later_items, v);
+        if (hipLaunchKernel(fn, dim3((unsigned)(buckets_wanted && p ? tiles_of(later_items) : tiles)), dim3(64 * kPassWaves), args, 0, s) != hipSuccess)
             return TCUSCAN_ERR_HIP;
+        if (buckets_wanted && p == 0) {
+            const BlockArgs B = {dst_k, dst_v, (uint32_t *)d_keys, (uint32_t *)d_vals, buckets, (uint32_t)n, {rest, P}};
+            if (launch_block_sort(B, kDigits, s) != hipSuccess) return TCUSCAN_ERR_HIP;
+        }
         uint32_t *t = src_k; src_k = dst_k; dst_k = t;
         t = src_v; src_v = dst_v; dst_v = t;
     }
