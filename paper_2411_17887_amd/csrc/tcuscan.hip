@@ -1197,7 +1197,16 @@ struct CompactArgs {
 // POS: the positions -- every element's destination index, the exclusive scan of the mask, to P.out -- go out from the same
 // products as in scan_kernel, with the mask still in registers: 11 bytes per element (half of them kept) instead of 16
 // in two kernels, the scan and one that reads its positions back (160,000,000 elements: 476 -> 284 us).
-template <int NT, int W, bool POS>
+//
+// AHEAD: a workgroup also reads the mask of the tile kAhead tiles on -- a generation of workgroups, two per compute unit -- and
+// publishes that tile's total.  The tile, when its turn comes, finds the totals of all tiles before it published and does not
+// wait for the slowest of their loads; its own read of the mask is served by the caches.  2^28 elements 364.5 -> 336.5 us, 2^26 91.1 ->
+// 87.1, but 2^24 26.5 -> 27.1, and with positions, which a tile stores longer than it waits, 2^26 123 -> 127.5; 448 tiles on are as good,
+// 640 and 1024 bring 339 and 342; asking for the totals before the tile's own loads 343.  The tile publishes its total itself as well:
+// the same word, or an older one over its finished prefix, past which the tiles behind look further back.  A tile may be stored
+// before tiles in front of it have been read, so the arrays must not overlap (compact_ahead).
+constexpr uint32_t kAhead = 512;
+template <int NT, int W, bool POS, bool AHEAD = false>
 __global__ __launch_bounds__(64 * W) void compact_kernel(Params P, CompactArgs C)
 {
     constexpr int DT = TCUSCAN_I8_I32;
@@ -1207,6 +1216,7 @@ __global__ __launch_bounds__(64 * W) void compact_kernel(Params P, CompactArgs C
     constexpr uint32_t kSlot = kEPW + 16u;
     __shared__ uint32_t s_wave_total[W];
     __shared__ uint32_t s_bcast;
+    __shared__ uint32_t s_ahead[AHEAD ? W : 1];
     __shared__ __attribute__((aligned(16))) uint32_t s_pack[W][kSlot];
 
     const int lane = threadIdx.x & 63;
@@ -1234,13 +1244,42 @@ __global__ __launch_bounds__(64 * W) void compact_kernel(Params P, CompactArgs C
         }
     }
     load_run_words<NT>(lane, C.values + base, rem, 0u, val);
+    const bool ahead = AHEAD && tile + kAhead < P.num_tiles - 1u;          // (a whole tile)
+    u32x4 mask_ahead[AHEAD ? NT : 1];
+    if constexpr (AHEAD) {
+        const uint8_t *far = C.mask + ((uint64_t)(tile + kAhead) * W + wave) * kEPW;
+        if (ahead) {
+#pragma unroll
+            for (int t = 0; t < NT; ++t) mask_ahead[t] = *(const u32x4 *)(far + (uint32_t)t * 1024u + 16u * lane);
+        }
+    }
     __builtin_amdgcn_s_setprio(0);
     const typename T::AConst Aop = T::make_compact(lane);
     LookBackPoll<uint32_t> lb;
     uint32_t wave_off, kept_run, wg_total;
     flags_set_out<W>(P, tile, lane, wave, reduce_run<DT, NT>(lane, Aop, g), s_wave_total, lb, wave_off, kept_run, wg_total);
     split_order<NT, kSlot, false>(lane, Aop, g, val, kept_run, rem, s_pack[wave], lb, P.num_tiles > 1 && wave == 0);
+    if constexpr (AHEAD) {
+        if (ahead) {
+            uint32_t c = 0u;
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+                for (int k = 0; k < 4; ++k) c += (uint32_t)__builtin_popcount(mask_ahead[t][k]);
+            c = wave_sum(c);
+            if (lane == 0) s_ahead[wave] = c;
+        }
+    }
     const uint32_t kept_before = flags_arrive(P, tile, lane, wave, wg_total, lb, &s_bcast);
+    if constexpr (AHEAD) {
+        if (ahead && wave == 1) {                                          // (behind the barrier of flags_arrive)
+            uint32_t c = 0u;
+#pragma unroll
+            for (int w = 0; w < W; ++w) c += s_ahead[w];
+            if (lane == 0)
+                __hip_atomic_store((uint64_t *)(P.ws + 1) + (size_t)(tile + kAhead) * kStatusStride, status_word(P.tag, kStateAggregate, c),
+                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
     if (C.count && tile == P.num_tiles - 1 && threadIdx.x == 0) *C.count = kept_before + wg_total;
     split_store<false>(lane, s_pack[wave], C.out, kept_before + wave_off, 0u, kept_run, 0u, n);
     if constexpr (POS) {
@@ -3019,6 +3058,14 @@ tcuscan_status_t flag_kernel_params(Params &P, size_t n, size_t tile, void *d_ws
 constexpr int kFlagNT = 2, kFlagW = 8;
 static_assert((size_t)kFlagNT * kFlagW * 1024 == chain_layout::kFlagTile, "tile of the fused split and compaction kernels");
 
+// Masks are counted ahead (compact_kernel) in large calls whose output lies apart from what is read.
+bool compact_ahead(const CompactArgs &C, size_t n)
+{
+    const uintptr_t out = (uintptr_t)C.out, values = (uintptr_t)C.values, mask = (uintptr_t)C.mask;
+    auto apart = [out, n](uintptr_t from, size_t bytes) { return out + 4 * n <= from || from + bytes <= out; };
+    return n >= ((size_t)1 << 25) && (mask & 15) == 0 && apart(values, 4 * n) && apart(mask, n);
+}
+
 }  // namespace
 
 // Used by tcuscan_split_radix_sort_u32 (apps.hip): the zero counts of all 32 bits, and one fused split pass.
@@ -3077,7 +3124,8 @@ tcuscan_status_t tcuscan_internal_compact_fused(const void *d_values, const void
     C.mask = (const uint8_t *)d_mask; C.values = (const uint32_t *)d_values; C.out = (uint32_t *)d_out; C.count = d_count;
     P.out = d_positions;
     void *args[] = {&P, &C};
-    const void *fn = d_positions ? (const void *)compact_kernel<NT, W, true> : (const void *)compact_kernel<NT, W, false>;
+    const void *fn = d_positions ? (const void *)compact_kernel<NT, W, true>
+                   : compact_ahead(C, n) ? (const void *)compact_kernel<NT, W, false, true> : (const void *)compact_kernel<NT, W, false>;
     return hipLaunchKernel(fn, dim3(P.num_tiles), dim3(64 * W), args, 0, s) == hipSuccess ? TCUSCAN_OK : TCUSCAN_ERR_HIP;
 }
 
