@@ -166,6 +166,7 @@ struct HistArgs {
     const uint32_t *keys, *vals;
     uint32_t *keys_copy, *vals_copy;      // null, or where the keys (and payloads) are copied for an odd number of passes
     uint32_t *hist;                       // [table][pass][digit], zero before unless `own`
+    uint32_t tables;
     uint32_t *status;                     // status words of all passes, zeroed here (16-byte aligned)
     uint64_t n, status_quads;
     Passes P;
@@ -232,7 +233,7 @@ __global__ __launch_bounds__(kHistThreads) void digit_histograms_kernel(HistArgs
         uint32_t sum = 0u;
 #pragma unroll
         for (int c = 0; c < kHistCopies; ++c) sum += s_hist[i * kHistCopies + c];
-        uint32_t *at = &H.hist[(blockIdx.x % kTables) * kTableWords + i];
+        uint32_t *at = &H.hist[(blockIdx.x % H.tables) * kTableWords + i];
         if (H.own) *at = sum;
         else if (sum) atomicAdd(at, sum);
     }
@@ -684,20 +685,20 @@ tcuscan_status_t tcuscan_internal_digit_sort(void *d_keys, void *d_vals, size_t 
     const bool odd = (P.count & 1) && !(buckets_wanted && surely);       // the first pass then starts from a copy, and the last ends at home
     const bool own = n <= (odd ? kOwnTables / 4 : kOwnTables) && !use_tickets;       // (few workgroups are slow copiers)
     const unsigned hist_grid = (unsigned)(want < 1 ? 1 : own && want > kTables ? kTables : want < kHistGrid ? want : kHistGrid);
-    const uint32_t tables = own ? hist_grid : kTables;
+    const uint32_t tables = own ? hist_grid : n < ((size_t)1 << 19) ? 1 : kTables;     // (300,000 keys, two passes: one table 25.5 us, eight 26.5)
     // scratch: digit counts of the passes from the next 16-byte boundary on, ticket counters, what the first pass finds out, status words
     uint32_t *hist = (uint32_t *)(((uintptr_t)d_scratch + 15) & ~(uintptr_t)15), *tickets = hist + tables * kTableWords;
     Buckets *buckets = (Buckets *)(tickets + kMaxPasses);
     uint32_t *status = (uint32_t *)(((uintptr_t)(buckets + 1) + 15) & ~(uintptr_t)15);
     const size_t pass_words = tiles * kDigits * (wide ? 2 : 1);
-    if (!own && tcuscan_internal_fill(hist, 4 * (kTables * kTableWords + kMaxPasses), s) != hipSuccess) return TCUSCAN_ERR_HIP;
+    if (!own && tcuscan_internal_fill(hist, 4 * (tables * kTableWords + kMaxPasses), s) != hipSuccess) return TCUSCAN_ERR_HIP;
 
     uint32_t *src_k = (uint32_t *)d_keys, *dst_k = (uint32_t *)d_keys_tmp, *src_v = (uint32_t *)d_vals, *dst_v = (uint32_t *)d_vals_tmp;
     {
         HistArgs H;
         H.keys = src_k; H.vals = src_v;
         H.keys_copy = odd ? dst_k : nullptr; H.vals_copy = odd && src_v ? dst_v : nullptr;
-        H.hist = hist; H.status = status; H.n = n; H.status_quads = pass_words * passes / 4; H.P = P; H.stream = around_cache; H.own = own;
+        H.hist = hist; H.tables = tables; H.status = status; H.n = n; H.status_quads = pass_words * passes / 4; H.P = P; H.stream = around_cache; H.own = own;
         if (buckets_wanted && surely) H.P = {1, {P.digit[P.count - 1]}};
         void *args[] = {&H};
         if (hipLaunchKernel((const void *)digit_histograms_kernel, dim3(hist_grid), dim3(kHistThreads), args, 0, s) != hipSuccess) return TCUSCAN_ERR_HIP;

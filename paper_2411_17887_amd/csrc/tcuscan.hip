@@ -30,8 +30,9 @@
 //            (partial lines per instruction measured 30 % slower).  No data pass through LDS.
 //
 // Variants of the same kernel: reverse scans (suffix sums: upper triangular blocks, granules mirrored, the
-// chain runs from the end of the row) and segmented scans (rows of different lengths stored back to back: a
-// tile looks up its row in a map the host side builds with two small kernels and this library's own int32
+// chain runs from the end of the row) and segmented scans (rows of different lengths stored back to back: one
+// range whose sums restart at the row starts, which every tile finds in the offsets; or rows in tiles of their own,
+// with a map from tiles to rows that the host side builds with two small kernels and this library's own int32
 // scan).  The C entry points at the bottom validate arguments on the host and launch these kernels.
 
 #include <hip/hip_runtime.h>
@@ -1613,9 +1614,9 @@ __global__ __launch_bounds__(256) void seg_first_rows_kernel(Params P, const lon
 
 struct FlatArgs {
     const long long *offsets;
-    const uint32_t *first_rows;            // seg_stream_kernel: every run's first row
-    uint32_t expect;                       // about how many rows start in a tile
-    uint32_t check_rows;                   // rows whose offsets a workgroup checks 
+    const uint32_t *first_rows;            // seg_stream_kernel: every run's first row (null: one window holds all offsets, or a search)
+    uint32_t expect;                       // about how many rows start in a tile, or in a run with first_rows
+    uint32_t check_rows;                   // rows whose offsets a workgroup checks (0: checked beforehand)
     uint32_t stream;                       // input and output do not fit the memory-side cache: the input is read around it (32-bit)
 };
 
@@ -2687,8 +2688,7 @@ tcuscan_status_t run(const void *d_in, void *d_out, size_t rows, size_t cols, in
 
 // ---- segmented scans (rows of different lengths, stored back to back)
 
-
-// The tile a segmented scan uses is decided by the average row length (the only thing the host knows): one
+// The tile of rows with tiles of their own is decided by the average row length (the only thing the host knows): one
 // wavefront per tile for short rows, the small workgroup tile, or the large one for very long rows.
 enum SegTile { kSegShort = 0, kSegSmall = 1, kSegLarge = 2 };
 
