@@ -123,6 +123,7 @@ static_assert(sizeof(TileDesc) == 32, "descriptor size");
 // of the granule whose results the lane holds in block p.
 
 template <int DT> struct Tr;
+template <int DT> constexpr bool kFloatAcc = DT == TCUSCAN_F16_F32 || DT == TCUSCAN_BF16_F32 || DT == TCUSCAN_F32_F32;
 
 // 64-bit word whose `cnt` lowest slots of `bits_per_slot` bits hold `one` (a slot pattern repeated over
 // the whole word is passed in), the rest zero: the part of a row of the triangular operand that falls
@@ -624,12 +625,16 @@ template <class A> __device__ __forceinline__ A row_exclusive_scan(A v)
 // a2 + a3 + a5 + a6 for the run, tile by tile with a running carry (`carry` = everything before the run).
 // Nothing passes through LDS: lane l feeds the MFMA with the granule it loaded, and results are stored
 // straight from the MFMA's result registers, 1 KiB of consecutive outputs per store instruction.
-// COUNT tiles of the run from tile t0 on; returns the carry behind them.
+// COUNT tiles of the run from tile t0 on; returns the carry behind them.  With COUNT < NT, floating-point sums keep what lies before
+// the run (`base`) apart from what the run has added to it so far (`carry`): the chain of carries then rounds at the size
+// of the run's sums (seg_stream_kernel).
 template <int DT, int NT, bool EXCL, bool REV, bool SEG = false, int COUNT = NT>
 __device__ __forceinline__ typename Tr<DT>::acc scan_and_store(int lane, const typename Tr<DT>::AConst &Aop, const Run &R,
-                                                               const u32x4 (&g)[NT], typename Tr<DT>::acc carry, const int t0 = 0)
+                                                               const u32x4 (&g)[NT], typename Tr<DT>::acc carry, const int t0 = 0,
+                                                               const typename Tr<DT>::acc base = {})
 {
     using T = Tr<DT>;
+    constexpr bool kApart = COUNT < NT && kFloatAcc<DT>;
     using A = typename T::acc;
     using A4 = typename T::acc4;
     constexpr int kBlocks = T::kBlocks;
@@ -649,6 +654,7 @@ __device__ __forceinline__ typename Tr<DT>::acc scan_and_store(int lane, const t
             if (EXCL) tot = acc_add(tot, acc_from_bits<A>(g[t][edge]));  // the strict product leaves that row's own element out
             const A inc = wave_inclusive_scan(tot);
             e[0] = acc_add(carry, wave_shift_up(inc));
+            if constexpr (kApart) e[0] = acc_add(base, e[0]);
             carry = acc_add(carry, uniform_from_lane(inc, 63));
         } else {
             // granule totals from the matrix unit (register p: granule (jmap(p, q), c)), scanned over c inside
@@ -664,9 +670,14 @@ __device__ __forceinline__ typename Tr<DT>::acc scan_and_store(int lane, const t
                     carry = acc_add(carry, uniform_from_lane(inc, 15));
                 } else {                                     // block p <-> granule rows 2p (lane rows 0, 1) and 2p + 1 (lane rows 2, 3)
                     const A lo = uniform_from_lane(inc, 15), hi = uniform_from_lane(inc, 47);
-                    const A mid = acc_add(carry, lo);
-                    e[p] = acc_add(q >= 2 ? mid : carry, ex);
-                    carry = acc_add(mid, hi);
+                    if constexpr (kApart) {                  // (one rounding of the carry, not two)
+                        e[p] = acc_add(base, acc_add(carry, q >= 2 ? acc_add(lo, ex) : ex));
+                        carry = acc_add(carry, acc_add(lo, hi));
+                    } else {
+                        const A mid = acc_add(carry, lo);
+                        e[p] = acc_add(q >= 2 ? mid : carry, ex);
+                        carry = acc_add(mid, hi);
+                    }
                 }
             }
         }
@@ -2027,11 +2038,11 @@ __global__ __launch_bounds__(64 * W) void seg_flat_narrow_kernel(Params P, FlatA
 // everything in front is masked out of the sum.  An MFMA tile that no row starts in takes scan_kernel's way (products with
 // the triangular blocks), one that is cut keeps level 0 in the lane, as in the flat kernels.
 
-// A tile of the run in which rows start: fb has this lane's, in processing order.  carry: the open row's sum in front of the tile,
-// and behind it.
+// A tile of the run in which rows start: fb has this lane's, in processing order.  base and carry: the open row's sum in front of
+// the run and from there to the tile (floating point; else all of it is in carry); behind the tile the row is the run's own.
 template <int DT, int NT, bool EXCL, bool REV>
 __device__ __forceinline__ void seg_scan_and_store_cut_tile(int lane, const Run &R, bool whole, int t, const u32x4 &gt, uint32_t fb,
-                                                            typename Tr<DT>::acc &carry)
+                                                            typename Tr<DT>::acc &carry, typename Tr<DT>::acc &base)
 {
     using A = typename Tr<DT>::acc;
     constexpr int G = Tr<DT>::kG, Q = G / 4;
@@ -2049,7 +2060,9 @@ __device__ __forceinline__ void seg_scan_and_store_cut_tile(int lane, const Run 
     uint32_t h = fb ? 1u : 0u;
     seg_wave_inclusive(v, h);
     const A vex = wave_shift_up(v);
-    const A in = dpp0<kWaveShr1>(h) ? vex : acc_add(carry, vex);
+    A open = acc_add(carry, vex), before = carry;
+    if constexpr (kFloatAcc<DT>) { open = acc_add(base, open); before = acc_add(base, before); }
+    const A in = dpp0<kWaveShr1>(h) ? vex : open;
     const uint32_t first = fb ? (uint32_t)__builtin_ctz(fb) : (uint32_t)G;
 #pragma unroll
     for (int i = 0; i < G; ++i)
@@ -2057,7 +2070,7 @@ __device__ __forceinline__ void seg_scan_and_store_cut_tile(int lane, const Run 
     u32x4 out[Q];
     if constexpr (EXCL) {
         A prev = wave_shift_up(y[G - 1]);
-        if (lane == 0) prev = carry;
+        if (lane == 0) prev = before;
         out[mem(0) >> 2][mem(0) & 3] = (fb & 1u) ? 0u : acc_bits(prev);
 #pragma unroll
         for (int i = 1; i < G; ++i) out[mem(i) >> 2][mem(i) & 3] = ((fb >> i) & 1u) ? 0u : acc_bits(y[i - 1]);
@@ -2066,6 +2079,7 @@ __device__ __forceinline__ void seg_scan_and_store_cut_tile(int lane, const Run 
         for (int i = 0; i < G; ++i) out[mem(i) >> 2][mem(i) & 3] = acc_bits(y[i]);
     }
     carry = uniform_from_lane(y[G - 1], 63);
+    base = acc_from_bits<A>(0u);
     // results change lanes, as in seg_flat_narrow_kernel
     uint32_t e[Q];
     if constexpr (Q == 4) {
@@ -2199,7 +2213,11 @@ __global__ __launch_bounds__(64 * W) void seg_stream_kernel(Params P, FlatArgs F
     const A open_sum = wave_sum(T::red_lane(rsum, lane));
 
     if (F.check_rows != 0u && wave != (REV ? W - 1 : 0)) seg_check_offsets(F.offsets, P, tile, F.check_rows, threadIdx.x - (REV ? 0u : 64u), 64u * (W - 1));
-    A carry = seg_open_sum_before_run<A, W, REV>(P, tile, lane, wave, open_sum, run_open, s_sum, s_head, &s_bcast);
+    // (2-norm error against 64 bits with the sum before the run in the carry from the first tile on / kept apart / with results held
+    // back while waiting, as the small kernels do: f16 rows of mean length 1451, from the end, 7.9e-8 / 5.2e-8 / 5.0e-8; bf16 rows of
+    // 30,865 1.0e-7 / 7.1e-8 / 7.6e-8, 64 of 2^21 1.7e-7 / 1.2e-7 / 1.8e-7; the time is the same: 139.2, 29.6 and 137 us)
+    const A before_run = seg_open_sum_before_run<A, W, REV>(P, tile, lane, wave, open_sum, run_open, s_sum, s_head, &s_bcast);
+    A row_base = kFloatAcc<DT> ? before_run : acc_from_bits<A>(0u), carry = kFloatAcc<DT> ? acc_from_bits<A>(0u) : before_run;
 
     // ---- tile by tile
 #pragma unroll
@@ -2213,8 +2231,8 @@ __global__ __launch_bounds__(64 * W) void seg_stream_kernel(Params P, FlatArgs F
         } else {
             fb = (w >> (j & 31u)) & kMask;
         }
-        if (__ballot(fb != 0u) == 0ull) carry = scan_and_store<DT, NT, EXCL, REV, true, 1>(lane, Aop, R, g, carry, t);
-        else seg_scan_and_store_cut_tile<DT, NT, EXCL, REV>(lane, R, whole_out, t, g[t], fb, carry);
+        if (__ballot(fb != 0u) == 0ull) carry = scan_and_store<DT, NT, EXCL, REV, true, 1>(lane, Aop, R, g, carry, t, row_base);
+        else seg_scan_and_store_cut_tile<DT, NT, EXCL, REV>(lane, R, whole_out, t, g[t], fb, carry, row_base);
     }
 }
 

@@ -105,3 +105,23 @@ def test_bad_offsets_raise_the_fault_word_in_every_kernel(name, break_at):
     tcuscan.segmented(d_in, d_out[4096:], torch.from_numpy(off).cuda(), lens.size, total, "i32", ws=ws)
     assert tcuscan.workspace_fault(ws) == 2
     assert bool((d_out[:4096] == -77).all()) and bool((d_out[4096 + total:] == -77).all())          # nothing outside the arrays is written
+
+
+@pytest.mark.parametrize("kind", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("flags", [0, 3])
+@pytest.mark.parametrize("mean", [1451, 30_000])
+def test_large_calls_round_as_rarely_as_results_held_back(mean, flags, kind):
+    """What lies before a run is added to its sums once.  An addition is off by up to half a unit in the last place, 2.5e-8 of the
+    sum in the root mean square; eight of them at the size of the result (granule, lanes, tile, run, wavefronts, workgroups) make 7.1e-8."""
+    import torch
+    total, dtype = LARGE + 8191, {"f16": torch.float16, "bf16": torch.bfloat16, "f32": torch.float32}[kind]
+    off = torch.from_numpy(offsets_from(spread(np.random.default_rng(mean), total // mean, total))).cuda()
+    x = torch.rand(total, generator=torch.Generator(device="cuda").manual_seed(mean), device="cuda").mul_(0.9995).to(dtype)
+    out, rows = torch.empty(total, device="cuda"), off.numel() - 1
+    tcuscan.segmented(x, out, off, rows, total, kind, flags=flags, ws=tcuscan.new_segmented_workspace(rows, total, kind))
+    inc = torch.cumsum(x.double(), 0)
+    ex = torch.cat([inc.new_zeros(1), inc])
+    row = torch.repeat_interleave(torch.arange(rows, device="cuda"), off[1:] - off[:-1])
+    ref = ex[off[row + 1]] - inc if flags == 3 else inc - ex[off[row]]             # 3: exclusive and reverse
+    err = float((out.double() - ref).norm() / ref.norm())
+    assert err < 7.1e-8
