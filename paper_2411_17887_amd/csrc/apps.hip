@@ -115,6 +115,7 @@ tcuscan_status_t tcuscan_split_radix_sort_u32(void *d_keys, void *d_vals, size_t
     if (((uintptr_t)d_keys % 16) || ((uintptr_t)d_keys_tmp % 16) || ((uintptr_t)d_flags % 16) || ((uintptr_t)d_positions % 4) ||
         ((uintptr_t)d_vals % 4) || ((uintptr_t)d_vals_tmp % 4))
         return TCUSCAN_ERR_INVALID_ARG;
+    if (!d_vals) d_vals_tmp = nullptr;                       // (below, source and destination change places: neither may look like payloads)
     hipStream_t s = (hipStream_t)stream;
     uint32_t *src_k = (uint32_t *)d_keys, *dst_k = (uint32_t *)d_keys_tmp;
     uint32_t *src_v = (uint32_t *)d_vals, *dst_v = (uint32_t *)d_vals_tmp;

@@ -92,3 +92,23 @@ def test_recorded_into_a_graph(n):
         graph.replay()
         torch.cuda.synchronize()
         assert np.array_equal(keys.cpu().numpy().view(np.uint32), np.sort(new.view(np.uint32)))
+
+
+@pytest.mark.parametrize("bits", [24, 32])
+@pytest.mark.parametrize("n", [9000, 100_003])
+@pytest.mark.parametrize("form", [0, 1, 2])
+def test_keys_alone_with_a_scratch_for_payloads(form, n, bits):
+    """The scratch is not used, and not written."""
+    import torch
+    k = inputs.int32_full(n, n + bits).view(np.uint32)
+    d_k = torch.from_numpy(k.view(np.int32).copy()).cuda()
+    tmp = torch.full((n,), -7, dtype=torch.int32, device="cuda")
+    tcuscan.set_sort_fusion(form)
+    try:
+        tcuscan.split_radix_sort_u32(d_k, torch.empty_like(d_k), torch.empty(n, dtype=torch.int8, device="cuda"), torch.empty_like(d_k),
+                                     vals_tmp=tmp, bits=bits, ws=tcuscan.new_workspace(1, n, "i8"))
+        torch.cuda.synchronize()
+    finally:
+        tcuscan.set_sort_fusion(1)
+    assert np.array_equal(d_k.cpu().numpy().view(np.uint32), k[np.argsort(k & np.uint32((1 << bits) - 1), kind="stable")])
+    assert bool((tmp == -7).all())
