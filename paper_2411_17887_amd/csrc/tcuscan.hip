@@ -61,7 +61,8 @@ constexpr int kThreads = 64 * kWaves;
 // 64-byte slot: thousands of tiles poll the words of the few hundred tiles in front of them, and with
 // the words packed 8 to a line that traffic lands on a handful of memory channels (measured: 5-9 %
 // of the whole kernel's run time).
-constexpr size_t kStatusStride = 8;    // in 64-bit words
+constexpr uint32_t kStatusStrideLog2 = 3;
+constexpr size_t kStatusStride = (size_t)1 << kStatusStrideLog2;    // in 64-bit words
 struct WsHeader {
     uint32_t fault;    // sticky: 1 = a look-back wait hit its spin bound, 2 = a segmented scan was given bad offsets
     uint32_t ticket;   // ticket policy only: the next tile index to hand out (cleared in front of every such call)
@@ -382,9 +383,10 @@ __device__ __forceinline__ uint64_t status_word(uint32_t tag, uint32_t state, ui
 // a status round trip under full memory load costs microseconds, so a wider window saves round trips,
 // but every extra word polled is uncached traffic that competes with the data (512 words per poll cost
 // 5 % of the run time against 128, and 1024 and more cost 50 %).
+// `stride`: log2 of the 64-bit words from one status word to the next.
 constexpr int kDepth = 2;
 template <class A>
-__device__ A look_back(const uint64_t *row_status, int tr, uint32_t tag, WsHeader *ws, uint32_t spin_limit)
+__device__ A look_back(const uint64_t *row_status, int tr, uint32_t tag, WsHeader *ws, uint32_t spin_limit, uint32_t stride = kStatusStrideLog2)
 {
     const int lane = __lane_id();
     A sum = acc_from_bits<A>(0u);
@@ -393,7 +395,7 @@ __device__ A look_back(const uint64_t *row_status, int tr, uint32_t tag, WsHeade
 #pragma unroll
         for (int u = 0; u < kDepth; ++u) {
             const int idx = base - 64 * u - lane;
-            if (idx >= 0) w[u] = __hip_atomic_load(row_status + (size_t)idx * kStatusStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (idx >= 0) w[u] = __hip_atomic_load(row_status + ((size_t)(uint32_t)idx << stride), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         // Take every total up to and including the nearest published prefix, skip everything behind it.
         bool done = false;
@@ -412,7 +414,7 @@ __device__ A look_back(const uint64_t *row_status, int tr, uint32_t tag, WsHeade
                         break;
                     }
                     __builtin_amdgcn_s_sleep(1);
-                    w[u] = __hip_atomic_load(row_status + (size_t)idx * kStatusStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    w[u] = __hip_atomic_load(row_status + ((size_t)(uint32_t)idx << stride), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
             }
             const uint64_t have_prefix = __ballot(state == kStatePrefix);
@@ -1629,6 +1631,7 @@ struct FlatArgs {
     uint32_t expect;                       // about how many rows start in a tile, or in a run with first_rows
     uint32_t check_rows;                   // rows whose offsets a workgroup checks (0: checked beforehand)
     uint32_t stream;                       // input and output do not fit the memory-side cache: the input is read around it (32-bit)
+    uint32_t stride;                       // the small kernels: log2 of the 64-bit words from one status word to the next
 };
 
 // (sum since the last row start, a row starts at or before here) of lanes 0 .. l, in lane l
@@ -1667,7 +1670,7 @@ template <class A> __device__ __forceinline__ void seg_wave_inclusive(A &v, uint
 // it; the others publish a total, look back, and publish their prefix.
 template <class A, int W, bool REV>
 __device__ __forceinline__ A seg_open_sum_before_run(const Params &P, uint32_t tile, int lane, int wave, A carry, bool run_open,
-                                                     uint32_t *s_sum, uint32_t *s_head, uint32_t *s_bcast)
+                                                     uint32_t *s_sum, uint32_t *s_head, uint32_t *s_bcast, uint32_t stride = kStatusStrideLog2)
 {
     const uint32_t tag = P.tag;
     if (lane == 0) { s_sum[wave] = acc_bits(carry); s_head[wave] = run_open ? 0u : 1u; }
@@ -1692,16 +1695,16 @@ __device__ __forceinline__ A seg_open_sum_before_run(const Params &P, uint32_t t
         if (wave == kFirst) {
             if (tile == 0 || wg_head) {
                 if (lane == 0)
-                    __hip_atomic_store(row_status + (size_t)tile * kStatusStride, status_word(tag, kStatePrefix, acc_bits(wg_sum)),
+                    __hip_atomic_store(row_status + ((size_t)tile << stride), status_word(tag, kStatePrefix, acc_bits(wg_sum)),
                                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if (tile != 0) prefix = look_back<A>(row_status, (int)tile, tag, P.ws, P.spin_limit);
+                if (tile != 0) prefix = look_back<A>(row_status, (int)tile, tag, P.ws, P.spin_limit, stride);
             } else {
                 if (lane == 0)
-                    __hip_atomic_store(row_status + (size_t)tile * kStatusStride, status_word(tag, kStateAggregate, acc_bits(wg_sum)),
+                    __hip_atomic_store(row_status + ((size_t)tile << stride), status_word(tag, kStateAggregate, acc_bits(wg_sum)),
                                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                prefix = look_back<A>(row_status, (int)tile, tag, P.ws, P.spin_limit);
+                prefix = look_back<A>(row_status, (int)tile, tag, P.ws, P.spin_limit, stride);
                 if (lane == 0)
-                    __hip_atomic_store(row_status + (size_t)tile * kStatusStride, status_word(tag, kStatePrefix, acc_bits(acc_add(prefix, wg_sum))),
+                    __hip_atomic_store(row_status + ((size_t)tile << stride), status_word(tag, kStatePrefix, acc_bits(acc_add(prefix, wg_sum))),
                                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
             if (for_all && lane == 0) *s_bcast = acc_bits(prefix);
@@ -1817,7 +1820,7 @@ __global__ __launch_bounds__(64 * W) void seg_flat_kernel(Params P, FlatArgs F)
     // (the wavefronts that do not look back check offsets meanwhile)
     if (wave != (REV ? W - 1 : 0))
         seg_check_offsets(F.offsets, P, tile, F.check_rows, threadIdx.x - (REV ? 0u : 64u), 64u * (W - 1));
-    const A wave_in = seg_open_sum_before_run<A, W, REV>(P, tile, lane, wave, carry, run_open, s_sum, s_head, &s_bcast);
+    const A wave_in = seg_open_sum_before_run<A, W, REV>(P, tile, lane, wave, carry, run_open, s_sum, s_head, &s_bcast, F.stride);
 
     // ---- what the open row brings, to the elements that no row start of the run precedes; store
     asm("" : "+v"(starts));                                    // (taken apart once more: kept from above, the parts cost 16 registers)
@@ -1975,7 +1978,7 @@ __global__ __launch_bounds__(64 * W) void seg_flat_narrow_kernel(Params P, FlatA
     // (the wavefronts that do not look back check offsets meanwhile)
     if (wave != (REV ? W - 1 : 0))
         seg_check_offsets(F.offsets, P, tile, F.check_rows, threadIdx.x - (REV ? 0u : 64u), 64u * (W - 1));
-    const A wave_in = seg_open_sum_before_run<A, W, REV>(P, tile, lane, wave, carry, run_open, s_sum, s_head, &s_bcast);
+    const A wave_in = seg_open_sum_before_run<A, W, REV>(P, tile, lane, wave, carry, run_open, s_sum, s_head, &s_bcast, F.stride);
 
     // ---- the open row's sum to the elements that no row start of their granule precedes; results change lanes; store
     A last = wave_in;
@@ -2779,6 +2782,12 @@ constexpr size_t kFlatTile = (size_t)2048 * kFlatW;
 constexpr size_t kFlatCheckRows = 4096;      // offsets a workgroup checks at most (rows far shorter than a tile of them)
 // From here on the large kernel (3 x 2^22 f32 of mean length 16 / 200 / 1500: 28.6 / 23.3 / 23.2 -> 22.9 / 20.7 / 21.9).
 constexpr size_t kSegStreamFrom = (size_t)3 << 22;
+// Where rows with tiles of their own would have large ones, the layout has fewer slots than the small kernels have tiles: up to here
+// their status words then lie closer together (us, tiles of their own / the large kernel / the small ones: 600,000 f32 in one row
+// 10.1 / 14.0 / 8.9, bf16 18.2 / 18.5 / 7.8; 2.4 million f32 in 4 rows 12.2 / 14.5 / 10.4, bf16 19.3 / 18.2 / 7.3; 2^22 f32 in
+// one row 12.6 / 11.7 / 10.6, from the end 12.6 / 12.0 / 12.8).  Beyond, one long chain of them loses to the large kernel: 6 x 2^20
+// f32 in 4 rows, from the end, 15.5 / 12.1 / 14.5, 7 x 2^20 i8 in 2 rows 17.5 / 10.6 / 12.4.
+constexpr size_t kFlatFewSlots = (size_t)1 << 22;
 // From 200 MB of input and output on, 32-bit inputs are read around the memory-side cache (2^26 f32 of mean length 16 115 -> 111,
 // 2^24 the other way round: 30 -> 35).
 constexpr size_t kSegAroundCacheFrom = (size_t)25 << 20;
@@ -2828,18 +2837,22 @@ template <int DT> tcuscan_status_t run_segmented_range_dt(Params P, const long l
 {
     using Short = SegStream<DT, false>;
     using Long = SegStream<DT, true>;
-    const bool flat = total < kSegStreamFrom && total / kFlatTile + 2 <= L.max_tiles;
+    const bool flat = total < kSegStreamFrom && (total / kFlatTile + 2 <= L.max_tiles || total <= kFlatFewSlots);
     const bool long_rows = total / rows >= (Tr<DT>::kEsz == 4 ? 2048 : 4096);
     const bool few_rows = rows < RunMarks<Short::kRun>::kWindow, first = !flat && !long_rows && !few_rows;     // (are first rows found beforehand?)
     if (Tr<DT>::kEsz == 4 && total >= kOwnTilesFrom && !few_rows && total / rows >= ((size_t)1 << 14)) return TCUSCAN_ERR_UNSUPPORTED;
     const size_t run = flat ? 2048 : long_rows ? Long::kRun : Short::kRun;
     const size_t tile = flat ? kFlatTile : long_rows ? Long::kTile : Short::kTile;
     const size_t tiles = total / tile + 2;                       // the range is at most `total` long and starts less than a granule late
-    if (tiles > L.max_tiles || (first && 4 * tiles * (tile / run) > L.first_rows_bytes)) return TCUSCAN_ERR_UNSUPPORTED;
+    uint32_t stride = kStatusStrideLog2;                         // until the status words fit the layout's slots
+    while (flat && stride > 0 && (tiles << stride) > kStatusStride * L.max_tiles) --stride;
+    const size_t slots = ((tiles << stride) + kStatusStride - 1) / kStatusStride;
+    if (slots > L.max_tiles || (first && 4 * tiles * (tile / run) > L.first_rows_bytes)) return TCUSCAN_ERR_UNSUPPORTED;
     P.num_tiles = (uint32_t)tiles;
     FlatArgs F;
     F.offsets = d_offsets; F.first_rows = nullptr;
     F.stream = total >= kSegAroundCacheFrom ? 1u : 0u;
+    F.stride = stride;
     const size_t per_run = rows / (total / run + 1);             // rows that start in a run (a quarter more: few need a second window)
     F.expect = (uint32_t)(per_run < run ? per_run + per_run / 4 + 16 : run);
     if (!first) F.expect *= (uint32_t)(tile / run);
@@ -2849,7 +2862,7 @@ template <int DT> tcuscan_status_t run_segmented_range_dt(Params P, const long l
     // The first rows lie where a later call of another shape may expect status words: the workspace is then no longer known to be
     // clean.  (The kernel that finds them clears this call's status words.)
     if (first) g_clean.mark_dirty((uintptr_t)d_ws, chain_tags::call_id(g_calls.load(std::memory_order_relaxed)).generation);
-    const tcuscan_status_t bst = begin_chain(P, d_ws, tiles, first, s, first);
+    const tcuscan_status_t bst = begin_chain(P, d_ws, slots, first, s, first);
     if (bst != TCUSCAN_OK) return bst;
     hipError_t e;
     if (flat) {

@@ -2,6 +2,7 @@
 launch_recorder_shim.cpp takes the place of the HIP runtime.  The addresses passed are never followed."""
 from __future__ import annotations
 
+import collections
 import json
 import os
 import re
@@ -10,6 +11,9 @@ import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB = os.path.join(os.path.dirname(HERE), "paper_2411_17887_amd", "libtcuscan.so")
+
+# stride: log2 of the 64-bit words between the status words of the small segmented kernels (else 0)
+Launch = collections.namedtuple("Launch", "kernel grid block stride")
 
 _CHILD = """
 import ctypes, json, sys
@@ -34,13 +38,13 @@ def build(folder) -> str:
 
 
 def launches(shim: str, calls):
-    """calls: [(entry point, [integers])], made in order in one process.  Returns for each (status, [(kernel, grid, block)])."""
+    """calls: [(entry point, [integers])], made in order in one process.  Returns for each (status, [Launch])."""
     done = subprocess.run([sys.executable, "-c", _CHILD, shim, LIB], input=json.dumps(calls), capture_output=True, text=True, timeout=120)
     assert done.returncode == 0, done.stderr
     result = []
     for rc, text in json.loads(done.stdout):
-        rows = [line.split(" ", 2) for line in text.splitlines()]
-        result.append((rc, [(_plain(name), int(grid), int(block)) for grid, block, name in rows]))
+        rows = [line.split(" ", 3) for line in text.splitlines()]
+        result.append((rc, [Launch(_plain(name), int(grid), int(block), int(stride)) for grid, block, stride, name in rows]))
     return result
 
 

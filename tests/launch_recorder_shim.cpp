@@ -9,6 +9,10 @@
 #include <string>
 
 struct Dim3 { unsigned x, y, z; };
+struct FlatArgs {                                            // as in tcuscan.hip
+    const void *offsets, *first_rows;
+    unsigned expect, check_rows, stream, stride;
+};
 
 static std::map<const void *, std::string> &names()
 {
@@ -34,10 +38,12 @@ void __hipRegisterFunction(void **, const void *host, char *, const char *name, 
     std::free(plain);
 }
 
-int hipLaunchKernel(const void *kernel, Dim3 grid, Dim3 block, void **, size_t, void *)
+int hipLaunchKernel(const void *kernel, Dim3 grid, Dim3 block, void **args, size_t, void *)
 {
     const auto it = names().find(kernel);
-    g_launches += std::to_string(grid.x) + " " + std::to_string(block.x) + " " + (it == names().end() ? "?" : it->second) + "\n";
+    const std::string name = it == names().end() ? "?" : it->second;
+    const unsigned stride = name.find("seg_flat") == std::string::npos ? 0u : ((const FlatArgs *)args[1])->stride;
+    g_launches += std::to_string(grid.x) + " " + std::to_string(block.x) + " " + std::to_string(stride) + " " + name + "\n";
     return 0;
 }
 int hipStreamIsCapturing(void *, int *status) { *status = 0; return 0; }

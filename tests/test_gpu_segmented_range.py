@@ -5,7 +5,8 @@ import numpy as np
 import pytest
 
 from paper_2411_17887_amd import inputs, tcuscan
-from test_gpu_segmented import INT_GEN, RND_GEN, check, offsets_from, run_segmented
+from gpu_util import out_dtype, to_device
+from test_gpu_segmented import GUARD, INT_GEN, RND_GEN, check, offsets_from, run_segmented
 
 pytestmark = pytest.mark.gpu
 
@@ -125,3 +126,65 @@ def test_large_calls_round_as_rarely_as_results_held_back(mean, flags, kind):
     ref = ex[off[row + 1]] - inc if flags == 3 else inc - ex[off[row]]             # 3: exclusive and reverse
     err = float((out.double() - ref).norm() / ref.norm())
     assert err < 7.1e-8
+
+
+def run_shifted(x, kind, off, flags, ws, shift_in, shift_out, inplace=False):
+    """run_segmented with arrays that start some elements into their allocations."""
+    import torch
+    big = to_device(np.concatenate([x[:shift_in], x]), kind)
+    d_in = big[shift_in:]
+    big_out = torch.full((x.size + shift_out,), GUARD, dtype=out_dtype(kind), device="cuda")
+    d_out = d_in if inplace else big_out[shift_out:]
+    tcuscan.segmented(d_in, d_out, torch.from_numpy(off).cuda(), off.size - 1, x.size, kind, flags=flags, ws=ws)
+    torch.cuda.synchronize()
+    assert bool((big_out[:shift_out] == GUARD).all()) and (not inplace or torch.equal(big[:shift_in], to_device(x[:shift_in], kind)))
+    return d_out.cpu().numpy().copy(), tcuscan.workspace_fault(ws)
+
+
+@pytest.mark.parametrize("kind", ["i32", "f16", "i8", "f32", "bf16"])
+@pytest.mark.parametrize("rows,total", [(1, 1 << 19), (1, 600_001), (1, 1 << 22), (3, 1_700_003), (8, 1 << 22), (7, 4_000_001)])
+def test_few_long_rows_of_a_small_call(rows, total, kind):
+    """Status words of small tiles in a layout for large ones, up to eight to a slot: all directions, tickets, misaligned and
+    in place, and the same workspace under calls that have a word to a slot."""
+    import torch
+    off = offsets_from(spread(np.random.default_rng(rows + total), rows, total))
+    x = (INT_GEN if kind in INT_GEN else RND_GEN)[kind](total, 9)
+    ws = tcuscan.new_segmented_workspace(rows, total, kind)
+    for flags in range(4):
+        for policy in ((0, 1) if flags == 2 else (0,)):
+            tcuscan.set_chain_policy(policy)
+            try:
+                got, fault = run_shifted(x, kind, off, flags, ws, 3 * (flags == 1), 5 * (flags == 1))
+            finally:
+                tcuscan.set_chain_policy(0)
+            assert fault == 0
+            check(x, kind, off, got, bool(flags & 1), bool(flags & 2))
+            n = total // 16                                            # a status word to a slot, on the same workspace
+            if tcuscan.segmented_workspace_bytes(1, n, kind) <= ws.numel() * 8:
+                got, fault = run_segmented(x[:n], kind, offsets_from([n]), flags=flags, ws=ws)
+                assert fault == 0
+                check(x[:n], kind, offsets_from([n]), got, bool(flags & 1), bool(flags & 2))
+
+
+def test_few_long_rows_recorded_into_a_graph():
+    """Recorded with status words that share slots; eager calls on the same workspace between the replays."""
+    import torch
+    rows, total = 2, 1_300_007
+    off = offsets_from(spread(np.random.default_rng(4), rows, total))
+    d_off, ws = torch.from_numpy(off).cuda(), tcuscan.new_segmented_workspace(rows, total, "i8")
+    d_in, d_out = torch.empty(total, dtype=torch.int8, device="cuda"), torch.empty(total, dtype=torch.int32, device="cuda")
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        tcuscan.segmented(d_in, d_out, d_off, rows, total, "i8", ws=ws)
+    for seed in (1, 2, 3):
+        x = INT_GEN["i8"](total, seed)
+        d_in.copy_(torch.from_numpy(x))
+        d_out.fill_(-77)
+        graph.replay()
+        torch.cuda.synchronize()
+        check(x, "i8", off, d_out.cpu().numpy(), False, False)
+        d_out.fill_(-77)
+        tcuscan.segmented(d_in, d_out, d_off, rows, total, "i8", flags=3, ws=ws)
+        torch.cuda.synchronize()
+        check(x, "i8", off, d_out.cpu().numpy(), True, True)
+    assert tcuscan.workspace_fault(ws) == 0

@@ -2,6 +2,7 @@
 import pytest
 
 import launch_recorder
+from paper_2411_17887_amd import tcuscan
 
 KEYS, TMP, VALS, VALS_TMP, FLAGS, POS, WS = (0x10000 + (i << 36) for i in range(7))
 WS_BYTES = 1 << 40
@@ -26,3 +27,27 @@ def test_keys_alone_take_the_same_kernels_with_a_scratch_for_payloads(run, form)
         alone, with_tmp = got[2 * at: 2 * at + 2]
         assert alone[0] == 0 and alone[1], (n, bits)
         assert with_tmp == alone, (n, bits)
+
+
+IN, OUT, OFFSETS = KEYS, TMP, VALS
+KINDS = ("i32", "f16", "i8", "f32", "bf16")
+
+
+def segmented(kind, total, rows, flags=0, ws=WS, d_in=IN, d_out=OUT):
+    return ("tcuscan_segmented", [d_in, d_out, OFFSETS, rows, total, tcuscan.DTYPES[kind], flags, ws, WS_BYTES, 0])
+
+
+@pytest.mark.parametrize("kind", KINDS)
+def test_few_long_rows_of_a_small_call_have_small_tiles(run, kind):
+    """Up to 2^22 elements, also where the layout counts large tiles: status words then share slots, and stay inside them."""
+    shapes = [(1 << 19, 1), (600_000, 1), (1_048_575, 1), (1_048_577, 2), (2_400_000, 4), (4_000_000, 7), (1 << 22, 1), (1 << 22, 8), (300_000, 3)]
+    strides = set()
+    for (total, rows), (rc, launched) in zip(shapes, run([segmented(kind, total, rows) for total, rows in shapes])):
+        assert rc == 0 and len(launched) == 1 and launched[0].kernel.startswith("seg_flat"), (total, rows, launched)
+        tiles = total // 8192 + 2
+        own_tile = 8192 if total // rows < 1 << 19 else tcuscan.large_tile_elems(kind)
+        slots = total // own_tile + 2 * rows + 1
+        assert launched[0].grid == tiles and (8 * tiles << launched[0].stride) <= 64 * slots, (total, rows, launched)
+        assert launched[0].stride == 3 or (16 * tiles << launched[0].stride) > 64 * slots
+        strides.add(launched[0].stride)
+    assert len(strides) >= 2
