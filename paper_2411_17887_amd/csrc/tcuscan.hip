@@ -599,6 +599,39 @@ __device__ __forceinline__ void load_run(const Run &R, int lane, u32x4 (&g)[NT])
     }
 }
 
+// The run of a range that begins or ends in it: whole granules in straight lines, then the one or two that the range only has
+// a part of, element by element.  (load_run decides granule by granule, which makes the loads come one after the other, and loads
+// every granule of a run element by element that begins in front of the array.)  The run starts at a 16-byte boundary.
+template <int DT, int NT, bool REV>
+__device__ __forceinline__ void load_range_end(const Run &R, int lane, u32x4 (&g)[NT])
+{
+    using T = Tr<DT>;
+    constexpr uint32_t G = T::kG;
+    auto slot = [lane](int t) { return G * (REV ? (uint32_t)(64 * (NT - 1 - t) + 63 - lane) : (uint32_t)(64 * t + lane)); };      // (slot_offset)
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        const uint32_t e0 = slot(t);
+        g[t] = u32x4{0u, 0u, 0u, 0u};
+        if (e0 >= R.lead && e0 + G <= R.rem) g[t] = *(const u32x4 *)(R.in + e0 * T::kEsz);
+    }
+    auto part = [&](uint32_t e) {                              // (a lane per element: one load, put together in scalar registers)
+        uint32_t v = 0u;
+        if ((uint32_t)lane < G && e + lane >= R.lead && e + lane < R.rem) {
+            if (T::kEsz == 4)      v = ((const uint32_t *)R.in)[e + lane];
+            else if (T::kEsz == 2) v = ((const uint16_t *)R.in)[e + lane];
+            else                   v = ((const uint8_t *)R.in)[e + lane];
+        }
+        uint32_t w[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+        for (uint32_t i = 0; i < G; ++i) w[(i * T::kEsz) >> 2] |= (uint32_t)__builtin_amdgcn_readlane((int)v, (int)i) << (8 * ((i * T::kEsz) & 3));
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+            if (slot(t) == e) g[t] = u32x4{w[0], w[1], w[2], w[3]};
+    };
+    if (R.lead % G != 0u && R.lead < R.rem) part(R.lead - R.lead % G);
+    if (R.rem % G != 0u && R.rem < (uint32_t)NT * 64u * G && R.rem > R.lead) part(R.rem - R.rem % G);
+}
+
 // Total of the run, taken from the granules as loaded: J * T accumulated over the tiles (every row of the
 // product with the all-ones matrix is the row of column totals, and the grand total does not depend on
 // which column a granule sits in), plain adds for 32-bit inputs.  No LDS traffic: the total is ready to be
@@ -759,7 +792,7 @@ __device__ __forceinline__ Run make_seg_run(const Params &P, long long off, uint
     const long long to_end = (long long)P.cols - first;                   // P.cols holds the number of elements of the arrays
     R.cap = to_end <= 0 ? 0u : to_end < 0x40000000ll ? (uint32_t)to_end : 0x40000000u;
     // (first < 0: a row that starts within the first granule of an array that is itself not 16-byte aligned; the
-    // aligned address below it lies before the array, so that run goes element by element)
+    // aligned address below it lies before the array, so that run goes element by element; load_range_end knows better)
     R.in_vec = first >= 0 && (((uintptr_t)R.in) & 15) == 0;
     R.out_vec = first >= 0 && (((uintptr_t)R.out) & 15) == 0;
     return R;
@@ -1717,8 +1750,9 @@ __device__ __forceinline__ A seg_open_sum_before_run(const Params &P, uint32_t t
     return before_head ? before : acc_add(prefix, before);
 }
 
+// (Waves per SIMD: what the kernels had without load_range_end, for which the register allocator else takes 230 registers.)
 template <int DT, int NT, bool EXCL, bool REV, int W>
-__global__ __launch_bounds__(64 * W) void seg_flat_kernel(Params P, FlatArgs F)
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(5))) void seg_flat_kernel(Params P, FlatArgs F)
 {
     using T = Tr<DT>;
     using A = typename T::acc;
@@ -1755,7 +1789,8 @@ __global__ __launch_bounds__(64 * W) void seg_flat_kernel(Params P, FlatArgs F)
     }
     const uint64_t pos = REV ? tiles - 1 - tile : tile;        // a reverse scan starts at the end of the range
     const uint64_t base = pos * kWgElems + (uint64_t)wave * kEPW;
-    const Run R = make_seg_run<DT>(P, lo, (uint64_t)(hi - lo), lead, base);
+    Run R = make_seg_run<DT>(P, lo, (uint64_t)(hi - lo), lead, base);
+    R.out_vec = ((uintptr_t)R.out & 15) == 0;                  // (also where the run begins in front of the arrays: nothing is stored there)
     // Everything below works in processing order: element i of a granule is its memory element mem(i); a reverse scan
     // mirrors the granules of the run (slot_offset), the elements inside a granule, the wavefronts and the tiles, and
     // restarts at row ENDS -- element j ends a row when a row starts at j + 1 (the offset behind the last row is
@@ -1770,7 +1805,7 @@ __global__ __launch_bounds__(64 * W) void seg_flat_kernel(Params P, FlatArgs F)
 #pragma unroll
         for (int t = 0; t < NT; ++t) g[t] = *(const u32x4 *)(R.in + ((uint32_t)t * 256u + 4u * lane) * 4u);
     } else {
-        load_run<DT, NT, REV, true>(R, lane, g);
+        load_range_end<DT, NT, REV>(R, lane, g);
     }
     marks.mark(lo - (long long)lead + (long long)(pos * kWgElems), F.expect, s_marks);
     const uint32_t *run_bits = s_marks.bits + kEPW / 32u * wave;
@@ -1880,7 +1915,7 @@ template <> __device__ __forceinline__ float narrow_elem<TCUSCAN_F16_F32>(const 
 }
 
 template <int DT, bool EXCL, bool REV, int W>
-__global__ __launch_bounds__(64 * W) void seg_flat_narrow_kernel(Params P, FlatArgs F)
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(7))) void seg_flat_narrow_kernel(Params P, FlatArgs F)
 {
     using T = Tr<DT>;
     using A = typename T::acc;
@@ -1919,7 +1954,8 @@ __global__ __launch_bounds__(64 * W) void seg_flat_narrow_kernel(Params P, FlatA
     }
     const uint64_t pos = REV ? tiles - 1 - tile : tile;        // a reverse scan starts at the end of the range
     const uint64_t base = pos * kWgElems + (uint64_t)wave * kEPW;
-    const Run R = make_seg_run<DT>(P, lo, (uint64_t)(hi - lo), lead, base);
+    Run R = make_seg_run<DT>(P, lo, (uint64_t)(hi - lo), lead, base);
+    R.out_vec = ((uintptr_t)R.out & 15) == 0;                  // (also where the run begins in front of the arrays: nothing is stored there)
     auto mem = [](int i) { return REV ? G - 1 - i : i; };      // processing order -> element of the granule (as in seg_flat_kernel)
     const bool whole_in = !REV && __builtin_amdgcn_readfirstlane((int)(R.in_vec && R.lead == 0u && R.rem >= kEPW)) != 0;
     const bool whole_out = __builtin_amdgcn_readfirstlane((int)(R.out_vec && R.lead == 0u && R.rem >= kEPW)) != 0;
@@ -1929,7 +1965,7 @@ __global__ __launch_bounds__(64 * W) void seg_flat_narrow_kernel(Params P, FlatA
 #pragma unroll
         for (int t = 0; t < NT; ++t) g[t] = *(const u32x4 *)(R.in + ((uint32_t)t * kTile + (uint32_t)G * lane) * T::kEsz);
     } else {
-        load_run<DT, NT, REV, true>(R, lane, g);
+        load_range_end<DT, NT, REV>(R, lane, g);
     }
     marks.mark(lo - (long long)lead + (long long)(pos * kWgElems), F.expect, s_marks);
     const uint32_t *run_bits = s_marks.bits + kEPW / 32u * wave;
@@ -2115,7 +2151,7 @@ __device__ __forceinline__ void seg_scan_and_store_cut_tile(int lane, const Run 
 }
 
 template <int DT, int NT, bool EXCL, bool REV, int W, bool SEARCH>
-__global__ __launch_bounds__(64 * W) void seg_stream_kernel(Params P, FlatArgs F)
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(!SEARCH ? 1 : DT == TCUSCAN_I8_I32 ? 5 : 4))) void seg_stream_kernel(Params P, FlatArgs F)
 {
     using T = Tr<DT>;
     using A = typename T::acc;
@@ -2155,7 +2191,8 @@ __global__ __launch_bounds__(64 * W) void seg_stream_kernel(Params P, FlatArgs F
     }
     const uint64_t pos = REV ? tiles - 1 - tile : tile;
     const uint64_t base = pos * kWgElems + (uint64_t)wave * kEPW;
-    const Run R = make_seg_run<DT>(P, lo, (uint64_t)(hi - lo), lead, base);
+    Run R = make_seg_run<DT>(P, lo, (uint64_t)(hi - lo), lead, base);
+    if constexpr (SEARCH) R.out_vec = ((uintptr_t)R.out & 15) == 0;       // (also where the run begins in front of the arrays)
     const bool inside = R.lead == 0u && R.rem >= kEPW;
     const bool whole_in = __builtin_amdgcn_readfirstlane((int)(R.in_vec && inside)) != 0;
     const bool whole_out = __builtin_amdgcn_readfirstlane((int)(R.out_vec && inside)) != 0;
@@ -2166,7 +2203,10 @@ __global__ __launch_bounds__(64 * W) void seg_stream_kernel(Params P, FlatArgs F
     } else if (whole_in) {
 #pragma unroll
         for (int t = 0; t < NT; ++t) g[t] = *(const u32x4 *)(R.in + slot_offset<DT, NT, REV>(t, lane) * T::kEsz);
+    } else if constexpr (SEARCH) {
+        load_range_end<DT, NT, REV>(R, lane, g);
     } else {
+        // (In the short rows' kernels its registers cost more than it gains: 2^26 i8 of mean length 200 54.8 -> 60 us.)
         load_run<DT, NT, REV, true>(R, lane, g);
     }
     __builtin_amdgcn_s_setprio(0);

@@ -131,13 +131,13 @@ def test_large_calls_round_as_rarely_as_results_held_back(mean, flags, kind):
 def run_shifted(x, kind, off, flags, ws, shift_in, shift_out, inplace=False):
     """run_segmented with arrays that start some elements into their allocations."""
     import torch
-    big = to_device(np.concatenate([x[:shift_in], x]), kind)
+    big = to_device(np.concatenate([np.zeros(shift_in, x.dtype), x]), kind)
     d_in = big[shift_in:]
     big_out = torch.full((x.size + shift_out,), GUARD, dtype=out_dtype(kind), device="cuda")
     d_out = d_in if inplace else big_out[shift_out:]
     tcuscan.segmented(d_in, d_out, torch.from_numpy(off).cuda(), off.size - 1, x.size, kind, flags=flags, ws=ws)
     torch.cuda.synchronize()
-    assert bool((big_out[:shift_out] == GUARD).all()) and (not inplace or torch.equal(big[:shift_in], to_device(x[:shift_in], kind)))
+    assert bool((big_out[:shift_out] == GUARD).all()) and bool((big[:shift_in] == 0).all())
     return d_out.cpu().numpy().copy(), tcuscan.workspace_fault(ws)
 
 
@@ -188,3 +188,37 @@ def test_few_long_rows_recorded_into_a_graph():
         torch.cuda.synchronize()
         check(x, "i8", off, d_out.cpu().numpy(), True, True)
     assert tcuscan.workspace_fault(ws) == 0
+
+
+@pytest.mark.parametrize("flags", range(4))
+@pytest.mark.parametrize("kind", ["i32", "f16", "i8", "f32", "bf16"])
+def test_ends_of_the_range(kind, flags):
+    """Ranges that begin and end at every element of a granule, in arrays that begin at every element of one (then the first run
+    begins in front of the array), down to arrays smaller than a granule; the small kernels."""
+    per = {"i8": 16, "f16": 8, "bf16": 8}.get(kind, 4)
+    x = (INT_GEN if kind in INT_GEN else RND_GEN)[kind](40_000, 3)
+    for n in (1, 2, per - 1, per, per + 1, 2 * per + 1, 64 * per - 1, 64 * per + 3, 2048 + per // 2, 8192, 8193, 8192 + 2048 + 1, 39_000 + per - 1):
+        for shift in {0, 1, per // 2, per - 1}:
+            for skip in {0, 1, per - 1, per, per + 1}:
+                off = offsets_from([n // 3, 0, n - n // 3 - n // 5, n // 5], start=skip)
+                y = x[:n + skip + (n + shift) % 3]
+                ws = tcuscan.new_segmented_workspace(off.size - 1, y.size, kind)
+                got, fault = run_shifted(y, kind, off, flags, ws, shift, (shift * 5 + skip) % 7)
+                assert fault == 0
+                check(y, kind, off, got, bool(flags & 1), bool(flags & 2))
+
+
+@pytest.mark.parametrize("flags", range(4))
+@pytest.mark.parametrize("kind", ["i32", "f16", "i8", "f32", "bf16"])
+def test_ends_of_a_large_range_of_long_rows(kind, flags):
+    per = {"i8": 16, "f16": 8, "bf16": 8}.get(kind, 4)
+    x = (INT_GEN if kind in INT_GEN else RND_GEN)[kind](LARGE + 70_000, 4)
+    for case, (n, shift_in, shift_out, skip) in enumerate([(LARGE, 0, 0, 0), (LARGE + 1, 1, 1, 0), (LARGE + 65_536 - 1, per - 1, per - 1, 1), (LARGE + per + 1, 1, 0, per + 2),
+                                                           (LARGE + 32_768 + 2, 8, 8, 3), (LARGE + 3, 0, 4, 0), (LARGE + 5, 4, 20, 31), (LARGE + 7, 24, 24, 2)]):
+        rows = (1, 3, 300, 2500)[case % 4]
+        off = offsets_from(spread(np.random.default_rng(case), rows, n), start=skip)
+        y = x[:n + skip + case % 3]
+        ws = tcuscan.new_segmented_workspace(rows, y.size, kind)
+        got, fault = run_shifted(y, kind, off, flags, ws, shift_in, shift_out)
+        assert fault == 0
+        check(y, kind, off, got, bool(flags & 1), bool(flags & 2))
