@@ -2820,7 +2820,9 @@ template <int DT> hipError_t launch_seg(Params P, bool excl, int cls, hipStream_
 constexpr int kFlatNT = 8, kFlatW = 4;
 constexpr size_t kFlatTile = (size_t)2048 * kFlatW;
 constexpr size_t kFlatCheckRows = 4096;      // offsets a workgroup checks at most (rows far shorter than a tile of them)
-// From here on the large kernel (3 x 2^22 f32 of mean length 16 / 200 / 1500: 28.6 / 23.3 / 23.2 -> 22.9 / 20.7 / 21.9).
+// From here on the large kernel: 1536 tiles of the small one for 32-bit inputs, six per compute unit, are what is resident at once (us,
+// small / large, inputs from HBM, f32 of mean length 16 / 200 / 1500 / 20,000: 10.5 million elements 24.2 / 24.2, 19.3 / 22.5, 19.7 / 24.1, 18.7 /
+// 19.8, 12 million 27.1 / 23.0, 21.8 / 20.8, 22.1 / 23.5, 20.8 / 20.7).
 constexpr size_t kSegStreamFrom = (size_t)3 << 22;
 // Where rows with tiles of their own would have large ones, the layout has fewer slots than the small kernels have tiles: up to here
 // their status words then lie closer together (us, tiles of their own / the large kernel / the small ones: 600,000 f32 in one row
@@ -2828,13 +2830,16 @@ constexpr size_t kSegStreamFrom = (size_t)3 << 22;
 // one row 12.6 / 11.7 / 10.6, from the end 12.6 / 12.0 / 12.8).  Beyond, one long chain of them loses to the large kernel: 6 x 2^20
 // f32 in 4 rows, from the end, 15.5 / 12.1 / 14.5, 7 x 2^20 i8 in 2 rows 17.5 / 10.6 / 12.4.
 constexpr size_t kFlatFewSlots = (size_t)1 << 22;
-// From 200 MB of input and output on, 32-bit inputs are read around the memory-side cache (2^26 f32 of mean length 16 115 -> 111,
-// 2^24 the other way round: 30 -> 35).
+// From 200 MB of input and output on, 32-bit inputs are read around the memory-side cache (2^26 f32 of mean length 16 115 -> 111; with
+// inputs from HBM 24 million of 400 43.0 -> 42.0, 16 million 27.7 -> 27.4, but with inputs that are in the cache 38.0 -> 40.9 and 26.0 -> 27.8).
 constexpr size_t kSegAroundCacheFrom = (size_t)25 << 20;
-// From here on 32-bit rows of 2^14 elements and more keep tiles of their own unless one window holds the offsets: a chain
-// over the whole range is longer than theirs and loses more than the launch in front costs (2^26 f32 in 3355 rows 108 / 100,
-// 2^27 in 2684 200 / 188; but 2^25 in 1677 53 / 57, and 2^26 in 223, without a search, 97 .. 104 / 108).
-constexpr size_t kOwnTilesFrom = (size_t)3 << 24;
+// From here on 32-bit rows keep tiles of their own where these take one launch in front (fewer than 4096 rows) or are long (2^14
+// elements), unless one window holds the offsets: a chain over the whole range is longer than theirs and loses more than the launch
+// costs (us, range / own tiles, inputs from HBM, f32 and i32: 33.5 million in rows of 16,500 54.9 / 56.8 and 52.4 / 57.9, 40 million 68.6 / 65.3 and
+// 67.1 / 66.2, 45 million 73.6 / 72.0 and 76.8 / 72.8, of 12,000 73.7 / 72.6 and 75.8 / 73.5; 50 million of 16,500 85.4 / 78.4 and 84.1 / 79.4, of 12,000, 4166
+// rows, 85.3 / 86.4; 2^26 in 3355 rows 108 / 100, 2^27 in 2684 200 / 188, and 2^26 in 223, without a search, 97 .. 104 / 108).  f32 rows
+// of 2^16 elements keep the range a little longer: 45 million in rows of 100,000 70.2 / 73.5, 52 million 85.5 / 82.7 (i32 76.1 / 73.3 and 85.7 / 83.0).
+template <int DT> constexpr size_t own_tiles_from(size_t mean) { return DT == TCUSCAN_F32_F32 && mean >= ((size_t)1 << 16) ? (size_t)3 << 24 : (size_t)9 << 22; }
 template <int DT> const void *seg_flat_kernel_for(bool excl, bool rev)
 {
     if constexpr (Tr<DT>::kEsz == 4) {
@@ -2880,7 +2885,8 @@ template <int DT> tcuscan_status_t run_segmented_range_dt(Params P, const long l
     const bool flat = total < kSegStreamFrom && (total / kFlatTile + 2 <= L.max_tiles || total <= kFlatFewSlots);
     const bool long_rows = total / rows >= (Tr<DT>::kEsz == 4 ? 2048 : 4096);
     const bool few_rows = rows < RunMarks<Short::kRun>::kWindow, first = !flat && !long_rows && !few_rows;     // (are first rows found beforehand?)
-    if (Tr<DT>::kEsz == 4 && total >= kOwnTilesFrom && !few_rows && total / rows >= ((size_t)1 << 14)) return TCUSCAN_ERR_UNSUPPORTED;
+    if (Tr<DT>::kEsz == 4 && total >= own_tiles_from<DT>(total / rows) && !few_rows && (total / rows >= ((size_t)1 << 14) || rows < kSegPrepRows))
+        return TCUSCAN_ERR_UNSUPPORTED;
     const size_t run = flat ? 2048 : long_rows ? Long::kRun : Short::kRun;
     const size_t tile = flat ? kFlatTile : long_rows ? Long::kTile : Short::kTile;
     const size_t tiles = total / tile + 2;                       // the range is at most `total` long and starts less than a granule late

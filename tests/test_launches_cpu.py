@@ -51,3 +51,14 @@ def test_few_long_rows_of_a_small_call_have_small_tiles(run, kind):
         assert launched[0].stride == 3 or (16 * tiles << launched[0].stride) > 64 * slots
         strides.add(launched[0].stride)
     assert len(strides) >= 2
+
+
+def test_which_rows_of_large_calls_keep_tiles_of_their_own(run):
+    """32-bit rows, 256 to 4095 of them or long ones, from 9 x 2^22 elements on (f32 rows of 2^16 and more: 3 x 2^24)."""
+    M = 1 << 20
+    shapes = [("i32", 36 * M, 36 * M // 12_000, True), ("i32", 36 * M - 1, 36 * M // 12_000, False), ("f32", 36 * M, 36 * M // 12_000, True), ("i32", 64 * M, 4096, True),
+              ("i32", 64 * M - 4096, 4096, False), ("i32", 60 * M, 4096, False), ("f32", 60 * M, 4095, True), ("f32", 128 * M, 8192, True), ("f32", 40 * M, 255, False),
+              ("i32", 40 * M, 256, True), ("f32", 40 * M, 256, False), ("f32", 40 * M, 641, True), ("f32", 48 * M, 256, True), ("bf16", 128 * M, 2000, False), ("i8", 128 * M, 2000, False)]
+    for (kind, total, rows, own), (rc, launched) in zip(shapes, run([segmented(kind, total, rows) for kind, total, rows, _ in shapes])):
+        last = launched[-1].kernel
+        assert rc == 0 and last.startswith("scan_kernel<" if own else "seg_stream_kernel<"), (kind, total, rows, launched)
