@@ -9,8 +9,8 @@
 // (the published scheme of least-significant-digit passes with a decoupled look-back per digit: Merrill and Garland 2016,
 // Adinets and Merrill, "Onesweep", 2022).  A full sort is four passes of 8 bytes per key (16 with payloads) and one reading of the keys for the first term.
 //
-// Sorts of up to 6.2 million keys on more than 16 bits do with one pass on the top eight bits if the 256 buckets then fit a
-// workgroup each, which sorts its bucket by the other bits in LDS: whether they do is seen on the device, and where they do not,
+// Sorts of up to 6,055,225 keys on more than 16 bits do with one pass on the top eight bits if the 256 buckets then are small
+// enough for a workgroup each, which sorts its bucket by the other bits in LDS: whether they do is seen on the device, and where they do not,
 // that first pass is the least significant one and the others follow (random keys, us before / now: 100,000 36.6 / 26, 10^6
 // 62.2 / 40, with payloads 76.4 / 49, 2^22 104 / 70, with payloads 125 / 90; keys that do not split, 10^6 equal ones 56 / 59, normally
 // distributed floats 62 / 64, 2^22 104 / 99).  Up to kBlockSortFew keys one workgroup does everything: one launch, keys and payloads
@@ -276,10 +276,11 @@ struct PassArgs {
     Digit digit;
     bool stream;                          // the arrays do not fit the memory-side cache: keys are read around it
     // Sorts that may take one pass and buckets (null otherwise).  First pass: the counts of the top digit, which is taken if no
-    // bucket has more than kBlockCapacity keys; later passes have nothing to do then.
+    // bucket has more than bucket_max keys; later passes have nothing to do then.
     const uint32_t *top_hist;
     Buckets *buckets;
     Digit top;
+    uint32_t bucket_max;
 };
 
 enum PassRole { kPlainPass, kChoosingPass, kLaterPass };
@@ -391,9 +392,9 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(sizeof(W
     ((CounterQuad *)s_cnt[wave])[lane] = 0u;
     const uint32_t *hist = A.hist;
     if constexpr (ROLE == kChoosingPass) {
-        // every wavefront looks at the counts: does the largest bucket fit a workgroup?
+        // every wavefront looks at the counts: is the largest bucket small enough?
         const u32x4 c = sum_of_tables((const u32x4 *)A.top_hist + lane, A.tables);
-        const bool fits = c[0] <= (uint32_t)kBlockCapacity && c[1] <= (uint32_t)kBlockCapacity && c[2] <= (uint32_t)kBlockCapacity && c[3] <= (uint32_t)kBlockCapacity;
+        const bool fits = c[0] <= A.bucket_max && c[1] <= A.bucket_max && c[2] <= A.bucket_max && c[3] <= A.bucket_max;
         const bool split = __ballot(!fits) == 0ull;
         // keys that one workgroup can sort, most of them in one bucket: without the detour
         const uint32_t half = (uint32_t)A.n / 2u;
@@ -608,11 +609,11 @@ hipError_t launch_block_sort(const BlockArgs &args_in, unsigned grid, hipStream_
     const void *fn = B.vals ? (const void *)block_sort_kernel<true> : (const void *)block_sort_kernel<false>;
     return hipLaunchKernel(fn, dim3(grid), dim3(64 * kBlockWaves), args, 0, s);
 }
-// May random keys be expected to have buckets (of 256) that fit a workgroup each: mean and six standard deviations?
+// May random keys be expected to have buckets (of 256) that are small enough: mean and six standard deviations?  (Up to 6,055,225 keys.)
 bool buckets_fit(size_t n)
 {
     const double mean = (double)n / kDigits;
-    return mean + 6.0 * __builtin_sqrt(mean) <= (double)kBlockCapacity;
+    return mean + 6.0 * __builtin_sqrt(mean) <= (double)bucket_limit(n, (uint32_t)kBlockCapacity);
 }
 
 // Keys per lane of a pass.  Few keys: many small tiles, so that all compute units have one and each is done sooner;
@@ -715,6 +716,7 @@ tcuscan_status_t tcuscan_internal_digit_sort(void *d_keys, void *d_vals, size_t 
         A.fault = (uint32_t *)d_fault;
         A.n = n; A.spin_limit = spin_limit; A.mute_tile = mute_tile; A.digit = P.digit[p]; A.stream = around_cache;
         A.top_hist = hist + (surely ? 0 : kDigits * (P.count - 1)); A.buckets = buckets; A.top = P.digit[P.count - 1];
+        A.bucket_max = surely ? (uint32_t)kBlockCapacity : bucket_limit(n, (uint32_t)kBlockCapacity);
         void *args[] = {&A};
         const bool v = d_vals != nullptr;
         // (passes that seldom have anything to do are cheaper with fewer, larger tiles)

@@ -8,5 +8,6 @@ unsigned long long shim_place32(unsigned long long before, unsigned start, unsig
 unsigned long long shim_place64(unsigned long long before, unsigned start, unsigned i) { return digit_place(digit_base<uint64_t>(before, start), i); }
 int shim_fits32(unsigned long long before, unsigned count, unsigned n) { return digit_range_fits<uint32_t>((uint32_t)before, count, n) ? 1 : 0; }
 int shim_fits64(unsigned long long before, unsigned count, unsigned n) { return digit_range_fits<uint64_t>(before, count, n) ? 1 : 0; }
+unsigned shim_bucket_limit(unsigned long long n, unsigned capacity) { return bucket_limit(n, capacity); }
 
 }

@@ -21,6 +21,7 @@ def shim(tmp_path_factory):
     L = ctypes.CDLL(so)
     for f in (L.shim_place32, L.shim_place64, L.shim_fits32, L.shim_fits64):
         f.argtypes = [ctypes.c_ulonglong, ctypes.c_uint, ctypes.c_uint]
+    L.shim_bucket_limit.argtypes, L.shim_bucket_limit.restype = [ctypes.c_ulonglong, ctypes.c_uint], ctypes.c_uint
     L.shim_place32.restype = L.shim_place64.restype = ctypes.c_ulonglong
     return L
 
@@ -42,3 +43,17 @@ def test_every_range_the_guard_lets_through_goes_to_its_own_bytes(shim, width, n
                         assert place(before, start, i) == 4 * (before + i - start) <= 4 * (n - 1), (before, start, i)
                         stored += 1
     assert stored > 30
+
+
+def test_buckets_that_a_workgroup_sorts_while_passes_would_sort_all_keys(shim):
+    """The limit on a bucket's keys: never more than fit, never so many that the passes were faster where both were measured, and
+    enough for the buckets of random keys (mean and six standard deviations) up to 6,055,225 keys."""
+    fit = 24576
+    for n, slower in [(20_000, 9000), (33_000, 9000), (70_000, 9000), (131_072, 12_000), (262_144, 14_000), (400_000, 16_384), (600_000, 16_384), (1_000_000, 24_000)]:
+        assert shim.shim_bucket_limit(n, fit) < slower
+    last = 0
+    for n in sorted([*range(16_385, 7_000_000, 4099), 6_055_225, 6_055_226]):
+        limit = shim.shim_bucket_limit(n, fit)
+        assert last <= limit <= fit
+        assert (n / 256 + 6 * (n / 256) ** 0.5 <= limit) == (n <= 6_055_225), n
+        last = limit

@@ -40,6 +40,18 @@ def test_keys_that_split_unevenly(name, n):
     check(keys_of(name, n).astype(np.uint32), True, 32)
 
 
+@pytest.mark.parametrize("n", [16_385, 20_000, 131_073, 600_000, 1_500_000, 6_055_225, 6_055_226])
+@pytest.mark.parametrize("over", [0, 1])
+def test_a_bucket_at_the_limit(n, over):
+    """The largest bucket that a workgroup sorts, and a key more, which takes the passes; both sides of the largest sort with buckets."""
+    limit = min(24_576, 6144 + n // 80)
+    r = inputs.int32_full(n, n + over).view(np.uint32)
+    keys = r % np.uint32(255 << 24) + np.uint32(1 << 24)
+    keys[np.random.default_rng(n).permutation(n)[:limit + over]] &= np.uint32(0xFFFFFF)
+    assert np.count_nonzero(keys < 1 << 24) == limit + over
+    check(keys, True, 32)
+
+
 @pytest.mark.parametrize("bits", [32, 20])
 def test_buckets_of_every_size_a_workgroup_has_code_for(bits):
     """Bucket b of the top digit holds 0, 1, 63, 64, 65 or about b * 96 keys: all row counts, each with part of a row."""
