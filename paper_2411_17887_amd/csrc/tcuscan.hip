@@ -771,6 +771,11 @@ __host__ __device__ __forceinline__ uint32_t row_lead(uintptr_t in_addr, uintptr
     }
     return (uint32_t)((in_addr + (uint64_t)off * esz) & 15u) / esz;
 }
+// The same for a range of rows, whose first run may begin in front of the arrays.
+__host__ __device__ __forceinline__ uint32_t range_lead(uintptr_t in_addr, uintptr_t out_addr, uint32_t esz, long long off, bool line)
+{
+    return line ? (uint32_t)((out_addr + 4u * (uint64_t)off) & 127u) / 4u : row_lead(in_addr, out_addr, esz, off, false);
+}
 // LINES false: where rows are never tiled from lines, without the code for it (in the kernel of rows of one MFMA tile it
 // cost 2 %: 2,927,933 x 65 i8 1016 us, 993 without; 397,664 x 76 bf16 114.9, 113.0).
 template <int DT, bool LINES = true>
@@ -1632,7 +1637,7 @@ __global__ __launch_bounds__(256) void seg_first_rows_kernel(Params P, const lon
     long long begin = offsets[0], end = offsets[P.rows];       // as the scan kernel takes them
     begin = begin < 0 ? 0 : (begin > total ? total : begin);
     end = end < begin ? begin : (end > total ? total : end);
-    begin -= (long long)row_lead((uintptr_t)P.in, (uintptr_t)P.out, esz, begin, false);
+    begin -= (long long)range_lead((uintptr_t)P.in, (uintptr_t)P.out, esz, begin, P.line != 0u);
     // runs, rounded up to whole tiles: a reverse scan counts tiles, and the runs of a tile, from the end
     const uint32_t tiles = (uint32_t)((uint64_t)(end - begin + TILE * W - 1) / (TILE * W)) * W;
     if (r < P.num_tiles) *((uint64_t *)(P.ws + 1) + r * kStatusStride) = 0ull;
@@ -1750,9 +1755,10 @@ __device__ __forceinline__ A seg_open_sum_before_run(const Params &P, uint32_t t
     return before_head ? before : acc_add(prefix, before);
 }
 
-// (Waves per SIMD: what the kernels had without load_range_end, for which the register allocator else takes 230 registers.)
+// (Waves per SIMD: with load_range_end the register allocator else takes 230 registers.  Six, so that the tiles of calls up to
+// kSegStreamFrom are resident together: 12,582,911 f32 of mean length 200 26.7 -> 18.9 us, of 20,000 from the end 26.3 -> 19.2.)
 template <int DT, int NT, bool EXCL, bool REV, int W>
-__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(5))) void seg_flat_kernel(Params P, FlatArgs F)
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(6))) void seg_flat_kernel(Params P, FlatArgs F)
 {
     using T = Tr<DT>;
     using A = typename T::acc;
@@ -1780,7 +1786,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(5))) voi
     const long long total = (long long)P.cols;
     lo = lo < 0 ? 0 : (lo > total ? total : lo);
     hi = hi < lo ? lo : (hi > total ? total : hi);
-    const uint32_t lead = seg_lead<DT, false>(P, lo);
+    const uint32_t lead = range_lead((uintptr_t)P.in, (uintptr_t)P.out, T::kEsz, lo, P.line != 0u);
     const uint64_t vlen = (uint64_t)(hi - lo) + lead;
     const uint64_t tiles = (vlen + kWgElems - 1) / kWgElems;
     if (tile >= tiles) {                                       // the grid is an upper bound
@@ -1945,7 +1951,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(7))) voi
     const long long total = (long long)P.cols;
     lo = lo < 0 ? 0 : (lo > total ? total : lo);
     hi = hi < lo ? lo : (hi > total ? total : hi);
-    const uint32_t lead = seg_lead<DT, false>(P, lo);
+    const uint32_t lead = range_lead((uintptr_t)P.in, (uintptr_t)P.out, T::kEsz, lo, P.line != 0u);
     const uint64_t vlen = (uint64_t)(hi - lo) + lead;
     const uint64_t tiles = (vlen + kWgElems - 1) / kWgElems;
     if (tile >= tiles) {                                       // the grid is an upper bound
@@ -2182,7 +2188,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(!SEARCH 
     const long long total = (long long)P.cols;
     lo = lo < 0 ? 0 : (lo > total ? total : lo);
     hi = hi < lo ? lo : (hi > total ? total : hi);
-    const uint32_t lead = seg_lead<DT, false>(P, lo);
+    const uint32_t lead = range_lead((uintptr_t)P.in, (uintptr_t)P.out, T::kEsz, lo, P.line != 0u);
     const uint64_t vlen = (uint64_t)(hi - lo) + lead;
     const uint64_t tiles = (vlen + kWgElems - 1) / kWgElems;
     if (tile >= tiles) {                                       // the grid is an upper bound
@@ -2821,8 +2827,9 @@ constexpr int kFlatNT = 8, kFlatW = 4;
 constexpr size_t kFlatTile = (size_t)2048 * kFlatW;
 constexpr size_t kFlatCheckRows = 4096;      // offsets a workgroup checks at most (rows far shorter than a tile of them)
 // From here on the large kernel: 1536 tiles of the small one for 32-bit inputs, six per compute unit, are what is resident at once (us,
-// small / large, inputs from HBM, f32 of mean length 16 / 200 / 1500 / 20,000: 10.5 million elements 24.2 / 24.2, 19.3 / 22.5, 19.7 / 24.1, 18.7 /
-// 19.8, 12 million 27.1 / 23.0, 21.8 / 20.8, 22.1 / 23.5, 20.8 / 20.7).
+// small / large, inputs from HBM, f32 of mean length 16 / 200 / 1500 / 20,000: 12,582,911 elements 23.9 / 26.7, 18.9 / 23.8, 18.7 / 26.1, 18.9 / 20.1, 14
+// million 29.8 / 29.0, 22.7 / 27.0, 22.6 / 28.1, 23.2 / 21.3; of 16 / 200 / 20,000 12,582,911 bf16 20.9 / 22.0, 16.0 / 19.4, 16.1 / 16.4, i8 19.8 / 19.0,
+// 14.3 / 17.7, 14.8 / 14.5).
 constexpr size_t kSegStreamFrom = (size_t)3 << 22;
 // Where rows with tiles of their own would have large ones, the layout has fewer slots than the small kernels have tiles: up to here
 // their status words then lie closer together (us, tiles of their own / the large kernel / the small ones: 600,000 f32 in one row
@@ -2889,7 +2896,7 @@ template <int DT> tcuscan_status_t run_segmented_range_dt(Params P, const long l
         return TCUSCAN_ERR_UNSUPPORTED;
     const size_t run = flat ? 2048 : long_rows ? Long::kRun : Short::kRun;
     const size_t tile = flat ? kFlatTile : long_rows ? Long::kTile : Short::kTile;
-    const size_t tiles = total / tile + 2;                       // the range is at most `total` long and starts less than a granule late
+    const size_t tiles = total / tile + 2;                       // the range is at most `total` long and starts less than a line late
     uint32_t stride = kStatusStrideLog2;                         // until the status words fit the layout's slots
     while (flat && stride > 0 && (tiles << stride) > kStatusStride * L.max_tiles) --stride;
     const size_t slots = ((tiles << stride) + kStatusStride - 1) / kStatusStride;
@@ -2927,6 +2934,10 @@ tcuscan_status_t run_segmented_range(const void *d_in, void *d_out, const long l
     P.tiles_per_row = 0; P.num_tiles = 0;
     P.ws = (WsHeader *)d_ws;
     P.reverse = reverse ? 1u : 0u; P.tile_desc = nullptr;
+    // From the output's line where that is possible, like rows with tiles of their own (us, from the 16-byte boundary / from the line,
+    // inputs from HBM, both arrays 8 elements into their allocations: 60 million bf16 in rows of 20,000 77.2 / 69.1, of 200 78.9 / 72.4, 33.5 million of
+    // 600,000 42.3 / 35.1, 60 million f32 of 200 98.8 / 92.8, of 600,000 from the end 103.3 / 92.5, 9 million 20.3 / 18.8).
+    P.line = total >= kLinesFrom && ((uintptr_t)d_out & 127) != 0 && line_compatible((uintptr_t)d_in, (uintptr_t)d_out, in_size(dt)) ? kFromLine : 0u;
     const bool ex = exclusive != 0;
     switch (dt) {
     case TCUSCAN_I32_I32:  return run_segmented_range_dt<TCUSCAN_I32_I32>(P, d_offsets, rows, total, ex, d_ws, L, s);
