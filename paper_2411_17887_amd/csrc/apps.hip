@@ -129,8 +129,7 @@ tcuscan_status_t tcuscan_split_radix_sort_u32(void *d_keys, void *d_vals, size_t
     if (form == 1) {
         const size_t need = chain_layout::bytes_for(n, d_vals && bits >= 2 ? chain_layout::kFlagTile / 2 : chain_layout::kFlagTile);
         if (need && (!d_ws || ws_bytes < need || ((uintptr_t)d_ws % 8) != 0)) return TCUSCAN_ERR_WORKSPACE;
-        return tcuscan_internal_digit_sort(d_keys, d_vals, n, bits, d_keys_tmp, d_vals_tmp, d_positions,
-                                             need || (d_ws && ws_bytes >= chain_layout::kHeaderBytes && ((uintptr_t)d_ws % 8) == 0) ? d_ws : nullptr, stream);
+        return tcuscan_internal_digit_sort(d_keys, d_vals, n, bits, d_keys_tmp, d_vals_tmp, d_positions, need ? d_ws : nullptr, stream);
     }
     // Form 2, one bit per pass: the mask and the positions are never written; the split kernel builds the flags from the
     // keys, scans them and scatters in one go.  How many keys have a zero at each bit does not change when the keys are

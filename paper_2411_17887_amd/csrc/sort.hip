@@ -9,7 +9,7 @@
 // (the published scheme of least-significant-digit passes with a decoupled look-back per digit: Merrill and Garland 2016,
 // Adinets and Merrill, "Onesweep", 2022).  A full sort is four passes of 8 bytes per key (16 with payloads) and one reading of the keys for the first term.
 //
-// Sorts of up to 6,055,225 keys on more than 16 bits do with one pass on the top eight bits if the 256 buckets then are small
+// Sorts of up to 6,055,225 keys on more than 16 bits (up to 16384 keys on more than 8) do with one pass on the top eight bits if the 256 buckets then are small
 // enough for a workgroup each, which sorts its bucket by the other bits in LDS: whether they do is seen on the device, and where they do not,
 // that first pass is the least significant one and the others follow (random keys, us before / now: 100,000 36.6 / 26, 10^6
 // 62.2 / 40, with payloads 76.4 / 49, 2^22 104 / 70, with payloads 125 / 90; keys that do not split, 10^6 equal ones 56 / 59, normally
@@ -259,7 +259,7 @@ constexpr size_t kBlockCapacity = (size_t)64 * kBlockWaves * kBlockItems;      /
 constexpr size_t kBlockSortMax = 16384;                                         // keys of a sort that one workgroup does, if it must
 
 // What the first pass finds out: have the keys gone into buckets by their top digit, and where does each begin.
-enum : uint32_t { kNotSplit = 0u, kSplit = 1u, kAllInOne = 2u };       // kAllInOne: nothing done, the first workgroup sorts all keys
+enum : uint32_t { kNotSplit = 0u, kSplit = 1u };
 struct Buckets { uint32_t split; uint32_t start[kDigits]; };
 
 struct PassArgs {
@@ -396,11 +396,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(sizeof(W
         const u32x4 c = sum_of_tables((const u32x4 *)A.top_hist + lane, A.tables);
         const bool fits = c[0] <= A.bucket_max && c[1] <= A.bucket_max && c[2] <= A.bucket_max && c[3] <= A.bucket_max;
         const bool split = __ballot(!fits) == 0ull;
-        // keys that one workgroup can sort, most of them in one bucket: without the detour
-        const uint32_t half = (uint32_t)A.n / 2u;
-        const bool one = A.n <= kBlockSortMax && __ballot(c[0] > half || c[1] > half || c[2] > half || c[3] > half) != 0ull;
-        if (tile == 0u && tid == 0) A.buckets->split = one ? kAllInOne : split ? kSplit : kNotSplit;
-        if (one) return;
+        if (tile == 0u && tid == 0) A.buckets->split = split ? kSplit : kNotSplit;
         if (split) { g = A.top; hist = A.top_hist; }
     }
     wavefront_sync();
@@ -487,10 +483,116 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(sizeof(W
     }
 }
 
+// ------------------------------------------------------------------------- the pass in front of a small sort's buckets
+//
+// Up to kBlockSortMax keys are four tiles at most: every workgroup counts the top digit of the others' keys itself, in place of a
+// launch in front and a carry chain.  Every bucket fits a workgroup, so there is nothing to choose.  (us, one workgroup / a
+// counting launch, a pass and buckets / this and buckets: 9000 random keys 25 / 17.0 / 14.0, 16,000 32 / 17.2 / 14.7, pairs 39 / 20.7 / 17.8; 12,000 and 16,000
+// keys below 2^24, all in one bucket, 25.5 / 28.9 / 26.1 and 31.6 / 34.5 / 31.0, half of them 25.9 / 29.8 / 21.0 and 31.9 / 35.4 / 25.0.)
+
+struct SpreadArgs {
+    const uint32_t *keys, *vals;
+    uint32_t *keys_out, *vals_out;
+    Buckets *buckets;
+    uint32_t n;
+    Digit top;
+};
+constexpr int kSpreadWaves = 16, kSpreadItems = 4;
+constexpr uint32_t kSpreadTile = 64 * kSpreadWaves * kSpreadItems, kSpreadTiles = (uint32_t)(kBlockSortMax / kSpreadTile);
+static_assert(kSpreadTiles * kSpreadTile == kBlockSortMax, "tiles of a small sort");
+
+template <bool VALS>
+__global__ __launch_bounds__(64 * kSpreadWaves) void spread_kernel(SpreadArgs A)
+{
+    constexpr int W = kSpreadWaves, ITEMS = kSpreadItems, kThreads = 64 * W;
+    __shared__ uint32_t s_order[kSpreadTile];
+    __shared__ __attribute__((aligned(16))) uint16_t s_cnt[W][kDigits];
+    static_assert(__alignof__(s_cnt) >= alignof(CounterQuad), "cleared four counters at a time");
+    __shared__ uint32_t s_other[2][kDigits];               // digit counts of the tiles in front and behind
+    __shared__ uint32_t s_dest[kDigits];
+    __shared__ uint32_t s_part[4];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t tile = blockIdx.x, first = (uint32_t)wave * 64u * ITEMS + (uint32_t)lane;
+    auto keys_of = [&](uint32_t t) { const uint32_t at = t * kSpreadTile; return at >= A.n ? 0u : A.n - at < kSpreadTile ? A.n - at : kSpreadTile; };
+    const uint32_t base = tile * kSpreadTile, valid = keys_of(tile);
+    uint32_t key[ITEMS], at[ITEMS], other[kSpreadTiles - 1][ITEMS];
+    load_rows<ITEMS>(A.keys + base, first, valid, valid == kSpreadTile, false, ~0u, key);
+#pragma unroll
+    for (uint32_t q = 0; q < kSpreadTiles - 1; ++q) {
+        const uint32_t t = q + (q >= tile ? 1u : 0u), left = keys_of(t);
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) other[q][r] = first + 64u * r < left ? A.keys[t * kSpreadTile + first + 64u * r] : 0u;
+    }
+    ((CounterQuad *)s_cnt[wave])[lane] = 0u;
+    if (tid < 2 * kDigits) s_other[tid / kDigits][tid % kDigits] = 0u;
+    __syncthreads();
+    rank_rows<ITEMS>(key, A.top, s_cnt[wave], at);
+#pragma unroll
+    for (uint32_t q = 0; q < kSpreadTiles - 1; ++q) {
+        const uint32_t left = keys_of(q + (q >= tile ? 1u : 0u));
+        uint32_t *counts = s_other[q >= tile ? 1 : 0];
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) {
+            // (lanes that agree with the first one are added at once: lanes that add to one word go one after the other)
+            const bool in = first + 64u * r < left;
+            const uint32_t d = digit_of(other[q][r], A.top), d0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)d);
+            const uint64_t as_first = __ballot(in && d == d0);
+            if (lane == 0 && in) atomicAdd(&counts[d0], (uint32_t)__builtin_popcountll(as_first));
+            if (in && d != d0) atomicAdd(&counts[d], 1u);
+        }
+    }
+    __syncthreads();
+    uint32_t count, start;
+    scan_counters<W, kUnit<ITEMS, W>>(s_cnt, s_part, count, start, [](uint32_t) {});
+    put_in_order<ITEMS, kUnit<ITEMS, W>>(key, A.top, s_cnt[wave], s_order, at);
+    uint32_t val[VALS ? ITEMS : 1];
+    if constexpr (VALS) load_rows<ITEMS>(A.vals + base, first, valid, valid == kSpreadTile, false, 0u, val);
+
+    // ---- where the digits begin in the whole array, and this tile's part of each
+    uint32_t all = 0u, inc = 0u;
+    if (tid < kDigits) {
+        // (the keys past the end of the last tile count as the highest digit)
+        all = s_other[0][tid] + s_other[1][tid] + count - (tid == (1 << A.top.width) - 1 ? kSpreadTile - valid : 0u);
+        inc = wave_inclusive_scan(all);
+        if (lane == 63) s_part[wave] = inc;
+    }
+    __syncthreads();
+    if (tid < kDigits) {
+        uint32_t begin = inc - all;
+        for (int w = 0; w < wave; ++w) begin += s_part[w];
+        if (tile == 0u) A.buckets->start[tid] = begin;
+        s_dest[tid] = digit_base<uint32_t>(begin + s_other[0][tid], start);
+    }
+    if (tile == 0u && tid == 0) A.buckets->split = kSplit;
+    __syncthreads();
+
+    uint32_t dst[ITEMS];
+    char *kout = (char *)A.keys_out, *vout = (char *)A.vals_out;
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+        const uint32_t i = (uint32_t)tid + (uint32_t)r * kThreads, k = s_order[i];
+        dst[r] = digit_place(s_dest[digit_of(k, A.top)], i);
+        if (i < valid) *(uint32_t *)(kout + dst[r]) = k;
+    }
+    if constexpr (VALS) {
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) *(uint32_t *)((char *)s_order + at[r]) = val[r];
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) {
+            const uint32_t i = (uint32_t)tid + (uint32_t)r * kThreads;
+            if (i < valid) *(uint32_t *)(vout + dst[r]) = s_order[i];
+        }
+    }
+}
+
 // ------------------------------------------------------------------------- a sort in one workgroup
 //
 // A whole sort of few keys, or a bucket of the keys that a first pass on the top digit has split.  What bounds it is the ranking's
-// instructions, so the rows per lane are counted out (kLaneCounts) -- each with code of its own: counted out by a loop, the
+// instructions, so the rows per lane are counted out (sort_in_block_of) -- each with code of its own: counted out by a loop, the
 // instructions of neighbouring rows lose their place between each other (12,000 keys 26 -> 30 us).
 
 struct BlockArgs {
@@ -498,7 +600,7 @@ struct BlockArgs {
     uint32_t *keys_out, *vals_out;        // (may be where the keys come from: a workgroup reads all of its own first)
     const Buckets *buckets;               // null: one workgroup sorts all keys; else workgroup b those of bucket b, if there are buckets
     uint32_t n;                           // keys in all
-    Passes P[2];                          // a bucket's digits, all digits
+    Passes P;                             // a bucket's digits, or all
 };
 struct BlockLds {
     uint32_t order[kBlockCapacity];
@@ -509,14 +611,14 @@ struct BlockLds {
 static_assert(sizeof(BlockLds) <= 160 * 1024, "LDS of a compute unit");
 
 template <int ITEMS, bool VALS>
-__device__ __forceinline__ void sort_in_block(const BlockArgs &B, bool all, uint32_t begin, uint32_t n, BlockLds &s)
+__device__ __forceinline__ void sort_in_block(const BlockArgs &B, uint32_t begin, uint32_t n, BlockLds &s)
 {
     constexpr int W = kBlockWaves;
     constexpr uint32_t kU = kUnit<ITEMS, W>;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const uint32_t first = (uint32_t)wave * 64u * ITEMS + (uint32_t)lane;
-    const uint32_t *keys = (all ? B.keys_out : B.keys) + begin, *vals = VALS ? (all ? B.vals_out : B.vals) + begin : nullptr;
+    const uint32_t *keys = B.keys + begin, *vals = VALS ? B.vals + begin : nullptr;
     uint32_t key[ITEMS], val[VALS ? ITEMS : 1], at[ITEMS];
 #pragma unroll
     for (int r = 0; r < ITEMS; ++r) {
@@ -525,8 +627,8 @@ __device__ __forceinline__ void sort_in_block(const BlockArgs &B, bool all, uint
         if constexpr (VALS) val[r] = i < n ? vals[i] : 0u;
     }
     for (int i = lane; i < kDigits; i += 64) s.masks[wave][i] = 0ull;
-    for (int p = 0; p < B.P[all].count; ++p) {
-        const Digit g = B.P[all].digit[p];
+    for (int p = 0; p < B.P.count; ++p) {
+        const Digit g = B.P.digit[p];
         ((CounterQuad *)s.cnt[wave])[lane] = 0u;
         wavefront_sync();
         rank_rows<ITEMS, (ITEMS <= 20)>(key, g, s.cnt[wave], at, s.masks[wave], (int)n - (int)first);       // (24 rows with payloads: registers)
@@ -562,13 +664,13 @@ __device__ __forceinline__ void sort_in_block(const BlockArgs &B, bool all, uint
 }
 // 1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 16, 18, 20 or 24 rows per lane.
 template <bool VALS, int ITEMS = 1>
-__device__ __forceinline__ void sort_in_block_of(const BlockArgs &B, bool all, uint32_t begin, uint32_t n, BlockLds &s)
+__device__ __forceinline__ void sort_in_block_of(const BlockArgs &B, uint32_t begin, uint32_t n, BlockLds &s)
 {
     if constexpr (ITEMS >= kBlockItems) {
-        sort_in_block<kBlockItems, VALS>(B, all, begin, n, s);
+        sort_in_block<kBlockItems, VALS>(B, begin, n, s);
     } else {
-        if (n <= 64u * kBlockWaves * ITEMS) sort_in_block<ITEMS, VALS>(B, all, begin, n, s);
-        else sort_in_block_of<VALS, ITEMS < 8 ? ITEMS + 1 : ITEMS < 20 ? ITEMS + 2 : ITEMS + 4>(B, all, begin, n, s);
+        if (n <= 64u * kBlockWaves * ITEMS) sort_in_block<ITEMS, VALS>(B, begin, n, s);
+        else sort_in_block_of<VALS, ITEMS < 8 ? ITEMS + 1 : ITEMS < 20 ? ITEMS + 2 : ITEMS + 4>(B, begin, n, s);
     }
 }
 
@@ -578,28 +680,22 @@ __global__ __launch_bounds__(64 * kBlockWaves) void block_sort_kernel(BlockArgs 
     __shared__ BlockLds s;
     static_assert(alignof(BlockLds) >= alignof(CounterQuad), "counters cleared four at a time");
     uint32_t begin = 0u, n = B.n;
-    bool all = true;                                       // all keys, which are where the sorted ones go
     if (B.buckets) {
-        const uint32_t split = B.buckets->split;
-        if (split == kNotSplit || (split == kAllInOne && blockIdx.x != 0u)) return;
-        all = split == kAllInOne;
-        if (!all) {
-            begin = B.buckets->start[blockIdx.x];
-            const uint32_t end = blockIdx.x + 1u < kDigits ? B.buckets->start[blockIdx.x + 1u] : B.n;
-            n = end > begin && end <= B.n ? end - begin : 0u;
-        }
+        if (B.buckets->split == kNotSplit) return;
+        begin = B.buckets->start[blockIdx.x];
+        const uint32_t end = blockIdx.x + 1u < kDigits ? B.buckets->start[blockIdx.x + 1u] : B.n;
+        n = end > begin && end <= B.n ? end - begin : 0u;
         n = n < (uint32_t)kBlockCapacity ? n : (uint32_t)kBlockCapacity;
     }
     n = (uint32_t)__builtin_amdgcn_readfirstlane((int)n);
-    if (n != 0u) sort_in_block_of<VALS>(B, all, begin, n, s);
+    if (n != 0u) sort_in_block_of<VALS>(B, begin, n, s);
 }
 
 // ------------------------------------------------------------------------- host side
 
-// us per sort of random keys, one workgroup / a pass and buckets (three launches): 7000 keys 16.6 / 17, 9000 22 / 17.4, 16,000 29 /
-// 17.4, 16,000 pairs 36 / 18.7.  Below kBlockSortMax every bucket fits, and most keys in one bucket (kAllInOne) cost the two launches
-// in front: 16,000 equal keys 30 -> 32.
-constexpr size_t kBlockSortFew = 7168;
+// Up to here one workgroup does everything (us per sort, one workgroup / a pass and buckets: 7169 random keys 18.0 / 14.0, but equal ones 16.5 /
+// 19.9).
+constexpr size_t kBlockSortFew = 8192;
 // Up to here the counting kernel has eight workgroups and no launch that clears tables in front (a quarter where it also copies).
 constexpr size_t kOwnTables = (size_t)1 << 17;
 hipError_t launch_block_sort(const BlockArgs &args_in, unsigned grid, hipStream_t s)
@@ -650,7 +746,7 @@ void split_digits(int bits, Passes &P)
 }  // namespace
 
 // Used by tcuscan_split_radix_sort_u32 (apps.hip), which has checked the arguments.  d_scratch: n words (4-byte aligned);
-// d_fault: the workspace's fault word (null where the call needs no workspace, which one workgroup then sorts).
+// d_fault: the workspace's fault word (null up to 16384 keys: no tile waits for another).
 extern "C" __attribute__((visibility("hidden")))
 tcuscan_status_t tcuscan_internal_digit_sort(void *d_keys, void *d_vals, size_t n, int bits, void *d_keys_tmp, void *d_vals_tmp,
                                              void *d_scratch, void *d_fault, tcuscan_stream_t stream)
@@ -660,20 +756,26 @@ tcuscan_status_t tcuscan_internal_digit_sort(void *d_keys, void *d_vals, size_t 
     split_digits(bits, P);
     unsigned use_tickets, spin_limit, mute_tile;
     tcuscan_internal_chain_knobs(&use_tickets, &spin_limit, &mute_tile);
-    const bool wide = n >= StatusWord<uint32_t>::kUnknown, surely = n <= kBlockSortMax;
-    // One pass on the top eight bits, if the buckets then fit a workgroup each, which sorts them by the other bits.
-    const bool buckets_wanted = !wide && d_fault && P.count >= (surely ? 2 : 3) && buckets_fit(n);
-    if (n <= kBlockSortMax && (n <= kBlockSortFew || !buckets_wanted || use_tickets)) {      // (tickets: more scratch than there is)
-        const BlockArgs B = {(const uint32_t *)d_keys, (const uint32_t *)d_vals, (uint32_t *)d_keys, (uint32_t *)d_vals, nullptr, (uint32_t)n, {P, P}};
-        return launch_block_sort(B, 1, s) == hipSuccess ? TCUSCAN_OK : TCUSCAN_ERR_HIP;
+    const bool wide = n >= StatusWord<uint32_t>::kUnknown;
+    if (n <= kBlockSortMax) {
+        BlockArgs B = {(const uint32_t *)d_keys, (const uint32_t *)d_vals, (uint32_t *)d_keys, (uint32_t *)d_vals, nullptr, (uint32_t)n, P};
+        if (n <= kBlockSortFew || P.count < 2) return launch_block_sort(B, 1, s) == hipSuccess ? TCUSCAN_OK : TCUSCAN_ERR_HIP;
+        B.keys = (const uint32_t *)d_keys_tmp; B.vals = (const uint32_t *)d_vals_tmp; B.buckets = (const Buckets *)d_scratch;
+        split_digits(bits - 8, B.P);
+        SpreadArgs A = {(const uint32_t *)d_keys, (const uint32_t *)d_vals, (uint32_t *)d_keys_tmp, (uint32_t *)d_vals_tmp, (Buckets *)d_scratch, (uint32_t)n, {bits - 8, 8}};
+        void *args[] = {&A};
+        const void *fn = d_vals ? (const void *)spread_kernel<true> : (const void *)spread_kernel<false>;
+        if (hipLaunchKernel(fn, dim3((unsigned)((n + kSpreadTile - 1) / kSpreadTile)), dim3(64 * kSpreadWaves), args, 0, s) != hipSuccess) return TCUSCAN_ERR_HIP;
+        return launch_block_sort(B, kDigits, s) == hipSuccess ? TCUSCAN_OK : TCUSCAN_ERR_HIP;
     }
+    // One pass on the top eight bits, if the buckets then are small enough for a workgroup each, which sorts them by the other bits.
+    const bool buckets_wanted = !wide && P.count >= 3 && buckets_fit(n);
     Passes rest = P;
     if (buckets_wanted) {
         split_digits(bits - 8, rest);                                    // (also for the passes that run where the buckets do not fit)
         P = rest;
         P.digit[P.count++] = {bits - 8, 8};
     }
-    const int passes = buckets_wanted && surely ? 1 : P.count;           // passes over the array that are launched
     const int items = pass_items(n);
     auto tiles_of = [n](int per_lane) { const size_t tile = (size_t)64 * kPassWaves * per_lane; return (n + tile - 1) / tile; };
     const size_t tiles = tiles_of(items);
@@ -683,7 +785,7 @@ tcuscan_status_t tcuscan_internal_digit_sort(void *d_keys, void *d_vals, size_t 
     // 169 against 175).
     const bool around_cache = n * (d_vals ? 16 : 8) > ((size_t)192 << 20);
     const size_t want = (n / 4 + 2 * kHistThreads - 1) / (2 * kHistThreads);
-    const bool odd = (P.count & 1) && !(buckets_wanted && surely);       // the first pass then starts from a copy, and the last ends at home
+    const bool odd = P.count & 1;                                        // the first pass then starts from a copy, and the last ends at home
     const bool own = n <= (odd ? kOwnTables / 4 : kOwnTables) && !use_tickets;       // (few workgroups are slow copiers)
     const unsigned hist_grid = (unsigned)(want < 1 ? 1 : own && want > kTables ? kTables : want < kHistGrid ? want : kHistGrid);
     const uint32_t tables = own ? hist_grid : n < ((size_t)1 << 19) ? 1 : kTables;     // (300,000 keys, two passes: one table 25.5 us, eight 26.5)
@@ -699,8 +801,7 @@ tcuscan_status_t tcuscan_internal_digit_sort(void *d_keys, void *d_vals, size_t 
         HistArgs H;
         H.keys = src_k; H.vals = src_v;
         H.keys_copy = odd ? dst_k : nullptr; H.vals_copy = odd && src_v ? dst_v : nullptr;
-        H.hist = hist; H.tables = tables; H.status = status; H.n = n; H.status_quads = pass_words * passes / 4; H.P = P; H.stream = around_cache; H.own = own;
-        if (buckets_wanted && surely) H.P = {1, {P.digit[P.count - 1]}};
+        H.hist = hist; H.tables = tables; H.status = status; H.n = n; H.status_quads = pass_words * P.count / 4; H.P = P; H.stream = around_cache; H.own = own;
         void *args[] = {&H};
         if (hipLaunchKernel((const void *)digit_histograms_kernel, dim3(hist_grid), dim3(kHistThreads), args, 0, s) != hipSuccess) return TCUSCAN_ERR_HIP;
     }
@@ -708,15 +809,15 @@ tcuscan_status_t tcuscan_internal_digit_sort(void *d_keys, void *d_vals, size_t 
         uint32_t *t = src_k; src_k = dst_k; dst_k = t;
         t = src_v; src_v = dst_v; dst_v = t;
     }
-    for (int p = 0; p < passes; ++p) {
+    for (int p = 0; p < P.count; ++p) {
         PassArgs A;
         A.keys = src_k; A.vals = src_v; A.keys_out = dst_k; A.vals_out = dst_v;
         A.status = status + pass_words * p; A.hist = hist + kDigits * p; A.tables = tables;
         A.ticket = use_tickets ? tickets + p : nullptr;
         A.fault = (uint32_t *)d_fault;
         A.n = n; A.spin_limit = spin_limit; A.mute_tile = mute_tile; A.digit = P.digit[p]; A.stream = around_cache;
-        A.top_hist = hist + (surely ? 0 : kDigits * (P.count - 1)); A.buckets = buckets; A.top = P.digit[P.count - 1];
-        A.bucket_max = surely ? (uint32_t)kBlockCapacity : bucket_limit(n, (uint32_t)kBlockCapacity);
+        A.top_hist = hist + kDigits * (P.count - 1); A.buckets = buckets; A.top = P.digit[P.count - 1];
+        A.bucket_max = bucket_limit(n, (uint32_t)kBlockCapacity);
         void *args[] = {&A};
         const bool v = d_vals != nullptr;
         // (passes that seldom have anything to do are cheaper with fewer, larger tiles)
@@ -726,7 +827,7 @@ tcuscan_status_t tcuscan_internal_digit_sort(void *d_keys, void *d_vals, size_t 
         if (hipLaunchKernel(fn, dim3((unsigned)(buckets_wanted && p ? tiles_of(later_items) : tiles)), dim3(64 * kPassWaves), args, 0, s) != hipSuccess)
             return TCUSCAN_ERR_HIP;
         if (buckets_wanted && p == 0) {
-            const BlockArgs B = {dst_k, dst_v, (uint32_t *)d_keys, (uint32_t *)d_vals, buckets, (uint32_t)n, {rest, P}};
+            const BlockArgs B = {dst_k, dst_v, (uint32_t *)d_keys, (uint32_t *)d_vals, buckets, (uint32_t)n, rest};
             if (launch_block_sort(B, kDigits, s) != hipSuccess) return TCUSCAN_ERR_HIP;
         }
         uint32_t *t = src_k; src_k = dst_k; dst_k = t;

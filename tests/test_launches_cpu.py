@@ -29,6 +29,21 @@ def test_keys_alone_take_the_same_kernels_with_a_scratch_for_payloads(run, form)
         assert with_tmp == alone, (n, bits)
 
 
+@pytest.mark.parametrize("pairs", [False, True])
+def test_launches_of_small_sorts(run, pairs):
+    """Up to 8192 keys one launch; up to 16384 two, for more than eight bits, also with tickets and without a workspace."""
+    v = dict(vals=VALS, vals_tmp=VALS_TMP) if pairs else {}
+    arg = "true" if pairs else "false"
+    sizes = [(n, bits) for n in (2, 8192, 8193, 12_289, 16_384) for bits in (8, 9, 32)]
+    others = [("tcuscan_set_chain_policy", [1]), sort(9000, 32, **v)] + ([] if pairs else [sort(9000, 32, ws=0)])      # (pairs need one)
+    got = run([sort(n, bits, **v) for n, bits in sizes] + others)
+    for (n, bits), (rc, launched) in zip(sizes, got):
+        one = n <= 8192 or bits == 8
+        assert rc == 0 and [(k.kernel, k.grid) for k in launched] == ([] if one else [(f"spread_kernel<{arg}>", -(-n // 4096))]) + [(f"block_sort_kernel<{arg}>", 1 if one else 256)]
+    for rc, launched in got[len(sizes) + 1:]:
+        assert rc == 0 and [k.kernel for k in launched] == [f"spread_kernel<{arg}>", f"block_sort_kernel<{arg}>"]
+
+
 IN, OUT, OFFSETS = KEYS, TMP, VALS
 KINDS = ("i32", "f16", "i8", "f32", "bf16")
 
