@@ -354,33 +354,39 @@ __device__ __forceinline__ Word digit_look_back(const Word *status, uint32_t d, 
 // (at 101 registers one workgroup was, 215 us a pass); 8192 keys per tile: 18 us a pass more, 12288: 15 us more.  The form for
 // 2^30 keys and more keeps 64-bit words and places and takes 80 to 82 registers, which is one workgroup: 2^30 + 12345 keys
 // 16.4 ms per sort, with payloads 25.1 (two-bit passes took 37.6 and 80.1), where 16 sorts of 2^26 keys take 12.2.
-template <int W, int ITEMS, bool VALS, class Word, PassRole ROLE = kPlainPass>
-__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(sizeof(Word) == 4 ? 8 : 4))) void digit_pass_kernel(PassArgs A)
+template <int W, int ITEMS, class Place> struct PassLds {
+    uint32_t order[64 * W * ITEMS];
+    alignas(16) uint16_t cnt[W][kDigits];
+    Place dest[kDigits];
+    uint32_t part[4], abort;
+};
+// The tile that a workgroup takes.
+__device__ __forceinline__ uint32_t take_tile(const PassArgs &A, uint32_t *slot)
+{
+    if (!A.ticket) return blockIdx.x;
+    if (threadIdx.x == 0) *slot = __hip_atomic_fetch_add(A.ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    const uint32_t tile = (uint32_t)__builtin_amdgcn_readfirstlane((int)*slot);
+    __syncthreads();
+    return tile;
+}
+template <int W, int ITEMS, bool VALS, class Word, PassRole ROLE>
+__device__ __forceinline__ void digit_pass(const PassArgs &A, PassLds<W, ITEMS, Word> &s, uint32_t tile)
 {
     using S = StatusWord<Word>;
     using Place = Word;                    // byte offsets in the destination: 32 bits hold those of 2^30 keys
     constexpr int kThreads = 64 * W;
     constexpr uint32_t kTile = kThreads * ITEMS;
     static_assert(W >= 4 && kTile <= 16384u, "one thread per digit; byte offsets inside a tile are 16 bits");
-    __shared__ uint32_t s_order[kTile];
-    __shared__ __attribute__((aligned(16))) uint16_t s_cnt[W][kDigits];
-    static_assert(__alignof__(s_cnt) >= alignof(CounterQuad), "cleared four counters at a time");
-    __shared__ Place s_dest[kDigits];
-    __shared__ uint32_t s_part[4], s_abort;
+    auto &s_order = s.order;
+    auto &s_cnt = s.cnt;
+    auto &s_dest = s.dest;
+    uint32_t *s_part = s.part;
+    static_assert(alignof(PassLds<W, ITEMS, Word>) >= alignof(CounterQuad), "counters cleared four at a time");
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    if constexpr (ROLE == kLaterPass) {
-        if (A.buckets->split != kNotSplit) return;
-    }
-    if (tid == 0) s_abort = 0u;
-    uint32_t tile = blockIdx.x;
-    if (A.ticket) {
-        if (tid == 0) s_part[0] = __hip_atomic_fetch_add(A.ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __syncthreads();
-        tile = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_part[0]);
-        __syncthreads();
-    }
+    if (tid == 0) s.abort = 0u;
     const uint64_t base = (uint64_t)tile * kTile;
     const uint32_t valid = A.n - base < kTile ? (uint32_t)(A.n - base) : kTile;
     Digit g = A.digit;
@@ -446,10 +452,10 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(sizeof(W
         // Nothing is stored of a tile that does not know its places, nor, in the passes after one that left tiles out, of a
         // tile whose places the counts over the array do not hold.  (The counts of the last tile include its keys past the
         // end; its stores are bounded one by one.)
-        if (!digit_range_fits<Place>(before, valid == kTile ? count : 0u, (uint32_t)A.n)) s_abort = 1u;
+        if (!digit_range_fits<Place>(before, valid == kTile ? count : 0u, (uint32_t)A.n)) s.abort = 1u;
     }
     __syncthreads();
-    if (s_abort) return;
+    if (s.abort) return;
 
     // ---- out: consecutive threads write consecutive places of a digit's range
     Place dst[VALS ? ITEMS : 1];
@@ -481,6 +487,15 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(sizeof(W
             if (valid == kTile || (i < valid && dst[r] / 4u < A.n)) *(uint32_t *)(vout + dst[r]) = s_order[i];
         }
     }
+}
+template <int W, int ITEMS, bool VALS, class Word, PassRole ROLE = kPlainPass>
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(sizeof(Word) == 4 ? 8 : 4))) void digit_pass_kernel(PassArgs A)
+{
+    __shared__ PassLds<W, ITEMS, Word> s;
+    if constexpr (ROLE == kLaterPass) {
+        if (A.buckets->split != kNotSplit) return;
+    }
+    digit_pass<W, ITEMS, VALS, Word, ROLE>(A, s, take_tile(A, s.part));
 }
 
 // ------------------------------------------------------------------------- the pass in front of a small sort's buckets
@@ -675,13 +690,11 @@ __device__ __forceinline__ void sort_in_block_of(const BlockArgs &B, uint32_t be
 }
 
 template <bool VALS>
-__global__ __launch_bounds__(64 * kBlockWaves) void block_sort_kernel(BlockArgs B)
+__device__ __forceinline__ void sort_block_or_bucket(const BlockArgs &B, BlockLds &s)
 {
-    __shared__ BlockLds s;
     static_assert(alignof(BlockLds) >= alignof(CounterQuad), "counters cleared four at a time");
     uint32_t begin = 0u, n = B.n;
     if (B.buckets) {
-        if (B.buckets->split == kNotSplit) return;
         begin = B.buckets->start[blockIdx.x];
         const uint32_t end = blockIdx.x + 1u < kDigits ? B.buckets->start[blockIdx.x + 1u] : B.n;
         n = end > begin && end <= B.n ? end - begin : 0u;
@@ -689,6 +702,29 @@ __global__ __launch_bounds__(64 * kBlockWaves) void block_sort_kernel(BlockArgs 
     }
     n = (uint32_t)__builtin_amdgcn_readfirstlane((int)n);
     if (n != 0u) sort_in_block_of<VALS>(B, begin, n, s);
+}
+template <bool VALS>
+__global__ __launch_bounds__(64 * kBlockWaves) void block_sort_kernel(BlockArgs B)
+{
+    __shared__ BlockLds s;
+    if (B.buckets && B.buckets->split == kNotSplit) return;
+    sort_block_or_bucket<VALS>(B, s);
+}
+
+// The buckets, or the second pass where there are none: a launch that returns at once is 1.2 us (two launches / one: 40,000 keys
+// below 2^24 34.4 / 33.2 us, four plain passes 32.6, random ones 23.6 / 22.2; 10^6 63.7 / 62.5, 61.5, 39.2 / 38.0).  The pass has one
+// workgroup per compute unit here, for the buckets' LDS, so it does for no more tiles than there are units (kTogetherMax).
+template <int ITEMS, bool VALS>
+__global__ __launch_bounds__(64 * kBlockWaves) void pass_or_buckets_kernel(PassArgs A, BlockArgs B, uint32_t tiles)
+{
+    constexpr int W = kBlockWaves;
+    __shared__ union { PassLds<W, ITEMS, uint32_t> pass; BlockLds block; } s;
+    if (A.buckets->split != kNotSplit) {
+        sort_block_or_bucket<VALS>(B, s.block);
+    } else {
+        const uint32_t tile = take_tile(A, s.pass.part);
+        if (tile < tiles) digit_pass<W, ITEMS, VALS, uint32_t, kLaterPass>(A, s.pass, tile);
+    }
 }
 
 // ------------------------------------------------------------------------- host side
@@ -730,6 +766,14 @@ template <PassRole ROLE> const void *pass_kernel(int items, bool vals)
 const void *wide_pass_kernel(bool vals)
 {
     return vals ? (const void *)digit_pass_kernel<kPassWaves, 16, true, uint64_t> : (const void *)digit_pass_kernel<kPassWaves, 16, false, uint64_t>;
+}
+
+// Up to here the second pass and the buckets are one launch: 256 tiles at most.
+constexpr size_t kTogetherMax = (size_t)1 << 21;
+const void *pass_or_buckets_kernel_for(int items, bool vals)
+{
+    if (items == 4) return vals ? (const void *)pass_or_buckets_kernel<4, true> : (const void *)pass_or_buckets_kernel<4, false>;
+    return vals ? (const void *)pass_or_buckets_kernel<8, true> : (const void *)pass_or_buckets_kernel<8, false>;
 }
 
 // `bits` low bits in digits as even as possible.
@@ -809,6 +853,12 @@ tcuscan_status_t tcuscan_internal_digit_sort(void *d_keys, void *d_vals, size_t 
         uint32_t *t = src_k; src_k = dst_k; dst_k = t;
         t = src_v; src_v = dst_v; dst_v = t;
     }
+    BlockArgs B = {dst_k, dst_v, (uint32_t *)d_keys, (uint32_t *)d_vals, buckets, (uint32_t)n, rest};       // (the buckets are where the first pass puts them)
+    const bool v = d_vals != nullptr, together = buckets_wanted && n <= kTogetherMax;
+    // (passes that seldom have anything to do are cheaper with fewer, larger tiles; where they do, 3.2 million pairs take 105.5 us with
+    // 8 rows per lane and 110 with 16, 2^22 the same with both)
+    const int later_items = n >= ((size_t)1 << 22) ? 16 : items;
+    const unsigned later_tiles = (unsigned)tiles_of(later_items);
     for (int p = 0; p < P.count; ++p) {
         PassArgs A;
         A.keys = src_k; A.vals = src_v; A.keys_out = dst_k; A.vals_out = dst_v;
@@ -818,18 +868,15 @@ tcuscan_status_t tcuscan_internal_digit_sort(void *d_keys, void *d_vals, size_t 
         A.n = n; A.spin_limit = spin_limit; A.mute_tile = mute_tile; A.digit = P.digit[p]; A.stream = around_cache;
         A.top_hist = hist + kDigits * (P.count - 1); A.buckets = buckets; A.top = P.digit[P.count - 1];
         A.bucket_max = bucket_limit(n, (uint32_t)kBlockCapacity);
-        void *args[] = {&A};
-        const bool v = d_vals != nullptr;
-        // (passes that seldom have anything to do are cheaper with fewer, larger tiles)
-        const int later_items = n >= ((size_t)3 << 20) ? 16 : items;
-        const void *fn = wide ? wide_pass_kernel(v) : !buckets_wanted ? pass_kernel<kPlainPass>(items, v)
-                       : p == 0 ? pass_kernel<kChoosingPass>(items, v) : pass_kernel<kLaterPass>(later_items, v);
-        if (hipLaunchKernel(fn, dim3((unsigned)(buckets_wanted && p ? tiles_of(later_items) : tiles)), dim3(64 * kPassWaves), args, 0, s) != hipSuccess)
-            return TCUSCAN_ERR_HIP;
-        if (buckets_wanted && p == 0) {
-            const BlockArgs B = {dst_k, dst_v, (uint32_t *)d_keys, (uint32_t *)d_vals, buckets, (uint32_t)n, rest};
-            if (launch_block_sort(B, kDigits, s) != hipSuccess) return TCUSCAN_ERR_HIP;
-        }
+        uint32_t pass_tiles = later_tiles;
+        void *args[] = {&A, &B, &pass_tiles};                            // (the kernels of a pass alone take the first)
+        hipError_t e = hipSuccess;
+        if (buckets_wanted && p == 1 && !together) e = launch_block_sort(B, kDigits, s);
+        if (e != hipSuccess) return TCUSCAN_ERR_HIP;
+        const void *fn = wide ? wide_pass_kernel(v) : !buckets_wanted ? pass_kernel<kPlainPass>(items, v) : p == 0 ? pass_kernel<kChoosingPass>(items, v)
+                       : p == 1 && together ? pass_or_buckets_kernel_for(items, v) : pass_kernel<kLaterPass>(later_items, v);
+        const unsigned grid = !buckets_wanted || p == 0 ? (unsigned)tiles : p == 1 && together ? (unsigned)kDigits : later_tiles;
+        if (hipLaunchKernel(fn, dim3(grid), dim3(64 * kPassWaves), args, 0, s) != hipSuccess) return TCUSCAN_ERR_HIP;
         uint32_t *t = src_k; src_k = dst_k; dst_k = t;
         t = src_v; src_v = dst_v; dst_v = t;
     }

@@ -52,6 +52,20 @@ def test_a_bucket_at_the_limit(n, over):
     check(keys, True, 32)
 
 
+@pytest.mark.parametrize("policy", [0, 1])                # 1: tiles by ticket
+@pytest.mark.parametrize("name", ["small", "lanes", "random"])
+@pytest.mark.parametrize("n", [16_385, 1 << 19, (1 << 19) + 1, 1 << 21, (1 << 21) + 1, (1 << 22) - 1, 1 << 22])
+def test_the_second_pass_with_and_beside_the_buckets(n, name, policy):
+    """Up to 2^21 keys one launch does the buckets or the second pass; tile shapes of the later passes change at 2^19 and 2^22."""
+    keys = inputs.int32_full(n, n).view(np.uint32) if name == "random" else keys_of(name, n).astype(np.uint32)
+    tcuscan.set_chain_policy(policy)
+    try:
+        check(keys, True, 32)
+        check(keys, False, 24)
+    finally:
+        tcuscan.set_chain_policy(0)
+
+
 @pytest.mark.parametrize("bits", [32, 20])
 def test_buckets_of_every_size_a_workgroup_has_code_for(bits):
     """Bucket b of the top digit holds 0, 1, 63, 64, 65 or about b * 96 keys: all row counts, each with part of a row."""

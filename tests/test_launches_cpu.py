@@ -44,6 +44,26 @@ def test_launches_of_small_sorts(run, pairs):
         assert rc == 0 and [k.kernel for k in launched] == [f"spread_kernel<{arg}>", f"block_sort_kernel<{arg}>"]
 
 
+@pytest.mark.parametrize("pairs", [False, True])
+@pytest.mark.parametrize("policy", [0, 1])                # 1: tiles by ticket
+def test_launches_of_sorts_with_buckets(run, pairs, policy):
+    """The second pass and the buckets in one launch of 256 workgroups, as long as its tiles are no more than that."""
+    v = dict(vals=VALS, vals_tmp=VALS_TMP) if pairs else {}
+    sizes = [(n, bits) for n in (16_385, 1 << 19, (1 << 19) + 1, 1 << 21, (1 << 21) + 1, (1 << 22) - 1, 1 << 22, 6_055_225) for bits in (17, 24, 32)]
+    got = run([("tcuscan_set_chain_policy", [policy])] + [sort(n, bits, **v) for n, bits in sizes])[1:]
+    for (n, bits), (rc, launched) in zip(sizes, got):
+        rows = 4 if n <= 1 << 19 else 8 if n < 5 << 20 else 16
+        later = rows if n < 1 << 22 else 16
+        later_tiles = -(-n // (1024 * later))
+        launched = [k for k in launched if "fill_zero" not in k.kernel]
+        passes = 1 + -(-(bits - 8) // 8)
+        second = [("pass_or_buckets_kernel", 256)] if n <= 1 << 21 else [("block_sort_kernel", 256), ("digit_pass_kernel", later_tiles)]
+        want = [("digit_pass_kernel", -(-n // (1024 * rows)))] + second + [("digit_pass_kernel", later_tiles)] * (passes - 2)
+        assert rc == 0 and launched[0].kernel.startswith("digit_histograms_kernel"), (n, bits)
+        assert [(k.kernel.split("<")[0], k.grid) for k in launched[1:]] == want, (n, bits)
+        assert n > 1 << 21 or later_tiles <= 256, (n, bits)
+
+
 IN, OUT, OFFSETS = KEYS, TMP, VALS
 KINDS = ("i32", "f16", "i8", "f32", "bf16")
 
