@@ -3146,12 +3146,13 @@ tcuscan_status_t flag_kernel_params(Params &P, size_t n, size_t tile, void *d_ws
 constexpr int kFlagNT = 2, kFlagW = 8;
 static_assert((size_t)kFlagNT * kFlagW * 1024 == chain_layout::kFlagTile, "tile of the fused split and compaction kernels");
 
-// Masks are counted ahead (compact_kernel) in large calls whose output lies apart from what is read.
+// Masks are counted ahead (compact_kernel) in large calls whose output and count lie apart from what is read.
 bool compact_ahead(const CompactArgs &C, size_t n)
 {
-    const uintptr_t out = (uintptr_t)C.out, values = (uintptr_t)C.values, mask = (uintptr_t)C.mask;
-    auto apart = [out, n](uintptr_t from, size_t bytes) { return out + 4 * n <= from || from + bytes <= out; };
-    return n >= ((size_t)1 << 25) && (mask & 15) == 0 && apart(values, 4 * n) && apart(mask, n);
+    const uintptr_t out = (uintptr_t)C.out, count = (uintptr_t)C.count, values = (uintptr_t)C.values, mask = (uintptr_t)C.mask;
+    auto apart = [](uintptr_t to, size_t written, uintptr_t from, size_t read) { return to + written <= from || from + read <= to; };
+    auto apart_from_both = [&](uintptr_t to, size_t written) { return apart(to, written, values, 4 * n) && apart(to, written, mask, n); };
+    return n >= ((size_t)1 << 25) && (mask & 15) == 0 && apart_from_both(out, 4 * n) && (!count || apart_from_both(count, 4));
 }
 
 }  // namespace

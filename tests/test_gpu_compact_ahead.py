@@ -60,6 +60,19 @@ def test_misaligned(off_values, off_mask, off_out):
     assert bool((out[:off_out] == -5).all())
 
 
+@pytest.mark.parametrize("off_mask", [16, 48, 4096 + 16])
+def test_a_mask_that_starts_inside_its_buffer(off_mask):
+    import torch
+    n = FROM + 12345
+    v, m = make(n + off_mask, "half", 4)
+    v, m = v[off_mask:], m[off_mask:]
+    out, count = torch.full((n + 3,), -5, dtype=torch.int32, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")
+    tcuscan.compact_u32(v, m, out[3:], None, count=count, ws=tcuscan.new_workspace(1, n, "i8"))
+    torch.cuda.synchronize()
+    check(v, m, out[3:], count, n)
+    assert bool((out[:3] == -5).all())
+
+
 def test_recorded_into_a_graph():
     import torch
     n = FROM + 777

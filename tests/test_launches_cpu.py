@@ -64,6 +64,26 @@ def test_launches_of_sorts_with_buckets(run, pairs, policy):
         assert n > 1 << 21 or later_tiles <= 256, (n, bits)
 
 
+def test_compactions_whose_masks_are_counted_ahead(run):
+    """Tiles may then be stored before tiles in front of them are read: not where the output or the count lies in the values or the mask."""
+    n, count = 1 << 25, POS
+    values, mask, out = KEYS + (1 << 32), FLAGS, TMP
+
+    def call(values=values, mask=mask, out=out, n=n, positions=0, count=count):
+        return ("tcuscan_compact_u32", [values, mask, out, n, positions, count, WS, WS_BYTES, 0])
+    cases = [(call(), True), (call(n=n - 1), False), (call(positions=VALS), False), (call(count=0), True),
+             (call(mask=mask + 16), True), (call(mask=mask + 1), False), (call(values=values + 4, out=out + 4), True),
+             (call(out=values), False), (call(out=values + 4 * n), True), (call(out=values + 4 * n - 4), False),
+             (call(out=values - 4 * n), True), (call(out=values - 4 * n + 4), False), (call(out=mask), False), (call(out=mask - 4 * n), True),
+             (call(out=mask + n - 4), False), (call(out=mask + n), True), (call(out=mask - 4 * n + 4), False),
+             (call(count=values), False), (call(count=values + 4 * n - 4), False), (call(count=values + 4 * n), True), (call(count=values - 4), True),
+             (call(count=mask + 8), False), (call(count=mask + n), True), (call(count=out), True)]
+    for at, ((_, ahead), (rc, launched)) in enumerate(zip(cases, run([c for c, _ in cases]))):
+        name = launched[-1].kernel
+        assert rc == 0 and name.startswith("compact_kernel<"), (at, launched)
+        assert (name.split(", ")[-1] == "true>") == ahead, (at, name)
+
+
 IN, OUT, OFFSETS = KEYS, TMP, VALS
 KINDS = ("i32", "f16", "i8", "f32", "bf16")
 
