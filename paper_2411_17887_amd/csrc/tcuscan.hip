@@ -1665,7 +1665,7 @@ __global__ __launch_bounds__(256) void seg_first_rows_kernel(Params P, const lon
 
 struct FlatArgs {
     const long long *offsets;
-    const uint32_t *first_rows;            // seg_stream_kernel: every run's first row (null: one window holds all offsets, or a search)
+    const uint32_t *first_rows;            // seg_stream_kernel of short rows: every run's first row
     uint32_t expect;                       // about how many rows start in a tile, or in a run with first_rows
     uint32_t check_rows;                   // rows whose offsets a workgroup checks (0: checked beforehand)
     uint32_t stream;                       // input and output do not fit the memory-side cache: the input is read around it (32-bit)
@@ -2174,7 +2174,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(!SEARCH 
     const uint32_t tile = take_tile(P, &s_bcast);
     if (tile >= P.num_tiles) return;
     // SEARCH: long rows, whose first ones are searched for here unless one window holds all offsets; else they have been found
-    // beforehand, or one window holds all.
+    // beforehand.
     const uint32_t entries = (uint32_t)P.rows + 1u;
     const bool search = SEARCH && entries > RunMarks<kEPW>::kWindow;
     uint32_t *run_bits = s_marks.bits + (kWords + (search ? 0u : 2u)) * wave;
@@ -2182,9 +2182,8 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(!SEARCH 
     RunMarks<kEPW> run_marks;
     __builtin_amdgcn_s_setprio(3);                  // loads first, as in scan_kernel
     if (search) marks.begin(F.offsets, entries, s_marks);
-    else run_marks.begin(F.offsets, entries, !SEARCH && F.first_rows ? F.first_rows[tile * W + (REV ? W - 1 - wave : wave)] : 0u,
-                         !SEARCH && F.first_rows ? F.expect : entries, lane, run_bits);
-    long long lo = F.offsets[0], hi = F.offsets[P.rows];       // (clamped: seg_first_rows_kernel has raised the fault word)
+    else run_marks.begin(F.offsets, entries, SEARCH ? 0u : F.first_rows[tile * W + (REV ? W - 1 - wave : wave)], SEARCH ? entries : F.expect, lane, run_bits);
+    long long lo = F.offsets[0], hi = F.offsets[P.rows];       // (clamped: seg_first_rows_kernel or seg_check_offsets raises the fault word)
     const long long total = (long long)P.cols;
     lo = lo < 0 ? 0 : (lo > total ? total : lo);
     hi = hi < lo ? lo : (hi > total ? total : hi);
@@ -2775,7 +2774,7 @@ struct SegLayout {
     size_t max_tiles;        // upper bound on the number of tiles = grid size
     size_t counts_off, starts_off, rowmap_off, inner_off, inner_bytes, total_bytes;
     bool short_rows;         // scanned as one range with row starts (run_segmented_range) unless that form is switched off
-    size_t first_rows_off, first_rows_bytes;   // every run's first row (run_segmented_range), in rows' place where that form has no use for them
+    size_t first_rows_off, first_rows_bytes;   // short rows: every run's first row (run_segmented_range)
 };
 
 bool seg_layout(int dt, size_t rows, size_t total, SegLayout &L)
@@ -2790,11 +2789,10 @@ bool seg_layout(int dt, size_t rows, size_t total, SegLayout &L)
     L.inner_off = up(L.rowmap_off + sizeof(TileDesc) * L.max_tiles);
     L.inner_bytes = tcuscan_workspace_bytes(1, rows + 1, TCUSCAN_I32_I32);
     L.short_rows = seg_tile_class(dt, rows, total) == kSegShort;
-    // (for short rows a word per tile of kFlatTile elements lies there; callers have sized their workspaces by a bit per element)
-    const size_t end = up(L.inner_off + L.inner_bytes);
-    L.first_rows_off = L.short_rows ? end : L.rowmap_off;
-    L.first_rows_bytes = L.short_rows ? 4 * ((total + 32) / 32 + 2) : sizeof(TileDesc) * L.max_tiles;
-    L.total_bytes = end + (L.short_rows ? L.first_rows_bytes : 0);
+    // (a word per run of the large kernel lies there, SegStream::kRun elements; callers have sized their workspaces by a bit per element)
+    L.first_rows_off = up(L.inner_off + L.inner_bytes);
+    L.first_rows_bytes = L.short_rows ? 4 * ((total + 32) / 32 + 2) : 0;
+    L.total_bytes = L.first_rows_off + L.first_rows_bytes;
     return true;
 }
 
@@ -2868,12 +2866,12 @@ template <int DT, bool LONG> struct SegStream {
 template <int DT, bool LONG> hipError_t launch_seg_stream(Params P, FlatArgs F, bool excl, uint32_t *first_rows, hipStream_t s)
 {
     using C = SegStream<DT, LONG>;
-    constexpr int NT = C::kNT, W = C::kW, kRun = (int)C::kRun;
-    if (first_rows) {
-        const long long *off = F.offsets; uint32_t esz = Tr<DT>::kEsz, *first = first_rows;
-        void *args[] = {&P, &off, &esz, &first};
+    constexpr int NT = C::kNT, W = C::kW;
+    if constexpr (!LONG) {
+        const long long *off = F.offsets; uint32_t esz = Tr<DT>::kEsz;
+        void *args[] = {&P, &off, &esz, &first_rows};
         const size_t threads = P.rows + 1 > P.num_tiles ? P.rows + 1 : P.num_tiles;
-        const hipError_t e = hipLaunchKernel((const void *)seg_first_rows_kernel<kRun, W>, dim3((unsigned)((threads + 255) / 256)), dim3(256), args, 0, s);
+        const hipError_t e = hipLaunchKernel((const void *)seg_first_rows_kernel<(int)C::kRun, W>, dim3((unsigned)((threads + 255) / 256)), dim3(256), args, 0, s);
         if (e != hipSuccess) return e;
     }
     F.first_rows = first_rows;
@@ -2891,7 +2889,8 @@ template <int DT> tcuscan_status_t run_segmented_range_dt(Params P, const long l
     using Long = SegStream<DT, true>;
     const bool flat = total < kSegStreamFrom && (total / kFlatTile + 2 <= L.max_tiles || total <= kFlatFewSlots);
     const bool long_rows = total / rows >= (Tr<DT>::kEsz == 4 ? 2048 : 4096);
-    const bool few_rows = rows < RunMarks<Short::kRun>::kWindow, first = !flat && !long_rows && !few_rows;     // (are first rows found beforehand?)
+    const bool few_rows = rows < RunMarks<Long::kRun>::kWindow, first = !flat && !long_rows;      // (first: a launch in front finds every run's first row)
+    static_assert(4 * (size_t)kSegShortNT * Geo<DT>::kTileElems >= (Tr<DT>::kEsz == 4 ? 2048 : 4096), "rows that are not long have room for first rows");
     if (Tr<DT>::kEsz == 4 && total >= own_tiles_from<DT>(total / rows) && !few_rows && (total / rows >= ((size_t)1 << 14) || rows < kSegPrepRows))
         return TCUSCAN_ERR_UNSUPPORTED;
     const size_t run = flat ? 2048 : long_rows ? Long::kRun : Short::kRun;
