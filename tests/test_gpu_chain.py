@@ -180,8 +180,8 @@ def test_a_tile_that_never_publishes_ends_in_a_fault_word_not_in_a_hang():
 
 
 def test_plain_call_after_segmented_calls_on_the_same_workspace():
-    """A segmented call keeps row maps where a plain call of another shape expects status words; the library clears
-    them itself before the plain call."""
+    """Segmented calls on one workspace with plain ones: as one range, a call's status words lie where a plain call has its own; with
+    rows in tiles of their own it keeps row maps there, which the library clears itself before the plain call."""
     import torch
     n = 1 << 22
     lengths = np.full(2000, n // 2000)
@@ -190,8 +190,12 @@ def test_plain_call_after_segmented_calls_on_the_same_workspace():
     x = inputs.int32_full(total, 5)
     ws = tcuscan.new_segmented_workspace(len(lengths), total, "i32")
     assert ws.numel() * 8 >= tcuscan.workspace_bytes(1, total, "i32")
-    for rep in range(2):
-        got, fault = seg.run_segmented(x, "i32", off, ws=ws)
+    for form in (1, 1, 0, 0):
+        tcuscan.set_segmented_form(form)
+        try:
+            got, fault = seg.run_segmented(x, "i32", off, ws=ws)
+        finally:
+            tcuscan.set_segmented_form(1)
         assert fault == 0
         seg.check(x, "i32", off, got, False, False)
         check(x, "i32", run_scan(x, "i32", "inclusive", ws=ws))

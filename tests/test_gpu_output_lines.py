@@ -215,10 +215,20 @@ def test_rows_from_lines_are_masked_and_chained(kind, how):
 def test_segmented_rows_from_lines(kind, rows):
     """Long rows of different lengths, prepared in one launch (few rows) and in three, outputs that start inside a line,
     inputs that fit them and one that does not, elements in front of the first row and behind the last, loud neighbours."""
+    segmented_rows_from_lines(kind, rows, 45_000_000)
+
+
+@pytest.mark.parametrize("kind,rows", [("i32", 300), ("f32", 300), ("f32", 4000), ("i32", 4500)])
+def test_segmented_rows_from_lines_in_tiles_of_their_own(kind, rows):
+    """The same from where 32-bit rows have tiles of their own: rows of 2^14 elements and more, or fewer than 4096 of them."""
+    segmented_rows_from_lines(kind, rows, 80_000_000)
+
+
+def segmented_rows_from_lines(kind, rows, about):
     import torch
     g = torch.Generator(device="cuda")
     g.manual_seed(rows)
-    lengths = torch.randint(0, 2 * (45_000_000 // rows), (rows,), generator=g, device="cuda")
+    lengths = torch.randint(0, 2 * (about // rows), (rows,), generator=g, device="cuda")
     lengths[::17] = 0
     off = torch.cat([lengths.new_tensor([37]), 37 + torch.cumsum(lengths, 0)])
     n, total = int(lengths.sum().item()), int(off[-1].item()) + 91

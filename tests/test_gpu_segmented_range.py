@@ -68,7 +68,7 @@ def test_row_starts_are_found(name, kinds, flags):
 @pytest.mark.parametrize("total", [LARGE - 1, LARGE, LARGE + 8191, 4 * LARGE - 3, 4 * LARGE])
 @pytest.mark.parametrize("rows", [3, 700, 3000])
 def test_edges_of_the_rules_and_one_workspace(total, rows):
-    """One workspace through both forms and a plain scan in between: status words, first rows and row maps do not get mixed up."""
+    """One workspace through both forms and a call of one row in between: status words, first rows and row maps do not get mixed up."""
     rng = np.random.default_rng(total + rows)
     off = offsets_from(spread(rng, rows, total))
     x = inputs.int32_full(total, 5)
@@ -222,3 +222,94 @@ def test_ends_of_a_large_range_of_long_rows(kind, flags):
         got, fault = run_shifted(y, kind, off, flags, ws, shift_in, shift_out)
         assert fault == 0
         check(y, kind, off, got, bool(flags & 1), bool(flags & 2))
+
+
+@pytest.mark.parametrize("flags", range(4))
+@pytest.mark.parametrize("kind", ["i32", "f16", "i8", "f32", "bf16"])
+def test_large_ranges_of_short_rows(kind, flags):
+    """The form with first rows found in front: arrays that start at and off 16-byte boundaries and lines, ranges that start late."""
+    per = {"i8": 16, "f16": 8, "bf16": 8}.get(kind, 4)
+    x = (INT_GEN if kind in INT_GEN else RND_GEN)[kind](LARGE + 70_000, 6)
+    for case, (n, mean, shift_in, shift_out, skip) in enumerate([(LARGE, 200, 1, 1, 0), (LARGE + 8191, 17, per - 1, 3, per + 2), (LARGE + 65_531, 1900, 24, 24, 2),
+                                                                 (LARGE + 5, 700, 0, 2, 0), (LARGE + 16_384, 60, 8, 40, 31)]):
+        off = offsets_from(spread(np.random.default_rng(case), n // mean, n), start=skip)
+        y = x[:n + skip + case % 3]
+        ws = tcuscan.new_segmented_workspace(off.size - 1, y.size, kind)
+        got, fault = run_shifted(y, kind, off, flags, ws, shift_in, shift_out)
+        assert fault == 0
+        check(y, kind, off, got, bool(flags & 1), bool(flags & 2))
+
+
+@pytest.mark.parametrize("flags", range(4))
+@pytest.mark.parametrize("kind", ["i32", "f32", "bf16"])
+@pytest.mark.parametrize("name", ["long:250", "long:2500", "short:200"])
+def test_large_ranges_in_place_and_by_ticket(name, kind, flags):
+    off = offsets_from(layout(name, np.random.default_rng(flags)), start=3)
+    x = (INT_GEN if kind in INT_GEN else RND_GEN)[kind](int(off[-1]), 7)
+    ws = tcuscan.new_segmented_workspace(off.size - 1, x.size, kind)
+    for shift, policy in ((0, 1), (5, 0)):
+        tcuscan.set_chain_policy(policy)
+        try:
+            got, fault = run_shifted(x, kind, off, flags, ws, shift, shift, inplace=kind != "bf16")
+        finally:
+            tcuscan.set_chain_policy(0)
+        assert fault == 0
+        if kind != "bf16":                                             # what lies outside the rows is still the input
+            assert np.array_equal(got[:3], x[:3].view(got.dtype))
+            got[:3] = GUARD
+        check(x, kind, off, got, bool(flags & 1), bool(flags & 2))
+
+
+@pytest.mark.parametrize("kind", ["i32", "i8", "bf16"])
+@pytest.mark.parametrize("name", ["long:250", "long:2500", "short:200"])
+def test_large_ranges_recorded_into_a_graph(name, kind):
+    """Replays with other inputs, and eager calls from the end on the same workspace between them."""
+    import torch
+    off = offsets_from(layout(name, np.random.default_rng(11)))
+    rows, total = off.size - 1, int(off[-1])
+    d_off, ws = torch.from_numpy(off).cuda(), tcuscan.new_segmented_workspace(rows, total, kind)
+    gen = (INT_GEN if kind in INT_GEN else RND_GEN)[kind]
+    d_in, d_out = to_device(gen(total, 0), kind), torch.empty(total, dtype=out_dtype(kind), device="cuda")
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        tcuscan.segmented(d_in, d_out, d_off, rows, total, kind, ws=ws)
+    for seed in (1, 2, 3):
+        x = gen(total, seed)
+        d_in.copy_(to_device(x, kind))
+        for flags in (0, 3):
+            d_out.fill_(GUARD)
+            torch.cuda.synchronize()
+            if flags == 0:
+                graph.replay()
+            else:
+                tcuscan.segmented(d_in, d_out, d_off, rows, total, kind, flags=flags, ws=ws)
+            torch.cuda.synchronize()
+            check(x, kind, off, d_out.cpu().numpy(), bool(flags & 1), bool(flags & 2))
+    assert tcuscan.workspace_fault(ws) == 0
+
+
+@pytest.mark.parametrize("kind", ["i32", "i8", "f32"])
+def test_first_rows_are_not_taken_for_status_words(kind):
+    """Short rows of a large call leave first rows in the workspace; plain scans, calls of one launch and few long rows with status
+    words that share slots follow on it, in an order in which each comes right behind the first rows."""
+    import torch
+    total = LARGE + 4099
+    x = (INT_GEN if kind in INT_GEN else RND_GEN)[kind](total, 8)
+    off = {name: offsets_from(layout(name, np.random.default_rng(5))) for name in ("short:200", "long:2500", "long:250", "small:3000")}
+    off["one"] = offsets_from([1_000_003])
+    ws = torch.zeros(max(tcuscan.segmented_workspace_bytes(o.size - 1, int(o[-1]), kind) for o in off.values()) // 8 + 1, dtype=torch.int64, device="cuda")
+    x = np.concatenate([x, x[:20_000]])
+    plain = torch.empty(total, dtype=out_dtype(kind), device="cuda")
+    for name in ("long:2500", "plain", "one", "small:3000", "long:250"):
+        for then in ("short:200", name, name):
+            if then == "plain":
+                tcuscan.scan(to_device(x[:total], kind), plain, 1, total, kind, ws=ws)
+                torch.cuda.synchronize()
+                whole = offsets_from([total])
+                check(x[:total], kind, whole, plain.cpu().numpy(), False, False)
+                continue
+            o = off[then]
+            y = x[:int(o[-1])]
+            got, fault = run_segmented(y, kind, o, ws=ws)
+            assert fault == 0, (name, then)
+            check(y, kind, o, got, False, False)

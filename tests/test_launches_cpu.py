@@ -117,3 +117,21 @@ def test_which_rows_of_large_calls_keep_tiles_of_their_own(run):
     for (kind, total, rows, own), (rc, launched) in zip(shapes, run([segmented(kind, total, rows) for kind, total, rows, _ in shapes])):
         last = launched[-1].kernel
         assert rc == 0 and last.startswith("scan_kernel<" if own else "seg_stream_kernel<"), (kind, total, rows, launched)
+
+
+@pytest.mark.parametrize("kind", KINDS)
+def test_a_workspace_with_first_rows_in_it_is_cleared(run, kind):
+    """A large call of short rows leaves first rows where others expect status words: the next call of another kind on that workspace
+    clears its own, and the call after that need not."""
+    n = 14_000_000
+    two = segmented(kind, n, n // 200)
+    plain = ("tcuscan_scan", [IN, OUT, 1, n, tcuscan.DTYPES[kind], 0, WS, WS_BYTES, 0])
+    one = segmented(kind, n, n // 20_000)
+    other = segmented(kind, n, n // 20_000, ws=WS + (1 << 30))
+    for after in (plain, one):
+        got = [[k.kernel.split("<")[0] for k in launched] for rc, launched in run([after, two, after, after, two, other, after])]
+        alone = got[0]
+        assert len(alone) == 1
+        assert got[1] == ["seg_first_rows_kernel", "seg_stream_kernel"] == got[4]
+        assert got[2] == ["fill_zero_kernel"] + alone and got[3] == alone
+        assert got[6] == ["fill_zero_kernel"] + alone
