@@ -395,7 +395,7 @@ def measure_variants(steps: int):
     ms = timed(lambda i: tcuscan.segmented(xf[i % len(xf)], d_of, d_off, nrows, m, "f32", ws=ws))
     covered = int(off[-1])
     res["segmented_short_rows"] = {"workload": f"{covered} fp32 elements in {nrows} rows, geometric lengths (mean 200), some empty, some of 8013; "
-                                               "the range scanned as one row with row-start bits",
+                                               "the range scanned as a whole, row starts looked up",
                                    "ms": ms, "gelems_per_s": covered / ms / 1e6, "frac_of_peak": covered * 8 / ms / 1e6 / PEAK_HBM_GBPS}
     tcuscan.set_segmented_form(False)
     try:
@@ -404,7 +404,7 @@ def measure_variants(steps: int):
                                                  "gelems_per_s": covered / ms / 1e6, "frac_of_peak": covered * 8 / ms / 1e6 / PEAK_HBM_GBPS}
     finally:
         tcuscan.set_segmented_form(True)
-    # the same length mix on 2^27 bf16 elements (level 0 of the row-start-bits form runs in the lane for 8/16-bit inputs)
+    # the same length mix on 2^27 bf16 elements
     del xf, ws
     m = 1 << 27
     lens = rng.geometric(1.0 / 200, size=int(m / 199)) - 1
@@ -424,7 +424,7 @@ def measure_variants(steps: int):
         finally:
             tcuscan.set_segmented_form(True)
         res[name] = {"workload": f"{covered} bf16 -> fp32 elements in {nrows} rows, geometric lengths (mean 200), "
-                                 + ("one range with row-start bits" if flat else "tiles of its own for every row"),
+                                 + ("the range scanned as a whole" if flat else "tiles of its own for every row"),
                      "ms": ms, "gelems_per_s": covered / ms / 1e6, "frac_of_peak": covered * 6 / ms / 1e6 / PEAK_HBM_GBPS}
     return res
 

@@ -150,12 +150,13 @@ tcuscan_status_t tcuscan_scan(const void *d_in, void *d_out, size_t rows, size_t
  * By default the range that the rows cover is scanned like one row whose sums restart at every row start, which every tile
  * looks up in the offsets: one launch, two in calls of 12,582,912 elements and more with short rows (average below 2048 / 4096
  * elements for 32-bit / narrower inputs).  32-bit rows of which there are 256 to 4095, or that average 16,384 elements and more,
- * do better from 37,748,736 elements in all on (fp32 rows of 65,536 elements and more from 50,331,648 on) with tiles of their own, as do all rows after tcuscan_set_segmented_form(0): tiles per row, their exclusive scan
- * (this library's int32 scan), one descriptor per tile (its row's extent and its place in the row), the scan itself; with fewer
- * than 4096 rows the first three are one launch.  The tile size follows the average row length total / rows.
+ * do better from 37,748,736 elements in all on (fp32 rows of 65,536 elements and more from 50,331,648 on) with tiles of their
+ * own, as do all rows after tcuscan_set_segmented_form(0): tiles per row, their exclusive scan (this library's int32 scan), one
+ * descriptor per tile (its row's extent and its place in the row), the scan itself; with fewer than 4096 rows the first three are
+ * one launch.  The tile size follows the average row length total / rows.
  * Rows may start at any element: the range, or a row with tiles of its own, is tiled from the 16-byte boundary at or below its
- * start (such a row from 2^23 elements on from the 128-byte line of the output it starts in), the elements in front are masked
- * out and not written.  Offsets that decrease or leave [0, total] are not followed: the
+ * start (from 2^23 elements on, where input and output allow it, from the 128-byte line of the output it starts in), the elements
+ * in front are masked out and not written.  Offsets that decrease or leave [0, total] are not followed: the
  * workspace's fault word is set to 2 (see tcuscan_workspace_fault) and the results of the call are unspecified (such
  * rows are skipped or clipped, rows may overlap); no access outside the n = total elements is made.
  * A segmented call of more than one launch keeps row maps in its workspace besides status words, at places that depend on

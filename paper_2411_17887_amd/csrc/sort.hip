@@ -9,12 +9,13 @@
 // (the published scheme of least-significant-digit passes with a decoupled look-back per digit: Merrill and Garland 2016,
 // Adinets and Merrill, "Onesweep", 2022).  A full sort is four passes of 8 bytes per key (16 with payloads) and one reading of the keys for the first term.
 //
-// Sorts of up to 6,055,225 keys on more than 16 bits (up to 16384 keys on more than 8) do with one pass on the top eight bits if the 256 buckets then are small
-// enough for a workgroup each, which sorts its bucket by the other bits in LDS: whether they do is seen on the device, and where they do not,
-// that first pass is the least significant one and the others follow (random keys, us before / now: 100,000 36.6 / 26, 10^6
-// 62.2 / 40, with payloads 76.4 / 49, 2^22 104 / 70, with payloads 125 / 90; keys that do not split, 10^6 equal ones 56 / 59, normally
-// distributed floats 62 / 64, 2^22 104 / 99).  Up to kBlockSortFew keys one workgroup does everything: one launch, keys and payloads
-// read and written once.
+// Sorts of up to 6,055,225 keys on more than 16 bits (up to 16384 keys on more than 8) do with one pass on the top eight bits if the 256
+// buckets then are small enough for a workgroup each, which sorts its bucket by the other bits in LDS (partition, then local sorts, as in
+// Stehle and Jacobsen, "A Memory Bandwidth-Efficient Hybrid Radix Sort on GPUs", 2017): whether they do is seen on the device, and
+// where they do not, that first pass is the least significant one and the others follow (random keys, us in four passes / with
+// buckets: 100,000 36.6 / 24.4, 10^6 61.6 / 38.0, with payloads 76.0 / 46.9, 2^22 104 / 70, with payloads 120 / 84; keys that do
+// not split, 10^6 equal ones 55.8 / 57.6, normally distributed floats 61.5 / 62.5, 2^22 103.7 / 103.4).  Up to kBlockSortFew keys one workgroup does
+// everything: one launch, keys and payloads read and written once.
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -40,14 +41,6 @@ struct Digit { int shift, width; };                        // digit = (key >> sh
 struct Passes { int count; Digit digit[kMaxPasses]; };
 
 __device__ __forceinline__ uint32_t digit_of(uint32_t key, Digit g) { return __builtin_amdgcn_ubfe(key, (uint32_t)g.shift, (uint32_t)g.width); }
-
-// What an LDS access of one lane wrote, other lanes of the wavefront see from here on.
-__device__ __forceinline__ void wavefront_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 constexpr unsigned kAndXnor = 0x90;        // truth table of a & ~(b ^ c)
 
@@ -832,7 +825,9 @@ tcuscan_status_t tcuscan_internal_digit_sort(void *d_keys, void *d_vals, size_t 
     const bool odd = P.count & 1;                                        // the first pass then starts from a copy, and the last ends at home
     const bool own = n <= (odd ? kOwnTables / 4 : kOwnTables) && !use_tickets;       // (few workgroups are slow copiers)
     const unsigned hist_grid = (unsigned)(want < 1 ? 1 : own && want > kTables ? kTables : want < kHistGrid ? want : kHistGrid);
-    const uint32_t tables = own ? hist_grid : n < ((size_t)1 << 19) ? 1 : kTables;     // (300,000 keys, two passes: one table 25.5 us, eight 26.5)
+    // (one table / eight, us: two passes of 131,073 keys 22.6 / 22.7, 524,287 29.7 / 29.3, 10^6 36.4 / 35.0; with buckets, random ones 25.6 /
+    // 26.5, 32.4 / 32.2, 38.8 / 37.7, keys below 2^24 39.5 / 40.1, 52.6 / 52.7, 63.8 / 62.3)
+    const uint32_t tables = own ? hist_grid : n < ((size_t)1 << 19) ? 1 : kTables;
     // scratch: digit counts of the passes from the next 16-byte boundary on, ticket counters, what the first pass finds out, status words
     uint32_t *hist = (uint32_t *)(((uintptr_t)d_scratch + 15) & ~(uintptr_t)15), *tickets = hist + tables * kTableWords;
     Buckets *buckets = (Buckets *)(tickets + kMaxPasses);

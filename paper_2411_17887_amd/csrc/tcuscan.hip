@@ -1344,8 +1344,9 @@ __global__ __launch_bounds__(64 * W) void compact_kernel(Params P, CompactArgs C
     }
 }
 
-// ------------------------------------------------------------- segmented scans, short rows
+// ------------------------------------------------------------- segmented scans, short rows in tiles of their own
 //
+// (Only where tcuscan_set_segmented_form(0) asks for it: else such rows go over their range as a whole, further down.)
 // Rows of a few hundred elements: a tile is one wavefront's run of kSegShortNT MFMA tiles, a wavefront takes
 // kSegUnroll consecutive tiles and a workgroup is kSegPack such wavefronts that share nothing (no LDS, no barrier).
 // A wavefront moves little data per tile, and descriptor -> loads -> products -> stores is a chain of waits, so
@@ -1446,14 +1447,6 @@ __global__ __launch_bounds__(64 * kSegPack) void seg_short_kernel(Params P)
 // their own they took three: 13.5 us for 10^5 elements, 7.3 now), and their tiles are small; the results stay in the
 // registers that held the inputs while the tile waits for what comes before it (seg_flat_kernel, seg_flat_narrow_kernel).
 // In large calls what counts is bytes in flight (seg_stream_kernel).
-
-// What an LDS access of one lane wrote, other lanes of the wavefront see from here on.
-__device__ __forceinline__ void wavefront_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 // The row starts of a tile -- elements first .. first + ELEMS of the arrays, the last one only for a reverse scan, in which it ends
 // the row before -- as bits in LDS.  All threads of the workgroup call.  The entries that matter are a stretch of the sorted

@@ -1,4 +1,4 @@
-// Sums and scans across the 64 lanes of a wavefront, on DPP lane moves (no LDS).  Shared by the kernels' sources.
+// Sums and scans across the 64 lanes of a wavefront, on DPP lane moves (no LDS), and its lanes' order in LDS.  Shared by the kernels' sources.
 #ifndef TCUSCAN_WAVE_OPS_H
 #define TCUSCAN_WAVE_OPS_H
 
@@ -24,6 +24,14 @@ template <> __device__ __forceinline__ float    acc_from_bits<float>(uint32_t b)
 template <> __device__ __forceinline__ uint32_t acc_from_bits<uint32_t>(uint32_t b) { return b; }
 
 template <class A, int CTRL> __device__ __forceinline__ A dpp_shr(A v) { return acc_from_bits<A>(dpp0<CTRL>(acc_bits(v))); }
+
+// What an LDS access of one lane wrote, other lanes of the wavefront see from here on.
+__device__ __forceinline__ void wavefront_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 
 // Sum over the 64 lanes, returned wave-uniform.  Row-local DPP shifts give every row's total in its
 // lane 15; row_bcast15 / row_bcast31 fold the four row totals into lane 63.
