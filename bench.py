@@ -55,9 +55,9 @@ DESCR = {
 # 1 GiB device copy; the table and the commands are in TRAFFIC_SOURCE.  The figures belong to the kernels they were
 # measured on: TRAFFIC_KERNEL_SHA is the hash of the kernel source at that time, and a run on any other source
 # reports `traffic: null` instead of a stale number.
-MEASURED_TRAFFIC_BYTES = {"C5": 1627269473, "C3": 1358298699, "C4": 805145807, "C2": 101639695}
+MEASURED_TRAFFIC_BYTES = {"C5": 1626909692, "C3": 1358323335, "C4": 805125867, "C2": 101627250}
 TRAFFIC_SOURCE = "profiles/scan_kernel_bench_default.md"
-TRAFFIC_KERNEL_SHA = "ed2d2bc9770f23f7"
+TRAFFIC_KERNEL_SHA = "76ee1347a9cb2112"
 KERNEL_SOURCE = os.path.join(ROOT, "paper_2411_17887_amd", "csrc", "tcuscan.hip")
 
 
