@@ -13,11 +13,12 @@
 // buckets then are small enough for a workgroup each, which sorts its bucket by the other bits in LDS (partition, then local sorts, as in
 // Stehle and Jacobsen, "A Memory Bandwidth-Efficient Hybrid Radix Sort on GPUs", 2017): whether they do is seen on the device, and
 // where they do not, that first pass is the least significant one and the others follow (random keys, us in four passes / with
-// buckets: 100,000 36.6 / 24.4, 10^6 61.6 / 38.0, with payloads 76.0 / 46.9, 2^22 104 / 70, with payloads 120 / 84; keys that do
+// buckets: 100,000 36.6 / 24.4, 10^6 61.6 / 34.4, with payloads 76.0 / 42.6, 2^22 104 / 61, with payloads 120 / 73; keys that do
 // not split, 10^6 equal ones 55.8 / 57.6, normally distributed floats 61.5 / 62.5, 2^22 103.7 / 103.4).  Up to kBlockSortFew keys one workgroup does
 // everything: one launch, keys and payloads read and written once.
 
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 #include "../../include/tcuscan.h"
@@ -597,6 +598,246 @@ __global__ __launch_bounds__(64 * kSpreadWaves) void spread_kernel(SpreadArgs A)
     }
 }
 
+// ------------------------------------------------------------------------- keys to their places by one partition in LDS
+//
+// The keys of a workgroup, n of them, go into bins by the highest of the bits they differ in: twice as many bins as keys or more (32,768 at
+// most), so that most keys have a bin of their own.  A bin's keys get their places from counters (additions that return what was
+// there: in no particular order), and where each belongs inside its bin is then seen by comparing it with the others there: key bits
+// below the bin's, then the key's place among the n, so the result is the stable order.  This takes the place of all passes: some ten
+// accesses to LDS and 45 vector instructions per row of 64 keys, where each pass on eight bits takes more than that.  What bounds it
+// is both: of 27,700 cycles for 16,320 keys on a compute unit 2800 go to the loads, 2700 to the counters, 4700 to their sums, 6000 to the
+// way into the bins, 7300 to the comparisons, 4000 to the way out (256 workgroups together 15.9 us; three passes 28).  Before -> now, us per
+// sort: 5000 keys 13.6 -> 8.2, 8192 18.4 -> 9.4, in order 19.3 -> 4.9 (without the copy of new ones), 2^22 in buckets 70.8 -> 61.3, pairs 85.5 -> 72.7.
+//   twice as many bins as keys and not as many: the comparisons of 256 x 16,320 keys 15,300 -> 9500 cycles.
+//   a bin's first place and the next one's from two aligned words: one read across words takes three times as long (6000 -> 18,500).
+//   payloads loaded when the keys have their places, not with them: 256 x 16,320 pairs 23.2 -> 20.4 us, 16,384 (18 rows) 28.9 -> 21.5.
+// Keys that crowd in a part of their range are seen before anything is moved, from a sample of pairs, or from the counters, and the passes do the work:
+// what that costs is 0.3 to 0.8 us.  Fewer than 2049 keys gain nothing, for more than 20,480 there are too few registers.
+
+constexpr uint32_t kBinMost = 16;                          // keys of a bin, at most
+constexpr uint32_t kBinMean = 2;                           // a bin has fewer on average
+constexpr uint32_t kAlikeMost = 6;                         // pairs of a sample that share a bin: fewer
+template <int W> struct BinParts { uint32_t differ[W], alike[W], sum[W], most[W]; };
+
+// body(r0, rows) for rows r0 .. r0 + rows - 1 of ITEMS, BATCH at a time, each call with constants of its own.
+template <int N> struct Constant { constexpr __device__ __forceinline__ operator int() const { return N; } };
+template <int ITEMS, int BATCH, int R0 = 0, class Body> __device__ __forceinline__ void in_batches(Body body)
+{
+    if constexpr (R0 < ITEMS) {
+        body(Constant<R0>(), Constant<(R0 + BATCH < ITEMS ? BATCH : ITEMS - R0)>());
+        in_batches<ITEMS, BATCH, R0 + BATCH>(body);
+    }
+}
+
+__device__ __forceinline__ uint32_t bits_below(uint32_t n) { return n <= 1u ? 0u : 32u - (uint32_t)__builtin_clz(n - 1u); }      // 2^result >= n
+
+// at[r]: byte offset in the ordered keys of this lane's key r, which is key first + 64 r of n (past the end, where
+// the caller has repeated a key: its own); false (in all threads, after a
+// barrier): not by bins.  `key0`: key 0; `bits`: those that the keys are ordered by; `bins`: 16-bit counters, 2^MAX_LOG of them,
+// and `order` 64 W ITEMS + kBinMost words, both free before and (true) after.
+template <int W, int ITEMS, uint32_t MAX_LOG>
+__device__ __forceinline__ bool places_by_bins(const uint32_t (&key)[ITEMS], uint32_t first, uint32_t n, uint32_t key0, uint32_t bits,
+                                               uint32_t *order, uint32_t *bins, BinParts<W> &parts, uint32_t (&at)[ITEMS], uint32_t &differ)
+{
+    differ = ~0u >> (32u - bits);
+    if (bits < 32u && n >> bits >= kBinMean) return false;
+    constexpr uint32_t kThreads = 64 * W, kBinChunks = (1u << MAX_LOG) / 2u / kThreads / 4u;
+    constexpr int kBatch = 4;
+    constexpr uint32_t kSlots = kThreads * ITEMS;
+    const uint32_t tid = threadIdx.x, lane = tid & 63u;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+    const uint32_t wave_first = (uint32_t)__builtin_amdgcn_readfirstlane((int)first);
+    const uint32_t index_bits = bits_below(n);
+    uint32_t log_bins = index_bits + 1u < 11u ? 11u : index_bits + 1u;
+    log_bins = log_bins < MAX_LOG ? log_bins : MAX_LOG;
+    for (uint32_t i = 4u * tid; i < 1u << (log_bins - 1u); i += 4u * kThreads)
+        *(u32x4 *)(bins + i) = u32x4{0u, 0u, 0u, 0u};
+    uint32_t mine = 0u;
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) mine |= key[r] ^ key0;
+    mine = wave_or(mine);
+    // Keys that crowd in a part of their range are mostly seen in a sample: a lane's first keys, 64 places apart, that fall into one bin.
+    // (normally distributed floats, us without / with it / by passes alone: 3000 8.3 / 8.0 / 7.6, 5000 11.3 / 11.0 / 10.4; pairs, 2100 8.1 / 7.6 / 6.8)
+    uint32_t alike = 0u;
+    constexpr int kSample = ITEMS < 4 ? ITEMS : 4;
+    const uint32_t range_of_wave = mine & differ;
+    if (wave_first + 64u * kSample <= n && range_of_wave != 0u) {
+        const uint32_t top = 32u - (uint32_t)__builtin_clz(range_of_wave);
+        const uint32_t window = differ & (top > log_bins ? ~0u << (top - log_bins) : ~0u);
+#pragma unroll
+        for (int a = 0; a < kSample; ++a)
+#pragma unroll
+            for (int b = 0; b < a; ++b) alike += (uint32_t)__builtin_popcountll(__ballot(((key[a] ^ key[b]) & window) == 0u));
+    }
+    if (lane == 0u) { parts.differ[wave] = mine; parts.alike[wave] = alike; }
+    __syncthreads();
+    differ &= wave_or(parts.differ[lane % W]);
+    if (differ == 0u) {                                    // all equal: in order
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) at[r] = 4u * (first + 64u * r);
+        return true;
+    }
+    const uint32_t high = 32u - (uint32_t)__builtin_clz(differ);
+    const uint32_t width = high < log_bins ? high : log_bins, shift = high - width;
+    // (bits that never differ, as low ones of numbers with few digits, make no bins)
+    if (n >> __builtin_popcount(differ >> shift) >= kBinMean || wave_sum(lane < W ? parts.alike[lane % W] : 0u) >= kAlikeMost) { __syncthreads(); return false; }
+
+    // Rows in batches of four, their accesses to LDS on their way together: one after the other, each row waits for its own.  (The
+    // scheduler is kept from putting a row's uses back between the next row's accesses.)  Lanes past the end add nothing to
+    // their bins and keep the places that they have.
+    const auto batches = [=](auto body) {
+        in_batches<ITEMS, kBatch>([&](auto r0, auto rows) {
+            body((int)r0, (int)rows, wave_first + 64u * (uint32_t)(r0 + rows) > n);
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+    const auto bin_of = [=](uint32_t k) {
+        asm("" : "+v"(k));                                 // (nothing, here and below, is kept from one use of a key to the next: registers)
+        return __builtin_amdgcn_ubfe(k, shift, width);
+    };
+    const auto word_of = [=](uint32_t bin) { return (uint32_t *)((char *)bins + ((bin << 1) & ~3u)); };
+    const auto index_of = [=](int r) {
+        uint32_t i = first;
+        asm("" : "+v"(i));
+        return i + 64u * r;
+    };
+
+    // ---- count
+    batches([&](int r0, int rows, bool ends) {
+        uint32_t bin[kBatch], one[kBatch];
+#pragma unroll
+        for (int q = 0; q < kBatch; ++q) if (q < rows) { bin[q] = bin_of(key[r0 + q]); one[q] = 1u; }
+        if (ends) {
+#pragma unroll
+            for (int q = 0; q < kBatch; ++q) if (q < rows) {
+                const uint32_t i = index_of(r0 + q);
+                if (i >= n) { bin[q] = __builtin_amdgcn_ubfe(i, 0u, width); one[q] = 0u; }      // (all over the bins: lanes that add to one go one after the other)
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < kBatch; ++q) if (q < rows) at[r0 + q] = atomicAdd(word_of(bin[q]), one[q] << ((bin[q] << 4) & 31u));
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < kBatch; ++q) if (q < rows) at[r0 + q] = __builtin_amdgcn_ubfe(at[r0 + q], bin[q] << 4, 16u);
+    });
+    __syncthreads();
+
+    // ---- counters -> first places
+    // (a thread's words, 8 kBinChunks at most, as uint4 where it has as many)
+    const uint32_t words = 1u << (width - 1u), each = words <= 4u * kThreads ? 4u : words / kThreads;
+    u32x4 w[kBinChunks];
+    uint32_t sum = 0u, most = 0u;
+#pragma unroll
+    for (uint32_t c = 0; c < kBinChunks; ++c) {
+        w[c] = 4u * c < each && tid * each < words ? *(const u32x4 *)(bins + tid * each + 4u * c) : u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t lo = w[c][i] & 0xFFFFu, hi = w[c][i] >> 16;
+            sum += lo + hi;
+            most = most > lo ? most : lo;
+            most = most > hi ? most : hi;
+        }
+    }
+    const uint32_t inc = wave_inclusive_scan(sum);
+    most = wave_max(most);
+    if (lane == 63u) { parts.sum[wave] = inc; parts.most[wave] = most; }
+    __syncthreads();
+    most = wave_max(parts.most[lane % W]);
+    if (most > kBinMost) return false;
+    uint32_t place = wave_sum(lane < wave ? parts.sum[lane % W] : 0u) + inc - sum;
+#pragma unroll
+    for (uint32_t c = 0; c < kBinChunks; ++c) {
+        if (4u * c < each && tid * each < words) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const uint32_t second = place + (w[c][i] & 0xFFFFu);
+                const uint32_t both = place | second << 16;
+                place = second + (w[c][i] >> 16);
+                w[c][i] = both;
+            }
+            *(u32x4 *)(bins + tid * each + 4u * c) = w[c];
+        }
+    }
+    if (tid == 0u) {
+        bins[words] = n;
+        order[kSlots] = order[kSlots + 1u] = ~0u;
+    }
+    __syncthreads();
+
+    // ---- into the bins
+    const uint32_t below = (1u << shift) - 1u;
+    const auto composed = [=](uint32_t k, int r) {
+        asm("" : "+v"(k));
+        return (k & below) << index_bits | index_of(r);
+    };
+    uint32_t range[ITEMS];                                 // first place of the key's bin, and keys of the bin << 16
+    batches([&](int r0, int rows, bool ends) {
+        uint32_t bin[kBatch], w0[kBatch], w1[kBatch];
+#pragma unroll
+        for (int q = 0; q < kBatch; ++q) if (q < rows) {
+            bin[q] = bin_of(key[r0 + q]);
+            w0[q] = word_of(bin[q])[0]; w1[q] = word_of(bin[q])[1];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        uint32_t place[kBatch];
+#pragma unroll
+        for (int q = 0; q < kBatch; ++q) if (q < rows) {
+            const uint32_t both = __builtin_amdgcn_alignbit(w1[q], w0[q], bin[q] << 4), start = both & 0xFFFFu;      // the bin's first place and the next one's
+            range[r0 + q] = both - (start << 16);
+            place[q] = start + at[r0 + q];
+            at[r0 + q] = start;
+        }
+        if (ends) {
+#pragma unroll
+            for (int q = 0; q < kBatch; ++q) if (q < rows) {
+                const uint32_t i = index_of(r0 + q);
+                if (i >= n) { range[r0 + q] = 0u; place[q] = at[r0 + q] = i; }
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < kBatch; ++q) if (q < rows) order[place[q]] = composed(key[r0 + q], r0 + q);
+    });
+    __syncthreads();
+
+    // ---- the keys of its bin that go in front of each
+    // (a key alone in its bin, and one of two, reads the two words behind all keys from there on: one address, no conflicts)
+    const auto two_of = [=](uint32_t in) { return order + (in >= 2u << 16 ? in & 0xFFFFu : kSlots); };
+    const auto more_of = [=](uint32_t in) { return order + (in >= 3u << 16 ? (in & 0xFFFFu) + 2u : kSlots); };
+    batches([&](int r0, int rows, bool) {
+        uint32_t x[kBatch][4];
+#pragma unroll
+        for (int q = 0; q < kBatch; ++q) if (q < rows) {
+            const uint32_t *two = two_of(range[r0 + q]), *more = more_of(range[r0 + q]);
+            x[q][0] = two[0]; x[q][1] = two[1]; x[q][2] = more[0]; x[q][3] = more[1];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < kBatch; ++q) if (q < rows) {
+            const int r = r0 + q;
+            const uint32_t mine = composed(key[r], r);
+            at[r] += (uint32_t)(x[q][0] < mine);
+            at[r] += (uint32_t)(x[q][1] < mine);
+            at[r] += (uint32_t)(x[q][2] < mine);
+            at[r] += (uint32_t)((range[r] >= 4u << 16) & (x[q][3] < mine));
+        }
+    });
+    if (most > 4u) {
+        in_batches<ITEMS, 1>([&](auto r, auto) {
+            const uint32_t count = range[r] >> 16;
+            if (__ballot(count > 4u)) {
+                const uint32_t mine = composed(key[r], r), *bin = order + (range[r] & 0xFFFFu);
+#pragma unroll 1
+                for (uint32_t j = 4u; j < most; ++j)
+                    if (j < count) at[r] += (uint32_t)(bin[j] < mine);
+            }
+        });
+    }
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) at[r] *= 4u;
+    __syncthreads();
+    return true;
+}
+
 // ------------------------------------------------------------------------- a sort in one workgroup
 //
 // A whole sort of few keys, or a bucket of the keys that a first pass on the top digit has split.  What bounds it is the ranking's
@@ -609,13 +850,24 @@ struct BlockArgs {
     const Buckets *buckets;               // null: one workgroup sorts all keys; else workgroup b those of bucket b, if there are buckets
     uint32_t n;                           // keys in all
     Passes P;                             // a bucket's digits, or all
+    uint32_t bits;                        // the bits they cover, from the lowest on
 };
+// Bins for up to 20 rows a lane (24 would not do with the registers): their counters lie behind as many keys, in part where 24 rows have theirs.
+constexpr int kBinFewItems = 3, kBinItems = 20;
+constexpr uint32_t kLogBins = 15, kBinsAt = 64u * kBlockWaves * kBinItems + kBinMost, kBinWords = (1u << kLogBins) / 2u + 4u;
 struct BlockLds {
     uint32_t order[kBlockCapacity];
-    alignas(16) uint16_t cnt[kBlockWaves][kDigits];
-    uint64_t masks[kBlockWaves][kDigits];
+    union {
+        struct {
+            alignas(16) uint16_t cnt[kBlockWaves][kDigits];
+            uint64_t masks[kBlockWaves][kDigits];
+        };
+        uint32_t bins_end[kBinsAt + kBinWords - kBlockCapacity];
+    };
     uint32_t part[4];
+    BinParts<kBlockWaves> bin_parts;
 };
+static_assert(offsetof(BlockLds, bins_end) == 4 * kBlockCapacity && kBinsAt % 4 == 0, "the bins' counters, from order + kBinsAt on, are the struct's own");
 static_assert(sizeof(BlockLds) <= 160 * 1024, "LDS of a compute unit");
 
 template <int ITEMS, bool VALS>
@@ -628,15 +880,56 @@ __device__ __forceinline__ void sort_in_block(const BlockArgs &B, uint32_t begin
     const uint32_t first = (uint32_t)wave * 64u * ITEMS + (uint32_t)lane;
     const uint32_t *keys = B.keys + begin, *vals = VALS ? B.vals + begin : nullptr;
     uint32_t key[ITEMS], val[VALS ? ITEMS : 1], at[ITEMS];
+    // (a 32-bit offset from a uniform address: 64-bit ones of every row would be kept from the loads to the stores)
+    const uint32_t lane4 = 4u * first;
+    auto row = [=](auto *p, int r) { return (decltype(p))((char *)(p + 64 * r) + lane4); };
+    // (past the end the last key is read again: no branches, so that all loads are on their way together)
+    auto load = [=](const uint32_t *p, int r) {
+        uint32_t i = first;
+        asm("" : "+v"(i));                                 // (not kept from keys to payloads, nor from loads to stores: registers)
+        i += 64u * r;
+        return *(const uint32_t *)((const char *)p + 4u * (i < n ? i : n - 1u));
+    };
 #pragma unroll
-    for (int r = 0; r < ITEMS; ++r) {
-        const uint32_t i = first + 64u * r;
-        key[r] = i < n ? keys[i] : ~0u;                    // past the end: last in every pass
-        if constexpr (VALS) val[r] = i < n ? vals[i] : 0u;
+    for (int r = 0; r < ITEMS; ++r) key[r] = load(keys, r);
+    const auto load_vals = [&] {
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) val[r] = load(vals, r);
+    };
+    uint32_t *keys_out = B.keys_out + begin, *vals_out = VALS ? B.vals_out + begin : nullptr;
+    uint32_t differ = ~0u;                                 // bits that the keys differ in, or more
+    const auto by_bins = [&] {
+        if constexpr (ITEMS >= kBinFewItems && ITEMS <= kBinItems) return places_by_bins<W, ITEMS, kLogBins>(key, first, n, keys[0], B.bits, s.order, s.order + kBinsAt, s.bin_parts, at, differ);
+        else return false;
+    };
+    if (by_bins()) {
+        if constexpr (VALS) load_vals();
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r)
+            *(uint32_t *)((char *)s.order + at[r]) = key[r];
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r)
+            if (first + 64u * r < n) *row(keys_out, r) = s.order[first + 64u * r];
+        if constexpr (VALS) {
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < ITEMS; ++r)
+                *(uint32_t *)((char *)s.order + at[r]) = val[r];
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < ITEMS; ++r)
+                if (first + 64u * r < n) *row(vals_out, r) = s.order[first + 64u * r];
+        }
+        return;
     }
+    if constexpr (VALS) load_vals();
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) key[r] = first + 64u * r < n ? key[r] : ~0u;                  // past the end: last in every pass
     for (int i = lane; i < kDigits; i += 64) s.masks[wave][i] = 0ull;
     for (int p = 0; p < B.P.count; ++p) {
         const Digit g = B.P.digit[p];
+        if (digit_of(differ, g) == 0u) continue;           // (the keys stay where they are)
         ((CounterQuad *)s.cnt[wave])[lane] = 0u;
         wavefront_sync();
         rank_rows<ITEMS, (ITEMS <= 20)>(key, g, s.cnt[wave], at, s.masks[wave], (int)n - (int)first);       // (24 rows with payloads: registers)
@@ -660,13 +953,11 @@ __device__ __forceinline__ void sort_in_block(const BlockArgs &B, uint32_t begin
         }
         // (the next pass's writes to s.order come after its barriers)
     }
-    uint32_t *keys_out = B.keys_out + begin, *vals_out = VALS ? B.vals_out + begin : nullptr;
 #pragma unroll
     for (int r = 0; r < ITEMS; ++r) {
-        const uint32_t i = first + 64u * r;
-        if (i < n) {
-            keys_out[i] = key[r];
-            if constexpr (VALS) vals_out[i] = val[r];
+        if (first + 64u * r < n) {
+            *row(keys_out, r) = key[r];
+            if constexpr (VALS) *row(vals_out, r) = val[r];
         }
     }
 }
@@ -795,10 +1086,11 @@ tcuscan_status_t tcuscan_internal_digit_sort(void *d_keys, void *d_vals, size_t 
     tcuscan_internal_chain_knobs(&use_tickets, &spin_limit, &mute_tile);
     const bool wide = n >= StatusWord<uint32_t>::kUnknown;
     if (n <= kBlockSortMax) {
-        BlockArgs B = {(const uint32_t *)d_keys, (const uint32_t *)d_vals, (uint32_t *)d_keys, (uint32_t *)d_vals, nullptr, (uint32_t)n, P};
+        BlockArgs B = {(const uint32_t *)d_keys, (const uint32_t *)d_vals, (uint32_t *)d_keys, (uint32_t *)d_vals, nullptr, (uint32_t)n, P, (uint32_t)bits};
         if (n <= kBlockSortFew || P.count < 2) return launch_block_sort(B, 1, s) == hipSuccess ? TCUSCAN_OK : TCUSCAN_ERR_HIP;
         B.keys = (const uint32_t *)d_keys_tmp; B.vals = (const uint32_t *)d_vals_tmp; B.buckets = (const Buckets *)d_scratch;
         split_digits(bits - 8, B.P);
+        B.bits = (uint32_t)bits - 8u;
         SpreadArgs A = {(const uint32_t *)d_keys, (const uint32_t *)d_vals, (uint32_t *)d_keys_tmp, (uint32_t *)d_vals_tmp, (Buckets *)d_scratch, (uint32_t)n, {bits - 8, 8}};
         void *args[] = {&A};
         const void *fn = d_vals ? (const void *)spread_kernel<true> : (const void *)spread_kernel<false>;
@@ -848,7 +1140,7 @@ tcuscan_status_t tcuscan_internal_digit_sort(void *d_keys, void *d_vals, size_t 
         uint32_t *t = src_k; src_k = dst_k; dst_k = t;
         t = src_v; src_v = dst_v; dst_v = t;
     }
-    BlockArgs B = {dst_k, dst_v, (uint32_t *)d_keys, (uint32_t *)d_vals, buckets, (uint32_t)n, rest};       // (the buckets are where the first pass puts them)
+    BlockArgs B = {dst_k, dst_v, (uint32_t *)d_keys, (uint32_t *)d_vals, buckets, (uint32_t)n, rest, (uint32_t)bits - 8u};       // (the buckets are where the first pass puts them)
     const bool v = d_vals != nullptr, together = buckets_wanted && n <= kTogetherMax;
     // (passes that seldom have anything to do are cheaper with fewer, larger tiles; where they do, 3.2 million pairs take 105.5 us with
     // 8 rows per lane and 110 with 16, 2^22 the same with both)

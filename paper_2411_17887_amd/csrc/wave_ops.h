@@ -50,6 +50,19 @@ template <class A> __device__ __forceinline__ A wave_sum(A v)
 {
     return acc_from_bits<A>((uint32_t)__builtin_amdgcn_readlane((int)acc_bits(wave_inclusive_scan(v)), 63));
 }
+// Bits set in any lane / the largest of the 64 lanes' values, wave-uniform.
+template <class Fold> __device__ __forceinline__ uint32_t wave_fold(uint32_t v, Fold fold)
+{   // (0 is the neutral element)
+    v = fold(v, dpp0<kRowShr + 1>(v));
+    v = fold(v, dpp0<kRowShr + 2>(v));
+    v = fold(v, dpp0<kRowShr + 4>(v));
+    v = fold(v, dpp0<kRowShr + 8>(v));
+    v = fold(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kRowBcast15, 0xa, 0xf, false));
+    v = fold(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kRowBcast31, 0xc, 0xf, false));
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+__device__ __forceinline__ uint32_t wave_or(uint32_t v)  { return wave_fold(v, [](uint32_t a, uint32_t b) { return a | b; }); }
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) { return wave_fold(v, [](uint32_t a, uint32_t b) { return a > b ? a : b; }); }
 constexpr int kWaveShr1 = 0x138;   // DPP control: shift right by one lane across the whole wavefront
 template <class A> __device__ __forceinline__ A wave_shift_up(A v)
 {   // lane l receives v[l - 1], lane 0 receives 0
