@@ -332,7 +332,8 @@ tcuscan_status_t tcuscan_compact_u32(const void *d_values, const void *d_mask, v
  * tile's keys, takes the carry of every bucket from the tiles before and stores the tile in order; a full sort is four
  * passes and one reading of the keys for the bucket sizes (up to 8192 keys: one kernel, one workgroup; from there one pass on the
  * top eight bits and a workgroup per bucket, up to 16384 keys on more than 8 bits, and up to 6,055,225 keys on more than 16 if no
- * bucket is too large).  d_flags is not used,
+ * bucket is too large; two passes on the top 13 or 14 bits and a workgroup per bucket for 3 * 2^23 to 77,004,800 keys on 26 bits and
+ * more, 25 in part, if no bucket has more than 10,240 keys).  d_flags is not used,
  * d_positions holds bucket sizes and status words.  tcuscan_set_sort_fusion(2) splits on one bit per pass in a
  * fused kernel (flags built from the keys, scanned on the MFMA unit, keys scattered), tcuscan_set_sort_fusion(0) selects
  * the three-kernel form of the reduction (mask kernel, tcuscan_exclusive, scatter kernel per bit), which is also what

@@ -15,7 +15,8 @@
 // where they do not, that first pass is the least significant one and the others follow (random keys, us in four passes / with
 // buckets: 100,000 36.6 / 24.4, 10^6 61.6 / 34.4, with payloads 76.0 / 42.6, 2^22 104 / 61, with payloads 120 / 73; keys that do
 // not split, 10^6 equal ones 55.8 / 57.6, normally distributed floats 61.5 / 62.5, 2^22 103.7 / 103.4).  Up to kBlockSortFew keys one workgroup does
-// everything: one launch, keys and payloads read and written once.
+// everything: one launch, keys and payloads read and written once.  Sorts of 3 * 2^23 to 77,004,800 keys do with two passes in the same way (2^26
+// random keys 664 -> 526 us).
 
 #include <hip/hip_runtime.h>
 #include <stddef.h>
@@ -33,6 +34,7 @@ extern "C" void tcuscan_internal_chain_knobs(unsigned *ticket, unsigned *spin_li
 namespace {
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 typedef uint64_t CounterQuad __attribute__((may_alias));   // four 16-bit counters in LDS
 
 constexpr int kDigits = 256;
@@ -187,10 +189,10 @@ template <class T> __device__ __forceinline__ T sum_of_tables(const T *hist, uin
     for (uint32_t t = 0; t < kTables; ++t) sum += x[t];
     return sum;
 }
-__global__ __launch_bounds__(kHistThreads) void digit_histograms_kernel(HistArgs H)
+constexpr int kHistWords = kMaxPasses * kDigits * kHistCopies;
+__device__ __forceinline__ void digit_histograms(const HistArgs &H, uint32_t *s_hist)
 {
-    __shared__ uint32_t s_hist[kMaxPasses * kDigits * kHistCopies];
-    for (int i = threadIdx.x; i < kMaxPasses * kDigits * kHistCopies; i += kHistThreads) s_hist[i] = 0u;
+    for (int i = threadIdx.x; i < kHistWords; i += kHistThreads) s_hist[i] = 0u;
     __syncthreads();
     const uint64_t stride = (uint64_t)gridDim.x * kHistThreads, t0 = (uint64_t)blockIdx.x * kHistThreads + threadIdx.x;
     const uint32_t copy = threadIdx.x & (kHistCopies - 1);
@@ -232,6 +234,11 @@ __global__ __launch_bounds__(kHistThreads) void digit_histograms_kernel(HistArgs
         else if (sum) atomicAdd(at, sum);
     }
 }
+__global__ __launch_bounds__(kHistThreads) void digit_histograms_kernel(HistArgs H)
+{
+    __shared__ uint32_t s_hist[kHistWords];
+    digit_histograms(H, s_hist);
+}
 
 // ------------------------------------------------------------------------- one pass over the array
 
@@ -256,6 +263,9 @@ constexpr size_t kBlockSortMax = 16384;                                         
 enum : uint32_t { kNotSplit = 0u, kSplit = 1u };
 struct Buckets { uint32_t split; uint32_t start[kDigits]; };
 
+// Keys from `base` on, `keys` of them (0: no tile), of a range; the range's first tile has `head`.
+struct TileOfRange { uint32_t base, keys, range, head; };
+
 struct PassArgs {
     const uint32_t *keys, *vals;
     uint32_t *keys_out, *vals_out;
@@ -275,9 +285,15 @@ struct PassArgs {
     Buckets *buckets;
     Digit top;
     uint32_t bucket_max;
+    // Sorts that may take two passes and small buckets (null otherwise): whether they do, and if so: the first goes by `top` and top_hist, one
+    // table; the second goes by `top` in each range of keys that the first has made, whose tiles `ranges` lists and whose buckets begin at
+    // range_start; later passes have nothing to do.
+    const TileOfRange *ranges;
+    const uint32_t *range_start;
+    const uint32_t *split;
 };
 
-enum PassRole { kPlainPass, kChoosingPass, kLaterPass };
+enum PassRole { kPlainPass, kChoosingPass, kLaterPass, kFirstOfTwo, kSecondOfTwo };
 
 template <int ITEMS>
 __device__ __forceinline__ void load_rows(const uint32_t *src, uint32_t first, uint32_t valid, bool whole, bool stream, uint32_t fill, uint32_t (&x)[ITEMS])
@@ -381,10 +397,22 @@ __device__ __forceinline__ void digit_pass(const PassArgs &A, PassLds<W, ITEMS, 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (tid == 0) s.abort = 0u;
-    const uint64_t base = (uint64_t)tile * kTile;
-    const uint32_t valid = A.n - base < kTile ? (uint32_t)(A.n - base) : kTile;
+    uint64_t base = (uint64_t)tile * kTile;
+    bool head = tile == 0u, of_range = false;              // the first of a chain; a chain per range
+    uint32_t valid = A.n - base < kTile ? (uint32_t)(A.n - base) : kTile, range = 0u;
     Digit g = A.digit;
-
+    if constexpr (ROLE == kSecondOfTwo) {                  // (as many workgroups as there may be tiles)
+        const TileOfRange at_range = A.ranges[tile];
+        of_range = *A.split != kNotSplit;
+        if (of_range) {
+            base = (uint32_t)__builtin_amdgcn_readfirstlane((int)at_range.base);
+            valid = (uint32_t)__builtin_amdgcn_readfirstlane((int)at_range.keys);
+            range = (uint32_t)__builtin_amdgcn_readfirstlane((int)at_range.range);
+            head = __builtin_amdgcn_readfirstlane((int)at_range.head) != 0;
+            g = A.top;
+        }
+        if (of_range ? valid == 0u : base >= A.n) return;
+    }
     // ---- the keys, in rows of 64 per wavefront; keys past the end have the highest digit and come last among its keys
     const uint32_t first = (uint32_t)wave * 64u * ITEMS + (uint32_t)lane;
     uint32_t key[ITEMS], at[ITEMS];
@@ -399,6 +427,10 @@ __device__ __forceinline__ void digit_pass(const PassArgs &A, PassLds<W, ITEMS, 
         if (tile == 0u && tid == 0) A.buckets->split = split ? kSplit : kNotSplit;
         if (split) { g = A.top; hist = A.top_hist; }
     }
+    uint32_t tables = A.tables;
+    if constexpr (ROLE == kFirstOfTwo) {
+        if (*A.split != kNotSplit) { g = A.top; hist = A.top_hist; tables = 1u; }
+    }
     wavefront_sync();
     rank_rows<ITEMS>(key, g, s_cnt[wave], at);
     __syncthreads();
@@ -409,7 +441,7 @@ __device__ __forceinline__ void digit_pass(const PassArgs &A, PassLds<W, ITEMS, 
     Word win[kWindow];
     uint32_t count, start;
     scan_counters<W, kUnit<ITEMS, W>>(s_cnt, s_part, count, start, [&](uint32_t c) {
-        if (tile != 0u) {
+        if (!head) {
             if (speaks) __hip_atomic_store(column + (size_t)tile * kDigits, S::make(kCountOfTile, c), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             request_window((const Word *)A.status, (uint32_t)tid, (int32_t)tile - 1, win);
         }
@@ -424,10 +456,12 @@ __device__ __forceinline__ void digit_pass(const PassArgs &A, PassLds<W, ITEMS, 
 
     // ---- the chain arrives: where the tile's keys of each digit go
     Word before = 0u;                                      // keys in front of the tile's first with this thread's digit
-    if (tile == 0u) {                                      // (uniform over the workgroup)
+    if (of_range && head) {                                // (uniform over the workgroup)
+        if (tid < 1 << g.width) before = A.range_start[(range << g.width) + (uint32_t)tid];
+    } else if (head) {
         uint32_t h = 0u, inc = 0u;
         if (tid < kDigits) {
-            h = sum_of_tables(hist + tid, A.tables);
+            h = sum_of_tables(hist + tid, tables);
             inc = wave_inclusive_scan(h);
             if (lane == 63) s_part[wave] = inc;
         }
@@ -487,7 +521,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(sizeof(W
 {
     __shared__ PassLds<W, ITEMS, Word> s;
     if constexpr (ROLE == kLaterPass) {
-        if (A.buckets->split != kNotSplit) return;
+        if (*A.split != kNotSplit) return;
     }
     digit_pass<W, ITEMS, VALS, Word, ROLE>(A, s, take_tile(A, s.part));
 }
@@ -617,7 +651,7 @@ __global__ __launch_bounds__(64 * kSpreadWaves) void spread_kernel(SpreadArgs A)
 constexpr uint32_t kBinMost = 16;                          // keys of a bin, at most
 constexpr uint32_t kBinMean = 2;                           // a bin has fewer on average
 constexpr uint32_t kAlikeMost = 6;                         // pairs of a sample that share a bin: fewer
-template <int W> struct BinParts { uint32_t differ[W], alike[W], sum[W], most[W]; };
+template <int W> struct BinParts { uint32_t differ[W], alike[W], sum[64], most[W]; };
 
 // body(r0, rows) for rows r0 .. r0 + rows - 1 of ITEMS, BATCH at a time, each call with constants of its own.
 template <int N> struct Constant { constexpr __device__ __forceinline__ operator int() const { return N; } };
@@ -644,6 +678,7 @@ __device__ __forceinline__ bool places_by_bins(const uint32_t (&key)[ITEMS], uin
     constexpr uint32_t kThreads = 64 * W, kBinChunks = (1u << MAX_LOG) / 2u / kThreads / 4u;
     constexpr int kBatch = 4;
     constexpr uint32_t kSlots = kThreads * ITEMS;
+    static_assert(W * kBinChunks <= 64, "a lane for each part of the counters");
     const uint32_t tid = threadIdx.x, lane = tid & 63u;
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
     const uint32_t wave_first = (uint32_t)__builtin_amdgcn_readfirstlane((int)first);
@@ -652,15 +687,15 @@ __device__ __forceinline__ bool places_by_bins(const uint32_t (&key)[ITEMS], uin
     log_bins = log_bins < MAX_LOG ? log_bins : MAX_LOG;
     for (uint32_t i = 4u * tid; i < 1u << (log_bins - 1u); i += 4u * kThreads)
         *(u32x4 *)(bins + i) = u32x4{0u, 0u, 0u, 0u};
-    uint32_t mine = 0u;
+    uint32_t own = 0u;
 #pragma unroll
-    for (int r = 0; r < ITEMS; ++r) mine |= key[r] ^ key0;
-    mine = wave_or(mine);
+    for (int r = 0; r < ITEMS; ++r) own |= key[r] ^ key0;
+    own = wave_or(own);
     // Keys that crowd in a part of their range are mostly seen in a sample: a lane's first keys, 64 places apart, that fall into one bin.
     // (normally distributed floats, us without / with it / by passes alone: 3000 8.3 / 8.0 / 7.6, 5000 11.3 / 11.0 / 10.4; pairs, 2100 8.1 / 7.6 / 6.8)
     uint32_t alike = 0u;
     constexpr int kSample = ITEMS < 4 ? ITEMS : 4;
-    const uint32_t range_of_wave = mine & differ;
+    const uint32_t range_of_wave = own & differ;
     if (wave_first + 64u * kSample <= n && range_of_wave != 0u) {
         const uint32_t top = 32u - (uint32_t)__builtin_clz(range_of_wave);
         const uint32_t window = differ & (top > log_bins ? ~0u << (top - log_bins) : ~0u);
@@ -669,7 +704,7 @@ __device__ __forceinline__ bool places_by_bins(const uint32_t (&key)[ITEMS], uin
 #pragma unroll
             for (int b = 0; b < a; ++b) alike += (uint32_t)__builtin_popcountll(__ballot(((key[a] ^ key[b]) & window) == 0u));
     }
-    if (lane == 0u) { parts.differ[wave] = mine; parts.alike[wave] = alike; }
+    if (lane == 0u) { parts.differ[wave] = own; parts.alike[wave] = alike; }
     __syncthreads();
     differ &= wave_or(parts.differ[lane % W]);
     if (differ == 0u) {                                    // all equal: in order
@@ -691,11 +726,16 @@ __device__ __forceinline__ bool places_by_bins(const uint32_t (&key)[ITEMS], uin
             __builtin_amdgcn_sched_barrier(0);
         });
     };
-    const auto bin_of = [=](uint32_t k) {
+    // Word i counts bins i and words + i, in its lower and upper half: both halves are added up at once.
+    const uint32_t words = 1u << (width - 1u);
+    const auto word_of = [=](uint32_t k) {
         asm("" : "+v"(k));                                 // (nothing, here and below, is kept from one use of a key to the next: registers)
-        return __builtin_amdgcn_ubfe(k, shift, width);
+        return (uint32_t *)((char *)bins + 4u * __builtin_amdgcn_ubfe(k, shift, width - 1u));
     };
-    const auto word_of = [=](uint32_t bin) { return (uint32_t *)((char *)bins + ((bin << 1) & ~3u)); };
+    const auto half_of = [=](uint32_t k) {                 // 0 or 16
+        asm("" : "+v"(k));
+        return __builtin_amdgcn_ubfe(k, high - 1u, 1u) << 4;
+    };
     const auto index_of = [=](int r) {
         uint32_t i = first;
         asm("" : "+v"(i));
@@ -704,131 +744,128 @@ __device__ __forceinline__ bool places_by_bins(const uint32_t (&key)[ITEMS], uin
 
     // ---- count
     batches([&](int r0, int rows, bool ends) {
-        uint32_t bin[kBatch], one[kBatch];
+        uint32_t half[kBatch], one[kBatch], *word[kBatch];
 #pragma unroll
-        for (int q = 0; q < kBatch; ++q) if (q < rows) { bin[q] = bin_of(key[r0 + q]); one[q] = 1u; }
+        for (int q = 0; q < kBatch; ++q) if (q < rows) { half[q] = half_of(key[r0 + q]); word[q] = word_of(key[r0 + q]); one[q] = 1u << half[q]; }
         if (ends) {
 #pragma unroll
             for (int q = 0; q < kBatch; ++q) if (q < rows) {
                 const uint32_t i = index_of(r0 + q);
-                if (i >= n) { bin[q] = __builtin_amdgcn_ubfe(i, 0u, width); one[q] = 0u; }      // (all over the bins: lanes that add to one go one after the other)
+                if (i >= n) { word[q] = bins + (i & (words - 1u)); one[q] = 0u; }      // (all over the bins: lanes that add to one go one after the other)
             }
         }
 #pragma unroll
-        for (int q = 0; q < kBatch; ++q) if (q < rows) at[r0 + q] = atomicAdd(word_of(bin[q]), one[q] << ((bin[q] << 4) & 31u));
+        for (int q = 0; q < kBatch; ++q) if (q < rows) at[r0 + q] = atomicAdd(word[q], one[q]);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int q = 0; q < kBatch; ++q) if (q < rows) at[r0 + q] = __builtin_amdgcn_ubfe(at[r0 + q], bin[q] << 4, 16u);
+        for (int q = 0; q < kBatch; ++q) if (q < rows) at[r0 + q] = __builtin_amdgcn_ubfe(at[r0 + q], half[q], 16u);
     });
     __syncthreads();
 
     // ---- counters -> first places
-    // (a thread's words, 8 kBinChunks at most, as uint4 where it has as many)
-    const uint32_t words = 1u << (width - 1u), each = words <= 4u * kThreads ? 4u : words / kThreads;
+    // (Four neighbouring words a thread at a time, the workgroup's one after the other.  Sixteen in a row for a thread would mean one sum for it
+    // instead of four, but threads 64 bytes apart meet in the banks: a quarter of all that LDS does here.)
+    const auto has = [=](uint32_t c) { return 4u * (c * kThreads + tid) < words; };
     u32x4 w[kBinChunks];
-    uint32_t sum = 0u, most = 0u;
+    uint32_t inc[kBinChunks], sums[kBinChunks];            // of both halves
+    u16x2 mosts = {0, 0};
 #pragma unroll
     for (uint32_t c = 0; c < kBinChunks; ++c) {
-        w[c] = 4u * c < each && tid * each < words ? *(const u32x4 *)(bins + tid * each + 4u * c) : u32x4{0u, 0u, 0u, 0u};
+        w[c] = has(c) ? *(const u32x4 *)(bins + 4u * (c * kThreads + tid)) : u32x4{0u, 0u, 0u, 0u};
+        sums[c] = w[c][0] + w[c][1] + w[c][2] + w[c][3];
+        inc[c] = wave_inclusive_scan(sums[c]);
+        if (lane == 63u) parts.sum[c * W + wave] = inc[c];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const uint32_t lo = w[c][i] & 0xFFFFu, hi = w[c][i] >> 16;
-            sum += lo + hi;
-            most = most > lo ? most : lo;
-            most = most > hi ? most : hi;
-        }
+        for (int i = 0; i < 4; ++i) mosts = __builtin_elementwise_max(mosts, __builtin_bit_cast(u16x2, (uint32_t)w[c][i]));
     }
-    const uint32_t inc = wave_inclusive_scan(sum);
-    most = wave_max(most);
-    if (lane == 63u) { parts.sum[wave] = inc; parts.most[wave] = most; }
+    uint32_t most = wave_max(mosts[0] > mosts[1] ? mosts[0] : mosts[1]);
+    if (lane == 63u) parts.most[wave] = most;
     __syncthreads();
     most = wave_max(parts.most[lane % W]);
     if (most > kBinMost) return false;
-    uint32_t place = wave_sum(lane < wave ? parts.sum[lane % W] : 0u) + inc - sum;
+    const uint32_t part = lane < W * kBinChunks ? parts.sum[lane % (W * kBinChunks)] : 0u, up_to = wave_inclusive_scan(part);
+    const uint32_t all = uniform_from_lane(up_to, 63);
 #pragma unroll
     for (uint32_t c = 0; c < kBinChunks; ++c) {
-        if (4u * c < each && tid * each < words) {
+        // (the upper half of the bins comes after all of the lower)
+        uint32_t place = uniform_from_lane(up_to - part, (int)(c * W + wave)) + (all << 16) + inc[c] - sums[c];
+        if (has(c)) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const uint32_t second = place + (w[c][i] & 0xFFFFu);
-                const uint32_t both = place | second << 16;
-                place = second + (w[c][i] >> 16);
-                w[c][i] = both;
+                const uint32_t size = w[c][i];
+                w[c][i] = place;
+                place += size;
             }
-            *(u32x4 *)(bins + tid * each + 4u * c) = w[c];
+            *(u32x4 *)(bins + 4u * (c * kThreads + tid)) = w[c];
         }
     }
     if (tid == 0u) {
-        bins[words] = n;
-        order[kSlots] = order[kSlots + 1u] = ~0u;
+        bins[words] = (all & 0xFFFFu) | n << 16;           // (as thread 0 has written it if there are fewer than four)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) order[kSlots + i] = ~0u;
     }
     __syncthreads();
 
     // ---- into the bins
     const uint32_t below = (1u << shift) - 1u;
-    const auto composed = [=](uint32_t k, int r) {
-        asm("" : "+v"(k));
-        return (k & below) << index_bits | index_of(r);
-    };
-    uint32_t range[ITEMS];                                 // first place of the key's bin, and keys of the bin << 16
+    uint32_t mine[ITEMS], count[ITEMS];                    // what keys of a bin are compared by; keys of the bin
     batches([&](int r0, int rows, bool ends) {
-        uint32_t bin[kBatch], w0[kBatch], w1[kBatch];
+        uint32_t w0[kBatch], w1[kBatch], place[kBatch];
 #pragma unroll
         for (int q = 0; q < kBatch; ++q) if (q < rows) {
-            bin[q] = bin_of(key[r0 + q]);
-            w0[q] = word_of(bin[q])[0]; w1[q] = word_of(bin[q])[1];
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        uint32_t place[kBatch];
-#pragma unroll
-        for (int q = 0; q < kBatch; ++q) if (q < rows) {
-            const uint32_t both = __builtin_amdgcn_alignbit(w1[q], w0[q], bin[q] << 4), start = both & 0xFFFFu;      // the bin's first place and the next one's
-            range[r0 + q] = both - (start << 16);
-            place[q] = start + at[r0 + q];
-            at[r0 + q] = start;
-        }
-        if (ends) {
-#pragma unroll
-            for (int q = 0; q < kBatch; ++q) if (q < rows) {
-                const uint32_t i = index_of(r0 + q);
-                if (i >= n) { range[r0 + q] = 0u; place[q] = at[r0 + q] = i; }
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < kBatch; ++q) if (q < rows) order[place[q]] = composed(key[r0 + q], r0 + q);
-    });
-    __syncthreads();
-
-    // ---- the keys of its bin that go in front of each
-    // (a key alone in its bin, and one of two, reads the two words behind all keys from there on: one address, no conflicts)
-    const auto two_of = [=](uint32_t in) { return order + (in >= 2u << 16 ? in & 0xFFFFu : kSlots); };
-    const auto more_of = [=](uint32_t in) { return order + (in >= 3u << 16 ? (in & 0xFFFFu) + 2u : kSlots); };
-    batches([&](int r0, int rows, bool) {
-        uint32_t x[kBatch][4];
-#pragma unroll
-        for (int q = 0; q < kBatch; ++q) if (q < rows) {
-            const uint32_t *two = two_of(range[r0 + q]), *more = more_of(range[r0 + q]);
-            x[q][0] = two[0]; x[q][1] = two[1]; x[q][2] = more[0]; x[q][3] = more[1];
+            const uint32_t *word = word_of(key[r0 + q]);
+            w0[q] = word[0]; w1[q] = word[1];
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int q = 0; q < kBatch; ++q) if (q < rows) {
             const int r = r0 + q;
-            const uint32_t mine = composed(key[r], r);
-            at[r] += (uint32_t)(x[q][0] < mine);
-            at[r] += (uint32_t)(x[q][1] < mine);
-            at[r] += (uint32_t)(x[q][2] < mine);
-            at[r] += (uint32_t)((range[r] >= 4u << 16) & (x[q][3] < mine));
+            const uint32_t half = half_of(key[r]), start = __builtin_amdgcn_ubfe(w0[q], half, 16u);
+            count[r] = __builtin_amdgcn_ubfe(w1[q], half, 16u) - start;
+            place[q] = start + at[r];
+            at[r] = start;
+            mine[r] = (key[r] & below) << index_bits | index_of(r);
+        }
+        if (ends) {
+#pragma unroll
+            for (int q = 0; q < kBatch; ++q) if (q < rows) {
+                const uint32_t i = index_of(r0 + q);
+                if (i >= n) { count[r0 + q] = 0u; place[q] = at[r0 + q] = i; }
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < kBatch; ++q) if (q < rows) order[place[q]] = mine[r0 + q];
+    });
+    __syncthreads();
+
+    // ---- the keys of its bin that go in front of each
+    // (a key alone in its bin, and one of two, reads the words behind all keys from there on: one address, no conflicts)
+    batches([&](int r0, int rows, bool) {
+        uint32_t x[kBatch][4];
+#pragma unroll
+        for (int q = 0; q < kBatch; ++q) if (q < rows) {
+            const int r = r0 + q;
+            const uint32_t *two = order + (count[r] >= 2u ? at[r] : kSlots), *more = order + (count[r] >= 3u ? at[r] : kSlots);
+            x[q][0] = two[0]; x[q][1] = two[1]; x[q][2] = more[2]; x[q][3] = more[3];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < kBatch; ++q) if (q < rows) {
+            const int r = r0 + q;
+            at[r] += (uint32_t)(x[q][0] < mine[r]);
+            at[r] += (uint32_t)(x[q][1] < mine[r]);
+            at[r] += (uint32_t)(x[q][2] < mine[r]);
+            at[r] += (uint32_t)((count[r] >= 4u) & (x[q][3] < mine[r]));
         }
     });
+    // (the few that share it with four and more look it up again: `at` is no longer where it starts)
     if (most > 4u) {
         in_batches<ITEMS, 1>([&](auto r, auto) {
-            const uint32_t count = range[r] >> 16;
-            if (__ballot(count > 4u)) {
-                const uint32_t mine = composed(key[r], r), *bin = order + (range[r] & 0xFFFFu);
+            if (__ballot(count[r] > 4u)) {
+                const uint32_t *bin = order + __builtin_amdgcn_ubfe(*word_of(key[r]), half_of(key[r]), 16u);
 #pragma unroll 1
                 for (uint32_t j = 4u; j < most; ++j)
-                    if (j < count) at[r] += (uint32_t)(bin[j] < mine);
+                    if (j < count[r]) at[r] += (uint32_t)(bin[j] < mine[r]);
             }
         });
     }
@@ -852,28 +889,31 @@ struct BlockArgs {
     Passes P;                             // a bucket's digits, or all
     uint32_t bits;                        // the bits they cover, from the lowest on
 };
-// Bins for up to 20 rows a lane (24 would not do with the registers): their counters lie behind as many keys, in part where 24 rows have theirs.
-constexpr int kBinFewItems = 3, kBinItems = 20;
-constexpr uint32_t kLogBins = 15, kBinsAt = 64u * kBlockWaves * kBinItems + kBinMost, kBinWords = (1u << kLogBins) / 2u + 4u;
-struct BlockLds {
-    uint32_t order[kBlockCapacity];
+// A workgroup of WAVES wavefronts that sorts up to ROWS rows a lane, FEW to BIN_ROWS of them by bins (more would not do with the registers),
+// whose counters lie behind as many keys, in part where more rows have theirs.
+template <int WAVES, int ROWS, int FEW, int BIN_ROWS, uint32_t LOG_BINS> struct BlockLdsOf {
+    static constexpr int kWaves = WAVES, kRows = ROWS, kBinFew = FEW, kBinRows = BIN_ROWS;
+    static constexpr uint32_t kCapacity = 64u * WAVES * ROWS, kLogBins = LOG_BINS, kBinsAt = 64u * WAVES * BIN_ROWS + kBinMost, kBinWords = (1u << LOG_BINS) / 2u + 4u;
+    uint32_t order[kCapacity];
     union {
         struct {
-            alignas(16) uint16_t cnt[kBlockWaves][kDigits];
-            uint64_t masks[kBlockWaves][kDigits];
+            alignas(16) uint16_t cnt[WAVES][kDigits];
+            uint64_t masks[WAVES][kDigits];
         };
-        uint32_t bins_end[kBinsAt + kBinWords - kBlockCapacity];
+        uint32_t bins_end[kBinsAt + kBinWords - kCapacity];
     };
     uint32_t part[4];
-    BinParts<kBlockWaves> bin_parts;
+    BinParts<WAVES> bin_parts;
 };
-static_assert(offsetof(BlockLds, bins_end) == 4 * kBlockCapacity && kBinsAt % 4 == 0, "the bins' counters, from order + kBinsAt on, are the struct's own");
+using BlockLds = BlockLdsOf<kBlockWaves, kBlockItems, 3, 20, 15>;
+static_assert(offsetof(BlockLds, bins_end) == 4 * kBlockCapacity && BlockLds::kBinsAt % 4 == 0, "the bins' counters, from order + kBinsAt on, are the struct's own");
+static_assert(alignof(BlockLds) >= alignof(CounterQuad), "counters cleared four at a time");
 static_assert(sizeof(BlockLds) <= 160 * 1024, "LDS of a compute unit");
 
-template <int ITEMS, bool VALS>
-__device__ __forceinline__ void sort_in_block(const BlockArgs &B, uint32_t begin, uint32_t n, BlockLds &s)
+template <int ITEMS, bool VALS, class Lds>
+__device__ __forceinline__ void sort_in_block(const BlockArgs &B, uint32_t begin, uint32_t n, Lds &s)
 {
-    constexpr int W = kBlockWaves;
+    constexpr int W = Lds::kWaves;
     constexpr uint32_t kU = kUnit<ITEMS, W>;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -899,7 +939,8 @@ __device__ __forceinline__ void sort_in_block(const BlockArgs &B, uint32_t begin
     uint32_t *keys_out = B.keys_out + begin, *vals_out = VALS ? B.vals_out + begin : nullptr;
     uint32_t differ = ~0u;                                 // bits that the keys differ in, or more
     const auto by_bins = [&] {
-        if constexpr (ITEMS >= kBinFewItems && ITEMS <= kBinItems) return places_by_bins<W, ITEMS, kLogBins>(key, first, n, keys[0], B.bits, s.order, s.order + kBinsAt, s.bin_parts, at, differ);
+        if constexpr (ITEMS >= Lds::kBinFew && ITEMS <= Lds::kBinRows)
+            return places_by_bins<W, ITEMS, Lds::kLogBins>(key, first, n, keys[0], B.bits, s.order, s.order + Lds::kBinsAt, s.bin_parts, at, differ);
         else return false;
     };
     if (by_bins()) {
@@ -962,13 +1003,13 @@ __device__ __forceinline__ void sort_in_block(const BlockArgs &B, uint32_t begin
     }
 }
 // 1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 16, 18, 20 or 24 rows per lane.
-template <bool VALS, int ITEMS = 1>
-__device__ __forceinline__ void sort_in_block_of(const BlockArgs &B, uint32_t begin, uint32_t n, BlockLds &s)
+template <bool VALS, int ITEMS = 1, class Lds>
+__device__ __forceinline__ void sort_in_block_of(const BlockArgs &B, uint32_t begin, uint32_t n, Lds &s)
 {
-    if constexpr (ITEMS >= kBlockItems) {
-        sort_in_block<kBlockItems, VALS>(B, begin, n, s);
+    if constexpr (ITEMS >= Lds::kRows) {
+        sort_in_block<Lds::kRows, VALS>(B, begin, n, s);
     } else {
-        if (n <= 64u * kBlockWaves * ITEMS) sort_in_block<ITEMS, VALS>(B, begin, n, s);
+        if (n <= 64u * Lds::kWaves * ITEMS) sort_in_block<ITEMS, VALS>(B, begin, n, s);
         else sort_in_block_of<VALS, ITEMS < 8 ? ITEMS + 1 : ITEMS < 20 ? ITEMS + 2 : ITEMS + 4>(B, begin, n, s);
     }
 }
@@ -976,7 +1017,6 @@ __device__ __forceinline__ void sort_in_block_of(const BlockArgs &B, uint32_t be
 template <bool VALS>
 __device__ __forceinline__ void sort_block_or_bucket(const BlockArgs &B, BlockLds &s)
 {
-    static_assert(alignof(BlockLds) >= alignof(CounterQuad), "counters cleared four at a time");
     uint32_t begin = 0u, n = B.n;
     if (B.buckets) {
         begin = B.buckets->start[blockIdx.x];
@@ -1008,6 +1048,205 @@ __global__ __launch_bounds__(64 * kBlockWaves) void pass_or_buckets_kernel(PassA
     } else {
         const uint32_t tile = take_tile(A, s.pass.part);
         if (tile < tiles) digit_pass<W, ITEMS, VALS, uint32_t, kLaterPass>(A, s.pass, tile);
+    }
+}
+
+// ------------------------------------------------------------------------- two passes and small buckets
+//
+// Sorts of more keys than one pass splits finely enough: two passes, on the upper and, in each of its ranges, the lower half of the top 13 or 14 bits, leave
+// buckets of some 2300 to 4700 keys, which a workgroup of four wavefronts each sorts by the other bits in LDS, in place.  That is three times
+// 8 bytes per key (16 with payloads) where four passes move 8 bytes each; and the second pass has a carry chain per range, of some 32 tiles,
+// and writes into 2 MiB (138 us for 2^26 keys, both by the whole array's chain 144; with six bits 132, with eight 144).
+// What the buckets' sizes are has to be known before the first pass: one table of all 2^14 counts in LDS, one addition per key,
+// in place of four.  Keys that crowd would have buckets too large: a sample of 8192 keys, taken by the kernel that clears the tables, says
+// whether it is worth counting; if the counts then say otherwise, the digits of the four passes are counted after all.
+// us for 2^26 random keys: sample 6, count 63, sizes and starts 10, passes 138 + 138, buckets 157, launches with nothing to do 14 (four
+// passes: 70 + 4 x 144).  What bounds the buckets' kernel is LDS (68 % of its time) and the vector unit (75 %) at 16 wavefronts a compute unit;
+// pairs, 2^25 of them 107 us, the memory.  Tried and dropped: tiles of 8192 and 4096 keys in four and eight smaller workgroups a unit (first pass 176
+// and 258), seven ballots for the seven bits (no change), buckets from the last one on, whose keys the memory-side cache may hold (157 -> 156.5).
+
+constexpr uint32_t kFineLogMost = 14, kSampleQuads = 2048;
+using FineLds = BlockLdsOf<4, 20, 1, 20, 13>;
+static_assert(offsetof(FineLds, bins_end) == 4 * FineLds::kCapacity && FineLds::kBinsAt % 4 == 0 && alignof(FineLds) >= alignof(CounterQuad), "as BlockLds");
+static_assert(4 * sizeof(FineLds) <= 160 * 1024, "four workgroups on a compute unit");
+using FineLargeLds = BlockLdsOf<8, 20, 1, 20, 14>;
+static_assert(offsetof(FineLargeLds, bins_end) == 4 * FineLargeLds::kCapacity && FineLargeLds::kBinsAt % 4 == 0 && alignof(FineLargeLds) >= alignof(CounterQuad), "as BlockLds");
+static_assert(2 * sizeof(FineLargeLds) <= 160 * 1024, "two workgroups on a compute unit");
+
+struct Fine {
+    uint32_t split;                       // are there buckets?
+    uint32_t tried;                       // the sample says so
+    uint32_t large;                       // buckets of more keys than FineLds holds ...
+    uint32_t pad;
+    uint32_t top[kDigits];                // counts of the first pass's digit
+    uint32_t start[1u << kFineLogMost];
+    uint32_t large_at[1u << kFineLogMost];                               // ... and which
+};
+struct FineArgs {
+    HistArgs H;                           // keys, the four passes' digits, status words to clear
+    Fine *fine;
+    uint32_t *counts;                     // [table][bucket], kTables of them
+    TileOfRange *ranges;                  // the second pass's tiles
+    uint32_t tile_keys;
+    uint32_t *clear;                      // words to clear: H.hist and what follows it, up to the status words
+    uint32_t clear_quads;
+    Digit all, second;                    // a bucket's bits, and the lower half of them
+    uint32_t sample_most, sample_wide_most, bucket_most;                 // keys of a sample in a bucket, in a 256th of all buckets; keys of a bucket
+    BlockArgs B;                          // buckets in their places
+};
+
+// One key of each lane to the count of its bucket; `look` gets sums that come out.  Where many lanes agree with the first one they are added at
+// once: keys in order or equal would be added one after the other (2^24 keys in order: the counting kernel 57 -> 16 us, the sample of equal ones 13 -> 8).
+template <class Look> __device__ __forceinline__ void add_to_bucket(uint32_t *counts, uint32_t bucket, Look look)
+{
+    const uint64_t as_first = __ballot(bucket == (uint32_t)__builtin_amdgcn_readfirstlane((int)bucket));
+    const uint32_t all = (uint32_t)__builtin_popcountll(as_first);
+    if (all < 16u) {
+        look(atomicAdd(&counts[bucket], 1u) + 1u);
+    } else {
+        const uint32_t lane = threadIdx.x & 63u;
+        const bool one_of = as_first >> lane & 1u, first = lane == (uint32_t)__builtin_ctzll(as_first);
+        if (!one_of || first) { const uint32_t add = first ? all : 1u; look(atomicAdd(&counts[bucket], add) + add); }
+    }
+}
+
+// Sample and clear.  (The sample: groups of four keys, one from each of kSampleQuads equal parts of the array, not at the same place of each.)
+__global__ __launch_bounds__(kHistThreads) void fine_sample_kernel(FineArgs F)
+{
+    __shared__ uint32_t s_count[1u << kFineLogMost], s_wide[kDigits];
+    const uint32_t tid = threadIdx.x;
+    if (blockIdx.x != 0u) {
+        const uint32_t found = (uint32_t)((const u32x4 *)F.fine - (const u32x4 *)F.clear);      // what workgroup 0 writes
+        for (uint32_t i = (blockIdx.x - 1u) * kHistThreads + tid; i < F.clear_quads; i += (gridDim.x - 1u) * kHistThreads)
+            if (i != found) ((u32x4 *)F.clear)[i] = u32x4{0u, 0u, 0u, 0u};
+        return;
+    }
+    const uint32_t buckets = 1u << F.all.width;
+    const uint32_t part = (uint32_t)(F.H.n / 4u / kSampleQuads);           // quads: at least one
+    u32x4 k[kSampleQuads / kHistThreads];
+#pragma unroll
+    for (uint32_t q = 0; q < kSampleQuads / kHistThreads; ++q) {
+        const uint32_t g = q * kHistThreads + tid;
+        k[q] = ((const u32x4 *)F.H.keys)[(uint64_t)g * part + (g * 0x9E3779B1u >> 8) % part];
+    }
+    for (uint32_t i = tid; i < buckets; i += kHistThreads) s_count[i] = 0u;
+    if (tid < kDigits) s_wide[tid] = 0u;
+    __syncthreads();
+    bool crowded = false;
+#pragma unroll
+    for (uint32_t q = 0; q < kSampleQuads / kHistThreads; ++q)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t bucket = digit_of(k[q][i], F.all);
+            add_to_bucket(s_count, bucket, [&](uint32_t sum) { crowded |= sum > F.sample_most; });
+            add_to_bucket(s_wide, bucket >> (F.all.width - 8), [&](uint32_t sum) { crowded |= sum > F.sample_wide_most; });
+        }
+    const bool any = __syncthreads_or(crowded);
+    if (tid == 0u) { F.fine->split = F.fine->tried = any ? 0u : 1u; F.fine->large = 0u; }
+}
+
+// The buckets' sizes, or the digits' counts.
+__global__ __launch_bounds__(kHistThreads) void fine_count_kernel(FineArgs F)
+{
+    __shared__ uint32_t s_count[kHistWords > (1 << kFineLogMost) ? kHistWords : 1 << kFineLogMost];
+    if (!F.fine->tried) { digit_histograms(F.H, s_count); return; }
+    const HistArgs &H = F.H;
+    const uint32_t tid = threadIdx.x, buckets = 1u << F.all.width;
+    for (uint32_t i = 4u * tid; i < buckets; i += 4u * kHistThreads) *(u32x4 *)(s_count + i) = u32x4{0u, 0u, 0u, 0u};
+    __syncthreads();
+    const uint64_t stride = (uint64_t)gridDim.x * kHistThreads, t0 = (uint64_t)blockIdx.x * kHistThreads + tid, quads = H.n / 4;
+    // (from the last key on: those written last may still be in the memory-side cache.  2^26 keys that were: 71 -> 63 us)
+    const u32x4 *keys4 = (const u32x4 *)H.keys + quads - 1;
+    constexpr int kAhead = 4;
+    u32x4 k[kAhead];
+    uint64_t i = t0;
+    for (; i + (kAhead - 1) * stride < quads; i += kAhead * stride) {
+#pragma unroll
+        for (int a = 0; a < kAhead; ++a) k[a] = H.stream ? __builtin_nontemporal_load(keys4 - (i + a * stride)) : *(keys4 - (i + a * stride));
+#pragma unroll
+        for (int a = 0; a < kAhead; ++a)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) add_to_bucket(s_count, digit_of(k[a][j], F.all), [](uint32_t) {});
+    }
+    for (; i < quads; i += stride) {
+        const u32x4 x = *(keys4 - i);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) add_to_bucket(s_count, digit_of(x[j], F.all), [](uint32_t) {});
+    }
+    if (t0 < (H.n & 3u)) atomicAdd(&s_count[digit_of(H.keys[4 * quads + t0], F.all)], 1u);
+    for (uint64_t q = t0; q < H.status_quads; q += stride) ((u32x4 *)H.status)[q] = u32x4{0u, 0u, 0u, 0u};
+    __syncthreads();
+    uint32_t *table = F.counts + (size_t)(blockIdx.x % kTables) * buckets;
+    for (uint32_t b = tid; b < buckets; b += kHistThreads)
+        if (s_count[b]) atomicAdd(&table[b], s_count[b]);
+}
+
+// Workgroup t: buckets t * 2^second.width on, one per thread.  Their sizes over all tables go to table 0.
+__global__ __launch_bounds__(kDigits) void fine_judge_kernel(FineArgs F)
+{
+    if (!F.fine->tried) return;
+    __shared__ uint32_t s_part[kDigits / 64];
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, buckets = 1u << F.all.width, row = 1u << F.second.width;
+    uint32_t size = 0u;
+    if (tid < row) {
+        const uint32_t b = blockIdx.x * row + tid;
+#pragma unroll
+        for (uint32_t t = 0; t < kTables; ++t) size += F.counts[(size_t)t * buckets + b];
+        F.counts[b] = size;
+        if (size > F.bucket_most) F.fine->split = kNotSplit;
+        if (size > FineLds::kCapacity) F.fine->large_at[atomicAdd(&F.fine->large, 1u)] = b;
+    }
+    const uint32_t sum = wave_sum(size);
+    if (lane == 0u) s_part[tid >> 6] = sum;
+    __syncthreads();
+    if (tid == 0u) F.fine->top[blockIdx.x] = s_part[0] + s_part[1] + s_part[2] + s_part[3];
+}
+
+// Where the buckets start, or, where the sample was wrong, the digits' counts.
+__global__ __launch_bounds__(kHistThreads) void fine_start_kernel(FineArgs F)
+{
+    __shared__ uint32_t s_count[kHistWords];
+    if (!F.fine->tried) return;
+    if (F.fine->split == kNotSplit) { digit_histograms(F.H, s_count); return; }
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6, row = 1u << F.second.width;
+    if (blockIdx.x >= 1u << (F.all.width - F.second.width) || tid >= kDigits) return;        // (the others of the workgroup wait for nobody)
+    // every wavefront adds up what lies in front of the row, and the parts of it in front of its own
+    uint32_t before = 0u, tiles = 0u;
+    for (uint32_t t = lane; t < blockIdx.x; t += 64u) { before += F.fine->top[t]; tiles += (F.fine->top[t] + F.tile_keys - 1u) / F.tile_keys; }
+    const uint32_t base = wave_sum(before), first = wave_sum(tiles);
+    const uint32_t *sizes = F.counts + blockIdx.x * row;
+    before = 0u;
+    for (uint32_t s = lane; s < 64u * wave && s < row; s += 64u) before += sizes[s];
+    before = base + wave_sum(before);
+    const uint32_t size = tid < row ? sizes[tid] : 0u;
+    const uint32_t inc = wave_inclusive_scan(size);
+    if (tid < row) F.fine->start[blockIdx.x * row + tid] = before + inc - size;
+    const uint32_t keys = F.fine->top[blockIdx.x];
+    for (uint32_t i = tid; i * F.tile_keys < keys; i += kDigits) {
+        const uint32_t left = keys - i * F.tile_keys;
+        F.ranges[first + i] = {base + i * F.tile_keys, left < F.tile_keys ? left : F.tile_keys, blockIdx.x, i == 0u ? 1u : 0u};
+    }
+}
+
+template <bool VALS>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void fine_sort_kernel(FineArgs F)
+{
+    __shared__ FineLds s;
+    if (F.fine->split == kNotSplit) return;
+    // (one bucket each: as a loop over buckets this takes too many registers, 157 -> 178 us for 2^26 keys, pairs far worse)
+    const uint32_t size = (uint32_t)__builtin_amdgcn_readfirstlane((int)F.counts[blockIdx.x]), begin = F.fine->start[blockIdx.x];
+    if (size > 1u && size <= FineLds::kCapacity) sort_in_block_of<VALS, 8>(F.B, begin, size, s);
+}
+template <bool VALS>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void fine_sort_large_kernel(FineArgs F)
+{
+    __shared__ FineLargeLds s;
+    if (F.fine->split == kNotSplit) return;
+    for (uint32_t i = blockIdx.x; i < F.fine->large; i += gridDim.x) {
+        const uint32_t b = F.fine->large_at[i];
+        const uint32_t size = (uint32_t)__builtin_amdgcn_readfirstlane((int)F.counts[b]);
+        sort_in_block_of<VALS, 10>(F.B, F.fine->start[b], size < FineLargeLds::kCapacity ? size : FineLargeLds::kCapacity, s);
+        __syncthreads();
     }
 }
 
@@ -1060,6 +1299,20 @@ const void *pass_or_buckets_kernel_for(int items, bool vals)
     return vals ? (const void *)pass_or_buckets_kernel<8, true> : (const void *)pass_or_buckets_kernel<8, false>;
 }
 
+// Two passes and small buckets: as few bits as leave 4700 keys or fewer on average (5120 is what a workgroup has places for), up to 2^14 buckets; the
+// bits that are left are enough for bins, and there are four passes to do otherwise (with three, an odd number starts from a copy).
+// us per sort, four passes / now: 3 * 2^23 random keys 264 / 226, 2^25 342 / 285, pairs 535 / 398, 2^26 664 / 526, 76 million 834 / 610, 2^26 in
+// order 667 / 492.  Keys that crowd pay for six launches with nothing to do, some 20 us: 2^26 normally distributed floats 649 / 674, 2^25 equal pairs 422 / 445, 3 * 2^23
+// floats 256 / 274, and a sort of fewer keys would have paid 8 to 13 % (2^24: 185 / 202, random 187 / 165), so it keeps the four passes.
+constexpr size_t kFineFew = (size_t)3 << 23, kFineMost = (size_t)4700 << kFineLogMost;
+int fine_bits(size_t n)
+{
+    int log = 2;
+    while ((n >> log) > 4700) ++log;
+    return log;
+}
+bool fine_wanted(size_t n, int bits) { return n >= kFineFew && n <= kFineMost && bits > 24 && bits >= fine_bits(n) + 12; }
+
 // `bits` low bits in digits as even as possible.
 void split_digits(int bits, Passes &P)
 {
@@ -1069,6 +1322,68 @@ void split_digits(int bits, Passes &P)
         P.digit[p] = {at < 32 ? at : 0, width};
         at += width;
     }
+}
+
+// `hist`: scratch from a 16-byte boundary on.
+tcuscan_status_t fine_sort(void *d_keys, void *d_vals, size_t n, int bits, void *d_keys_tmp, void *d_vals_tmp, uint32_t *hist, const Passes &P, size_t tiles,
+                           bool around_cache, unsigned use_tickets, unsigned spin_limit, unsigned mute_tile, void *d_fault, hipStream_t s)
+{
+    const int log = fine_bits(n), low = log / 2;
+    const uint32_t buckets = 1u << log;
+    const bool v = d_vals != nullptr;
+    FineArgs F;
+    // scratch: digit counts, tickets, what the kernels find out, the buckets' counts (all cleared), status words
+    uint32_t *tickets = hist + kTables * kTableWords;
+    F.fine = (Fine *)(tickets + kMaxPasses);
+    F.counts = (uint32_t *)(F.fine + 1);
+    F.ranges = (TileOfRange *)(F.counts + kTables * buckets);
+    F.tile_keys = 64u * kPassWaves * 16u;
+    const size_t most_tiles = tiles + ((size_t)1 << (log - low));        // of the second pass
+    uint32_t *status = (uint32_t *)(F.ranges + most_tiles);
+    static_assert(sizeof(Fine) % 16 == 0 && kTableWords % 4 == 0 && kMaxPasses % 4 == 0, "16-byte boundaries");
+    F.clear = hist;
+    F.clear_quads = (uint32_t)(status - hist) / 4u;
+    F.all = {bits - log, log};
+    F.second = {bits - log, low};
+    const Digit top = {bits - log + low, log - low};
+    F.bucket_most = FineLargeLds::kCapacity;
+    // The sample: a 256th of all buckets that holds as many keys as if nine tenths of the largest were in each (keys that crowd gently: bell-shaped), and a bucket
+    // with twice as many as the largest, and eight, which even keys do not come to by chance.
+    const double sample = 4.0 * kSampleQuads, largest = (double)F.bucket_most / (double)n;
+    F.sample_wide_most = (uint32_t)(0.9 * sample * largest * (double)(buckets / kDigits));
+    F.sample_most = (uint32_t)(2.0 * sample * largest) + 8u;
+    const size_t pass_words = most_tiles * kDigits;
+    HistArgs &H = F.H;
+    H.keys = (const uint32_t *)d_keys; H.vals = nullptr; H.keys_copy = H.vals_copy = nullptr;
+    H.hist = hist; H.tables = kTables; H.status = status; H.n = n; H.status_quads = pass_words * P.count / 4; H.P = P; H.stream = around_cache; H.own = false;
+    F.B = {(const uint32_t *)d_keys, (const uint32_t *)d_vals, (uint32_t *)d_keys, (uint32_t *)d_vals, nullptr, (uint32_t)n, {}, (uint32_t)(bits - log)};
+    split_digits(bits - log, F.B.P);
+    void *fine_args[] = {&F};
+    const auto launch = [&](const void *fn, size_t grid, int block, void **args) { return hipLaunchKernel(fn, dim3((unsigned)grid), dim3(block), args, 0, s) == hipSuccess; };
+    if (!launch((const void *)fine_sample_kernel, 1 + 64, kHistThreads, fine_args)) return TCUSCAN_ERR_HIP;
+    if (!launch((const void *)fine_count_kernel, kHistGrid, kHistThreads, fine_args)) return TCUSCAN_ERR_HIP;
+    if (!launch((const void *)fine_judge_kernel, (size_t)1 << (log - low), kDigits, fine_args)) return TCUSCAN_ERR_HIP;
+    if (!launch((const void *)fine_start_kernel, 256, kHistThreads, fine_args)) return TCUSCAN_ERR_HIP;
+    uint32_t *src_k = (uint32_t *)d_keys, *dst_k = (uint32_t *)d_keys_tmp, *src_v = (uint32_t *)d_vals, *dst_v = (uint32_t *)d_vals_tmp;
+    for (int p = 0; p < P.count; ++p) {
+        PassArgs A = {};
+        A.keys = src_k; A.vals = src_v; A.keys_out = dst_k; A.vals_out = dst_v;
+        A.status = status + pass_words * p; A.hist = hist + kDigits * p; A.tables = kTables;
+        A.ticket = use_tickets ? tickets + p : nullptr;
+        A.fault = (uint32_t *)d_fault;
+        A.n = n; A.spin_limit = spin_limit; A.mute_tile = mute_tile; A.digit = P.digit[p]; A.stream = around_cache;
+        A.split = &F.fine->split;
+        A.top = p == 0 ? top : F.second;
+        A.top_hist = F.fine->top; A.ranges = F.ranges; A.range_start = F.fine->start;
+        void *args[] = {&A};
+        const void *fn = p == 0 ? pass_kernel_of<16, kFirstOfTwo>(v) : p == 1 ? pass_kernel_of<16, kSecondOfTwo>(v) : pass_kernel_of<16, kLaterPass>(v);
+        if (!launch(fn, p == 1 ? most_tiles : tiles, 64 * kPassWaves, args)) return TCUSCAN_ERR_HIP;
+        uint32_t *t = src_k; src_k = dst_k; dst_k = t;
+        t = src_v; src_v = dst_v; dst_v = t;
+    }
+    if (!launch(v ? (const void *)fine_sort_kernel<true> : (const void *)fine_sort_kernel<false>, buckets, 256, fine_args)) return TCUSCAN_ERR_HIP;
+    if (!launch(v ? (const void *)fine_sort_large_kernel<true> : (const void *)fine_sort_large_kernel<false>, 512, 512, fine_args)) return TCUSCAN_ERR_HIP;
+    return TCUSCAN_OK;
 }
 
 }  // namespace
@@ -1105,6 +1420,7 @@ tcuscan_status_t tcuscan_internal_digit_sort(void *d_keys, void *d_vals, size_t 
         P = rest;
         P.digit[P.count++] = {bits - 8, 8};
     }
+    const bool fine_form = !buckets_wanted && !wide && fine_wanted(n, bits);
     const int items = pass_items(n);
     auto tiles_of = [n](int per_lane) { const size_t tile = (size_t)64 * kPassWaves * per_lane; return (n + tile - 1) / tile; };
     const size_t tiles = tiles_of(items);
@@ -1125,6 +1441,7 @@ tcuscan_status_t tcuscan_internal_digit_sort(void *d_keys, void *d_vals, size_t 
     Buckets *buckets = (Buckets *)(tickets + kMaxPasses);
     uint32_t *status = (uint32_t *)(((uintptr_t)(buckets + 1) + 15) & ~(uintptr_t)15);
     const size_t pass_words = tiles * kDigits * (wide ? 2 : 1);
+    if (fine_form) return fine_sort(d_keys, d_vals, n, bits, d_keys_tmp, d_vals_tmp, hist, P, tiles, around_cache, use_tickets, spin_limit, mute_tile, d_fault, s);
     if (!own && tcuscan_internal_fill(hist, 4 * (tables * kTableWords + kMaxPasses), s) != hipSuccess) return TCUSCAN_ERR_HIP;
 
     uint32_t *src_k = (uint32_t *)d_keys, *dst_k = (uint32_t *)d_keys_tmp, *src_v = (uint32_t *)d_vals, *dst_v = (uint32_t *)d_vals_tmp;
@@ -1155,6 +1472,7 @@ tcuscan_status_t tcuscan_internal_digit_sort(void *d_keys, void *d_vals, size_t 
         A.n = n; A.spin_limit = spin_limit; A.mute_tile = mute_tile; A.digit = P.digit[p]; A.stream = around_cache;
         A.top_hist = hist + kDigits * (P.count - 1); A.buckets = buckets; A.top = P.digit[P.count - 1];
         A.bucket_max = bucket_limit(n, (uint32_t)kBlockCapacity);
+        A.split = &buckets->split;
         uint32_t pass_tiles = later_tiles;
         void *args[] = {&A, &B, &pass_tiles};                            // (the kernels of a pass alone take the first)
         hipError_t e = hipSuccess;

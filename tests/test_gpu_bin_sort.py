@@ -73,3 +73,97 @@ def test_buckets_of_every_size_that_has_bins(bits):
     low = rng.integers(0, 1 << (bits - 8), top.size, dtype=np.uint32)
     check(top << np.uint32(bits - 8) | low, True, bits)
     check(top << np.uint32(bits - 8) | low, False, bits)
+
+
+LARGE = 3 << 23                                          # the first size with two passes and small buckets; up to 4700 << 14 keys
+
+
+@pytest.mark.parametrize("pairs", [False, True], ids=["keys", "pairs"])
+@pytest.mark.parametrize("n", [LARGE - 1, LARGE, (4701 << 13) - 1, 4701 << 13])         # 2^13, 2^14 buckets
+def test_two_passes_and_small_buckets(n, pairs):
+    check(inputs.int32_full(n, n).view(np.uint32), pairs, 32)
+
+
+@pytest.mark.parametrize("bits", [24, 25, 26, 28, 31])
+def test_widths_of_large_sorts(bits):
+    check(inputs.int32_full(LARGE, bits).view(np.uint32), bits % 2 == 0, bits)
+
+
+def large_keys(name, n):
+    r, i = inputs.int32_full(n, 17).view(np.uint32), np.arange(n, dtype=np.uint32)
+    share = lambda parts: i % np.uint32(parts) == 0
+    return {
+        "two_thirds_of_the_range": (r.astype(np.uint64) * 2 // 3).astype(np.uint32),
+        "five_eighths_empty": r % np.uint32(3 << 29),                                   # buckets of 5500 to 8000 keys
+        "equal_in_buckets": r & np.uint32(0xFFFF0000),                                  # many equal keys in every bucket
+        "few_bits_in_buckets": r & np.uint32(0xFFE000FF),
+        "crowded": np.random.default_rng(3).standard_normal(n).astype(np.float32).view(np.uint32),
+        "equal": np.full(n, 7, np.uint32),
+        "in_order": np.sort(r),
+        "one_bucket_of_10240": np.where(i < 10240, r & np.uint32(0x7FFFF), r | np.uint32(1 << 19)),       # what the larger workgroups hold
+        "one_bucket_of_10241": np.where(i < 10241, r & np.uint32(0x7FFFF), r | np.uint32(1 << 19)),       # and more, which no sample sees
+        "one_bucket_of_20000": np.where(i < 20000, r & np.uint32(0x7FFFF), r | np.uint32(1 << 19)),
+        "every_thousandth_equal": np.where(share(1000), np.uint32(5), r),
+        "every_tenth_equal": np.where(share(10), np.uint32(5), r),
+    }[name].astype(np.uint32)
+
+
+@pytest.mark.parametrize("name", ["two_thirds_of_the_range", "five_eighths_empty", "equal_in_buckets", "few_bits_in_buckets", "crowded", "equal", "in_order",
+                                  "one_bucket_of_10240", "one_bucket_of_10241", "one_bucket_of_20000", "every_thousandth_equal", "every_tenth_equal"])
+def test_large_sorts_of_keys_that_split_unevenly(name):
+    check(large_keys(name, LARGE + 77_777), True, 32)
+
+
+def test_large_sorts_by_ticket_and_in_a_graph():
+    import torch
+    from paper_2411_17887_amd import tcuscan
+    n = LARGE + 99_999
+    tcuscan.set_chain_policy(1)
+    try:
+        check(inputs.int32_full(n, 1).view(np.uint32), True, 32)
+        check(large_keys("crowded", n), True, 32)
+    finally:
+        tcuscan.set_chain_policy(0)
+    k = torch.from_numpy(inputs.int32_full(n, 7)).cuda()
+    keys, tmp, pos = torch.empty_like(k), torch.empty_like(k), torch.empty_like(k)
+    flags, ws = torch.empty(n, dtype=torch.int8, device="cuda"), tcuscan.new_workspace(1, n, "i8")
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        keys.copy_(k)
+        tcuscan.split_radix_sort_u32(keys, tmp, flags, pos, ws=ws)
+    for new in (inputs.int32_full(n, 8), np.full(n, 5, np.int32), large_keys("one_bucket_of_20000", n).view(np.int32), inputs.int32_full(n, 9)):
+        k.copy_(torch.from_numpy(new))
+        torch.cuda.synchronize()
+        pos.fill_(-1)                                                     # eager work on the scratch between the replays
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(keys.cpu().numpy().view(np.uint32), np.sort(new.view(np.uint32)))
+
+
+@pytest.mark.parametrize("name", ["random", "crowded"])
+def test_a_tile_of_a_large_sort_that_does_not_know_its_places_is_not_stored(name):
+    """Tile 3 of every pass keeps silent: all kernels end, nothing is written outside the arrays, the fault word reads 1, and the same call sorts again."""
+    import torch
+    from paper_2411_17887_amd import tcuscan
+    n = LARGE + 99_999
+    k = inputs.int32_full(n, 2).view(np.uint32) if name == "random" else large_keys(name, n)
+    room = (n + 3) // 4 * 4 + 128
+    buf = torch.full((5, room), -7, dtype=torch.int32, device="cuda")
+    d_k, d_kt, d_v, d_vt, d_p = (buf[i, 64:64 + n] for i in range(5))
+    d_f, ws = torch.empty(n, dtype=torch.int8, device="cuda"), tcuscan.new_workspace(1, n, "i8")
+    order = np.argsort(k, kind="stable")
+    for silent in (True, False):
+        d_k.copy_(torch.from_numpy(k.view(np.int32)))
+        d_v.copy_(torch.arange(n, dtype=torch.int32))
+        if silent:
+            tcuscan.test_chain_fault(4096, 3)
+        try:
+            tcuscan.split_radix_sort_u32(d_k, d_kt, d_f, d_p, vals=d_v, vals_tmp=d_vt, ws=ws)
+            torch.cuda.synchronize()
+        finally:
+            tcuscan.test_chain_fault(0, -1)
+        assert tcuscan.workspace_fault(ws) == (1 if silent else 0)
+        for b in buf:
+            assert bool((b[:64] == -7).all()) and bool((b[64 + n:] == -7).all())
+        tcuscan.workspace_init(ws)
+    assert np.array_equal(d_k.cpu().numpy().view(np.uint32), k[order]) and np.array_equal(d_v.cpu().numpy(), order.astype(np.int32))
