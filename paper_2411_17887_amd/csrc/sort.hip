@@ -16,7 +16,7 @@
 // buckets: 100,000 36.6 / 24.4, 10^6 61.6 / 34.4, with payloads 76.0 / 42.6, 2^22 104 / 61, with payloads 120 / 73; keys that do
 // not split, 10^6 equal ones 55.8 / 57.6, normally distributed floats 61.5 / 62.5, 2^22 103.7 / 103.4).  Up to kBlockSortFew keys one workgroup does
 // everything: one launch, keys and payloads read and written once.  Sorts of 3 * 2^23 to 77,004,800 keys do with two passes in the same way (2^26
-// random keys 664 -> 526 us).
+// random keys 664 -> 513 us).
 
 #include <hip/hip_runtime.h>
 #include <stddef.h>
@@ -437,11 +437,12 @@ __device__ __forceinline__ void digit_pass(const PassArgs &A, PassLds<W, ITEMS, 
 
     // ---- counters -> places; the chain sets out (thread d: digit d)
     Word *column = (Word *)A.status + (tid & (kDigits - 1));
+    const bool has_digit = tid < 1 << g.width;             // (a digit of seven bits: nobody asks for the other 128 words.  138 -> 132 us a pass over 2^26 keys)
     const bool speaks = tile != A.mute_tile;
     Word win[kWindow];
     uint32_t count, start;
     scan_counters<W, kUnit<ITEMS, W>>(s_cnt, s_part, count, start, [&](uint32_t c) {
-        if (!head) {
+        if (!head && has_digit) {
             if (speaks) __hip_atomic_store(column + (size_t)tile * kDigits, S::make(kCountOfTile, c), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             request_window((const Word *)A.status, (uint32_t)tid, (int32_t)tile - 1, win);
         }
@@ -471,10 +472,10 @@ __device__ __forceinline__ void digit_pass(const PassArgs &A, PassLds<W, ITEMS, 
             for (int w = 0; w < wave; ++w) before += s_part[w];
             if constexpr (ROLE == kChoosingPass) A.buckets->start[tid] = (uint32_t)before;
         }
-    } else if (tid < kDigits) {
+    } else if (has_digit) {
         before = digit_look_back((const Word *)A.status, (uint32_t)tid, (int32_t)tile - 1, win, A);
     }
-    if (tid < kDigits) {
+    if (has_digit) {
         if (speaks) __hip_atomic_store(column + (size_t)tile * kDigits, S::make(kCountUpToTile, before + count), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         s_dest[tid] = digit_base<Place>(before, start);
         // Nothing is stored of a tile that does not know its places, nor, in the passes after one that left tiles out, of a
@@ -1056,11 +1057,11 @@ __global__ __launch_bounds__(64 * kBlockWaves) void pass_or_buckets_kernel(PassA
 // Sorts of more keys than one pass splits finely enough: two passes, on the upper and, in each of its ranges, the lower half of the top 13 or 14 bits, leave
 // buckets of some 2300 to 4700 keys, which a workgroup of four wavefronts each sorts by the other bits in LDS, in place.  That is three times
 // 8 bytes per key (16 with payloads) where four passes move 8 bytes each; and the second pass has a carry chain per range, of some 32 tiles,
-// and writes into 2 MiB (138 us for 2^26 keys, both by the whole array's chain 144; with six bits 132, with eight 144).
+// and writes into 2 MiB (135 us for 2^26 keys on seven bits, the first 132; on six bits 125, on eight 145; a second one over the whole array takes 6 more).
 // What the buckets' sizes are has to be known before the first pass: one table of all 2^14 counts in LDS, one addition per key,
 // in place of four.  Keys that crowd would have buckets too large: a sample of 8192 keys, taken by the kernel that clears the tables, says
 // whether it is worth counting; if the counts then say otherwise, the digits of the four passes are counted after all.
-// us for 2^26 random keys: sample 6, count 63, sizes and starts 10, passes 138 + 138, buckets 157, launches with nothing to do 14 (four
+// us for 2^26 random keys: sample 6, count 63, sizes and starts 10, passes 132 + 135, buckets 157, launches with nothing to do 14 (four
 // passes: 70 + 4 x 144).  What bounds the buckets' kernel is LDS (68 % of its time) and the vector unit (75 %) at 16 wavefronts a compute unit;
 // pairs, 2^25 of them 107 us, the memory.  Tried and dropped: tiles of 8192 and 4096 keys in four and eight smaller workgroups a unit (first pass 176
 // and 258), seven ballots for the seven bits (no change), buckets from the last one on, whose keys the memory-side cache may hold (157 -> 156.5).
@@ -1301,9 +1302,9 @@ const void *pass_or_buckets_kernel_for(int items, bool vals)
 
 // Two passes and small buckets: as few bits as leave 4700 keys or fewer on average (5120 is what a workgroup has places for), up to 2^14 buckets; the
 // bits that are left are enough for bins, and there are four passes to do otherwise (with three, an odd number starts from a copy).
-// us per sort, four passes / now: 3 * 2^23 random keys 264 / 226, 2^25 342 / 285, pairs 535 / 398, 2^26 664 / 526, 76 million 834 / 610, 2^26 in
-// order 667 / 492.  Keys that crowd pay for six launches with nothing to do, some 20 us: 2^26 normally distributed floats 649 / 674, 2^25 equal pairs 422 / 445, 3 * 2^23
-// floats 256 / 274, and a sort of fewer keys would have paid 8 to 13 % (2^24: 185 / 202, random 187 / 165), so it keeps the four passes.
+// us per sort, four passes / now: 3 * 2^23 random keys 263 / 230, pairs 369 / 285, 2^25 341 / 283, pairs 530 / 387, 2^26 662 / 512, 76 million 836 / 598, 2^26 in
+// order 670 / 481.  Keys that crowd pay for six launches with nothing to do, some 20 us: 2^26 normally distributed floats 650 / 678, 2^25 equal pairs 419 / 446, 3 * 2^23
+// floats 258 / 277, and a sort of fewer keys would have paid 8 to 13 % (2^24: 185 / 202, random 187 / 165), so it keeps the four passes.
 constexpr size_t kFineFew = (size_t)3 << 23, kFineMost = (size_t)4700 << kFineLogMost;
 int fine_bits(size_t n)
 {
@@ -1328,9 +1329,9 @@ void split_digits(int bits, Passes &P)
 tcuscan_status_t fine_sort(void *d_keys, void *d_vals, size_t n, int bits, void *d_keys_tmp, void *d_vals_tmp, uint32_t *hist, const Passes &P, size_t tiles,
                            bool around_cache, unsigned use_tickets, unsigned spin_limit, unsigned mute_tile, void *d_fault, hipStream_t s)
 {
-    const int log = fine_bits(n), low = log / 2;
-    const uint32_t buckets = 1u << log;
     const bool v = d_vals != nullptr;
+    const int log = fine_bits(n), low = v ? (log + 2) / 2 : log / 2;    // (2^26 keys, the second pass on 7 / 8 / 6 bits of 14: 512 / 516 / 521 us; 2^25 pairs 392 / 387 / 391)
+    const uint32_t buckets = 1u << log;
     FineArgs F;
     // scratch: digit counts, tickets, what the kernels find out, the buckets' counts (all cleared), status words
     uint32_t *tickets = hist + kTables * kTableWords;

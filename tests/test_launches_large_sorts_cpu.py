@@ -19,8 +19,8 @@ def test_launches_of_large_sorts(run, pairs, policy):    # noqa: F811
         if not (FEW <= n <= MOST and bits >= 25 and bits >= log + 12):
             assert rc == 0 and names == ["digit_histograms_kernel"] + ["digit_pass_kernel"] * -(-bits // 8), (n, bits)
             continue
-        tiles = -(-n // 16384)
-        want = [("fine_sample_kernel", 65), ("fine_count_kernel", 512), ("fine_judge_kernel", 1 << (log - log // 2)), ("fine_start_kernel", 256),
-                ("digit_pass_kernel", tiles), ("digit_pass_kernel", tiles + (1 << (log - log // 2))), ("digit_pass_kernel", tiles), ("digit_pass_kernel", tiles),
+        tiles, ranges = -(-n // 16384), 1 << (log - ((log + 2) // 2 if pairs else log // 2))
+        want = [("fine_sample_kernel", 65), ("fine_count_kernel", 512), ("fine_judge_kernel", ranges), ("fine_start_kernel", 256),
+                ("digit_pass_kernel", tiles), ("digit_pass_kernel", tiles + ranges), ("digit_pass_kernel", tiles), ("digit_pass_kernel", tiles),
                 ("fine_sort_kernel", 1 << log), ("fine_sort_large_kernel", 512)]
         assert rc == 0 and [(k.kernel.split("<")[0], k.grid) for k in launched] == want, (n, bits)
