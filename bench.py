@@ -478,7 +478,7 @@ def measure_apps(steps: int):
         return bool((k[1:] >= k[:-1]).all().item())
 
     ms2 = timed(sort_once, max(2, steps // 2))
-    res["split_radix_sort"] = {"workload": "n=2^26 random 32-bit keys, four passes on eight bits each (ranks, carry chain, scatter: one "
+    res["split_radix_sort"] = {"workload": "n=2^26 random 32-bit keys, two passes on seven bits each and a workgroup per small bucket (ranks, carry chain, scatter: one "
                                            "kernel per pass), includes one 256 MiB copy per run",
                                "ms": ms2, "mkeys_per_s": m / (ms2 * 1e-3) / 1e6, "sorted": is_sorted()}
     try:
