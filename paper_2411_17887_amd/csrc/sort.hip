@@ -647,7 +647,7 @@ __global__ __launch_bounds__(64 * kSpreadWaves) void spread_kernel(SpreadArgs A)
 //   a bin's first place and the next one's from two aligned words: one read across words takes three times as long (6000 -> 18,500).
 //   payloads loaded when the keys have their places, not with them: 256 x 16,320 pairs 23.2 -> 20.4 us, 16,384 (18 rows) 28.9 -> 21.5.
 // Keys that crowd in a part of their range are seen before anything is moved, from a sample of pairs, or from the counters, and the passes do the work:
-// what that costs is 0.3 to 0.8 us.  Fewer than 2049 keys gain nothing, for more than 20,480 there are too few registers.
+// what that costs is 0.3 to 0.8 us.  Fewer than 2049 keys gain nothing, for more than 20,480 (18,432 with payloads: BlockLdsOf) there are too few registers.
 
 constexpr uint32_t kBinMost = 16;                          // keys of a bin, at most
 constexpr uint32_t kBinMean = 2;                           // a bin has fewer on average
@@ -890,10 +890,14 @@ struct BlockArgs {
     Passes P;                             // a bucket's digits, or all
     uint32_t bits;                        // the bits they cover, from the lowest on
 };
-// A workgroup of WAVES wavefronts that sorts up to ROWS rows a lane, FEW to BIN_ROWS of them by bins (more would not do with the registers),
-// whose counters lie behind as many keys, in part where more rows have theirs.
-template <int WAVES, int ROWS, int FEW, int BIN_ROWS, uint32_t LOG_BINS> struct BlockLdsOf {
-    static constexpr int kWaves = WAVES, kRows = ROWS, kBinFew = FEW, kBinRows = BIN_ROWS;
+// A workgroup of WAVES wavefronts that sorts up to ROWS rows a lane, FEW to BIN_ROWS of them by bins (PAIR_ROWS with payloads; more would not do with
+// the registers), whose counters lie behind as many keys, in part where more rows have theirs.
+// 20 rows with payloads by bins spill 13 registers a lane, and a kernel with scratch starts 0.4 us later, whatever it sorts: 1033 to 2048 pairs 11.9 us
+// without that form in the kernel and 12.3 with it, 8000 pairs 12.7 and 13.2.  For buckets of 18,433 to 20,480 pairs it is still the faster way (4.8 million pairs 87.8 us, by
+// passes 93.4), so they have a kernel of their own (block_sort_pairs20_kernel).
+template <int WAVES, int ROWS, int FEW, int BIN_ROWS, uint32_t LOG_BINS, int PAIR_ROWS = 18> struct BlockLdsOf {
+    static constexpr int kWaves = WAVES, kRows = ROWS, kBinFew = FEW;
+    template <bool VALS> static constexpr int kBinRows = VALS ? PAIR_ROWS : BIN_ROWS;
     static constexpr uint32_t kCapacity = 64u * WAVES * ROWS, kLogBins = LOG_BINS, kBinsAt = 64u * WAVES * BIN_ROWS + kBinMost, kBinWords = (1u << LOG_BINS) / 2u + 4u;
     uint32_t order[kCapacity];
     union {
@@ -907,6 +911,7 @@ template <int WAVES, int ROWS, int FEW, int BIN_ROWS, uint32_t LOG_BINS> struct 
     BinParts<WAVES> bin_parts;
 };
 using BlockLds = BlockLdsOf<kBlockWaves, kBlockItems, 3, 20, 15>;
+using BlockLdsPairs20 = BlockLdsOf<kBlockWaves, kBlockItems, 3, 20, 15, 20>;
 static_assert(offsetof(BlockLds, bins_end) == 4 * kBlockCapacity && BlockLds::kBinsAt % 4 == 0, "the bins' counters, from order + kBinsAt on, are the struct's own");
 static_assert(alignof(BlockLds) >= alignof(CounterQuad), "counters cleared four at a time");
 static_assert(sizeof(BlockLds) <= 160 * 1024, "LDS of a compute unit");
@@ -940,7 +945,7 @@ __device__ __forceinline__ void sort_in_block(const BlockArgs &B, uint32_t begin
     uint32_t *keys_out = B.keys_out + begin, *vals_out = VALS ? B.vals_out + begin : nullptr;
     uint32_t differ = ~0u;                                 // bits that the keys differ in, or more
     const auto by_bins = [&] {
-        if constexpr (ITEMS >= Lds::kBinFew && ITEMS <= Lds::kBinRows)
+        if constexpr (ITEMS >= Lds::kBinFew && ITEMS <= Lds::template kBinRows<VALS>)
             return places_by_bins<W, ITEMS, Lds::kLogBins>(key, first, n, keys[0], B.bits, s.order, s.order + Lds::kBinsAt, s.bin_parts, at, differ);
         else return false;
     };
@@ -1015,8 +1020,8 @@ __device__ __forceinline__ void sort_in_block_of(const BlockArgs &B, uint32_t be
     }
 }
 
-template <bool VALS>
-__device__ __forceinline__ void sort_block_or_bucket(const BlockArgs &B, BlockLds &s)
+template <bool VALS, class Lds>
+__device__ __forceinline__ void sort_block_or_bucket(const BlockArgs &B, Lds &s)
 {
     uint32_t begin = 0u, n = B.n;
     if (B.buckets) {
@@ -1034,6 +1039,12 @@ __global__ __launch_bounds__(64 * kBlockWaves) void block_sort_kernel(BlockArgs 
     __shared__ BlockLds s;
     if (B.buckets && B.buckets->split == kNotSplit) return;
     sort_block_or_bucket<VALS>(B, s);
+}
+__global__ __launch_bounds__(64 * kBlockWaves) void block_sort_pairs20_kernel(BlockArgs B)
+{
+    __shared__ BlockLdsPairs20 s;
+    if (B.buckets->split == kNotSplit) return;
+    sort_block_or_bucket<true>(B, s);
 }
 
 // The buckets, or the second pass where there are none: a launch that returns at once is 1.2 us (two launches / one: 40,000 keys
@@ -1262,7 +1273,9 @@ hipError_t launch_block_sort(const BlockArgs &args_in, unsigned grid, hipStream_
 {
     BlockArgs B = args_in;
     void *args[] = {&B};
-    const void *fn = B.vals ? (const void *)block_sort_kernel<true> : (const void *)block_sort_kernel<false>;
+    // (evenly spread keys: the largest of 256 buckets has three standard deviations more than the mean, so 18,432 are exceeded from a mean of 18,000 on)
+    const bool pairs20 = B.buckets && B.n / kDigits > 18000u && B.n / kDigits <= 20480u;
+    const void *fn = !B.vals ? (const void *)block_sort_kernel<false> : pairs20 ? (const void *)block_sort_pairs20_kernel : (const void *)block_sort_kernel<true>;
     return hipLaunchKernel(fn, dim3(grid), dim3(64 * kBlockWaves), args, 0, s);
 }
 // May random keys be expected to have buckets (of 256) that are small enough: mean and six standard deviations?  (Up to 6,055,225 keys.)
