@@ -647,12 +647,12 @@ __global__ __launch_bounds__(64 * kSpreadWaves) void spread_kernel(SpreadArgs A)
 //   a bin's first place and the next one's from two aligned words: one read across words takes three times as long (6000 -> 18,500).
 //   payloads loaded when the keys have their places, not with them: 256 x 16,320 pairs 23.2 -> 20.4 us, 16,384 (18 rows) 28.9 -> 21.5.
 // Keys that crowd in a part of their range are seen before anything is moved, from a sample of pairs, or from the counters, and the passes do the work:
-// what that costs is 0.3 to 0.8 us.  Fewer than 2049 keys gain nothing, for more than 20,480 (18,432 with payloads: BlockLdsOf) there are too few registers.
+// what that costs is 0.5 to 0.9 us (below).  Fewer than 2049 keys gain nothing, for more than 20,480 (18,432 with payloads: BlockLdsOf) there are too few registers.
 
 constexpr uint32_t kBinMost = 16;                          // keys of a bin, at most
 constexpr uint32_t kBinMean = 2;                           // a bin has fewer on average
 constexpr uint32_t kAlikeMost = 6;                         // pairs of a sample that share a bin: fewer
-template <int W> struct BinParts { uint32_t differ[W], alike[W], sum[64], most[W]; };
+template <int W> struct BinParts { uint32_t differ[W], one[W], alike[W], sum[64], most[W]; };
 
 // body(r0, rows) for rows r0 .. r0 + rows - 1 of ITEMS, BATCH at a time, each call with constants of its own.
 template <int N> struct Constant { constexpr __device__ __forceinline__ operator int() const { return N; } };
@@ -667,12 +667,12 @@ template <int ITEMS, int BATCH, int R0 = 0, class Body> __device__ __forceinline
 __device__ __forceinline__ uint32_t bits_below(uint32_t n) { return n <= 1u ? 0u : 32u - (uint32_t)__builtin_clz(n - 1u); }      // 2^result >= n
 
 // at[r]: byte offset in the ordered keys of this lane's key r, which is key first + 64 r of n (past the end, where
-// the caller has repeated a key: its own); false (in all threads, after a
-// barrier): not by bins.  `key0`: key 0; `bits`: those that the keys are ordered by; `bins`: 16-bit counters, 2^MAX_LOG of them,
+// the caller has repeated a key: its own); false (in all threads, none of which looks at `bins` any more): not by bins.
+// `bits`: those that the keys are ordered by; `bins`: 16-bit counters, 2^MAX_LOG of them,
 // and `order` 64 W ITEMS + kBinMost words, both free before and (true) after.
 template <int W, int ITEMS, uint32_t MAX_LOG>
-__device__ __forceinline__ bool places_by_bins(const uint32_t (&key)[ITEMS], uint32_t first, uint32_t n, uint32_t key0, uint32_t bits,
-                                               uint32_t *order, uint32_t *bins, BinParts<W> &parts, uint32_t (&at)[ITEMS], uint32_t &differ)
+__device__ __forceinline__ bool places_by_bins(const uint32_t (&key)[ITEMS], uint32_t first, uint32_t n, uint32_t bits, uint32_t *order, uint32_t *bins, BinParts<W> &parts,
+                                               uint32_t (&at)[ITEMS], uint32_t &differ)
 {
     differ = ~0u >> (32u - bits);
     if (bits < 32u && n >> bits >= kBinMean) return false;
@@ -688,12 +688,16 @@ __device__ __forceinline__ bool places_by_bins(const uint32_t (&key)[ITEMS], uin
     log_bins = log_bins < MAX_LOG ? log_bins : MAX_LOG;
     for (uint32_t i = 4u * tid; i < 1u << (log_bins - 1u); i += 4u * kThreads)
         *(u32x4 *)(bins + i) = u32x4{0u, 0u, 0u, 0u};
+    // (a wavefront's keys are compared with one of its own, and those with each other below: key 0 of all would have to be loaded)
     uint32_t own = 0u;
+    const uint32_t one = (uint32_t)__builtin_amdgcn_readfirstlane((int)key[0]);
 #pragma unroll
-    for (int r = 0; r < ITEMS; ++r) own |= key[r] ^ key0;
+    for (int r = 0; r < ITEMS; ++r) own |= key[r] ^ one;
     own = wave_or(own);
     // Keys that crowd in a part of their range are mostly seen in a sample: a lane's first keys, 64 places apart, that fall into one bin.
-    // (normally distributed floats, us without / with it / by passes alone: 3000 8.3 / 8.0 / 7.6, 5000 11.3 / 11.0 / 10.4; pairs, 2100 8.1 / 7.6 / 6.8)
+    // (normally distributed floats, us in a row of sorts with the copy of new keys, by passes alone / with the look: 2049 10.8 / 11.4, 3000 11.3 / 12.0, 5000 14.1 / 14.8, 8192
+    // 19.1 / 19.6; pairs, 13.2 / 14.0, 14.2 / 15.1, 17.7 / 18.6, 23.5 / 24.0.  0.1 us of it is the sample, the rest what all wavefronts find out together.  Without the sample
+    // the counters would see it, 0.3 us later.  Evenly spread ones 10.6 / 6.3, 11.1 / 6.7, 13.8 / 7.8, 18.8 / 9.6.)
     uint32_t alike = 0u;
     constexpr int kSample = ITEMS < 4 ? ITEMS : 4;
     const uint32_t range_of_wave = own & differ;
@@ -705,9 +709,11 @@ __device__ __forceinline__ bool places_by_bins(const uint32_t (&key)[ITEMS], uin
 #pragma unroll
             for (int b = 0; b < a; ++b) alike += (uint32_t)__builtin_popcountll(__ballot(((key[a] ^ key[b]) & window) == 0u));
     }
-    if (lane == 0u) { parts.differ[wave] = own; parts.alike[wave] = alike; }
+    if (lane == 0u) { parts.differ[wave] = own; parts.one[wave] = one; parts.alike[wave] = alike; }
     __syncthreads();
-    differ &= wave_or(parts.differ[lane % W]);
+    uint32_t one_of = parts.one[lane % W], differ_of = parts.differ[lane % W], alike_of = parts.alike[lane % W];
+    differ &= row_or(differ_of | (one_of ^ (uint32_t)__builtin_amdgcn_readfirstlane((int)one_of)));
+    alike = row_sum(lane % 16u < W ? alike_of : 0u);
     if (differ == 0u) {                                    // all equal: in order
 #pragma unroll
         for (int r = 0; r < ITEMS; ++r) at[r] = 4u * (first + 64u * r);
@@ -716,7 +722,7 @@ __device__ __forceinline__ bool places_by_bins(const uint32_t (&key)[ITEMS], uin
     const uint32_t high = 32u - (uint32_t)__builtin_clz(differ);
     const uint32_t width = high < log_bins ? high : log_bins, shift = high - width;
     // (bits that never differ, as low ones of numbers with few digits, make no bins)
-    if (n >> __builtin_popcount(differ >> shift) >= kBinMean || wave_sum(lane < W ? parts.alike[lane % W] : 0u) >= kAlikeMost) { __syncthreads(); return false; }
+    if (n >> __builtin_popcount(differ >> shift) >= kBinMean || alike >= kAlikeMost) return false;
 
     // Rows in batches of four, their accesses to LDS on their way together: one after the other, each row waits for its own.  (The
     // scheduler is kept from putting a row's uses back between the next row's accesses.)  Lanes past the end add nothing to
@@ -946,7 +952,7 @@ __device__ __forceinline__ void sort_in_block(const BlockArgs &B, uint32_t begin
     uint32_t differ = ~0u;                                 // bits that the keys differ in, or more
     const auto by_bins = [&] {
         if constexpr (ITEMS >= Lds::kBinFew && ITEMS <= Lds::template kBinRows<VALS>)
-            return places_by_bins<W, ITEMS, Lds::kLogBins>(key, first, n, keys[0], B.bits, s.order, s.order + Lds::kBinsAt, s.bin_parts, at, differ);
+            return places_by_bins<W, ITEMS, Lds::kLogBins>(key, first, n, B.bits, s.order, s.order + Lds::kBinsAt, s.bin_parts, at, differ);
         else return false;
     };
     if (by_bins()) {

@@ -63,6 +63,17 @@ template <class Fold> __device__ __forceinline__ uint32_t wave_fold(uint32_t v, 
 }
 __device__ __forceinline__ uint32_t wave_or(uint32_t v)  { return wave_fold(v, [](uint32_t a, uint32_t b) { return a | b; }); }
 __device__ __forceinline__ uint32_t wave_max(uint32_t v) { return wave_fold(v, [](uint32_t a, uint32_t b) { return a > b ? a : b; }); }
+// The same and the sum over lanes 0 to 15.
+template <class Fold> __device__ __forceinline__ uint32_t row_fold(uint32_t v, Fold fold)
+{
+    v = fold(v, dpp0<kRowShr + 1>(v));
+    v = fold(v, dpp0<kRowShr + 2>(v));
+    v = fold(v, dpp0<kRowShr + 4>(v));
+    v = fold(v, dpp0<kRowShr + 8>(v));
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 15);
+}
+__device__ __forceinline__ uint32_t row_or(uint32_t v)  { return row_fold(v, [](uint32_t a, uint32_t b) { return a | b; }); }
+__device__ __forceinline__ uint32_t row_sum(uint32_t v) { return row_fold(v, [](uint32_t a, uint32_t b) { return a + b; }); }
 constexpr int kWaveShr1 = 0x138;   // DPP control: shift right by one lane across the whole wavefront
 template <class A> __device__ __forceinline__ A wave_shift_up(A v)
 {   // lane l receives v[l - 1], lane 0 receives 0
