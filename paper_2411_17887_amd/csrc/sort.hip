@@ -650,7 +650,6 @@ __global__ __launch_bounds__(64 * kSpreadWaves) void spread_kernel(SpreadArgs A)
 // what that costs is 0.5 to 0.9 us (below).  Fewer than 2049 keys gain nothing, for more than 20,480 (18,432 with payloads: BlockLdsOf) there are too few registers.
 
 constexpr uint32_t kBinMost = 16;                          // keys of a bin, at most
-constexpr uint32_t kBinMean = 2;                           // a bin has fewer on average
 constexpr uint32_t kAlikeMost = 6;                         // pairs of a sample that share a bin: fewer
 template <int W> struct BinParts { uint32_t differ[W], one[W], alike[W], sum[64], most[W]; };
 
@@ -675,7 +674,7 @@ __device__ __forceinline__ bool places_by_bins(const uint32_t (&key)[ITEMS], uin
                                                uint32_t (&at)[ITEMS], uint32_t &differ)
 {
     differ = ~0u >> (32u - bits);
-    if (bits < 32u && n >> bits >= kBinMean) return false;
+    if (bits < 32u && !bins_suffice(n, bits)) return false;
     constexpr uint32_t kThreads = 64 * W, kBinChunks = (1u << MAX_LOG) / 2u / kThreads / 4u;
     constexpr int kBatch = 4;
     constexpr uint32_t kSlots = kThreads * ITEMS;
@@ -722,7 +721,7 @@ __device__ __forceinline__ bool places_by_bins(const uint32_t (&key)[ITEMS], uin
     const uint32_t high = 32u - (uint32_t)__builtin_clz(differ);
     const uint32_t width = high < log_bins ? high : log_bins, shift = high - width;
     // (bits that never differ, as low ones of numbers with few digits, make no bins)
-    if (n >> __builtin_popcount(differ >> shift) >= kBinMean || alike >= kAlikeMost) return false;
+    if (!bins_suffice(n, (uint32_t)__builtin_popcount(differ >> shift)) || alike >= kAlikeMost) return false;
 
     // Rows in batches of four, their accesses to LDS on their way together: one after the other, each row waits for its own.  (The
     // scheduler is kept from putting a row's uses back between the next row's accesses.)  Lanes past the end add nothing to
@@ -1279,8 +1278,9 @@ hipError_t launch_block_sort(const BlockArgs &args_in, unsigned grid, hipStream_
 {
     BlockArgs B = args_in;
     void *args[] = {&B};
-    // (evenly spread keys: the largest of 256 buckets has three standard deviations more than the mean, so 18,432 are exceeded from a mean of 18,000 on)
-    const bool pairs20 = B.buckets && B.n / kDigits > 18000u && B.n / kDigits <= 20480u;
+    // (evenly spread keys: the largest of 256 buckets has three standard deviations more than the mean, so 18,432 are exceeded from a mean of 18,000 on; where
+    // two passes do, they are as fast: 5 million pairs on 24 bits 92.5 us, 95.8 by bins)
+    const bool pairs20 = B.buckets && B.n / kDigits > 18000u && B.n / kDigits <= 20480u && B.P.count > 2;
     const void *fn = !B.vals ? (const void *)block_sort_kernel<false> : pairs20 ? (const void *)block_sort_pairs20_kernel : (const void *)block_sort_kernel<true>;
     return hipLaunchKernel(fn, dim3(grid), dim3(64 * kBlockWaves), args, 0, s);
 }
