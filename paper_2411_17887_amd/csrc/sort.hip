@@ -24,6 +24,7 @@
 
 #include "../../include/tcuscan.h"
 #include "digit_places.h"
+#include "large_sort_plan.h"
 #include "wave_ops.h"
 
 // tcuscan.hip: clears `bytes` bytes on the stream; the process-wide chain policy, the look-back's poll limit and the tile
@@ -37,8 +38,8 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 typedef uint64_t CounterQuad __attribute__((may_alias));   // four 16-bit counters in LDS
 
-constexpr int kDigits = 256;
-constexpr int kMaxPasses = 4;
+constexpr int kDigits = large_sort::kDigits;
+constexpr int kMaxPasses = large_sort::kMaxPasses;
 
 struct Digit { int shift, width; };                        // digit = (key >> shift) & (2^width - 1), width 1 .. 8
 struct Passes { int count; Digit digit[kMaxPasses]; };
@@ -47,13 +48,13 @@ __device__ __forceinline__ uint32_t digit_of(uint32_t key, Digit g) { return __b
 
 constexpr unsigned kAndXnor = 0x90;        // truth table of a & ~(b ^ c)
 
-// The lanes whose digit agrees with this lane's in every bit, from eight ballots: 36 vector instructions.
-__device__ __forceinline__ void same_digit_by_ballots(uint32_t d, uint32_t &lo, uint32_t &hi)
+// The lanes whose digit agrees with this lane's in every bit, from a ballot per bit: eight are 36 vector instructions.
+template <int BITS> __device__ __forceinline__ void same_digit_by_ballots(uint32_t d, uint32_t &lo, uint32_t &hi)
 {
-    uint32_t sign[8];
-    uint64_t ones[8];
+    uint32_t sign[BITS];
+    uint64_t ones[BITS];
 #pragma unroll
-    for (int b = 0; b < 8; ++b) {
+    for (int b = 0; b < BITS; ++b) {
         sign[b] = (uint32_t)__builtin_amdgcn_sbfe((int)d, b, 1);                           // the bit in all 32 places
         asm("" : "+v"(sign[b]));                           // (kept: else it is taken out of the digit once more for the compare)
         ones[b] = __builtin_amdgcn_ballot_w64(sign[b] != 0u);
@@ -61,7 +62,7 @@ __device__ __forceinline__ void same_digit_by_ballots(uint32_t d, uint32_t &lo, 
     lo = ~((uint32_t)ones[0] ^ sign[0]);
     hi = ~((uint32_t)(ones[0] >> 32) ^ sign[0]);
 #pragma unroll
-    for (int b = 1; b < 8; ++b) {
+    for (int b = 1; b < BITS; ++b) {
         lo = __builtin_amdgcn_bitop3_b32(lo, (uint32_t)ones[b], sign[b], kAndXnor);
         hi = __builtin_amdgcn_bitop3_b32(hi, (uint32_t)(ones[b] >> 32), sign[b], kAndXnor);
     }
@@ -76,7 +77,7 @@ __device__ __forceinline__ void same_digit_by_ballots(uint32_t d, uint32_t &lo, 
 // `valid`: the lane's keys from row ceil(valid / 64) on are past the end -- with the highest digit, behind everything -- and set
 // no bits: lanes that add to one mask go one after the other (16,000 equal keys: 30 us by ballots, 45 with masks, 30 with the lanes
 // of the first one's digit left out).
-template <int ITEMS, bool MASKS = false>
+template <int ITEMS, bool MASKS = false, int BITS = 8>
 __device__ __forceinline__ void rank_rows(const uint32_t (&key)[ITEMS], Digit g, uint16_t *counters, uint32_t (&rank)[ITEMS], uint64_t *masks = nullptr, int valid = 64 * ITEMS)
 {
 #pragma unroll
@@ -94,7 +95,7 @@ __device__ __forceinline__ void rank_rows(const uint32_t (&key)[ITEMS], Digit g,
             lo = (uint32_t)m;
             hi = (uint32_t)(m >> 32);
         } else {
-            same_digit_by_ballots(d, lo, hi);
+            same_digit_by_ballots<BITS>(d, lo, hi);
         }
         const uint32_t before = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
         const uint32_t all = (uint32_t)(__builtin_popcount(lo) + __builtin_popcount(hi));
@@ -179,7 +180,7 @@ struct HistArgs {
 constexpr int kHistCopies = 16, kHistThreads = 1024, kHistGrid = 512;
 // The workgroups add up in one of eight tables -- additions to one word from all dies go one after the other, 27 ns each: 2^22
 // keys 14.5 -> 7 us -- and up to eight workgroups have one each, which then needs no clearing in front (HistArgs::own).
-constexpr uint32_t kTables = 8, kTableWords = kMaxPasses * kDigits;
+constexpr uint32_t kTables = large_sort::kTables, kTableWords = kMaxPasses * kDigits;
 template <class T> __device__ __forceinline__ T sum_of_tables(const T *hist, uint32_t tables)
 {
     T x[kTables], sum = T{};
@@ -287,13 +288,20 @@ struct PassArgs {
     uint32_t bucket_max;
     // Sorts that may take two passes and small buckets (null otherwise): whether they do, and if so: the first goes by `top` and top_hist, one
     // table; the second goes by `top` in each range of keys that the first has made, whose tiles `ranges` lists and whose buckets begin at
-    // range_start; later passes have nothing to do.
+    // range_start; later passes do the huge buckets, if there are any.
     const TileOfRange *ranges;
     const uint32_t *range_start;
     const uint32_t *split;
+    // Later passes of those: huge buckets, by `top`.
+    const large_sort::Found *found;
+    const uint32_t *huge, *sizes;
+    uint32_t huge_tiles;
 };
 
-enum PassRole { kPlainPass, kChoosingPass, kLaterPass, kFirstOfTwo, kSecondOfTwo };
+// What kernels in front have written, the same for all lanes: one scalar load, which no vector load in front of it delays.
+template <class T> __device__ __forceinline__ T uniform_load(const T *p) { return *(const __attribute__((address_space(4))) T *)(uintptr_t)p; }
+
+enum PassRole { kPlainPass, kChoosingPass, kLaterPass, kFirstOfTwo, kSecondOfTwo, kAfterTwo };
 
 template <int ITEMS>
 __device__ __forceinline__ void load_rows(const uint32_t *src, uint32_t first, uint32_t valid, bool whole, bool stream, uint32_t fill, uint32_t (&x)[ITEMS])
@@ -402,13 +410,13 @@ __device__ __forceinline__ void digit_pass(const PassArgs &A, PassLds<W, ITEMS, 
     uint32_t valid = A.n - base < kTile ? (uint32_t)(A.n - base) : kTile, range = 0u;
     Digit g = A.digit;
     if constexpr (ROLE == kSecondOfTwo) {                  // (as many workgroups as there may be tiles)
-        const TileOfRange at_range = A.ranges[tile];
-        of_range = *A.split != kNotSplit;
+        const u32x4 at_range = uniform_load((const u32x4 *)(A.ranges + tile));
+        of_range = uniform_load(A.split) != kNotSplit;
         if (of_range) {
-            base = (uint32_t)__builtin_amdgcn_readfirstlane((int)at_range.base);
-            valid = (uint32_t)__builtin_amdgcn_readfirstlane((int)at_range.keys);
-            range = (uint32_t)__builtin_amdgcn_readfirstlane((int)at_range.range);
-            head = __builtin_amdgcn_readfirstlane((int)at_range.head) != 0;
+            base = at_range[0];
+            valid = at_range[1];
+            range = at_range[2];
+            head = at_range[3] != 0u;
             g = A.top;
         }
         if (of_range ? valid == 0u : base >= A.n) return;
@@ -429,7 +437,7 @@ __device__ __forceinline__ void digit_pass(const PassArgs &A, PassLds<W, ITEMS, 
     }
     uint32_t tables = A.tables;
     if constexpr (ROLE == kFirstOfTwo) {
-        if (*A.split != kNotSplit) { g = A.top; hist = A.top_hist; tables = 1u; }
+        if (uniform_load(A.split) != kNotSplit) { g = A.top; hist = A.top_hist; tables = 1u; }
     }
     wavefront_sync();
     rank_rows<ITEMS>(key, g, s_cnt[wave], at);
@@ -517,14 +525,131 @@ __device__ __forceinline__ void digit_pass(const PassArgs &A, PassLds<W, ITEMS, 
         }
     }
 }
+// Buckets of large sorts with more keys than a workgroup sorts in LDS (one value many times over, say): two stable passes on the nine or ten bits of half a bucket's
+// other bits each, in the launches of the third and fourth pass, which have nothing else to do then.  A bucket's tiles know of each other as in spread_kernel: each counts the
+// digits of all the others' keys itself, so no tile waits for another.  That is a reading of the whole bucket per tile, which is why there is a limit to their
+// sizes (large_sort::kHugeMost) and to what they read in all (Plan::huge_work: all keys of 3 * 2^23 in such buckets, three tiles each, 443 us, four passes 299).  (us per sort, four
+// passes alone / four passes after the counts / now: 2^26 keys, one in 2000 the same, 764 / 844 / 640; 3 * 2^23 289 / 335 / 278, pairs 446 / 494 / 380.)
+struct HugeLds {
+    static constexpr int kWaves = 16, kItems = large_sort::kHugeTile / (64 * kWaves), kBits = 10;
+    static constexpr uint32_t kCount = 1u << kBits;
+    uint32_t order[large_sort::kHugeTile];
+    alignas(16) uint16_t cnt[kWaves][kCount];
+    uint32_t other[2][kCount];            // digit counts of the bucket's tiles in front and behind
+    uint32_t part[2][kWaves];
+};
+static_assert(64 * HugeLds::kWaves == HugeLds::kCount, "a thread per digit");
+
+// One key of each lane to the count of its digit or bucket, `one` each.  Where many lanes agree with the first one they are added at
+// once: keys in order or equal would be added one after the other (2^24 keys in order: the counting kernel of large sorts 57 -> 16 us, the sample of equal ones 13 -> 8).
+__device__ __forceinline__ void add_to_count(uint32_t *counts, uint32_t at, uint32_t one = 1u)
+{
+    const bool as_first = at == (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+    const uint64_t those = __ballot(as_first);
+    const uint32_t all = (uint32_t)__builtin_popcountll(those);
+    if (all < 16u) {
+        atomicAdd(&counts[at], one);
+    } else {
+        const bool first = as_first && __builtin_amdgcn_mbcnt_hi((uint32_t)(those >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)those, 0u)) == 0u;
+        if (!as_first || first) atomicAdd(&counts[at], first ? all * one : one);
+    }
+}
+
+template <bool VALS>
+__device__ __forceinline__ void huge_pass(const PassArgs &A, uint32_t tiles, HugeLds &s)
+{
+    constexpr int W = HugeLds::kWaves, ITEMS = HugeLds::kItems;
+    constexpr uint32_t kThreads = 64 * W, kTile = large_sort::kHugeTile;
+    const Digit g = A.top;
+    tiles = tiles < A.huge_tiles ? tiles : A.huge_tiles;
+    for (uint32_t t = blockIdx.x; t < tiles; t += gridDim.x) {
+        uint32_t tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));                      // (no addresses are kept from one round to the next: registers)
+        const uint32_t lane = tid & 63u, wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+        const uint32_t first = wave * 64u * ITEMS + lane;
+        const uint32_t entry = uniform_load(A.huge + t), bucket = entry & ((1u << large_sort::kLogMost) - 1u), base = (entry >> large_sort::kLogMost) * kTile;
+        const uint32_t begin = uniform_load(&A.found->start[bucket]), size = uniform_load(A.sizes + bucket);
+        const uint32_t valid = size - base < kTile ? size - base : kTile;
+        const uint32_t *keys = A.keys + begin;
+        uint32_t key[ITEMS], at[ITEMS];
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) key[r] = first + 64u * r < valid ? keys[base + first + 64u * r] : ~0u;
+        for (uint32_t i = tid; i < sizeof(s.cnt) / 16u; i += kThreads) ((u32x4 *)s.cnt)[i] = u32x4{0u, 0u, 0u, 0u};
+        s.other[0][tid] = s.other[1][tid] = 0u;
+        __syncthreads();
+        for (uint32_t i = tid; i < base; i += kThreads) add_to_count(s.other[0], digit_of(keys[i], g));
+        for (uint32_t i = base + valid + tid; i < size; i += kThreads) add_to_count(s.other[1], digit_of(keys[i], g));
+        rank_rows<ITEMS, false, HugeLds::kBits>(key, g, s.cnt[wave], at);
+        __syncthreads();
+        // ---- thread d: digit d, in the tile and in the bucket
+        uint32_t count = 0u;
+#pragma unroll 4
+        for (int w = 0; w < W; ++w) count += s.cnt[w][tid];
+        // (keys past the end of the last tile count as the highest digit)
+        const uint32_t in_front = s.other[0][tid], all = in_front + s.other[1][tid] + count - (tid == (1u << g.width) - 1u ? kTile - valid : 0u);
+        const uint32_t inc = wave_inclusive_scan(count), inc_all = wave_inclusive_scan(all);
+        if (lane == 63u) { s.part[0][wave] = inc; s.part[1][wave] = inc_all; }
+        __syncthreads();
+        uint32_t start = inc - count, to = inc_all - all + in_front;
+        for (uint32_t w = 0; w < wave; ++w) { start += s.part[0][w]; to += s.part[1][w]; }
+        s.other[0][tid] = digit_base<uint32_t>(to, start);                  // (its own word: no other thread looks at it before the barrier)
+#pragma unroll 4
+        for (int w = 0; w < W; ++w) {
+            const uint32_t c = s.cnt[w][tid];
+            s.cnt[w][tid] = (uint16_t)start;
+            start += c;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) {
+            at[r] += s.cnt[wave][digit_of(key[r], g)];
+            s.order[at[r]] = key[r];
+        }
+        uint32_t val[VALS ? ITEMS : 1], dst[VALS ? ITEMS : 1];
+        if constexpr (VALS) {
+            const uint32_t *vals = A.vals + begin + base;
+#pragma unroll
+            for (int r = 0; r < ITEMS; ++r) val[r] = first + 64u * r < valid ? vals[first + 64u * r] : 0u;
+        }
+        __syncthreads();
+        char *kout = (char *)(A.keys_out + begin), *vout = VALS ? (char *)(A.vals_out + begin) : nullptr;
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) {
+            const uint32_t i = tid + (uint32_t)r * kThreads, k = s.order[i], place = digit_place(s.other[0][digit_of(k, g)], i);
+            if (i < valid) *(uint32_t *)(kout + place) = k;
+            if constexpr (VALS) dst[r] = place;
+        }
+        __syncthreads();
+        if constexpr (VALS) {
+#pragma unroll
+            for (int r = 0; r < ITEMS; ++r) s.order[at[r]] = val[r];
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < ITEMS; ++r) {
+                const uint32_t i = tid + (uint32_t)r * kThreads;
+                if (i < valid) *(uint32_t *)(vout + dst[r]) = s.order[i];
+            }
+            __syncthreads();
+        }
+    }
+}
 template <int W, int ITEMS, bool VALS, class Word, PassRole ROLE = kPlainPass>
 __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(sizeof(Word) == 4 ? 8 : 4))) void digit_pass_kernel(PassArgs A)
 {
-    __shared__ PassLds<W, ITEMS, Word> s;
-    if constexpr (ROLE == kLaterPass) {
-        if (*A.split != kNotSplit) return;
+    if constexpr (ROLE == kAfterTwo) {
+        __shared__ union { PassLds<W, ITEMS, Word> pass; HugeLds huge; } s;
+        const u32x4 found = uniform_load((const u32x4 *)A.found);
+        static_assert(offsetof(large_sort::Found, split) == 0 && offsetof(large_sort::Found, huge) == 12, "found[0], found[3]");
+        if (found[0] != kNotSplit && found[3] == 0u) return;
+        if (found[0] != kNotSplit) huge_pass<VALS>(A, found[3], s.huge);
+        else digit_pass<W, ITEMS, VALS, Word, ROLE>(A, s.pass, take_tile(A, s.pass.part));
+    } else {
+        __shared__ PassLds<W, ITEMS, Word> s;
+        if constexpr (ROLE == kLaterPass) {
+            if (uniform_load(A.split) != kNotSplit) return;
+        }
+        digit_pass<W, ITEMS, VALS, Word, ROLE>(A, s, take_tile(A, s.part));
     }
-    digit_pass<W, ITEMS, VALS, Word, ROLE>(A, s, take_tile(A, s.part));
 }
 
 // ------------------------------------------------------------------------- the pass in front of a small sort's buckets
@@ -665,6 +790,23 @@ template <int ITEMS, int BATCH, int R0 = 0, class Body> __device__ __forceinline
 
 __device__ __forceinline__ uint32_t bits_below(uint32_t n) { return n <= 1u ? 0u : 32u - (uint32_t)__builtin_clz(n - 1u); }      // 2^result >= n
 
+// Bits in which the keys differ, or more (exchanges with other wavefronts are the caller's: two parts).
+template <int ITEMS> __device__ __forceinline__ uint32_t bits_that_differ(const uint32_t (&key)[ITEMS], uint32_t &one)
+{
+    // (a wavefront's keys are compared with one of its own, and those with each other: key 0 of all would have to be loaded)
+    uint32_t own = 0u;
+    one = (uint32_t)__builtin_amdgcn_readfirstlane((int)key[0]);
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) own |= key[r] ^ one;
+    return wave_or(own);
+}
+template <int W> __device__ __forceinline__ uint32_t bits_that_differ_in_all(const BinParts<W> &parts)
+{
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t one_of = parts.one[lane % W], differ_of = parts.differ[lane % W];
+    return row_or(differ_of | (one_of ^ (uint32_t)__builtin_amdgcn_readfirstlane((int)one_of)));
+}
+
 // at[r]: byte offset in the ordered keys of this lane's key r, which is key first + 64 r of n (past the end, where
 // the caller has repeated a key: its own); false (in all threads, none of which looks at `bins` any more): not by bins.
 // `bits`: those that the keys are ordered by; `bins`: 16-bit counters, 2^MAX_LOG of them,
@@ -687,12 +829,8 @@ __device__ __forceinline__ bool places_by_bins(const uint32_t (&key)[ITEMS], uin
     log_bins = log_bins < MAX_LOG ? log_bins : MAX_LOG;
     for (uint32_t i = 4u * tid; i < 1u << (log_bins - 1u); i += 4u * kThreads)
         *(u32x4 *)(bins + i) = u32x4{0u, 0u, 0u, 0u};
-    // (a wavefront's keys are compared with one of its own, and those with each other below: key 0 of all would have to be loaded)
-    uint32_t own = 0u;
-    const uint32_t one = (uint32_t)__builtin_amdgcn_readfirstlane((int)key[0]);
-#pragma unroll
-    for (int r = 0; r < ITEMS; ++r) own |= key[r] ^ one;
-    own = wave_or(own);
+    uint32_t one;
+    const uint32_t own = bits_that_differ(key, one);
     // Keys that crowd in a part of their range are mostly seen in a sample: a lane's first keys, 64 places apart, that fall into one bin.
     // (normally distributed floats, us in a row of sorts with the copy of new keys, by passes alone / with the look: 2049 10.8 / 11.4, 3000 11.3 / 12.0, 5000 14.1 / 14.8, 8192
     // 19.1 / 19.6; pairs, 13.2 / 14.0, 14.2 / 15.1, 17.7 / 18.6, 23.5 / 24.0.  0.1 us of it is the sample, the rest what all wavefronts find out together.  Without the sample
@@ -710,8 +848,8 @@ __device__ __forceinline__ bool places_by_bins(const uint32_t (&key)[ITEMS], uin
     }
     if (lane == 0u) { parts.differ[wave] = own; parts.one[wave] = one; parts.alike[wave] = alike; }
     __syncthreads();
-    uint32_t one_of = parts.one[lane % W], differ_of = parts.differ[lane % W], alike_of = parts.alike[lane % W];
-    differ &= row_or(differ_of | (one_of ^ (uint32_t)__builtin_amdgcn_readfirstlane((int)one_of)));
+    const uint32_t alike_of = parts.alike[lane % W];
+    differ &= bits_that_differ_in_all(parts);
     alike = row_sum(lane % 16u < W ? alike_of : 0u);
     if (differ == 0u) {                                    // all equal: in order
 #pragma unroll
@@ -952,6 +1090,15 @@ __device__ __forceinline__ void sort_in_block(const BlockArgs &B, uint32_t begin
     const auto by_bins = [&] {
         if constexpr (ITEMS >= Lds::kBinFew && ITEMS <= Lds::template kBinRows<VALS>)
             return places_by_bins<W, ITEMS, Lds::kLogBins>(key, first, n, B.bits, s.order, s.order + Lds::kBinsAt, s.bin_parts, at, differ);
+        else if constexpr (ITEMS > Lds::template kBinRows<VALS> && W < kBlockWaves) {
+            // (small buckets of large sorts: the passes leave out digits in which no key differs.  3 * 2^23 pairs of 5000 values, buckets of one value: 402 -> 352 us)
+            uint32_t one;
+            const uint32_t own = bits_that_differ(key, one);
+            if (lane == 0) { s.bin_parts.differ[wave] = own; s.bin_parts.one[wave] = one; }
+            __syncthreads();
+            differ = bits_that_differ_in_all(s.bin_parts);
+            return false;
+        }
         else return false;
     };
     if (by_bins()) {
@@ -1075,67 +1222,57 @@ __global__ __launch_bounds__(64 * kBlockWaves) void pass_or_buckets_kernel(PassA
 // 8 bytes per key (16 with payloads) where four passes move 8 bytes each; and the second pass has a carry chain per range, of some 32 tiles,
 // and writes into 2 MiB (135 us for 2^26 keys on seven bits, the first 132; on six bits 125, on eight 145; a second one over the whole array takes 6 more).
 // What the buckets' sizes are has to be known before the first pass: one table of all 2^14 counts in LDS, one addition per key,
-// in place of four.  Keys that crowd would have buckets too large: a sample of 8192 keys, taken by the kernel that clears the tables, says
-// whether it is worth counting; if the counts then say otherwise, the digits of the four passes are counted after all.
-// us for 2^26 random keys: sample 6, count 63, sizes and starts 10, passes 132 + 135, buckets 157, launches with nothing to do 14 (four
+// in place of four.  Buckets of up to 10,240 keys are sorted by eight wavefronts, a few larger ones by passes of their own (huge_pass).  Keys that crowd would have too
+// many of these: a sample of 8192 keys, taken by the kernel that clears the tables, says whether it is worth counting; if the counts then say otherwise, the
+// digits of the four passes are counted after all.
+// us for 2^26 random keys: sample 8, count 66, sizes and starts 10, passes 132 + 133, buckets 159, launches with nothing to do 15 (four
 // passes: 70 + 4 x 144).  What bounds the buckets' kernel is LDS (68 % of its time) and the vector unit (75 %) at 16 wavefronts a compute unit;
 // pairs, 2^25 of them 107 us, the memory.  Tried and dropped: tiles of 8192 and 4096 keys in four and eight smaller workgroups a unit (first pass 176
-// and 258), seven ballots for the seven bits (no change), buckets from the last one on, whose keys the memory-side cache may hold (157 -> 156.5).
+// and 258), seven ballots for the seven bits (no change), buckets from the last one on, whose keys the memory-side cache may hold (157 -> 156.5), eight wavefronts for
+// all buckets, which would save a launch (2^26 keys 611 -> 662).
+// us per sort with the copy of new keys, four passes alone / now: 3 * 2^23 random keys 290 / 260, pairs 447 / 362, 2^25 378 / 323, pairs 633 / 486, 2^26 764 / 610, pairs 1450 / 1070, 76
+// million 935 / 706, 2^26 in order 768 / 577.
+// Keys that crowd pay for the sample (6 us; 3 of them because its places are far apart), for four launches with nothing to do (11) and for passes that ask which way the sort goes (4):
+// normally distributed floats, 3 * 2^23 287 / 306, pairs 431 / 453, 2^25 375 / 396, pairs 610 / 629, 2^26 750 / 777, pairs 1390 / 1417, 76 million 890 / 918; and so
+// do 3 * 2^23 keys of 16,000 values, whose buckets go by passes (281 / 311; pairs 410 / 415; 2^26 of them 720 / 547).  Fewer keys would lose more of what four passes take
+// (2^24: 8 to 13 %) than others gain (11 %), so they keep the four passes.
 
-constexpr uint32_t kFineLogMost = 14, kSampleQuads = 2048;
+using large_sort::kLogMost;
+using large_sort::kSampleQuads;
+static_assert((1u << large_sort::kLogLeast) % (4u * kHistThreads) == 0u && large_sort::kLogLeast == 13 && kLogMost == 14 && kDigits == 256, "who looks at what of a sample");
 using FineLds = BlockLdsOf<4, 20, 1, 20, 13>;
 static_assert(offsetof(FineLds, bins_end) == 4 * FineLds::kCapacity && FineLds::kBinsAt % 4 == 0 && alignof(FineLds) >= alignof(CounterQuad), "as BlockLds");
 static_assert(4 * sizeof(FineLds) <= 160 * 1024, "four workgroups on a compute unit");
 using FineLargeLds = BlockLdsOf<8, 20, 1, 20, 14>;
 static_assert(offsetof(FineLargeLds, bins_end) == 4 * FineLargeLds::kCapacity && FineLargeLds::kBinsAt % 4 == 0 && alignof(FineLargeLds) >= alignof(CounterQuad), "as BlockLds");
 static_assert(2 * sizeof(FineLargeLds) <= 160 * 1024, "two workgroups on a compute unit");
+static_assert(FineLds::kCapacity == large_sort::kSmallMost && FineLargeLds::kCapacity == large_sort::kLargeMost, "as planned");
 
-struct Fine {
-    uint32_t split;                       // are there buckets?
-    uint32_t tried;                       // the sample says so
-    uint32_t large;                       // buckets of more keys than FineLds holds ...
-    uint32_t pad;
-    uint32_t top[kDigits];                // counts of the first pass's digit
-    uint32_t start[1u << kFineLogMost];
-    uint32_t large_at[1u << kFineLogMost];                               // ... and which
-};
 struct FineArgs {
     HistArgs H;                           // keys, the four passes' digits, status words to clear
-    Fine *fine;
+    large_sort::Found *fine;
     uint32_t *counts;                     // [table][bucket], kTables of them
     TileOfRange *ranges;                  // the second pass's tiles
     uint32_t tile_keys;
     uint32_t *clear;                      // words to clear: H.hist and what follows it, up to the status words
     uint32_t clear_quads;
     Digit all, second;                    // a bucket's bits, and the lower half of them
-    uint32_t sample_most, sample_wide_most, bucket_most;                 // keys of a sample in a bucket, in a 256th of all buckets; keys of a bucket
+    uint32_t *huge;                       // tiles of huge buckets: bucket in the lower 14 bits, tile above
+    large_sort::Plan plan;
     BlockArgs B;                          // buckets in their places
 };
 
-// One key of each lane to the count of its bucket; `look` gets sums that come out.  Where many lanes agree with the first one they are added at
-// once: keys in order or equal would be added one after the other (2^24 keys in order: the counting kernel 57 -> 16 us, the sample of equal ones 13 -> 8).
-template <class Look> __device__ __forceinline__ void add_to_bucket(uint32_t *counts, uint32_t bucket, Look look)
-{
-    const uint64_t as_first = __ballot(bucket == (uint32_t)__builtin_amdgcn_readfirstlane((int)bucket));
-    const uint32_t all = (uint32_t)__builtin_popcountll(as_first);
-    if (all < 16u) {
-        look(atomicAdd(&counts[bucket], 1u) + 1u);
-    } else {
-        const uint32_t lane = threadIdx.x & 63u;
-        const bool one_of = as_first >> lane & 1u, first = lane == (uint32_t)__builtin_ctzll(as_first);
-        if (!one_of || first) { const uint32_t add = first ? all : 1u; look(atomicAdd(&counts[bucket], add) + add); }
-    }
-}
-
 // Sample and clear.  (The sample: groups of four keys, one from each of kSampleQuads equal parts of the array, not at the same place of each.)
+// Nobody waits for a sum while keys are added; all sums are looked at afterwards.  The upper half of a counter counts first keys of a group: those of a group
+// may share a bucket, as they do in an array in order, where the number of buckets with keys would say that there are few.
 __global__ __launch_bounds__(kHistThreads) void fine_sample_kernel(FineArgs F)
 {
-    __shared__ uint32_t s_count[1u << kFineLogMost], s_wide[kDigits];
+    __shared__ uint32_t s_count[1u << kLogMost];
     const uint32_t tid = threadIdx.x;
     if (blockIdx.x != 0u) {
         const uint32_t found = (uint32_t)((const u32x4 *)F.fine - (const u32x4 *)F.clear);      // what workgroup 0 writes
         for (uint32_t i = (blockIdx.x - 1u) * kHistThreads + tid; i < F.clear_quads; i += (gridDim.x - 1u) * kHistThreads)
-            if (i != found) ((u32x4 *)F.clear)[i] = u32x4{0u, 0u, 0u, 0u};
+            if (i != found && i != found + 1u) ((u32x4 *)F.clear)[i] = u32x4{0u, 0u, 0u, 0u};
         return;
     }
     const uint32_t buckets = 1u << F.all.width;
@@ -1146,26 +1283,55 @@ __global__ __launch_bounds__(kHistThreads) void fine_sample_kernel(FineArgs F)
         const uint32_t g = q * kHistThreads + tid;
         k[q] = ((const u32x4 *)F.H.keys)[(uint64_t)g * part + (g * 0x9E3779B1u >> 8) % part];
     }
-    for (uint32_t i = tid; i < buckets; i += kHistThreads) s_count[i] = 0u;
-    if (tid < kDigits) s_wide[tid] = 0u;
+    for (uint32_t i = 4u * tid; i < buckets; i += 4u * kHistThreads) *(u32x4 *)(s_count + i) = u32x4{0u, 0u, 0u, 0u};
     __syncthreads();
-    bool crowded = false;
 #pragma unroll
     for (uint32_t q = 0; q < kSampleQuads / kHistThreads; ++q)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const uint32_t bucket = digit_of(k[q][i], F.all);
-            add_to_bucket(s_count, bucket, [&](uint32_t sum) { crowded |= sum > F.sample_most; });
-            add_to_bucket(s_wide, bucket >> (F.all.width - 8), [&](uint32_t sum) { crowded |= sum > F.sample_wide_most; });
+        for (int i = 0; i < 4; ++i) add_to_count(s_count, digit_of(k[q][i], F.all), i == 0 ? 0x10001u : 1u);
+    __syncthreads();
+    // Four buckets a thread at a time; 16 lanes, or 8 (2^13 buckets), have a 256th of them.
+    uint32_t used = 0u, work = 0u;
+    bool crowded = false;
+    const uint32_t last_of = F.all.width == kLogMost ? 15u : 7u;
+    for (uint32_t i = 4u * tid; i < buckets; i += 4u * kHistThreads) {
+        const u32x4 c = *(const u32x4 *)(s_count + i);
+        uint32_t wide = 0u, most = 0u;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const uint32_t keys = c[j] & 0xFFFFu;
+            wide += keys;
+            most = keys > most ? keys : most;
+            used += c[j] > 0xFFFFu ? 1u : 0u;
         }
+        if (__ballot(most > F.plan.some_most)) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t keys = c[j] & 0xFFFFu;
+                if (keys > F.plan.some_most) work += keys * (1u + (uint32_t)((uint64_t)keys * F.H.n / (large_sort::kSample * large_sort::kHugeTile)));
+            }
+        }
+        wide += dpp0<kRowShr + 1>(wide);
+        wide += dpp0<kRowShr + 2>(wide);
+        wide += dpp0<kRowShr + 4>(wide);
+        if (last_of == 15u) wide += dpp0<kRowShr + 8>(wide);
+        crowded |= most > F.plan.huge_most || ((tid & last_of) == last_of && wide > F.plan.wide_most);
+    }
+    __shared__ uint32_t s_work[kHistThreads / 64], s_used[kHistThreads / 64];
+    work = wave_sum(work);                                 // (at most 8192 keys and what a bucket of all of them reads: no overflow)
+    used = wave_sum(used);
+    if ((tid & 63u) == 0u) { s_work[tid >> 6] = work; s_used[tid >> 6] = used; }
     const bool any = __syncthreads_or(crowded);
-    if (tid == 0u) { F.fine->split = F.fine->tried = any ? 0u : 1u; F.fine->large = 0u; }
+    if (tid >= 64u) return;
+    work = row_sum(s_work[tid & 15u]);
+    used = row_sum(s_used[tid & 15u]);
+    if (tid < 8u) ((uint32_t *)F.fine)[tid] = tid < 2u && !any && work <= F.plan.work_most && used >= F.plan.few_most ? 1u : 0u;
 }
 
 // The buckets' sizes, or the digits' counts.
 __global__ __launch_bounds__(kHistThreads) void fine_count_kernel(FineArgs F)
 {
-    __shared__ uint32_t s_count[kHistWords > (1 << kFineLogMost) ? kHistWords : 1 << kFineLogMost];
+    __shared__ uint32_t s_count[kHistWords > (1 << kLogMost) ? kHistWords : 1 << kLogMost];
     if (!F.fine->tried) { digit_histograms(F.H, s_count); return; }
     const HistArgs &H = F.H;
     const uint32_t tid = threadIdx.x, buckets = 1u << F.all.width;
@@ -1183,12 +1349,12 @@ __global__ __launch_bounds__(kHistThreads) void fine_count_kernel(FineArgs F)
 #pragma unroll
         for (int a = 0; a < kAhead; ++a)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) add_to_bucket(s_count, digit_of(k[a][j], F.all), [](uint32_t) {});
+            for (int j = 0; j < 4; ++j) add_to_count(s_count, digit_of(k[a][j], F.all));
     }
     for (; i < quads; i += stride) {
         const u32x4 x = *(keys4 - i);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) add_to_bucket(s_count, digit_of(x[j], F.all), [](uint32_t) {});
+        for (int j = 0; j < 4; ++j) add_to_count(s_count, digit_of(x[j], F.all));
     }
     if (t0 < (H.n & 3u)) atomicAdd(&s_count[digit_of(H.keys[4 * quads + t0], F.all)], 1u);
     for (uint64_t q = t0; q < H.status_quads; q += stride) ((u32x4 *)H.status)[q] = u32x4{0u, 0u, 0u, 0u};
@@ -1210,8 +1376,15 @@ __global__ __launch_bounds__(kDigits) void fine_judge_kernel(FineArgs F)
 #pragma unroll
         for (uint32_t t = 0; t < kTables; ++t) size += F.counts[(size_t)t * buckets + b];
         F.counts[b] = size;
-        if (size > F.bucket_most) F.fine->split = kNotSplit;
-        if (size > FineLds::kCapacity) F.fine->large_at[atomicAdd(&F.fine->large, 1u)] = b;
+        if (size > large_sort::kHugeMost) {
+            F.fine->split = kNotSplit;
+        } else if (size > large_sort::kLargeMost) {
+            const uint32_t tiles = large_sort::tiles_of(size), at = atomicAdd(&F.fine->huge, tiles);
+            atomicAdd(&F.fine->work, (size >> 10) * tiles);
+            for (uint32_t i = 0; i < tiles && at + i < F.plan.huge_tiles; ++i) F.huge[at + i] = b | i << kLogMost;
+        } else if (size > large_sort::kSmallMost) {
+            F.fine->large_at[atomicAdd(&F.fine->large, 1u)] = b;
+        }
     }
     const uint32_t sum = wave_sum(size);
     if (lane == 0u) s_part[tid >> 6] = sum;
@@ -1224,7 +1397,13 @@ __global__ __launch_bounds__(kHistThreads) void fine_start_kernel(FineArgs F)
 {
     __shared__ uint32_t s_count[kHistWords];
     if (!F.fine->tried) return;
-    if (F.fine->split == kNotSplit) { digit_histograms(F.H, s_count); return; }
+    // (where the huge buckets are too much work, all workgroups find so, whether they see that the first has written it or not)
+    const bool over = F.fine->work > F.plan.huge_work || F.fine->huge > F.plan.huge_tiles;
+    if (F.fine->split == kNotSplit || over) {
+        if (over && blockIdx.x == 0u && threadIdx.x == 0u) F.fine->split = kNotSplit;
+        digit_histograms(F.H, s_count);
+        return;
+    }
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6, row = 1u << F.second.width;
     if (blockIdx.x >= 1u << (F.all.width - F.second.width) || tid >= kDigits) return;        // (the others of the workgroup wait for nobody)
     // every wavefront adds up what lies in front of the row, and the parts of it in front of its own
@@ -1319,20 +1498,6 @@ const void *pass_or_buckets_kernel_for(int items, bool vals)
     return vals ? (const void *)pass_or_buckets_kernel<8, true> : (const void *)pass_or_buckets_kernel<8, false>;
 }
 
-// Two passes and small buckets: as few bits as leave 4700 keys or fewer on average (5120 is what a workgroup has places for), up to 2^14 buckets; the
-// bits that are left are enough for bins, and there are four passes to do otherwise (with three, an odd number starts from a copy).
-// us per sort, four passes / now: 3 * 2^23 random keys 263 / 230, pairs 369 / 285, 2^25 341 / 283, pairs 530 / 387, 2^26 662 / 512, 76 million 836 / 598, 2^26 in
-// order 670 / 481.  Keys that crowd pay for six launches with nothing to do, some 20 us: 2^26 normally distributed floats 650 / 678, 2^25 equal pairs 419 / 446, 3 * 2^23
-// floats 258 / 277, and a sort of fewer keys would have paid 8 to 13 % (2^24: 185 / 202, random 187 / 165), so it keeps the four passes.
-constexpr size_t kFineFew = (size_t)3 << 23, kFineMost = (size_t)4700 << kFineLogMost;
-int fine_bits(size_t n)
-{
-    int log = 2;
-    while ((n >> log) > 4700) ++log;
-    return log;
-}
-bool fine_wanted(size_t n, int bits) { return n >= kFineFew && n <= kFineMost && bits > 24 && bits >= fine_bits(n) + 12; }
-
 // `bits` low bits in digits as even as possible.
 void split_digits(int bits, Passes &P)
 {
@@ -1349,29 +1514,26 @@ tcuscan_status_t fine_sort(void *d_keys, void *d_vals, size_t n, int bits, void 
                            bool around_cache, unsigned use_tickets, unsigned spin_limit, unsigned mute_tile, void *d_fault, hipStream_t s)
 {
     const bool v = d_vals != nullptr;
-    const int log = fine_bits(n), low = v ? (log + 2) / 2 : log / 2;    // (2^26 keys, the second pass on 7 / 8 / 6 bits of 14: 512 / 516 / 521 us; 2^25 pairs 392 / 387 / 391)
-    const uint32_t buckets = 1u << log;
     FineArgs F;
-    // scratch: digit counts, tickets, what the kernels find out, the buckets' counts (all cleared), status words
+    F.plan = large_sort::plan(n, v);
+    const int log = F.plan.log, low = F.plan.low;          // (2^26 keys, the second pass on 7 / 8 / 6 bits of 14: 512 / 516 / 521 us; 2^25 pairs 392 / 387 / 391)
+    const uint32_t buckets = 1u << log;
+    const size_t most_tiles = F.plan.most_tiles;
+    // scratch: digit counts, tickets, what the kernels find out, the buckets' counts, tiles (all cleared), status words
     uint32_t *tickets = hist + kTables * kTableWords;
-    F.fine = (Fine *)(tickets + kMaxPasses);
-    F.counts = (uint32_t *)(F.fine + 1);
-    F.ranges = (TileOfRange *)(F.counts + kTables * buckets);
-    F.tile_keys = 64u * kPassWaves * 16u;
-    const size_t most_tiles = tiles + ((size_t)1 << (log - low));        // of the second pass
-    uint32_t *status = (uint32_t *)(F.ranges + most_tiles);
-    static_assert(sizeof(Fine) % 16 == 0 && kTableWords % 4 == 0 && kMaxPasses % 4 == 0, "16-byte boundaries");
+    F.fine = (large_sort::Found *)(hist + F.plan.found);
+    F.counts = hist + F.plan.counts;
+    F.ranges = (TileOfRange *)(hist + F.plan.ranges);
+    F.huge = hist + F.plan.huge;
+    F.tile_keys = large_sort::kPassTile;
+    uint32_t *status = hist + F.plan.status;
+    static_assert(sizeof(TileOfRange) == 16 && large_sort::kPassTile == 64u * kPassWaves * 16u, "as planned");
     F.clear = hist;
-    F.clear_quads = (uint32_t)(status - hist) / 4u;
+    F.clear_quads = (uint32_t)F.plan.status / 4u;
     F.all = {bits - log, log};
     F.second = {bits - log, low};
     const Digit top = {bits - log + low, log - low};
-    F.bucket_most = FineLargeLds::kCapacity;
-    // The sample: a 256th of all buckets that holds as many keys as if nine tenths of the largest were in each (keys that crowd gently: bell-shaped), and a bucket
-    // with twice as many as the largest, and eight, which even keys do not come to by chance.
-    const double sample = 4.0 * kSampleQuads, largest = (double)F.bucket_most / (double)n;
-    F.sample_wide_most = (uint32_t)(0.9 * sample * largest * (double)(buckets / kDigits));
-    F.sample_most = (uint32_t)(2.0 * sample * largest) + 8u;
+    const int half = (bits - log + 1) / 2;                 // (at most ten: 2^13 buckets leave 19 bits of 32)
     const size_t pass_words = most_tiles * kDigits;
     HistArgs &H = F.H;
     H.keys = (const uint32_t *)d_keys; H.vals = nullptr; H.keys_copy = H.vals_copy = nullptr;
@@ -1393,10 +1555,11 @@ tcuscan_status_t fine_sort(void *d_keys, void *d_vals, size_t n, int bits, void 
         A.fault = (uint32_t *)d_fault;
         A.n = n; A.spin_limit = spin_limit; A.mute_tile = mute_tile; A.digit = P.digit[p]; A.stream = around_cache;
         A.split = &F.fine->split;
-        A.top = p == 0 ? top : F.second;
+        A.top = p == 0 ? top : p == 1 ? F.second : p == 2 ? Digit{0, half} : Digit{half, bits - log - half};
         A.top_hist = F.fine->top; A.ranges = F.ranges; A.range_start = F.fine->start;
+        A.found = F.fine; A.huge = F.huge; A.sizes = F.counts; A.huge_tiles = F.plan.huge_tiles;
         void *args[] = {&A};
-        const void *fn = p == 0 ? pass_kernel_of<16, kFirstOfTwo>(v) : p == 1 ? pass_kernel_of<16, kSecondOfTwo>(v) : pass_kernel_of<16, kLaterPass>(v);
+        const void *fn = p == 0 ? pass_kernel_of<16, kFirstOfTwo>(v) : p == 1 ? pass_kernel_of<16, kSecondOfTwo>(v) : pass_kernel_of<16, kAfterTwo>(v);
         if (!launch(fn, p == 1 ? most_tiles : tiles, 64 * kPassWaves, args)) return TCUSCAN_ERR_HIP;
         uint32_t *t = src_k; src_k = dst_k; dst_k = t;
         t = src_v; src_v = dst_v; dst_v = t;
@@ -1440,7 +1603,7 @@ tcuscan_status_t tcuscan_internal_digit_sort(void *d_keys, void *d_vals, size_t 
         P = rest;
         P.digit[P.count++] = {bits - 8, 8};
     }
-    const bool fine_form = !buckets_wanted && !wide && fine_wanted(n, bits);
+    const bool fine_form = !buckets_wanted && !wide && large_sort::wanted(n, bits);
     const int items = pass_items(n);
     auto tiles_of = [n](int per_lane) { const size_t tile = (size_t)64 * kPassWaves * per_lane; return (n + tile - 1) / tile; };
     const size_t tiles = tiles_of(items);

@@ -14,6 +14,7 @@ template <int CTRL> __device__ __forceinline__ uint32_t dpp0(uint32_t v)
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, false);
 }
 constexpr int kRowShr = 0x110;   // DPP control: shift right by n lanes inside each row of 16
+constexpr int kQuadPerm1032 = 0xB1, kQuadPerm2301 = 0x4E;      // lanes 0 to 3 of each four from lanes 1, 0, 3, 2 / 2, 3, 0, 1
 
 __device__ __forceinline__ float    acc_add(float a, float b)       { return a + b; }
 __device__ __forceinline__ uint32_t acc_add(uint32_t a, uint32_t b) { return a + b; }
