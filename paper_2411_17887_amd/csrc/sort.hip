@@ -169,6 +169,7 @@ struct HistArgs {
     Passes P;
     bool stream;                          // as in PassArgs
     bool own;                             // no more workgroups than tables
+    bool from_end;                        // the last key first
 };
 
 // All passes' digit counts in one reading of the keys: the counts do not change when keys change places.  A digit has
@@ -176,7 +177,8 @@ struct HistArgs {
 // meet four at a time and not all 64, and random ones meet less often in a bank.  What bounds it is the four LDS
 // additions per key.  2^22 keys in all, payloads on top: 8 counters per digit and workgroups of 256 cost 13 us more, 32
 // counters (one workgroup per compute unit) 2 us more; 1024 workgroups instead of 512 add as much again in the final
-// additions to the same 1024 words.
+// additions to the same 1024 words.  Large arrays without a copy are read from the last key on: those written last may still be in the memory-side cache (2^26 normally
+// distributed floats, which take four passes, 776 -> 762 us, 3 * 2^23 no change; with the copy that an odd number of passes starts from, 2^24 pairs on 24 bits 284 -> 289).
 constexpr int kHistCopies = 16, kHistThreads = 1024, kHistGrid = 512;
 // The workgroups add up in one of eight tables -- additions to one word from all dies go one after the other, 27 ns each: 2^22
 // keys 14.5 -> 7 us -- and up to eight workgroups have one each, which then needs no clearing in front (HistArgs::own).
@@ -204,16 +206,17 @@ __device__ __forceinline__ void digit_histograms(const HistArgs &H, uint32_t *s_
     };
     const uint64_t quads = H.n / 4;
     const u32x4 *keys4 = (const u32x4 *)H.keys;
+    const auto at = [=](uint64_t i) { return H.from_end ? quads - 1 - i : i; };
     // the next four keys are on their way while four are counted
     u32x4 next = {0u, 0u, 0u, 0u};
     auto load = [&](uint64_t i) {
-        if (i < quads) next = H.stream ? __builtin_nontemporal_load(keys4 + i) : keys4[i];
+        if (i < quads) next = H.stream ? __builtin_nontemporal_load(keys4 + at(i)) : keys4[at(i)];
     };
     load(t0);
     for (uint64_t i = t0; i < quads; i += stride) {
         const u32x4 k = next;
         load(i + stride);
-        if (H.keys_copy) ((u32x4 *)H.keys_copy)[i] = k;
+        if (H.keys_copy) ((u32x4 *)H.keys_copy)[at(i)] = k;
         add(k[0]); add(k[1]); add(k[2]); add(k[3]);
     }
     if (t0 < (H.n & 3u)) {
@@ -1233,7 +1236,7 @@ __global__ __launch_bounds__(64 * kBlockWaves) void pass_or_buckets_kernel(PassA
 // us per sort with the copy of new keys, four passes alone / now: 3 * 2^23 random keys 290 / 260, pairs 447 / 362, 2^25 378 / 323, pairs 633 / 486, 2^26 764 / 610, pairs 1450 / 1070, 76
 // million 935 / 706, 2^26 in order 768 / 577.
 // Keys that crowd pay for the sample (6 us; 3 of them because its places are far apart), for four launches with nothing to do (11) and for passes that ask which way the sort goes (4):
-// normally distributed floats, 3 * 2^23 287 / 306, pairs 431 / 453, 2^25 375 / 396, pairs 610 / 629, 2^26 750 / 777, pairs 1390 / 1417, 76 million 890 / 918; and so
+// normally distributed floats, 3 * 2^23 287 / 306, pairs 431 / 453, 2^25 375 / 396, pairs 610 / 629, 2^26 750 / 764, pairs 1390 / 1400, 76 million 890 / 897; and so
 // do 3 * 2^23 keys of 16,000 values, whose buckets go by passes (281 / 311; pairs 410 / 415; 2^26 of them 720 / 547).  Fewer keys would lose more of what four passes take
 // (2^24: 8 to 13 %) than others gain (11 %), so they keep the four passes.
 
@@ -1537,7 +1540,7 @@ tcuscan_status_t fine_sort(void *d_keys, void *d_vals, size_t n, int bits, void 
     const size_t pass_words = most_tiles * kDigits;
     HistArgs &H = F.H;
     H.keys = (const uint32_t *)d_keys; H.vals = nullptr; H.keys_copy = H.vals_copy = nullptr;
-    H.hist = hist; H.tables = kTables; H.status = status; H.n = n; H.status_quads = pass_words * P.count / 4; H.P = P; H.stream = around_cache; H.own = false;
+    H.hist = hist; H.tables = kTables; H.status = status; H.n = n; H.status_quads = pass_words * P.count / 4; H.P = P; H.stream = around_cache; H.own = false; H.from_end = true;
     F.B = {(const uint32_t *)d_keys, (const uint32_t *)d_vals, (uint32_t *)d_keys, (uint32_t *)d_vals, nullptr, (uint32_t)n, {}, (uint32_t)(bits - log)};
     split_digits(bits - log, F.B.P);
     void *fine_args[] = {&F};
@@ -1632,7 +1635,7 @@ tcuscan_status_t tcuscan_internal_digit_sort(void *d_keys, void *d_vals, size_t 
         HistArgs H;
         H.keys = src_k; H.vals = src_v;
         H.keys_copy = odd ? dst_k : nullptr; H.vals_copy = odd && src_v ? dst_v : nullptr;
-        H.hist = hist; H.tables = tables; H.status = status; H.n = n; H.status_quads = pass_words * P.count / 4; H.P = P; H.stream = around_cache; H.own = own;
+        H.hist = hist; H.tables = tables; H.status = status; H.n = n; H.status_quads = pass_words * P.count / 4; H.P = P; H.stream = around_cache; H.own = own; H.from_end = false;
         void *args[] = {&H};
         if (hipLaunchKernel((const void *)digit_histograms_kernel, dim3(hist_grid), dim3(kHistThreads), args, 0, s) != hipSuccess) return TCUSCAN_ERR_HIP;
     }
