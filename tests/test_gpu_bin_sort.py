@@ -5,6 +5,7 @@ import pytest
 
 from paper_2411_17887_amd import inputs
 from test_gpu_digit_sort import check
+from test_gpu_sort_forms import check_large
 
 pytestmark = pytest.mark.gpu
 
@@ -94,9 +95,11 @@ def large_keys(name, n):
     share = lambda parts: i % np.uint32(parts) == 0
     return {
         "two_thirds_of_the_range": (r.astype(np.uint64) * 2 // 3).astype(np.uint32),
-        "five_eighths_empty": r % np.uint32(3 << 29),                                   # buckets of 5500 to 8000 keys
+        "five_eighths_empty": r % np.uint32(3 << 29),                                   # buckets of 5800 to 9600 keys: the sample says no
+        "lower_half_of_the_range": r >> np.uint32(1),                                   # buckets of 5800 to 6500 keys, for eight wavefronts
         "equal_in_buckets": r & np.uint32(0xFFFF0000),                                  # many equal keys in every bucket
-        "few_bits_in_buckets": r & np.uint32(0xFFE000FF),
+        "few_bits_in_buckets": r & np.uint32(0xFFE000FF),                               # 2048 buckets of some 12,300 keys: the sample says no
+        "few_bits_in_every_bucket": r & np.uint32(0xFFF800FF),
         "crowded": np.random.default_rng(3).standard_normal(n).astype(np.float32).view(np.uint32),
         "equal": np.full(n, 7, np.uint32),
         "in_order": np.sort(r),
@@ -108,10 +111,18 @@ def large_keys(name, n):
     }[name].astype(np.uint32)
 
 
-@pytest.mark.parametrize("name", ["two_thirds_of_the_range", "five_eighths_empty", "equal_in_buckets", "few_bits_in_buckets", "crowded", "equal", "in_order",
-                                  "one_bucket_of_10240", "one_bucket_of_10241", "one_bucket_of_20000", "every_thousandth_equal", "every_tenth_equal"])
-def test_large_sorts_of_keys_that_split_unevenly(name):
-    check(large_keys(name, LARGE + 77_777), True, 32)
+HALF = 1 << 12                                           # of the buckets
+
+
+@pytest.mark.parametrize("name,split,large,huge", [
+    ("two_thirds_of_the_range", 1, 0, 0), ("five_eighths_empty", 0, 0, 0), ("lower_half_of_the_range", 1, HALF, 0), ("equal_in_buckets", 1, 0, 0),
+    ("few_bits_in_buckets", 0, 0, 0), ("few_bits_in_every_bucket", 1, 0, 0), ("crowded", 0, 0, 0), ("equal", 0, 0, 0), ("in_order", 1, 0, 0),
+    ("one_bucket_of_10240", 1, HALF + 1, 0), ("one_bucket_of_10241", 1, HALF, 2), ("one_bucket_of_20000", 1, HALF, 3), ("every_thousandth_equal", 1, 0, 4),
+    ("every_tenth_equal", 0, 0, 0)])
+def test_large_sorts_of_keys_that_split_unevenly(name, split, large, huge):
+    """The order, and the way it was come by: buckets or four passes, buckets for eight wavefronts, tiles of larger ones."""
+    got = check_large(large_keys(name, LARGE + 77_777), True, 32)
+    assert (got["split"], got["large"], got["huge"]) == (split, large, huge)
 
 
 def test_large_sorts_by_ticket_and_in_a_graph():

@@ -1,7 +1,6 @@
-"""Which large sorts take two passes and small buckets, and that their scratch fits the words they are given (no GPU: see launch_recorder.py)."""
+"""Which large sorts take two passes and small buckets: kernels and grids (no GPU: see launch_recorder.py; where their scratch lies: test_sort_rules_cpu.py)."""
 import pytest
 
-import launch_recorder
 from test_launches_cpu import VALS, VALS_TMP, run, sort    # noqa: F401  (run: a fixture)
 
 FEW, MOST = 3 << 23, 4700 << 14
