@@ -329,11 +329,14 @@ tcuscan_status_t tcuscan_compact_u32(const void *d_values, const void *d_mask, v
  *   d_flags                  scratch, n bytes, 16-byte aligned
  *   d_positions              scratch, n int32
  * By default the reduction runs with 256 buckets instead of two: passes on up to eight bits, each one kernel that ranks a
- * tile's keys, takes the carry of every bucket from the tiles before and stores the tile in order; a full sort is four
- * passes and one reading of the keys for the bucket sizes (up to 8192 keys: one kernel, one workgroup; from there one pass on the
- * top eight bits and a workgroup per bucket, up to 16384 keys on more than 8 bits, and up to 6,055,225 keys on more than 16 if no
- * bucket is too large; two passes on the top 13 or 14 bits and a workgroup per bucket for 3 * 2^23 to 77,004,800 keys on 26 bits and
- * more, 25 in part, if no bucket has more than 10,240 keys).  d_flags is not used,
+ * tile's keys, takes the carry of every bucket from the tiles before and stores the tile in order; four of them and one reading
+ * of the keys for the bucket sizes sort by 32 bits.  Most sizes do with fewer:
+ *   up to 8192 keys                            one kernel, one workgroup
+ *   up to 16,384 on more than 8 bits, up to    one pass on the top eight bits and a workgroup per bucket
+ *   6,055,225 on more than 16
+ *   3 * 2^23 to 77,004,800 on 26 bits and      two passes on the top 13 or 14 bits and a workgroup per bucket; buckets of 10,241 to 2^18 keys by
+ *   more, up to 38,510,591 also on 25          two passes of their own
+ * From 16,385 keys on the kernels see whether too many keys share a bucket, and then make all passes.  d_flags is not used,
  * d_positions holds bucket sizes and status words.  tcuscan_set_sort_fusion(2) splits on one bit per pass in a
  * fused kernel (flags built from the keys, scanned on the MFMA unit, keys scattered), tcuscan_set_sort_fusion(0) selects
  * the three-kernel form of the reduction (mask kernel, tcuscan_exclusive, scatter kernel per bit), which is also what

@@ -7,7 +7,8 @@
 //     workgroup        the counters of the wavefronts, added up digit by digit
 //     array            one status word per tile and digit, published and looked up as in the scan kernels' carry chain
 // (the published scheme of least-significant-digit passes with a decoupled look-back per digit: Merrill and Garland 2016,
-// Adinets and Merrill, "Onesweep", 2022).  A full sort is four passes of 8 bytes per key (16 with payloads) and one reading of the keys for the first term.
+// Adinets and Merrill, "Onesweep", 2022).  By passes alone a full sort is
+// four of 8 bytes per key (16 with payloads) and one reading of the keys for the first term.
 //
 // Sorts of up to 6,055,225 keys on more than 16 bits (up to 16384 keys on more than 8) do with one pass on the top eight bits if the 256
 // buckets then are small enough for a workgroup each, which sorts its bucket by the other bits in LDS (partition, then local sorts, as in
@@ -768,14 +769,15 @@ __global__ __launch_bounds__(64 * kSpreadWaves) void spread_kernel(SpreadArgs A)
 // there: in no particular order), and where each belongs inside its bin is then seen by comparing it with the others there: key bits
 // below the bin's, then the key's place among the n, so the result is the stable order.  This takes the place of all passes: some ten
 // accesses to LDS and 45 vector instructions per row of 64 keys, where each pass on eight bits takes more than that.  What bounds it
-// is both: of 27,700 cycles for 16,320 keys on a compute unit 2800 go to the loads, 2700 to the counters, 4700 to their sums, 6000 to the
-// way into the bins, 7300 to the comparisons, 4000 to the way out (256 workgroups together 15.9 us; three passes 28).  Before -> now, us per
-// sort: 5000 keys 13.6 -> 8.2, 8192 18.4 -> 9.4, in order 19.3 -> 4.9 (without the copy of new ones), 2^22 in buckets 70.8 -> 61.3, pairs 85.5 -> 72.7.
-//   twice as many bins as keys and not as many: the comparisons of 256 x 16,320 keys 15,300 -> 9500 cycles.
-//   a bin's first place and the next one's from two aligned words: one read across words takes three times as long (6000 -> 18,500).
+// is both (256 buckets of 16,384 keys 19.8 us, pairs 22.0, by three passes 33.9; in small buckets of large sorts LDS is busy for 68 % of the time, the
+// vector unit for 75).  By passes -> now, us per sort: 5000 keys 13.6 -> 8.3, 8192 18.4 -> 9.7, in order 19.3 -> 4.9 (without the copy of new
+// ones), 2^22 in buckets 70.1 -> 61.5, pairs 83.4 -> 72.
+//   twice as many bins as keys and not as many: most of the comparisons, which were the largest part, fall away.
+//   a bin's first place and the next one's from two aligned words: one read across words takes three times as long.
+//   four neighbouring counters a thread when they are added up, not a thread's whole share in a row: that was a quarter of what LDS did (below).
 //   payloads loaded when the keys have their places, not with them: 256 x 16,320 pairs 23.2 -> 20.4 us, 16,384 (18 rows) 28.9 -> 21.5.
 // Keys that crowd in a part of their range are seen before anything is moved, from a sample of pairs, or from the counters, and the passes do the work:
-// what that costs is 0.5 to 0.9 us (below).  Fewer than 2049 keys gain nothing, for more than 20,480 (18,432 with payloads: BlockLdsOf) there are too few registers.
+// what that costs is 0.5 to 1.1 us (below).  Fewer than 2049 keys gain nothing, for more than 20,480 (18,432 with payloads: BlockLdsOf) there are too few registers.
 
 constexpr uint32_t kBinMost = 16;                          // keys of a bin, at most
 constexpr uint32_t kAlikeMost = 6;                         // pairs of a sample that share a bin: fewer

@@ -243,7 +243,8 @@ def set_sort_fusion(form: int) -> None:
 
 
 def split_radix_sort_u32(keys, keys_tmp, flags, positions, vals=None, vals_tmp=None, bits: int = 32, ws=None, stream=None) -> None:
-    """Stable LSD radix sort of 32-bit keys (and optional payloads) by its low `bits` bits, eight (one: set_sort_fusion) per pass."""
+    """Stable radix sort of 32-bit keys (and optional payloads) by their low `bits` bits: passes on up to eight bits, or fewer of them and a workgroup
+    per bucket (set_sort_fusion: one bit per pass)."""
     rc = load().tcuscan_split_radix_sort_u32(_ptr(keys), _ptr(vals), keys.numel(), int(bits), _ptr(keys_tmp), _ptr(vals_tmp),
                                              _ptr(flags), _ptr(positions), *_ws_args(ws), _stream(stream))
     if rc != OK:
