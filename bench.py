@@ -430,7 +430,7 @@ def measure_variants(steps: int):
 
 
 def measure_apps(steps: int):
-    """Stream compaction on the C3 mask (n = 2^28) and the 32-pass split radix sort (n = 2^26 random 32-bit keys)."""
+    """Stream compaction on the C3 mask (n = 2^28) and the split radix sort in its three forms (n = 2^26 random 32-bit keys)."""
     import torch
 
     def timed(fn, reps):
